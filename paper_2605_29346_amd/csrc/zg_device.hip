@@ -36,34 +36,32 @@ namespace zg {
 // =================================================================================================
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr uint64_t kStAggregate = 1ull << 62; // tile total published
-constexpr uint64_t kStPrefix = 2ull << 62;    // inclusive prefix published
-constexpr uint64_t kStValueMask = (1ull << 62) - 1;
+constexpr uint64_t kStAggregate = 1ull << 62; // status word of a ticket: its total published ...
+constexpr uint64_t kStPrefix = 2ull << 62;    // ... or its inclusive prefix
 constexpr uint32_t kSpinLimit = 1u << 22;     // bounded wait: polls before giving up with ZG_FLAG_INTERNAL
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane)
+// value of the lane a DPP control names, 0 where there is none
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+// inclusive sum over the wavefront's lanes, all of them active: six register moves (a shuffle through LDS per step costs the
+// latency-bound launches about 0.3 us per scan)
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
+{
+    v += dpp_or_zero<0x111, 0xF>(v); // row_shr:1, 2, 4, 8: within rows of 16 lanes
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v); // row_bcast:15: last lane of rows 0 and 2 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v); // row_bcast:31: lane 31 into rows 2 and 3
     return v;
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
-{
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
-
-__device__ __forceinline__ uint64_t wave_sum64(uint64_t v)
-{
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, d, 64);
-    return v;
-}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return lane_value(wave_incl_scan(v), 63u); }
 
 __device__ __forceinline__ void st_store(uint64_t *p, uint64_t v)
 {
@@ -75,58 +73,47 @@ __device__ __forceinline__ uint64_t st_load(uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Single-pass chained scan across workgroups: ticket `tile` (tickets are handed out in start order, so every
-// predecessor is already running) publishes its total and then looks back over the predecessors' status words until
-// it meets a published inclusive prefix.  A status word carries state (2 bits) and value (62 bits) together, so one
-// relaxed 64-bit access is enough.  One wavefront looks back, 64 predecessors per round (sharing a look-back among
-// eight wavefronts so that one round covers 512 predecessors was measured: no faster - the wait is for the
-// predecessors to publish, not for the rounds - and eight times the polling).  The wait is bounded; when it runs out
-// the step is flagged invalid (sticky and per-step word) and a clamped value is used.
-__device__ __forceinline__ uint64_t lookback_round(uint64_t *status, int64_t base, Drmb *d, int lane, bool &found)
+// Single-pass chained scan across workgroups: ticket t (tickets are handed out in start order, so every predecessor is
+// already running) publishes its total, and later looks back over the predecessors' status words until it meets a
+// published inclusive prefix.  A status word carries state and value together, so one relaxed 64-bit access is enough.  One
+// wavefront looks back, 64 predecessors per round.  (Measured and not kept: sharing a look-back among eight wavefronts -
+// the wait is for the predecessors to publish, not for the rounds; a second level of one word per 32 tickets that each
+// ticket adds to and every later ticket polls - the polls of one line queue up behind each other, launches of 400
+// tickets took twice as long.)  The wait is bounded; when it runs out the step is flagged invalid (sticky and per-step word)
+// and what is there is used.  Values are taken modulo 2^32: more than that is only reached beyond a cap, by dropped rows.
+__device__ __forceinline__ void chain_publish(uint64_t *status, uint32_t t, uint32_t total)
 {
-    // the 64 status words base, base-1, .. base-63 (indices below zero count as an inclusive prefix of zero)
-    const int64_t idx = base - lane;
-    uint64_t st;
-    uint32_t spins = 0;
-    for (;;) {
-        st = idx >= 0 ? st_load(&status[idx]) : kStPrefix;
-        const bool invalid = (st >> 62) == 0;
-        if (!__any(invalid)) break;
-        if (++spins > kSpinLimit) {
-            if (lane == 0) { // the step's outputs are invalid: both the sticky and the per-step word say so
-                atomicOr(&d->flags, ZG_FLAG_INTERNAL);
-                atomicOr(&d->step_flags, ZG_FLAG_INTERNAL);
-            }
-            if (invalid) st = kStAggregate;
-            break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
-    const unsigned long long pm = __ballot((st >> 62) == 2);
-    const uint64_t val = st & kStValueMask;
-    found = pm != 0ull;
-    if (pm) {
-        const int first = __ffsll((long long)pm) - 1;
-        return wave_sum64(lane <= first ? val : 0ull);
-    }
-    return wave_sum64(val);
+    st_store(&status[t], (t == 0u ? kStPrefix : kStAggregate) | total);
 }
 
-// all 64 lanes of one wavefront: publish, then look back 64 at a time
-__device__ uint64_t chained_exclusive_prefix(uint64_t *status, uint32_t tile, uint64_t total, Drmb *d, int lane)
+// all 64 lanes of one wavefront: the sum of the totals of tickets 0 .. t-1, after this ticket's own was published
+__device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, uint32_t total, Drmb *d, int lane)
 {
-    if (lane == 0) st_store(&status[tile], (tile == 0 ? kStPrefix : kStAggregate) | total);
-    uint64_t excl = 0;
-    if (tile > 0) {
-        int64_t base = (int64_t)tile - 1;
+    uint32_t excl = 0, spins = 0;
+    if (t == 0u) return 0u;
+    for (int64_t base = (int64_t)t - 1;; base -= 64) {
+        // the 64 status words base, base-1, .. base-63 (indices below zero count as an inclusive prefix of zero)
+        const int64_t idx = base - lane;
+        uint64_t st;
         for (;;) {
-            bool found;
-            excl += lookback_round(status, base, d, lane, found);
-            if (found) break;
-            base -= 64;
+            st = idx >= 0 ? st_load(&status[idx]) : kStPrefix;
+            const bool invalid = (st >> 62) == 0;
+            if (!__any(invalid)) break;
+            if (++spins > kSpinLimit) {
+                if (lane == 0) { // the step's outputs are invalid: both the sticky and the per-step word say so
+                    atomicOr(&d->flags, ZG_FLAG_INTERNAL);
+                    atomicOr(&d->step_flags, ZG_FLAG_INTERNAL);
+                }
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
         }
-        if (lane == 0) st_store(&status[tile], kStPrefix | ((excl + total) & kStValueMask));
+        const unsigned long long pm = __ballot((st >> 62) == 2);
+        const int last = pm ? __ffsll((long long)pm) - 1 : 63;
+        excl += wave_sum(lane <= last ? (uint32_t)st : 0u);
+        if (pm || base < 64 || spins > kSpinLimit) break;
     }
+    if (lane == 0) st_store(&status[t], kStPrefix | (uint32_t)(excl + total));
     return excl;
 }
 
@@ -150,7 +137,13 @@ __device__ __forceinline__ uint64_t philox_draw(uint32_t key_lo, uint32_t key_hi
     return (uint64_t)c0 | ((uint64_t)c1 << 32);
 }
 
-// The G lanes of a wavefront that hold the slots of one frontier vertex, as the group interface of
+// floor(x * b / 2^64) for a 32-bit b: two 32 x 32 products instead of a 64 x 64 one
+__device__ __forceinline__ uint32_t scale_draw(uint64_t x, uint32_t b)
+{
+    return (uint32_t)(((x >> 32) * b + (((x & 0xFFFFFFFFull) * b) >> 32)) >> 32);
+}
+
+// The F consecutive lanes of a wavefront that hold the slots of one frontier vertex, as the group interface of
 // floyd_position (zg_floyd.h): slot j of the group sits in lane gbase + j.
 struct WaveGroup {
     int gbase;
@@ -206,9 +199,12 @@ struct IngestArgs {
 // stays in device memory.  Otherwise: the mailbox slot of the device-side step counter.
 __device__ __forceinline__ void read_step_inputs(const Drmb *d, const Drmb *gate, const Mailbox *mailbox, unsigned long long *out)
 {
-    if (!gate && d->pre_valid && d->pre_epoch == d->epoch) {
-        out[0] = d->pre_seeds;
-        out[1] = d->pre_key;
+    // (all of it on its way at once: the branch below would make two round trips of it)
+    const uint32_t valid = d->pre_valid, pre_epoch = d->pre_epoch, epoch = d->epoch;
+    const unsigned long long pre_seeds = d->pre_seeds, pre_key = d->pre_key;
+    if (!gate && valid && pre_epoch == epoch) {
+        out[0] = pre_seeds;
+        out[1] = pre_key;
         return;
     }
     const uint32_t slot = (gate ? gate->epoch - 1u : d->epoch) % kMailboxSlots;
@@ -278,6 +274,18 @@ __device__ __forceinline__ void relabel_block(const RelabelArgs &a, uint32_t blo
     }
 }
 
+// The last hop's new vertices carry, in the top bits of their id-map entry, the tag of the edge whose mark was the last to
+// land on the vertex's byte: that edge - and the odd other edge to the vertex with the same tag, which stores the same bytes -
+// writes the vertex's row of X.  As many tag bits as the node cap leaves of an int32's 31 (at most 7); with none left every
+// edge to a new vertex writes its row.
+struct MarkTag {
+    int32_t shift; // tag = entry >> shift; 0: entries are plain local ids
+    uint32_t mask; // tag bits in use
+    __device__ __forceinline__ int32_t entry(uint32_t lid, uint32_t mark) const { return shift ? (int32_t)(lid | ((mark & mask) << shift)) : (int32_t)lid; }
+    __device__ __forceinline__ int32_t local_id(int32_t e) const { return shift && e >= 0 ? e & (int32_t)((1u << shift) - 1u) : e; }
+    __device__ __forceinline__ bool owns(int32_t e, uint32_t edge) const { return shift == 0 || ((uint32_t)e >> shift) == (edge & mask); }
+};
+
 struct RowArgs {
     const float *src;       // gather: feature table; aggregate: input rows
     float *dst;
@@ -288,8 +296,8 @@ struct RowArgs {
     const uint32_t *n_cols; // aggregate: device address of the number of valid input rows, or null if `col_limit` holds it
     uint32_t col_limit;     // aggregate: number of valid input rows when n_cols is null (num_nodes for global ids)
     float *x_dst;           // aggregate reading the table: X, whose rows of newly discovered vertices it writes on the way (or null)
-    const int32_t *x_row;   // ... per edge, the row of X (the local id)
-    const uint8_t *own;     // ... per edge, whether this edge is the one that writes it
+    const uint8_t *own;     // ... per edge, whether this edge is the one that writes it (null: the id map's entry carries its tag)
+    MarkTag tag;            // ... how the id map's entries carry it
     int64_t ld_x;
     int64_t ld_src, ld_dst;
     uint64_t inv;
@@ -299,7 +307,7 @@ struct RowArgs {
     int32_t vec4;           // rows are moved in 16-byte pieces (else element by element)
     int32_t nt;             // aggregate inside a step: what it writes (means, rows of X) is stored past the caches (non-temporal)
     const int32_t *local_id; // aggregate that relabels its block's edges itself: the id map ...
-    int32_t *col_out;        // ... and where col[e] = local id of nbr_gid[e] goes (null: `x_row` holds it already)
+    int32_t *col_out;        // ... and where col[e] = local id of nbr_gid[e] goes
     uint32_t blocks; // workgroups given to this role (0: role absent)
 };
 
@@ -392,122 +400,154 @@ struct HopArgs {
     const Mailbox *mailbox;   // launch 0 reads the step's inputs itself (the gate owner's mailbox when gated)
     int32_t *S;
     int32_t *local_id;
-    uint32_t *bitmap_prev;    // launches 1..H: the bitmap hop l-1 filled; ranked, consumed and cleared here
-    uint32_t *bitmap_next;    // launches 0..H-1: the bitmap this launch's sampling fills
+    uint32_t *marks_prev;    // launches 1..H: the bitmap hop l-1 filled; ranked, consumed and cleared here
+    uint32_t *marks_next;    // launches 0..H-1: the bitmap this launch's sampling fills
     uint32_t *seen;
     int32_t *row_ptr;         // block of hop l (launches 0..H-1)
     int32_t *nbr;
-    uint8_t *own;             // last hop, when the aggregation writes X: per edge, whether it was the first to reach its vertex
-    uint64_t *status_cnt;     // chained scan over the launch's tickets: vertices ranked ...
-    uint64_t *status_edge;    // ... and edges sampled
+    uint8_t *own;             // last hop, when it marks bits and the aggregation writes X: per edge, whether it was the first to reach its vertex
+    MarkTag tag;              // closing launch, when the last hop marked bytes and the aggregation writes X (see MarkTag)
+    int32_t bytes_prev;       // marks_prev / marks_next hold a byte per vertex instead of a bit
+    int32_t bytes_next;
+    int32_t tag_next;         // the marks of this launch's sampling carry their edge's tag
+    uint64_t *status_cnt;     // chained scans: vertices ranked, over the launch's ranking tiles ...
+    uint64_t *status_edge;    // ... and edges sampled, over all its tickets
     uint32_t num_nodes;
     int32_t launch;           // l
     int32_t num_hops;         // H
     int32_t fanout;
-    int32_t group_log2;       // lanes per row: 2^group_log2 >= max(4, fanout)
+    uint32_t rows_per_wave;   // rows whose slots a wavefront takes at a time: 64 / fanout
+    uint32_t inv_fanout;      // lane / fanout == (lane * inv_fanout) >> 16 for lane < 64
+    uint32_t rows_per_ticket; // old rows per ticket, at least
+    uint32_t max_tickets;     // ... doubled until the launch's tickets stay within this (1024 rows at most)
     int32_t replace;
-    uint32_t tiles_per_ticket; // consecutive tiles of old rows per ticket
     uint32_t cap_rows;        // capacity of n_l
     uint32_t edge_cap;        // capacity of E_l
-    uint32_t words_per_tile;  // ranking tile (a power of two, 32..8192)
+    uint32_t stage_edges;     // ids a workgroup holds in LDS between loading and storing them
+    uint32_t words_per_tile;  // ranking tile (a multiple of 32)
     uint32_t rank_tiles;      // 0 for launch 0
     uint32_t batch;
     uint32_t blocks;          // workgroups of this role (the launch's first ones)
 };
 
-// LDS of a hop-kernel workgroup: up to 256 rows of the block being sampled (vertex, degree, first edge offset, row
-// length, first edge position), the dedup set of one sampling pass, scan scratch
-constexpr int kHopRows = 256;
+// LDS of a sampling workgroup of the hop kernel: up to 1024 rows of the block being sampled (vertex, degree, first edge
+// offset, first edge), scan scratch; behind it (dynamic) the sampled ids on their way, the dedup set of a pass that marks
+// bits, and a ranking tile's words
+constexpr int kHopRows = kHopBlock; // one row per lane
 struct HopShared {
     uint32_t ticket;
     uint32_t base_cnt;
-    unsigned long long base_edge;
+    uint32_t base_edge;
     unsigned long long in[2];
-    uint32_t wsum[kHopBlock / 64];
-    uint32_t wk[4];
+    uint32_t wsum[64];                 // per round of the tile's words and wavefront: new vertices
+    uint32_t wk[kHopBlock / 64];
     int32_t v[kHopRows];
-    uint32_t deg[kHopRows], k[kHopRows], rp[kHopRows];
+    uint32_t deg[kHopRows], rp[kHopRows + 1];
     unsigned long long off[kHopRows];
-    uint32_t set[kSampleHashSlots];
 };
 
-// One sampling pass over rows row0 .. row0 + 1024/G - 1 of the workgroup's LDS rows: lane (t, j) takes slot j of row
-// row0 + t (vertex sh.v, degree sh.deg, sh.k slots, first edge position sh.rp): j itself if deg <= F, else Floyd's
-// subset algorithm with one Philox draw per slot, all slots resolved at once (zg_floyd.h); with replacement one draw
-// per slot.  The lane loads the neighbor id and stores it to nbr_gid (consecutive lanes, consecutive addresses).
-// Dedup starts here: the ids go through a hash set in LDS so that each distinct id of the pass reaches the hop's bitmap
-// with at most one device-scope atomic - popular vertices are sampled hundreds of times per hop and same-address atomics
-// serialise at the memory side.  Ids that are already in D_l reach the bitmap too: the next launch masks it with "seen"
-// (looking every id up in "seen" here was measured: one more dependent random load per edge, slower on every workload).
-__device__ __forceinline__ void sample_pass(const HopArgs &a, HopShared &sh, uint32_t key_lo, uint32_t key_hi, uint32_t row0, int tid,
-                                            int lane)
+constexpr uint32_t kMarkByte = 0x80u; // a vertex's mark byte: this bit, and the 7 low bits of the marking edge's index where tags are asked for
+
+// which of four mark bytes are set, as the low four bits
+__device__ __forceinline__ uint32_t marks4(uint32_t x) { return (((x >> 7) & 0x01010101u) * 0x10204080u) >> 28; }
+
+// The slot positions of rows row0 .. row0 + 64/F - 1 of the workgroup's LDS rows, one wavefront: lane (r, j) = r F + j takes slot
+// j of row row0 + r (vertex sh.v, degree sh.deg, first edge sh.rp): j itself if deg <= F, else Floyd's subset
+// algorithm with one Philox draw per slot, all slots resolved at once (zg_floyd.h); with replacement one draw per slot.  Rows
+// beyond `rows` and lanes beyond the last whole group take no slot.  Groups of F lanes instead of the next power of two: a
+// wavefront holds 6 rows of fanout 10 instead of 4, 12 of fanout 5 instead of 8 - and Philox is what the pass computes most.
+struct Slot {
+    bool taken;
+    uint32_t edge;          // its edge, counted from the batch's first
+    unsigned long long src; // where its neighbor's id is
+};
+
+__device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &sh, uint32_t key_lo, uint32_t key_hi, uint32_t row0, uint32_t rows,
+                                             int lane)
 {
-    const int glog = a.group_log2;
     const uint32_t F = (uint32_t)a.fanout;
-    const int G = 1 << glog;
-    const int gl = lane & (G - 1);
-    const int gbase = lane & ~(G - 1);
-    const uint32_t t = row0 + ((uint32_t)tid >> glog);
-    const int32_t tv = sh.v[t];
-    const uint32_t tdeg = sh.deg[t], tk = sh.k[t], trp = sh.rp[t];
-    const unsigned long long toff = sh.off[t];
-    const bool slot = (uint32_t)gl < tk;
-    uint32_t pos = (uint32_t)gl;
+    const uint32_t sub = ((uint32_t)lane * a.inv_fanout) >> 16;
+    const uint32_t gl = (uint32_t)lane - sub * F;
+    const uint32_t t = row0 + sub;
+    const bool row = sub < a.rows_per_wave && t < rows;
+    const uint32_t tl = row ? t : 0u;
+    const int32_t tv = sh.v[tl];
+    const uint32_t tdeg = row ? sh.deg[tl] : 0u;
+    const bool slot = a.replace ? tdeg > 0u : gl < tdeg;
+    uint32_t pos = gl;
     if (a.replace) {
-        if (slot) pos = (uint32_t)__umul64hi(philox_draw(key_lo, key_hi, (uint32_t)a.launch, (uint32_t)tv, (uint32_t)gl), (uint64_t)tdeg);
+        if (slot) pos = scale_draw(philox_draw(key_lo, key_hi, (uint32_t)a.launch, (uint32_t)tv, gl), tdeg);
     } else {
         const bool floyd = slot && tdeg > F;
         if (__any(floyd)) {
-            uint32_t cand = (uint32_t)gl;
-            if (floyd)
-                cand = (uint32_t)__umul64hi(philox_draw(key_lo, key_hi, (uint32_t)a.launch, (uint32_t)tv, (uint32_t)gl),
-                                            (uint64_t)(tdeg - F + (uint32_t)gl) + 1ull);
-            WaveGroup grp{gbase};
-            pos = floyd_position(grp, (uint32_t)gl, F, tdeg, floyd, cand);
+            uint32_t cand = gl;
+            if (floyd) cand = scale_draw(philox_draw(key_lo, key_hi, (uint32_t)a.launch, (uint32_t)tv, gl), tdeg - F + gl + 1u);
+            WaveGroup grp{(int)(sub * F)};
+            pos = floyd_position(grp, gl, F, tdeg, floyd, cand);
         }
     }
-    if (slot && trp + (uint32_t)gl < a.edge_cap) {
-        const int32_t g = a.indices[toff + pos];
-        a.nbr[trp + (uint32_t)gl] = g;
-        if ((uint32_t)g < a.num_nodes) {
-            // first lane of the pass to insert g into the LDS set marks it (at most 1024 insertions into 2048 slots)
-            uint32_t h = ((uint32_t)g * 2654435761u) >> (32 - kSampleHashBits);
-            bool first = false;
-            for (;;) {
-                const uint32_t old = atomicCAS(&sh.set[h], 0xFFFFFFFFu, (uint32_t)g);
-                if (old == 0xFFFFFFFFu) {
-                    first = true;
-                    break;
-                }
-                if (old == (uint32_t)g) break;
-                h = (h + 1) & (kSampleHashSlots - 1);
-            }
-            // The one atomic that finds the bit clear belongs to the first edge of the hop to reach the vertex.  For the last
-            // hop that edge is remembered: the aggregation reads the vertex's feature row for it anyway and, if the vertex
-            // turns out to be new, copies the row into X on the way (any one edge would do: they all carry the same row).
-            bool mine = false;
-            if (first) {
-                const uint32_t bit = 1u << (g & 31);
-                if (a.own)
-                    mine = (atomicOr(&a.bitmap_next[(uint32_t)g >> 5], bit) & bit) == 0u;
-                else
-                    atomicOr(&a.bitmap_next[(uint32_t)g >> 5], bit);
-            }
-            if (a.own) a.own[trp + (uint32_t)gl] = mine ? 1 : 0;
-        } else if (a.own) {
-            a.own[trp + (uint32_t)gl] = 0;
-        }
-    }
+    Slot r;
+    r.edge = sh.rp[tl] + gl;
+    r.taken = slot;
+    r.src = sh.off[tl] + pos;
+    return r;
 }
 
-// "Row lengths" of the workgroup's LDS rows: lanes 0..255 take the vertex sh.v[tid] (-1 beyond `nrows`), load its two
-// offsets, and leave degree, first edge offset and k = min(F, deg) (F whenever deg > 0 with replacement) in LDS.
-// Returns this lane's k.
+// Marks.  A hop that reaches many of the graph's vertices (bytes_next) stores a byte per sampled edge: idempotent stores
+// need no dedup and no answer, and run at 50-150 G/s where atomics to the same addresses run at 12-25 G/s (2 M edges over 2.4 M
+// vertices: 16 us against 86 us) and far slower on a hub's word.  The stores are plain byte stores, which the caches keep apart
+// byte by byte; whichever of several edges' stores lands last, the byte says "reached", and nobody looks before the next
+// launch.  (Stores that write through to memory at once queue up on a hub's byte like atomics: 129 -> 212 us in a launch of
+// 2 M edges, against 81 us; a look at the byte first costs more than it spares, 84 us.)
+// A hop that reaches few of them (a byte map of 110 M vertices takes the next launch 25 us to read) sets a bit, after a hash
+// set in LDS: each distinct id of the pass reaches the hop's bitmap with at most one device-scope atomic - popular
+// vertices are sampled hundreds of times per hop and same-address atomics serialise at the memory side.
+// Ids that are already in D_l are marked too: the next launch masks them with "seen" (looking every id up in "seen" here was
+// measured: one more dependent random load per edge, slower on every workload).
+__device__ __forceinline__ void mark_byte(const HopArgs &a, uint32_t edge, int32_t g)
+{
+    if ((uint32_t)g < a.num_nodes)
+        __hip_atomic_store(reinterpret_cast<uint8_t *>(a.marks_next) + (uint32_t)g, (uint8_t)(kMarkByte | (a.tag_next ? edge & 0x7Fu : 0u)),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ void mark_bit(const HopArgs &a, uint32_t *set, uint32_t edge, int32_t g)
+{
+    bool mine = false;
+    if ((uint32_t)g < a.num_nodes) {
+        // first lane of the pass to insert g into the LDS set marks it (at most 1024 insertions into 2048 slots)
+        uint32_t h = ((uint32_t)g * 2654435761u) >> (32 - kSampleHashBits);
+        bool first = false;
+        for (;;) {
+            const uint32_t old = atomicCAS(&set[h], 0xFFFFFFFFu, (uint32_t)g);
+            if (old == 0xFFFFFFFFu) {
+                first = true;
+                break;
+            }
+            if (old == (uint32_t)g) break;
+            h = (h + 1) & (kSampleHashSlots - 1);
+        }
+        // The one atomic that finds the bit clear belongs to the first edge of the hop to reach the vertex.  For the last
+        // hop that edge is remembered: the aggregation reads the vertex's feature row for it anyway and, if the vertex
+        // turns out to be new, copies the row into X on the way (any one edge would do: they all carry the same row).
+        if (first) {
+            const uint32_t bit = 1u << (g & 31);
+            if (a.own)
+                mine = (atomicOr(&a.marks_next[(uint32_t)g >> 5], bit) & bit) == 0u;
+            else
+                atomicOr(&a.marks_next[(uint32_t)g >> 5], bit);
+        }
+    }
+    if (a.own) a.own[edge] = mine ? 1 : 0;
+}
+
+// "Row lengths" of the workgroup's LDS rows: lane t takes the vertex sh.v[t] (none beyond `nrows`), loads its two offsets, and
+// leaves degree and first edge offset in LDS.  Returns this lane's k = min(F, deg) (F whenever deg > 0 with replacement).
 template <typename OffT>
 __device__ __forceinline__ uint32_t load_rows(const HopArgs &a, HopShared &sh, uint32_t nrows, int tid)
 {
-    if (tid >= kHopRows) return 0u;
-    const int32_t v = (uint32_t)tid < nrows ? sh.v[tid] : -1;
+    if ((uint32_t)tid >= nrows) return 0u;
+    const int32_t v = sh.v[tid];
     uint32_t deg = 0;
     unsigned long long off0 = 0;
     if (v >= 0) {
@@ -516,13 +556,10 @@ __device__ __forceinline__ uint32_t load_rows(const HopArgs &a, HopShared &sh, u
         off0 = (unsigned long long)o0;
         deg = (uint32_t)(o1 - o0);
     }
-    const uint32_t F = (uint32_t)a.fanout;
-    const uint32_t k = a.replace ? (deg > 0 ? F : 0u) : (deg < F ? deg : F);
-    sh.v[tid] = v;
     sh.deg[tid] = deg;
     sh.off[tid] = off0;
-    sh.k[tid] = k;
-    return k;
+    const uint32_t F = (uint32_t)a.fanout;
+    return a.replace ? (deg > 0 ? F : 0u) : (deg < F ? deg : F);
 }
 
 // the lowest q set bits of x
@@ -538,330 +575,437 @@ __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
     return out;
 }
 
-// The hop kernel.  A workgroup of 1024 lanes takes a ticket; tickets are handed out in start order, so every ticket a
-// workgroup ever waits for belongs to a workgroup that already runs.  In ticket order the launch's work is the row
-// order of block l:
-//   tickets 0 .. t_old-1   rows that were already in D_{l-1} (launch 0: the seeds), up to 256 per ticket;
-//   then the ranking tiles of hop l-1's bitmap, W words each, in ascending vertex id: the bits that are not "seen"
+// The hop kernel's launches 0 .. H-1 (k_hop) and the closing launch H (k_close).  A workgroup takes a ticket; tickets are
+// handed out in start order, so every ticket a workgroup ever waits for belongs to a workgroup that already runs.  In ticket
+// order a launch's work is the row order of block l:
+//   tickets 0 .. t_old-1   rows that were already in D_{l-1} (launch 0: the seeds);
+//   then the ranking tiles of hop l-1's marks, 32 W vertices each, in ascending vertex id: those marked and not "seen"
 //                          are the hop's new vertices; their rank - n_{l-1} plus the new vertices before them - is
 //                          their local id and their row in block l, so they land behind D_{l-1} in ascending id.
-// Two single-pass chained scans run over the tickets (status word = state + value, bounded wait): new vertices and
-// sampled edges.  A ticket first finds its rows' lengths k_i = min(F, deg) ("row lengths"; 256 rows at a time, held in
-// LDS), publishes both totals, takes its exclusive prefixes (wavefront 0 and wavefront 1, side by side), and then
-// writes S, the id map and row_ptr ("offsets scan") and samples its rows in passes of 1024 / G rows, one lane per
-// (row, slot) ("sample").  A ranking tile holds its bitmap words in registers (up to WPL per lane: 8, or 16 in the
-// instantiation for sparse launches over very long bitmaps), adds the kept
-// bits to "seen" and clears the words.  Vertices ranked beyond the cap are dropped (no row, local id -1, not "seen")
-// and the hop's overflow bit is raised; the rows kept are a prefix of the row order, so the block stays consistent up
-// to the cap.  Launch H ranks only.  The launch's surplus workgroups (the grid is sized by the caps) find no ticket
-// and return.
-template <typename OffT, int WPL>
-__global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, RelabelArgs rel, IngestArgs ing, RowArgs gat)
+// Two single-pass chained scans run over the tickets: new vertices and sampled edges.  A ticket first finds its rows'
+// lengths k_i = min(F, deg) ("row lengths"; a row per lane, 1024 at a time, held in LDS), publishes both totals, takes its
+// exclusive prefixes (wavefront 0 and wavefront 1, side by side), and then writes S, the id map and row_ptr ("offsets
+// scan") and samples its rows, F lanes per row ("sample").  New vertices join "seen", consumed marks are cleared.  Vertices
+// ranked beyond the cap are dropped (no row, local id -1, not "seen") and the hop's overflow bit is raised; the rows kept are
+// a prefix of the row order, so the block stays consistent up to the cap.  Launch H ranks only.  The launch's surplus
+// workgroups (the grid is sized by the caps) find no ticket and return.
+//
+// Bound by latency: a ticket is a chain of about eight dependent memory accesses, so a launch costs the length of that chain,
+// the code it walks through cold and its slowest ticket.  Hence one instantiation per kind of launch and of marks (one
+// kernel for all spilled 140 scalar and 6 vector registers), wide scans in registers, and a chain of two levels.
+
+// The words of a ranking tile, bit b of word w: vertex 32 w + b is marked and not "seen".  A lane holds pieces of four words,
+// piece u NT + tid in round u: 16-byte accesses, consecutive lanes consecutive.
+__device__ __forceinline__ uint32_t piece_word(const uint4 &x, uint32_t c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; }
+__device__ __forceinline__ uint32_t piece_any(const uint4 &x) { return x.x | x.y | x.z | x.w; }
+
+// Reads a tile's marks, masks them with "seen", and clears them for the hop after next (tagged: a new vertex's byte stays until
+// its tag has been read).  Mark bytes become words in LDS first, 16 bytes per lane.  With JOIN the new vertices join
+// "seen" at once: this workgroup is its words' only reader and writer in the launch.  The loads of all rounds are on their
+// way before the first is looked at, and so are the words of "seen".
+template <int NT, int R, bool BYTES, bool JOIN>
+__device__ __forceinline__ void load_tile(const HopArgs &a, size_t tile0, uint32_t np, uint32_t tid, uint4 (&x)[R], uint32_t *s_words)
 {
-    __shared__ HopShared sh;
-    if (gate_closed(a.gate)) return;
-    // Roles by workgroup index.  The closing launch may carry the copy of the frontier's feature rows (their ids are final
-    // by now): its copy workgroups alternate with the ticket workgroups at the head of the grid, so that the copy - bound by
-    // bandwidth - runs while the tickets - chains of dependent accesses - wait, instead of after them (tickets are handed
-    // out in start order, whichever workgroups ask).  Then the remaining tickets, the relabel and ingest roles, the
-    // remaining copy workgroups.
-    {
-        uint32_t b = blockIdx.x;
-        const uint32_t pairs = a.blocks < gat.blocks ? a.blocks : gat.blocks; // (0 without the copy role)
-        bool ticket_role;
-        uint32_t copy_block = 0xFFFFFFFFu;
-        if (b < 2u * pairs) {
-            ticket_role = (b & 1u) == 0u;
-            if (!ticket_role) copy_block = b >> 1;
-        } else {
-            b -= 2u * pairs;
-            ticket_role = b < a.blocks - pairs;
-            if (!ticket_role) {
-                b -= a.blocks - pairs;
-                if (b < rel.blocks) {
-                    relabel_block(rel, b);
-                    return;
-                }
-                b -= rel.blocks;
-                if (b < ing.blocks) {
-                    ingest_block(ing, b, sh.in);
-                    return;
-                }
-                copy_block = pairs + (b - ing.blocks);
-            }
+    uint4 *src = reinterpret_cast<uint4 *>(a.marks_prev) + (BYTES ? tile0 * 2u : tile0 / 4u), *seen = reinterpret_cast<uint4 *>(a.seen + tile0);
+    if (BYTES) {
+        uint16_t *half = reinterpret_cast<uint16_t *>(s_words);
+#pragma unroll 4
+        for (uint32_t q = tid; q < 8u * np; q += (uint32_t)NT) {
+            const uint4 y = src[q];
+            half[q] = (uint16_t)(marks4(y.x) | (marks4(y.y) << 4) | (marks4(y.z) << 8) | (marks4(y.w) << 12));
         }
-        if (!ticket_role) {
-            if (gat.vec4)
-                gather_rows_block<4>(gat, copy_block, sh.v);
-            else
-                gather_rows_block<1>(gat, copy_block, sh.v);
-            return;
-        }
-    }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    Drmb *d = a.drmb;
-    const bool first = a.launch == 0, sampling = a.launch < a.num_hops;
-    if (tid == 0) sh.ticket = atomicAdd(&d->ticket[a.launch], 1u);
-    if (first && tid == 64) read_step_inputs(d, a.gate, a.mailbox, sh.in);
-    const uint32_t n_old = first ? a.batch : d->n[a.launch - 1]; // (in flight while the ticket comes back)
-    const uint32_t key_lo_d = d->key_lo, key_hi_d = d->key_hi;
-    __syncthreads();
-    const uint32_t ticket = sh.ticket;
-    const uint32_t T = (uint32_t)kHopBlock >> a.group_log2;  // rows per sampling pass, 16..256
-    const uint32_t R = T * a.tiles_per_ticket;               // old rows per ticket, <= 256
-    const uint32_t t_old = sampling ? (n_old + R - 1) / R : 0u;
-    const uint32_t n_tickets = t_old + a.rank_tiles;
-    if (ticket >= n_tickets) return;
-    const bool old = ticket < t_old; // uniform over the workgroup
-    const uint32_t key_lo = first ? (uint32_t)(sh.in[1] & 0xFFFFFFFFull) : key_lo_d;
-    const uint32_t key_hi = first ? (uint32_t)(sh.in[1] >> 32) : key_hi_d;
-
-    // ---- what this ticket's rows are
-    uint32_t m;                       // rows of this ticket: old rows, or the tile's new vertices
-    uint32_t lex = 0;                 // ranking tile: in-tile index of this lane's first new vertex
-    uint32_t nw[WPL]; // ranking tile: this lane's new vertices (bitmap bits that are not "seen")
-    uint32_t had = 0;                 // ... and which of its bitmap words were not empty
-    const uint32_t r0 = ticket * R;   // old rows: the first row
-    const uint32_t W = a.words_per_tile;
-    const uint32_t wpl = W >= (uint32_t)kHopBlock ? W / (uint32_t)kHopBlock : 1u;
-    const size_t w0 = old ? 0 : (size_t)(ticket - t_old) * W + (size_t)tid * wpl; // ranking tile: this lane's first word
-#pragma unroll
-    for (uint32_t r = 0; r < WPL; ++r) nw[r] = 0u;
-    if (old) {
-        m = n_old - r0 < R ? n_old - r0 : R;
-    } else {
-        const bool owner = W >= (uint32_t)kHopBlock || (uint32_t)tid < W;
-        // the lane's words of the hop's bitmap, then - only where a word is not empty - the same words of "seen"
-        // (wide loads: a lane's words are consecutive)
-        auto load_words = [&](const uint32_t *src, uint32_t (&x)[WPL]) {
-            if (wpl >= 4) {
-#pragma unroll
-                for (uint32_t q = 0; q < (uint32_t)WPL / 4u; ++q)
-                    if (4u * q < wpl) {
-                        const uint4 p = *reinterpret_cast<const uint4 *>(src + w0 + 4u * q);
-                        x[4 * q] = p.x, x[4 * q + 1] = p.y, x[4 * q + 2] = p.z, x[4 * q + 3] = p.w;
-                    }
-            } else if (wpl == 2) {
-                const uint2 p = *reinterpret_cast<const uint2 *>(src + w0);
-                x[0] = p.x, x[1] = p.y;
-            } else {
-                x[0] = src[w0];
-            }
-        };
-        if (owner) load_words(a.bitmap_prev, nw);
-#pragma unroll
-        for (uint32_t r = 0; r < WPL; ++r)
-            if (nw[r]) had |= 1u << r;
-        if (had) {
-            if (wpl >= 4) {
-#pragma unroll
-                for (uint32_t q = 0; q < (uint32_t)WPL / 4u; ++q)
-                    if (4u * q < wpl && ((had >> (4u * q)) & 0xFu)) {
-                        const uint4 sn = *reinterpret_cast<const uint4 *>(a.seen + w0 + 4u * q);
-                        nw[4 * q] &= ~sn.x, nw[4 * q + 1] &= ~sn.y, nw[4 * q + 2] &= ~sn.z, nw[4 * q + 3] &= ~sn.w;
-                    }
-            } else if (wpl == 2) {
-                const uint2 sn = *reinterpret_cast<const uint2 *>(a.seen + w0);
-                nw[0] &= ~sn.x, nw[1] &= ~sn.y;
-            } else {
-                nw[0] &= ~a.seen[w0];
-            }
-        }
-        uint32_t cnt = 0;
-#pragma unroll
-        for (uint32_t r = 0; r < WPL; ++r) cnt += __popc(nw[r]);
-        const uint32_t incl = wave_incl_scan(cnt, lane);
-        if (lane == 63) sh.wsum[wave] = incl;
         __syncthreads();
-        lex = incl - cnt;
-        m = 0;
+    }
+    uint4 sn[R];
 #pragma unroll
-        for (int w = 0; w < kHopBlock / 64; ++w) {
-            if (w < wave) lex += sh.wsum[w];
-            m += sh.wsum[w];
+    for (int u = 0; u < R; ++u) {
+        const uint32_t q = u * (uint32_t)NT + tid;
+        x[u] = make_uint4(0u, 0u, 0u, 0u);
+        if (q < np) x[u] = BYTES ? reinterpret_cast<const uint4 *>(s_words)[q] : src[q];
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (piece_any(x[u])) sn[u] = seen[u * (uint32_t)NT + tid];
+    const bool tagged = BYTES && !JOIN && a.tag.shift != 0;
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (piece_any(x[u])) {
+            const uint32_t q = u * (uint32_t)NT + tid;
+            const uint4 marked = x[u];
+            x[u].x &= ~sn[u].x, x[u].y &= ~sn[u].y, x[u].z &= ~sn[u].z, x[u].w &= ~sn[u].w;
+            if (JOIN && piece_any(x[u])) seen[q] = make_uint4(sn[u].x | x[u].x, sn[u].y | x[u].y, sn[u].z | x[u].z, sn[u].w | x[u].w);
+            if (!BYTES) {
+                src[q] = make_uint4(0u, 0u, 0u, 0u);
+            } else {
+#pragma unroll
+                for (uint32_t c = 0; c < 4u; ++c) {
+                    const uint32_t w = piece_word(marked, c), fresh = piece_word(x[u], c);
+                    uint4 *b = src + 2u * (4u * q + c); // the word's 32 bytes
+                    if (w && (!tagged || fresh == 0u))
+                        b[0] = b[1] = make_uint4(0u, 0u, 0u, 0u);
+                    else
+                        for (uint32_t old = w & ~fresh; old; old &= old - 1u) reinterpret_cast<uint8_t *>(b)[__ffs((int)old) - 1] = 0;
+                }
+            }
         }
-        __syncthreads(); // sh.wsum is used again below
+}
+
+// Ranks within the tile: lex[u] = new vertices before the lane's piece of round u.  Returns their number.  `wsum` holds a count
+// per round and wavefront (64 at most); one barrier.
+template <int NT, int R>
+__device__ __forceinline__ uint32_t rank_pieces(const uint4 (&x)[R], uint32_t (&lex)[R], uint32_t *wsum, uint32_t np, uint32_t wave, uint32_t lane)
+{
+    constexpr uint32_t NW = NT / 64;
+    static_assert(R * NW <= 64, "one count per lane");
+    uint32_t rounds = 0;
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (u * (uint32_t)NT < np) {
+            const uint32_t c = __popc(x[u].x) + __popc(x[u].y) + __popc(x[u].z) + __popc(x[u].w), incl = wave_incl_scan(c);
+            if (lane == 63u) wsum[u * NW + wave] = incl;
+            lex[u] = incl - c;
+            rounds = u + 1u;
+        }
+    __syncthreads();
+    const uint32_t e = lane < rounds * NW ? wsum[lane] : 0u;
+    const uint32_t s = wave_incl_scan(e);
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+        if (u * (uint32_t)NT < np) lex[u] += lane_value(s, u * NW + wave) - lane_value(e, u * NW + wave);
+    return lane_value(s, 63u);
+}
+
+// the new vertices number c0 .. c0 + n - 1 of the tile into v
+__device__ __forceinline__ void expand_piece(const uint4 &x, uint32_t j, uint32_t first_word, uint32_t c0, uint32_t n, int32_t *v)
+{
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c)
+        for (uint32_t w = piece_word(x, c); w; w &= w - 1u, ++j)
+            if (j - c0 < n) v[j - c0] = (int32_t)(((first_word + c) << 5) + (uint32_t)__ffs((int)w) - 1u);
+}
+
+struct HopRoles { // the other workgroups of launches 0 .. H-1
+    RelabelArgs rel; // launches 2 ..
+    IngestArgs ing;  // launch 0
+};
+
+template <typename OffT, bool FIRST, bool PREV_BYTES, bool NEXT_BYTES>
+__global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
+{
+    constexpr int R = (PREV_BYTES ? kHopMaxTileWords : kHopFatTileWords) / 4 / kHopBlock; // rounds of a tile
+    __shared__ HopShared sh;
+    extern __shared__ __align__(16) uint32_t s_dyn[]; // the sampled ids on their way, the dedup set of a bit-marking pass, a ranking tile's words
+    if (gate_closed(a.gate)) return;
+    // roles by workgroup index: the tickets, then the ingest or relabel role
+    if (blockIdx.x >= a.blocks) {
+        if (FIRST)
+            ingest_block(o.ing, blockIdx.x - a.blocks, sh.in);
+        else
+            relabel_block(o.rel, blockIdx.x - a.blocks);
+        return;
+    }
+    int32_t *const s_ids = reinterpret_cast<int32_t *>(s_dyn);
+    uint32_t *const s_set = s_dyn + a.stage_edges;
+    uint32_t *const s_words = s_set + (NEXT_BYTES ? 0 : kSampleHashSlots);
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    Drmb *d = a.drmb;
+    if (tid == 0) sh.ticket = atomicAdd(&d->ticket[a.launch], 1u);
+    if (FIRST && tid == 64) read_step_inputs(d, a.gate, a.mailbox, sh.in);
+    const uint32_t n_old = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while the ticket comes back)
+    const uint32_t key_lo_d = FIRST ? 0u : d->key_lo, key_hi_d = FIRST ? 0u : d->key_hi;
+    __syncthreads();
+    const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ticket);
+    // old rows per ticket: more than the plan's when there are so many that the launch would need a second round of workgroups
+    uint32_t rows = a.rows_per_ticket;
+    if (!FIRST && rows < 128u) rows = 128u;
+    if (!FIRST)
+        while (rows < (uint32_t)kHopRows / 2u + 1u && (n_old + rows - 1u) / rows + a.rank_tiles > a.max_tickets) rows *= 2u;
+    const uint32_t t_old = (n_old + rows - 1u) / rows;
+    const uint32_t n_tickets = t_old + (FIRST ? 0u : a.rank_tiles);
+    if (ticket >= n_tickets) return;
+    const bool old = FIRST || ticket < t_old; // uniform over the workgroup
+    const uint32_t key_lo = FIRST ? (uint32_t)(sh.in[1] & 0xFFFFFFFFull) : key_lo_d;
+    const uint32_t key_hi = FIRST ? (uint32_t)(sh.in[1] >> 32) : key_hi_d;
+
+    // ---- what this ticket's rows are: m old rows from r0 on, or the tile's m new vertices
+    uint32_t m;
+    uint32_t lex[R];
+    const uint32_t r0 = ticket * rows, tile = ticket - t_old;
+    const uint32_t np = a.words_per_tile / 4u; // the tile's pieces
+    const size_t tile0 = (size_t)tile * a.words_per_tile;
+    uint4 *const s_piece = reinterpret_cast<uint4 *>(s_words);
+    if (old) {
+        m = n_old - r0 < rows ? n_old - r0 : rows;
+    } else {
+        uint4 x[R];
+        load_tile<kHopBlock, R, PREV_BYTES, true>(a, tile0, np, tid, x, s_words);
+        m = rank_pieces<kHopBlock, R>(x, lex, sh.wsum, np, wave, lane);
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (u * (uint32_t)kHopBlock + tid < np) s_piece[u * kHopBlock + tid] = x[u]; // (read back by this lane only)
+        if (tid == 0) chain_publish(a.status_cnt, tile, m);
     }
 
-    // rows c0 .. c0 + 255 of the ticket into sh.v: old rows from the frontier list (launch 0: the seeds, an
-    // out-of-range one becoming -1, a vertex without neighbors), new vertices expanded from the lane's bitmap words
+    // rows c0 .. c0 + 1023 of the ticket into sh.v: old rows from the frontier list (launch 0: the seeds, an
+    // out-of-range one becoming -1, a vertex without neighbors), new vertices expanded from the lane's words
     auto fill_rows = [&](uint32_t c0) {
         if (old) {
-            if (tid < kHopRows && (uint32_t)tid < m) {
-                int32_t v = first ? reinterpret_cast<const int32_t *>(sh.in[0])[r0 + tid] : a.S[r0 + tid];
-                if (first && (uint32_t)v >= a.num_nodes) v = -1;
+            if (tid < m) {
+                int32_t v = FIRST ? reinterpret_cast<const int32_t *>(sh.in[0])[r0 + tid] : a.S[r0 + tid];
+                if (FIRST && (uint32_t)v >= a.num_nodes) v = -1;
                 sh.v[tid] = v;
             }
         } else {
-            const uint32_t c1 = c0 + kHopRows;
-            uint32_t j = lex;
 #pragma unroll
-            for (uint32_t r = 0; r < WPL; ++r) {
-                uint32_t x = nw[r];
-                const uint32_t pc = __popc(x);
-                if (j + pc <= c0 || j >= c1) { // all before this batch, or this batch is full: nothing to write
-                    j += pc;
-                    continue;
-                }
-                while (x) {
-                    const int b = __ffs((int)x) - 1;
-                    x &= x - 1u;
-                    if (j >= c0 && j < c1) sh.v[j - c0] = (int32_t)((((uint32_t)w0 + r) << 5) + (uint32_t)b);
-                    ++j;
-                }
-            }
+            for (int u = 0; u < R; ++u)
+                if (u * (uint32_t)kHopBlock + tid < np)
+                    expand_piece(s_piece[u * kHopBlock + tid], lex[u], (uint32_t)tile0 + (u * (uint32_t)kHopBlock + tid) * 4u, c0, kHopRows, sh.v);
         }
         __syncthreads();
     };
 
-    // ---- row lengths, 256 rows at a time; their total goes into the edge chain
-    const uint32_t supers = sampling ? (m + kHopRows - 1) / kHopRows : 0u;
-    uint64_t ticket_edges = 0;
-    if (sampling) {
-        uint32_t ksum = 0;
+    // ---- row lengths, a row per lane; their total goes into the edge chain
+    const uint32_t supers = (m + kHopRows - 1) / kHopRows;
+    uint32_t k = 0, kincl = 0; // this lane's row's length and the wavefront's sum up to it (of the last batch of rows)
+    {
+        uint32_t before = 0; // earlier batches
         for (uint32_t q = 0; q < supers; ++q) {
             const uint32_t c0 = q * kHopRows;
             fill_rows(c0);
-            ksum += load_rows<OffT>(a, sh, m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows, tid);
+            before += lane_value(kincl, 63u);
+            k = load_rows<OffT>(a, sh, m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows, tid);
+            kincl = wave_incl_scan(k);
             if (q + 1 < supers) __syncthreads(); // the next fill overwrites sh.v
         }
-        if (wave < 4) {
-            const uint32_t ws = wave_sum(ksum);
-            if (lane == 0) sh.wk[wave] = ws;
-        }
-        __syncthreads();
-        ticket_edges = (uint64_t)sh.wk[0] + sh.wk[1] + sh.wk[2] + sh.wk[3];
-    }
-    // ---- both chains, side by side: wavefront 0 looks back over the new-vertex counts, wavefront 1 over the edge
-    // counts.  Old rows hold no new vertex: their count chain entry is an inclusive prefix at once.
-    if (wave == 0) {
-        if (old) {
-            if (lane == 0) st_store(&a.status_cnt[ticket], kStPrefix);
-        } else {
-            const uint64_t r = chained_exclusive_prefix(a.status_cnt, ticket, (uint64_t)m, d, lane);
-            if (lane == 0) sh.base_cnt = (uint32_t)r;
-        }
-    }
-    if (wave == 1 && sampling) {
-        const uint64_t e = chained_exclusive_prefix(a.status_edge, ticket, ticket_edges, d, lane);
-        if (lane == 0) sh.base_edge = e;
+        if (lane == 63u) sh.wk[wave] = before + kincl;
     }
     __syncthreads();
-    const uint32_t rank0 = old ? r0 : n_old + sh.base_cnt;                       // row index of the ticket's first row
-    const uint32_t room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;          // how many of its rows fit (old rows: all)
-    uint64_t ebase = sampling ? sh.base_edge : 0ull;
+    uint32_t wk = lane < (uint32_t)kHopBlock / 64u ? sh.wk[lane] : 0u, wks = wave_incl_scan(wk);
+    const uint32_t ticket_edges = lane_value(wks, 63u);
+    if (tid == 0) chain_publish(a.status_edge, ticket, ticket_edges);
 
-    if (sampling) {
-        // ---- offsets scan + sample, 256 rows at a time.  A single batch of rows is still in LDS from above; several
-        // are redone (their loads hit the cache).
-        for (uint32_t q = 0; q < supers; ++q) {
-            const uint32_t c0 = q * kHopRows;
-            const uint32_t nrows = m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows;
-            const uint32_t keep = room > c0 ? (room - c0 < nrows ? room - c0 : nrows) : 0u;
-            if (supers > 1) {
-                fill_rows(c0);
-                (void)load_rows<OffT>(a, sh, nrows, tid);
-            }
-            uint32_t k = 0, kincl = 0;
-            if (wave < 4) {
-                k = (uint32_t)tid < keep ? sh.k[tid] : 0u; // dropped rows sample nothing
-                kincl = wave_incl_scan(k, lane);
-                if (lane == 63) sh.wsum[wave] = kincl;
-            }
+    // ---- sample and offsets scan, a batch of 1024 rows at a time, as many of them at once as their ids fit into LDS.  A single
+    // batch is still in LDS from above; several are redone (their loads hit the cache).  The first ids are loaded
+    // before the chains are asked for: what a ticket waits for longest - the ids, out of an array of gigabytes, and the
+    // tickets before it - it waits for once.  Marks are set behind the chains: rows beyond the cap leave none.
+    const uint32_t rpw = a.rows_per_wave, step = rpw * (uint32_t)(kHopBlock / 64);
+    const uint32_t stage_rows = a.stage_edges / (uint32_t)a.fanout;
+    uint32_t rank0 = r0, room = 0xFFFFFFFFu, ebase = 0;
+    bool chained = false;
+    auto take_prefixes = [&]() { // wavefront 0 sums up the new vertices before this tile, wavefront 1 the edges before this ticket
+        if (wave == 0u && !old) {
+            const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane);
+            if (lane == 0) sh.base_cnt = c;
+        }
+        if (wave == 1u) {
+            const uint32_t e = chain_prefix(a.status_edge, ticket, ticket_edges, d, (int)lane);
+            if (lane == 0) sh.base_edge = e;
+        }
+        __syncthreads();
+        if (!old) rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.base_cnt); // row index of the ticket's first row
+        room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;                                   // how many of its rows fit (old rows: all)
+        ebase = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.base_edge);
+        chained = true;
+    };
+    for (uint32_t q = 0; q < supers; ++q) {
+        const uint32_t c0 = q * kHopRows;
+        const uint32_t nrows = m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows;
+        if (supers > 1) {
+            if (q) __syncthreads(); // the last batch's rows have been read
+            fill_rows(c0);
+            k = load_rows<OffT>(a, sh, nrows, tid);
+            kincl = wave_incl_scan(k);
+            if (lane == 63u) sh.wk[wave] = kincl;
             __syncthreads();
-            uint32_t total = 0;
-            if (wave < 4) {
-                uint32_t wbase = 0;
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    if (w < wave) wbase += sh.wsum[w];
-                const uint32_t rp = (uint32_t)ebase + wbase + kincl - k;
-                sh.k[tid] = k;
-                sh.rp[tid] = rp;
-                if ((uint32_t)tid < keep) {
-                    a.row_ptr[rank0 + c0 + tid] = (int32_t)rp;
-                    if (!old) {
-                        const int32_t gid = sh.v[tid];
-                        a.S[rank0 + c0 + tid] = gid;
-                        a.local_id[gid] = (int32_t)(rank0 + c0 + tid);
-                    }
-                } else if ((uint32_t)tid < nrows) {
-                    a.local_id[sh.v[tid]] = -1;
-                }
+            wk = lane < (uint32_t)kHopBlock / 64u ? sh.wk[lane] : 0u;
+            wks = wave_incl_scan(wk);
+        }
+        const uint32_t batch_edges = lane_value(wks, 63u);
+        if (tid < nrows) sh.rp[tid] = lane_value(wks, wave) - lane_value(wk, wave) + kincl - k;
+        if (tid == 0) sh.rp[nrows] = batch_edges;
+        __syncthreads();
+        uint32_t keep = 0;
+        for (uint32_t b0 = 0; b0 < nrows; b0 += stage_rows) {
+            const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0];
+            for (uint32_t row0 = b0 + wave * rpw; row0 < b1; row0 += step) {
+                const Slot slot = resolve_slot(a, sh, key_lo, key_hi, row0, b1, lane);
+                if (slot.taken) s_ids[slot.edge - e0] = a.indices[slot.src];
             }
-            total = sh.wsum[0] + sh.wsum[1] + sh.wsum[2] + sh.wsum[3];
-            ebase += total;
-            for (uint32_t row0 = 0; row0 < keep; row0 += T) {
-                for (int x = tid; x < kSampleHashSlots; x += kHopBlock) sh.set[x] = 0xFFFFFFFFu;
+            if (!chained)
+                take_prefixes();
+            else
                 __syncthreads();
-                sample_pass(a, sh, key_lo, key_hi, row0, tid, lane);
-                __syncthreads(); // the set is reset by the next pass, the LDS rows are reused by the next batch
-            }
-        }
-    } else {
-        // ---- closing launch: ranks only
-        uint32_t j = lex;
-#pragma unroll
-        for (uint32_t r = 0; r < WPL; ++r) {
-            uint32_t x = nw[r];
-            while (x) {
-                const int b = __ffs((int)x) - 1;
-                x &= x - 1u;
-                const int32_t gid = (int32_t)((((uint32_t)w0 + r) << 5) + (uint32_t)b);
-                if (j < room) {
-                    a.S[rank0 + j] = gid;
-                    a.local_id[gid] = (int32_t)(rank0 + j);
-                } else {
-                    a.local_id[gid] = -1;
+            keep = room > c0 ? (room - c0 < nrows ? room - c0 : nrows) : 0u; // dropped rows sample nothing
+            const uint32_t e1 = keep > b0 ? sh.rp[keep < b1 ? keep : b1] : e0;
+            if (NEXT_BYTES) {
+                for (uint32_t e = e0 + tid; e < e1; e += (uint32_t)kHopBlock) {
+                    const uint32_t edge = ebase + e;
+                    if (edge < a.edge_cap) {
+                        const int32_t g = s_ids[e - e0];
+                        a.nbr[edge] = g;
+                        mark_byte(a, edge, g);
+                    }
                 }
-                ++j;
+            } else {
+                for (uint32_t f = e0; f < e1; f += (uint32_t)kHopBlock) {
+                    for (uint32_t x = tid; x < (uint32_t)kSampleHashSlots; x += (uint32_t)kHopBlock) s_set[x] = 0xFFFFFFFFu;
+                    __syncthreads();
+                    const uint32_t e = f + tid, edge = ebase + e;
+                    if (e < e1 && edge < a.edge_cap) {
+                        const int32_t g = s_ids[e - e0];
+                        a.nbr[edge] = g;
+                        mark_bit(a, s_set, edge, g);
+                    }
+                    if (f + (uint32_t)kHopBlock < e1) __syncthreads(); // the set is reset by the next pass
+                }
+            }
+            if (b1 < nrows) __syncthreads(); // the ids and the set are reused
+        }
+        if (tid < nrows) {
+            const int32_t gid = sh.v[tid];
+            if (tid < keep) {
+                a.row_ptr[rank0 + c0 + tid] = (int32_t)(ebase + sh.rp[tid]);
+                if (!old) {
+                    a.S[rank0 + c0 + tid] = gid;
+                    a.local_id[gid] = (int32_t)(rank0 + c0 + tid);
+                }
+            } else {
+                a.local_id[gid] = -1;
             }
         }
+        ebase += sh.rp[keep];
     }
+    if (!chained) take_prefixes(); // (a tile without a new vertex)
 
     if (old) {
-        if (first && ticket == t_old - 1 && tid == 0) { // launch 0 has no ranking tiles: the block ends with these rows
+        if (FIRST && ticket == t_old - 1u && tid == 0) { // launch 0 has no ranking tiles: the block ends with these rows
             a.row_ptr[n_old] = (int32_t)ebase;
-            d->E[a.launch] = (uint32_t)ebase;
+            d->E[a.launch] = ebase;
         }
         return;
     }
 
-    // ---- the kept vertices join "seen" (not after the last hop: nothing is sampled from them), consumed words are
-    // cleared for the hop after next; this lane is the only writer of its words during the launch
-    if (had) {
-        uint32_t left = lex < room ? room - lex : 0u; // how many of this lane's vertices are kept
+    if (m > room) {
+        // ---- the cap cuts into this tile: the vertices dropped leave "seen" again
 #pragma unroll
-        for (uint32_t r = 0; r < WPL; ++r)
-            if (had & (1u << r)) {
-                const uint32_t pc = __popc(nw[r]);
-                if (sampling && nw[r]) {
-                    const uint32_t keep = left >= pc ? nw[r] : lowest_set_bits(nw[r], left);
-                    if (keep) __hip_atomic_fetch_or(&a.seen[w0 + r], keep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); // no value comes back: nothing to wait for
+        for (int u = 0; u < R; ++u)
+            if (u * (uint32_t)kHopBlock + tid < np) {
+                const uint4 x = s_piece[u * kHopBlock + tid];
+                uint32_t j = lex[u];
+#pragma unroll
+                for (uint32_t c = 0; c < 4u; ++c) {
+                    const uint32_t w = piece_word(x, c), pc = __popc(w);
+                    const uint32_t kept = j < room ? lowest_set_bits(w, room - j) : 0u;
+                    if (kept != w) a.seen[tile0 + (u * (uint32_t)kHopBlock + tid) * 4u + c] &= ~(w & ~kept);
+                    j += pc;
                 }
-                left = left >= pc ? left - pc : 0u;
-                a.bitmap_prev[w0 + r] = 0u;
             }
     }
 
     // ---- end of the block: the tile in which the cap falls closes a truncated block; the last ticket publishes the
     // hop's sizes and, when everything fitted, closes the block
     if (tid == 0) {
-        if (sampling && rank0 <= a.cap_rows && (uint64_t)rank0 + m > a.cap_rows) {
+        if (rank0 <= a.cap_rows && (uint64_t)rank0 + m > a.cap_rows) {
             a.row_ptr[a.cap_rows] = (int32_t)ebase;
-            d->E[a.launch] = (uint32_t)ebase;
+            d->E[a.launch] = ebase;
         }
-        if (ticket == n_tickets - 1) {
+        if (ticket == n_tickets - 1u) {
             const uint64_t exact = (uint64_t)rank0 + m;
             d->n_exact[a.launch] = (uint32_t)exact;
             d->n[a.launch] = exact < a.cap_rows ? (uint32_t)exact : a.cap_rows;
             if (exact > a.cap_rows) {
                 atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
                 atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
-            } else if (sampling) {
+            } else {
                 a.row_ptr[exact] = (int32_t)ebase;
-                d->E[a.launch] = (uint32_t)ebase;
+                d->E[a.launch] = ebase;
             }
+        }
+    }
+}
+
+struct CloseRoles { // the closing launch's other workgroups
+    RelabelArgs rel; // the edges of hop H-2
+    RowArgs gat;     // the copy of the frontier's feature rows (their ids are final by now), if the step has no gather launch
+};
+
+// The closing launch: ranks the last hop's vertices, half a compute unit's lanes less per ticket than a sampling launch, tickets
+// first in the grid: chains of dependent accesses, they all start at once and leave most of the chip to the copy, which is
+// bound by bandwidth and runs beside them.  Measured at 110 M vertices, 433 k new ones and a copy of 157 k rows of 512 bytes
+// (160 MB, 34 us alone): 54 us; 1024 lanes per ticket, tickets and copy alternating in the grid: 56 us.  Without a copy,
+// 2.4 M vertices and 668 k new ones: 31 us; 137 k new: 21 us, with 1024 lanes 26 us.
+template <bool BYTES>
+__global__ __launch_bounds__(kCloseBlock) void k_close(HopArgs a, CloseRoles o)
+{
+    constexpr int R = kHopMaxTileWords / 4 / kCloseBlock;
+    constexpr uint32_t kBatch = 1024; // vertices expanded at a time
+    __shared__ uint32_t s_ticket, s_base, s_wsum[64];
+    __shared__ int32_t s_v[kBatch];
+    extern __shared__ __align__(16) uint32_t s_words[]; // byte marks: the tile's words
+    if (gate_closed(a.gate)) return;
+    if (blockIdx.x >= a.blocks) {
+        uint32_t b = blockIdx.x - a.blocks;
+        if (b < o.rel.blocks) {
+            relabel_block(o.rel, b);
+            return;
+        }
+        b -= o.rel.blocks;
+        if (o.gat.vec4)
+            gather_rows_block<4>(o.gat, b, s_v);
+        else
+            gather_rows_block<1>(o.gat, b, s_v);
+        return;
+    }
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    Drmb *d = a.drmb;
+    if (tid == 0) s_ticket = atomicAdd(&d->ticket[a.launch], 1u);
+    const uint32_t n_old = d->n[a.launch - 1];
+    __syncthreads();
+    const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_ticket); // (the grid holds no more tickets than tiles)
+    const uint32_t np = a.words_per_tile / 4u;
+    const size_t tile0 = (size_t)tile * a.words_per_tile;
+    uint4 x[R];
+    uint32_t lex[R];
+    load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
+    const uint32_t m = rank_pieces<kCloseBlock, R>(x, lex, s_wsum, np, wave, lane);
+    if (wave == 0u) {
+        if (lane == 0) chain_publish(a.status_cnt, tile, m);
+        const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane);
+        if (lane == 0) s_base = c;
+    }
+    uint32_t rank0 = 0, room = 0;
+    const bool tagged = BYTES && a.tag.shift != 0;
+    uint8_t *const bytes = reinterpret_cast<uint8_t *>(a.marks_prev);
+    for (uint32_t c0 = 0; c0 == 0 || c0 < m; c0 += kBatch) {
+        if (c0) __syncthreads(); // the last batch has been read
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (u * (uint32_t)kCloseBlock + tid < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + tid) * 4u, c0, kBatch, s_v);
+        __syncthreads();
+        rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_base);
+        room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;
+#pragma unroll
+        for (uint32_t i = 0; i < kBatch; i += kCloseBlock) {
+            const uint32_t j = c0 + i + tid;
+            if (j < m) {
+                const int32_t gid = s_v[i + tid];
+                uint32_t mark = 0u;
+                if (tagged) {
+                    mark = bytes[gid];
+                    bytes[gid] = 0;
+                }
+                if (j < room) a.S[rank0 + j] = gid;
+                a.local_id[gid] = j < room ? a.tag.entry(rank0 + j, mark) : -1;
+            }
+        }
+    }
+    if (tid == 0 && tile == a.rank_tiles - 1u) { // the last ticket publishes the hop's size
+        const uint64_t exact = (uint64_t)rank0 + m;
+        d->n_exact[a.launch] = (uint32_t)exact;
+        d->n[a.launch] = exact < a.cap_rows ? (uint32_t)exact : a.cap_rows;
+        if (exact > a.cap_rows) {
+            atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
+            atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
         }
     }
 }
@@ -1023,15 +1167,13 @@ __device__ __forceinline__ void aggregate_block(const RowArgs &a, uint32_t block
         const uint32_t c = (uint32_t)a.col[e_begin + t];
         const bool valid = c < n_in;
         s_col[t] = valid ? (int32_t)c : -1;
-        int32_t lid = -1;
         if (a.col_out) { // "relabel edges" of this block, done here: c is the sampled global id
-            lid = valid ? a.local_id[c] : -1;
+            const int32_t entry = valid ? a.local_id[c] : -1;
+            const int32_t lid = a.tag.local_id(entry);
             a.col_out[e_begin + t] = lid;
-        } else if (a.x_dst) {
-            lid = a.x_row[e_begin + t];
+            // one edge to a vertex writes its row of X, if the vertex is new (the frontier's rows are the gather's)
+            if (a.x_dst) s_dst[t] = lid >= (int32_t)n && (a.own ? a.own[e_begin + t] != 0 : a.tag.owns(entry, (uint32_t)(e_begin + (int32_t)t))) ? lid : -1;
         }
-        // the hop's first edge to a vertex writes its row of X, if the vertex is new (the frontier's rows are the gather's)
-        if (a.x_dst) s_dst[t] = (valid && a.own[e_begin + t] && lid >= (int32_t)n) ? lid : -1;
     }
     __syncthreads();
     if (a.x_dst)
@@ -1397,6 +1539,21 @@ int launch_aggregate(int vec, const RowArgs &agg, const FinishArgs &fa, hipStrea
     return ZG_OK;
 }
 
+// how the last hop's new vertices carry their marking edge's tag (all zero: they do not)
+MarkTag mark_tag(const zg_plan_t *p)
+{
+    const Layout &L = p->lay;
+    MarkTag t = {0, 0u};
+    if (!x_written_by_aggregation(p) || !L.byte_marks[L.num_hops - 1]) return t;
+    int lid_bits = 1;
+    while (lid_bits < 31 && ((int64_t)1 << lid_bits) < L.node_cap[L.num_hops]) ++lid_bits;
+    const int bits = std::min(7, 31 - lid_bits);
+    if (bits <= 0) return t; // no room for a tag: every edge to a new vertex writes its row
+    t.shift = 31 - bits;
+    t.mask = (1u << bits) - 1u;
+    return t;
+}
+
 // The step's two feature launches.  Two passes: the gather copies every row of S_{H-1} into X and the mean reads X.
 // One pass (and ZG_PLAN_FUSED_INPUT): the gather copies the rows of the frontier D_{H-1} only; the mean reads its input
 // rows from the table, addressed by the sampled global ids (feat[nbr_gid[e]] is the row X[col[e]] holds), and - unless
@@ -1420,7 +1577,8 @@ void step_feature_args(const zg_plan_t *p, RowArgs *gat, RowArgs *agg, int *vec)
     if (one_pass) {
         agg->x_dst = p->X();
         agg->ld_x = L.ld_out;
-        agg->own = p->own();
+        agg->own = L.byte_marks[H - 1] ? nullptr : p->own();
+        agg->tag = mark_tag(p);
     }
     if (fused || one_pass) agg->nt = 1;
     *gat = gather_args(p, p->d_feat, p->ld_feat, L.feat_dim, p->X(), L.ld_out, (fused || one_pass) ? H - 1 : H, &v2);
@@ -1440,6 +1598,23 @@ struct StepProbe {
     hipEvent_t before, after;
     hipError_t error; // what recording them returned (the step is enqueued either way)
 };
+
+template <typename OffT>
+void launch_hop(const HopArgs &ha, const HopRoles &o, unsigned grid, size_t lds, hipStream_t st)
+{
+    const dim3 g(grid), b(kHopBlock);
+    const bool prev = ha.bytes_prev != 0, next = ha.bytes_next != 0;
+    if (ha.launch == 0) {
+        if (next) hipLaunchKernelGGL((k_hop<OffT, true, false, true>), g, b, lds, st, ha, o);
+        else hipLaunchKernelGGL((k_hop<OffT, true, false, false>), g, b, lds, st, ha, o);
+    } else if (prev) {
+        if (next) hipLaunchKernelGGL((k_hop<OffT, false, true, true>), g, b, lds, st, ha, o);
+        else hipLaunchKernelGGL((k_hop<OffT, false, true, false>), g, b, lds, st, ha, o);
+    } else {
+        if (next) hipLaunchKernelGGL((k_hop<OffT, false, false, true>), g, b, lds, st, ha, o);
+        else hipLaunchKernelGGL((k_hop<OffT, false, false, false>), g, b, lds, st, ha, o);
+    }
+}
 
 // a whole step, in order, on one stream (captured once, or issued eagerly): the hop kernel's launches 0..H, then the
 // two feature launches.  With `gate` the kernels are those of gate's worst-case twin `p`, run on gate's inputs and
@@ -1468,21 +1643,29 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         ha.mailbox = gate ? gate->mailbox_dev : p->mailbox_dev;
         ha.S = p->S();
         ha.local_id = p->local_id();
-        ha.bitmap_prev = l > 0 ? p->bitmap(l - 1) : nullptr;
-        ha.bitmap_next = l < H ? p->bitmap(l) : nullptr;
+        ha.marks_prev = l > 0 ? p->bitmap(l - 1) : nullptr;
+        ha.marks_next = l < H ? p->bitmap(l) : nullptr;
         ha.seen = p->seen();
         ha.row_ptr = l < H ? p->row_ptr(l) : nullptr;
         ha.nbr = l < H ? p->nbr(l) : nullptr;
-        ha.own = (l == H - 1 && x_written_by_aggregation(p)) ? p->own() : nullptr;
+        ha.bytes_prev = l > 0 ? L.byte_marks[l - 1] : 0;
+        ha.bytes_next = l < H ? L.byte_marks[l] : 0;
+        if (l == H - 1 && x_written_by_aggregation(p)) {
+            ha.own = ha.bytes_next ? nullptr : p->own();
+            ha.tag_next = ha.bytes_next;
+        }
+        if (l == H) ha.tag = mark_tag(p);
         ha.status_cnt = p->status_cnt(l);
         ha.status_edge = p->status_edge(l);
+        ha.max_tickets = (uint32_t)L.max_tickets;
         ha.num_nodes = (uint32_t)g->num_nodes;
         ha.launch = l;
         ha.num_hops = H;
         ha.fanout = l < H ? L.fanout[l] : 1;
-        ha.group_log2 = sample_group_log2(ha.fanout);
+        ha.rows_per_wave = 64u / (uint32_t)ha.fanout;
+        ha.inv_fanout = 65536u / (uint32_t)ha.fanout + 1u;
         ha.replace = (p->flags & ZG_PLAN_REPLACE) ? 1 : 0;
-        ha.tiles_per_ticket = l < H ? (uint32_t)L.old_tpt[l] : 1u;
+        ha.rows_per_ticket = l < H ? (uint32_t)(sample_tile_nodes(L.fanout[l]) * L.old_tpt[l]) : 256u;
         ha.cap_rows = (uint32_t)L.node_cap[l];
         ha.edge_cap = l < H ? (uint32_t)L.edge_cap[l] : 0u;
         ha.words_per_tile = l > 0 ? (uint32_t)L.tile_words[l] : (uint32_t)kHopMinTileWords;
@@ -1504,26 +1687,29 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
             ia.num_nodes = (uint32_t)g->num_nodes;
             ia.blocks = (uint32_t)((p->batch + kHopBlock - 1) / kHopBlock);
         }
-        // the closing launch can carry the copy of the frontier's rows: D_{H-1} is final since launch H-1 (a workgroup
-        // of 1024 lanes takes four times the rows of the 256-lane gather, 256 at most: its ids sit in the LDS row slots)
-        RowArgs ga = no_rows;
-        if (l == H && ride) {
-            ga = gat;
-            ga.rows = std::min<uint32_t>(kHopRows, gat.rows * (kHopBlock / kBlock));
-            ga.blocks = (uint32_t)((L.node_cap[H - 1] + ga.rows - 1) / ga.rows);
-        }
-        const unsigned grid = ha.blocks + ra.blocks + ia.blocks + ga.blocks;
-        const bool fat = ha.words_per_tile > (uint32_t)kHopMaxTileWords; // a sparse ranking launch over a very long bitmap
-        if (g->offsets_dtype == ZG_I64) {
-            if (fat)
-                hipLaunchKernelGGL((k_hop<int64_t, kHopFatWordsPerLane>), dim3(grid), dim3(kHopBlock), 0, st, ha, ra, ia, ga);
+        if (l == H) {
+            // the closing launch can carry the copy of the frontier's rows: D_{H-1} is final since launch H-1
+            CloseRoles roles = {ra, ride ? gat : no_rows};
+            roles.gat.rows *= kCloseBlock / kBlock;
+            roles.gat.blocks = ride ? (uint32_t)((L.node_cap[H - 1] + roles.gat.rows - 1) / roles.gat.rows) : 0u;
+            const dim3 grid(ha.blocks + ra.blocks + roles.gat.blocks), block(kCloseBlock);
+            if (ha.bytes_prev)
+                hipLaunchKernelGGL(k_close<true>, grid, block, (size_t)ha.words_per_tile * 4, st, ha, roles);
             else
-                hipLaunchKernelGGL((k_hop<int64_t, kHopMaxWordsPerLane>), dim3(grid), dim3(kHopBlock), 0, st, ha, ra, ia, ga);
+                hipLaunchKernelGGL(k_close<false>, grid, block, 0, st, ha, roles);
         } else {
-            if (fat)
-                hipLaunchKernelGGL((k_hop<int32_t, kHopFatWordsPerLane>), dim3(grid), dim3(kHopBlock), 0, st, ha, ra, ia, ga);
+            const HopRoles roles = {ra, ia};
+            const unsigned grid = ha.blocks + ra.blocks + ia.blocks;
+            // The dynamic LDS: ids on their way, a bit-marking pass's dedup set, a ranking tile's words.  As many ids as leave room
+            // for two workgroups on a compute unit (a tile of 16 words per lane: one), at least 4096 - 64 rows of any fanout.
+            const size_t words = (l > 0 ? ha.words_per_tile : 0u) + (!ha.bytes_next ? (uint32_t)kSampleHashSlots : 0u);
+            const size_t room = kHopLdsBytes / 4 - sizeof(HopShared) / 4;
+            ha.stage_edges = (uint32_t)std::min<size_t>(kHopMaxStage, room > words + kHopMinStage ? (room - words) / 64 * 64 : kHopMinStage);
+            const size_t lds = (ha.stage_edges + words) * 4u;
+            if (g->offsets_dtype == ZG_I64)
+                launch_hop<int64_t>(ha, roles, grid, lds, st);
             else
-                hipLaunchKernelGGL((k_hop<int32_t, kHopMaxWordsPerLane>), dim3(grid), dim3(kHopBlock), 0, st, ha, ra, ia, ga);
+                launch_hop<int32_t>(ha, roles, grid, lds, st);
         }
         ZG_HIP(hipGetLastError());
     }
@@ -1610,8 +1796,8 @@ static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &
     if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_log, 0, (size_t)kLogCapacity * ZG_LOG_STRIDE * 4, st);
     if (init_scratch) {
         if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_seen, 0, (size_t)L.bitmap_words * 4, st);
-        if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_bitmap[0], 0, (size_t)L.bitmap_words * 4, st);
-        if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_bitmap[1], 0, (size_t)L.bitmap_words * 4, st);
+        if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_bitmap[0], 0, L.bitmap_bytes[0], st);
+        if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_bitmap[1], 0, L.bitmap_bytes[1], st);
         if (e == hipSuccess) e = hipMemsetAsync(p->ws + L.off_status, 0, L.status_words * 8, st);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);

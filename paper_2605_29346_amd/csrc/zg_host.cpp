@@ -222,44 +222,67 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
         if (L.edge_cap[h] >= (int64_t)1 << 31) return fail(ZG_EINVAL, "edge capacity of a hop reaches 2^31");
         pi.edge_cap[h] = L.edge_cap[h];
     }
+    // byte marks where the hop's edges are many enough for the graph: the caps bound them, and so does the model's frontier size
+    for (int h = 0; h < num_hops; ++h) {
+        double edges = (double)L.edge_cap[h];
+        if (!g->degrees.empty()) edges = std::min(edges, std::ceil(mean[h]) * fanouts[h]);
+        L.byte_marks[h] = (double)V <= (double)kByteMarkVerticesPerEdge * edges ? 1 : 0;
+    }
     {
         // Launch l of the hop kernel (l = 0..H) samples hop l for the rows of D_l and, for l > 0, first ranks the vertices
         // hop l-1 discovered.  Rows that were already in D_{l-1} come in tiles of 1024 / G rows, a ticket covering 1..4
-        // tiles (every ticket is one atomic on a shared counter, about 15 ns each on MI355X, hence the budget).  The
-        // discovered vertices come in ranking tiles: W consecutive words of the hop's bitmap per workgroup, W a power of
-        // two chosen so that a tile holds about one sampling pass (1024 / G vertices) of new rows at the cap, within the
-        // ticket budget and between 32 and 8192 words.
+        // tiles or more (every ticket is one atomic on a shared counter, about 13 ns each on MI355X, hence the budget).
+        // The discovered vertices come in ranking tiles: W consecutive words (32 vertices each) of the hop's marks per
+        // workgroup, so many that a tile holds about one sampling pass (1024 / G vertices) of new rows at the cap, within
+        // the ticket budget and between 32 and 8192 words.
         const int64_t words = (V + 31) / 32;
-        L.bitmap_words = (int64_t)align_up((size_t)words, (size_t)kHopFatTileWords);
+        L.max_tickets = max_tickets;
+        L.bitmap_words = (int64_t)align_up((size_t)words, (size_t)kHopFatTileWords) + kHopBlock; // (a last tile reaches < 1024 words past)
         for (int l = 0; l <= num_hops; ++l) {
             // The launch's tickets share one budget: workgroups beyond what the chip holds at once (two of 1024 lanes per
             // compute unit) only start when earlier ones have finished - a second round that doubles the launch's time.
             const int64_t rows = l == 0 ? batch : L.node_cap[l - 1];
             const int64_t T = l < num_hops ? sample_tile_nodes(fanouts[l]) : 256;
-            const int64_t fattest_old = l < num_hops ? (rows + 255) / 256 : 0; // old tickets if each took 256 rows
             if (l > 0) {
-                const int64_t budget = std::max<int64_t>(std::max<int64_t>(1, max_tickets / 2), max_tickets - fattest_old);
-                const int64_t want = std::max<int64_t>(1, std::min<int64_t>(budget, (L.node_cap[l] + T - 1) / T));
-                int64_t W = kHopMinTileWords;
+                // New and old rows share the budget in proportion.  Within it a sampling pass of rows per tile up to 160 tiles,
+                // then 320 rows per tile: a ticket costs 13 ns of the shared counter and a share of the look-backs, its rows only
+                // time of their own while there are few.  (15 k new rows: 245 tiles 18.4 us, 139 tiles 17.0 us; 33 k: 390 tiles
+                // 22.5 us, 204 tiles 19.8 us; 285 k: 256 tickets 79 us, 480 tickets 57 us.)  The closing launch only
+                // ranks: half the budget.  (137 k new vertices: 469 tickets 25 us, 235 tickets 21 us.)
+                const int64_t fresh = L.node_cap[l] - rows;
+                const int64_t share = (int64_t)((double)max_tickets * (double)fresh / (double)L.node_cap[l]);
+                const int64_t budget = std::max<int64_t>(1, l < num_hops ? std::max(max_tickets / 4, share) : max_tickets / 2);
+                const int64_t per_pass = std::min<int64_t>(160, (L.node_cap[l] + T - 1) / T);
+                const int64_t want = std::max<int64_t>(1, std::min(budget, std::max(per_pass, (L.node_cap[l] + 319) / 320)));
+                int64_t W = std::max<int64_t>(kHopMinTileWords, (int64_t)align_up((size_t)((words + want - 1) / want), kHopMinTileWords));
                 // A launch that samples for few rows over a very long bitmap (its tile count is set by the rows, not by the
                 // budget) takes tiles of 16 words per lane: half the tickets, each still about one sampling pass of rows.
-                // (At 110 M vertices: 210 instead of 420 tickets in the launch that ranks hop 0's ~9 k discoveries, -2 to -4 %
-                // step time; the same for a launch at the ticket budget doubles its rows per ticket and costs +16 %.)
-                const int64_t max_words = (l < num_hops && want < budget) ? kHopFatTileWords : kHopMaxTileWords;
-                while (W < max_words && W * want < words) W *= 2;
+                // (At 110 M vertices and 25 k rows: 27.5 us instead of 29.3 us; a launch whose tiles hold several passes of rows
+                // each loses more by the longer tickets, 53 -> 57 us with 157 k rows.  A byte-marked tile stays at 256 KB.)
+                const int64_t max_words = l < num_hops && 2 * ((L.node_cap[l] + T - 1) / T) < 3 * budget && !L.byte_marks[l - 1] ? kHopFatTileWords : kHopMaxTileWords;
+                if (W > kHopBlock) { // whole rounds of the workgroup beyond one word per lane
+                    W = kHopBlock;
+                    while (W < max_words && W * want < words) W *= 2;
+                }
                 L.tile_words[l] = (int32_t)W;
                 L.rank_tiles[l] = (words + W - 1) / W;
             }
             if (l < num_hops) {
                 L.old_tiles[l] = (rows + T - 1) / T;
                 L.old_tpt[l] = 1;
-                // (a ticket's rows are held in 256 LDS entries)
+                // (256 rows at most here; the kernel goes on to 1024 where the true row count asks for it)
                 while (L.old_tpt[l] < kHopMaxTpt && 2 * L.old_tpt[l] * T <= 256 &&
                        (L.old_tiles[l] + L.old_tpt[l] - 1) / L.old_tpt[l] + L.rank_tiles[l] > max_tickets)
                     L.old_tpt[l] *= 2;
                 L.old_tickets[l] = (L.old_tiles[l] + L.old_tpt[l] - 1) / L.old_tpt[l];
             }
         }
+    }
+
+    for (int b = 0; b < 2; ++b) {
+        bool bytes = false;
+        for (int h = b; h < num_hops; h += 2) bytes = bytes || L.byte_marks[h] != 0;
+        L.bitmap_bytes[b] = (size_t)L.bitmap_words * (bytes ? 32 : 4);
     }
 
     size_t off = 0;
@@ -294,18 +317,18 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
     L.off_own = place((size_t)L.edge_cap[num_hops - 1]);
     L.envelope_end = off;
     L.off_local_id = place((size_t)V * 4);
-    L.off_bitmap[0] = place((size_t)L.bitmap_words * 4); // the bitmap hop h fills is [h & 1]: launch h+1 ranks and clears it
-    L.off_bitmap[1] = place((size_t)L.bitmap_words * 4); // while its own sampling fills the other one
+    L.off_bitmap[0] = place(L.bitmap_bytes[0]); // the map hop h marks is [h & 1]: launch h+1 ranks and clears it
+    L.off_bitmap[1] = place(L.bitmap_bytes[1]); // while its own sampling marks the other one
     L.off_seen = place((size_t)L.bitmap_words * 4);
     L.status_words = 0;
-    for (int l = 0; l <= num_hops; ++l) L.status_words += 2 * ((size_t)L.old_tickets[l] + (size_t)L.rank_tiles[l]);
+    for (int l = 0; l <= num_hops; ++l) L.status_words += (size_t)L.rank_tiles[l] + (size_t)(L.old_tickets[l] + L.rank_tiles[l]);
     L.off_status = place(L.status_words * 8);
     size_t w = 0;
     for (int l = 0; l <= num_hops; ++l) {
-        const size_t n = (size_t)L.old_tickets[l] + (size_t)L.rank_tiles[l];
         L.off_status_cnt[l] = L.off_status + w * 8;
-        L.off_status_edge[l] = L.off_status + (w + n) * 8;
-        w += 2 * n;
+        w += (size_t)L.rank_tiles[l];
+        L.off_status_edge[l] = L.off_status + w * 8;
+        w += (size_t)(L.old_tickets[l] + L.rank_tiles[l]);
     }
     L.total = off;
 

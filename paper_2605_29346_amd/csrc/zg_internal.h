@@ -12,14 +12,21 @@
 namespace zg {
 
 constexpr int kBlock = 256;             // threads per workgroup (4 wavefronts of 64)
-constexpr int kHopBlock = 1024;         // threads per workgroup of the hop kernel: (1024 / G) vertices x G slots when it samples
-constexpr int kMaxTickets = 480;        // tickets per launch of the hop kernel: what 256 compute units hold at once (2 x 1024 lanes each), less a margin
-constexpr int kHopMaxTpt = 4;           // most consecutive tiles of frontier rows a workgroup takes per ticket
-constexpr int kHopMaxWordsPerLane = 8;  // bitmap words a lane owns in a ranking tile (held in registers)
+constexpr int kHopBlock = 1024;         // threads per workgroup of the hop kernel's sampling launches
+constexpr int kCloseBlock = 512;        // ... and of the closing launch, which only ranks
+constexpr int kMaxTickets = 480;       // tickets per launch of the hop kernel: what 256 compute units hold at once (2 x 1024 lanes each), less a margin
+constexpr int kHopMaxTpt = 4;           // most consecutive tiles of frontier rows the plan gives a ticket
+constexpr int kHopMaxWordsPerLane = 8;  // bitmap words of a ranking tile per lane of a 1024-lane workgroup
+constexpr size_t kHopLdsBytes = 78 << 10; // LDS of a sampling workgroup: half a compute unit's
+constexpr size_t kHopMinStage = 4096, kHopMaxStage = 12288; // sampled ids it holds at once
 constexpr int kHopMinTileWords = 32;    // smallest ranking tile: 32 words = 1024 vertices
 constexpr int kHopMaxTileWords = kHopBlock * kHopMaxWordsPerLane; // largest: 8192 words = 262144 vertices
 constexpr int kHopFatWordsPerLane = 16; // ... 16 in a launch whose tile count is set by its (few) rows, not by the ticket budget
 constexpr int kHopFatTileWords = kHopBlock * kHopFatWordsPerLane; // 16384 words = 524288 vertices
+// A hop that marks E of V vertices: bits cost E device-scope atomics (12-25 G/s on this chip whatever the address pattern, and
+// hubs serialise further), bytes cost E plain stores (50-150 G/s) and a map eight times as large to read back (5 TB/s).  The two
+// break even at V = 290 E at 15 and 60 G/s; the line is drawn below that because E is known from above only.
+constexpr int64_t kByteMarkVerticesPerEdge = 40;
 constexpr int kSampleHashBits = 11;      // LDS dedup set of a sampling workgroup: 2048 slots for <= 1024 ids
 constexpr int kSampleHashSlots = 1 << kSampleHashBits;
 constexpr uint64_t kGatherStreamBytes = 160ull << 20; // gathered matrices above this size are copied with non-temporal accesses
@@ -56,11 +63,14 @@ struct Layout {
     int64_t edge_cap[ZG_MAX_HOPS] = {};
     int32_t fanout[ZG_MAX_HOPS] = {};
     int64_t bitmap_words = 0; // padded to whole ranking tiles of the largest size
+    // how hop h records the vertices it reaches: 0 = a bit per vertex (atomicOr), 1 = a byte per vertex (plain stores)
+    int32_t byte_marks[ZG_MAX_HOPS] = {};
     // launch l = 0..H of the hop kernel samples hop l (l < H) and ranks the vertices that hop l-1 discovered (l > 0)
     int64_t old_tiles[ZG_MAX_HOPS] = {};        // launch l < H: tiles of 1024 / G rows of the previous frontier (cap)
     int32_t old_tpt[ZG_MAX_HOPS] = {};          // consecutive such tiles per ticket (1..kHopMaxTpt)
     int64_t old_tickets[ZG_MAX_HOPS + 1] = {};  // = ceil(tiles / tiles per ticket); 0 for launch H
-    int32_t tile_words[ZG_MAX_HOPS + 1] = {};   // launch l > 0: bitmap words per ranking tile (a power of two)
+    int32_t tile_words[ZG_MAX_HOPS + 1] = {};   // launch l > 0: bitmap words per ranking tile (a multiple of 32)
+    int64_t max_tickets = 0;                    // the budget the tiles were sized for
     int64_t rank_tiles[ZG_MAX_HOPS + 1] = {};   // launch l > 0: ranking tiles; 0 for launch 0
     // byte offsets into the workspace
     size_t off_drmb = 0, off_log = 0, off_S = 0;
@@ -68,8 +78,9 @@ struct Layout {
     size_t off_X = 0, off_agg = 0;
     size_t envelope_end = 0;
     size_t off_local_id = 0, off_bitmap[2] = {}, off_seen = 0, off_status = 0;
-    size_t off_own = 0; // last hop: per edge, whether it was the hop's first edge to reach its vertex
-    size_t status_words = 0; // uint64 words: per launch, one vertex-count chain and one edge-count chain over its tickets
+    size_t bitmap_bytes[2] = {}; // size of the two mark maps: a bit or a byte per vertex, whichever the hops that fill them need
+    size_t off_own = 0; // last hop, when it marks bits: per edge, whether it was the hop's first edge to reach its vertex
+    size_t status_words = 0; // uint64 words: per launch, one vertex-count chain over its ranking tiles and one edge-count chain over its tickets
     size_t off_status_cnt[ZG_MAX_HOPS + 1] = {}, off_status_edge[ZG_MAX_HOPS + 1] = {};
     size_t total = 0;
 };

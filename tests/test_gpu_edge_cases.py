@@ -201,3 +201,24 @@ def test_worked_example_from_the_published_known_answer(oracle):
         g = W.Graph(d + 1, torch.as_tensor(off), torch.arange(1, d + 1, dtype=torch.int32))
         _, res, _ = run_and_compare(oracle, g, None, np.array([0], dtype=np.int32), (1,), 0)
         assert res.nbr_gid[0].tolist() == [expect + 1] and res.S.tolist() == [0, expect + 1]
+
+
+@pytest.mark.parametrize("nodes,draws,batch,fanouts,max_tickets", [
+    (8000, 160_000, 40, (5, 5), 0),          # 200 edges of hop 0: at the line between byte and bit marks ...
+    (8001, 160_000, 40, (5, 5), 0),          # ... and one vertex beyond it (bits, then bytes)
+    (33, 400, 2, (3, 2, 2), 0),              # one word and a bit
+    (70_000, 1_400_000, 700, (11, 6), 0),    # ranking tiles of 32 k words that are no power of two, groups of 11 and 6 lanes
+    (40_000, 2_400_000, 1500, (64, 9), 1),   # one tile holds thousands of rows: several batches of 1024, each its ids in parts
+    (40_000, 2_400_000, 1500, (64, 9), 3),
+    (1_100_000, 2_000_000, 500, (10, 4), 2), # bits all the way, two rounds of words per tile
+])
+@pytest.mark.parametrize("replace", [False, True])
+def test_marks_tiles_and_batches_at_their_edges(oracle, nodes, draws, batch, fanouts, max_tickets, replace):
+    g = W.rmat_graph(nodes, draws, 5)
+    feat = W.feature_table(nodes, 8, 3)
+    og = to_host_graph(oracle, g)
+    pool = W.SeedPool(g, batch, 9)
+    plan = None
+    for s in range(3):
+        plan, _, _ = run_and_compare(oracle, g, feat, pool.batch_for(s).numpy(), fanouts, 900 + s, plan=plan, og=og, replace=replace,
+                                     env=zg.make_envelope(zg.ENV_MAX, flags=zg.PLAN_REPLACE if replace else 0, max_tickets=max_tickets))
