@@ -34,7 +34,9 @@ namespace zg {
 // =================================================================================================
 // device helpers
 // =================================================================================================
-typedef float v4f __attribute__((ext_vector_type(4)));
+// four floats moved as one access, at any float's address: the memory system takes 16 bytes at a 4-byte boundary in one
+// instruction, so rows of any width >= 4 and any stride go this way
+typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr uint64_t kStAggregate = 1ull << 62; // status word of a ticket: its total published ...
 constexpr uint64_t kStPrefix = 2ull << 62;    // ... or its inclusive prefix
@@ -301,10 +303,11 @@ struct RowArgs {
     int64_t ld_x;
     int64_t ld_src, ld_dst;
     uint64_t inv;
-    uint32_t dimv;
+    uint32_t dimv;          // pieces per row ...
+    uint32_t last;          // ... and the element at which the last one starts: the row's last four, which may overlap the piece before
     uint32_t rows;
     uint32_t max_fanout;
-    int32_t vec4;           // rows are moved in 16-byte pieces (else element by element)
+    int32_t vec4;           // rows are moved in pieces of four floats (else, below four, element by element)
     int32_t nt;             // aggregate inside a step: what it writes (means, rows of X) is stored past the caches (non-temporal)
     const int32_t *local_id; // aggregate that relabels its block's edges itself: the id map ...
     int32_t *col_out;        // ... and where col[e] = local id of nbr_gid[e] goes
@@ -339,7 +342,8 @@ __device__ __forceinline__ void gather_rows(const RowArgs &a, uint32_t row0, uin
                 r[u] = (uint32_t)(((uint64_t)e * a.inv) >> 32);
                 c[u] = e - r[u] * a.dimv;
                 const int32_t g = s_id[r[u]];
-                const T *src = reinterpret_cast<const T *>(a.src + (int64_t)g * a.ld_src + (int64_t)c[u] * VEC);
+                c[u] = c[u] * VEC < a.last ? c[u] * VEC : a.last;
+                const T *src = reinterpret_cast<const T *>(a.src + (int64_t)g * a.ld_src + c[u]);
                 val[u] = g >= 0 ? (STREAM ? __builtin_nontemporal_load(src) : *src) : VecOf<VEC>::zero();
             }
         }
@@ -347,7 +351,7 @@ __device__ __forceinline__ void gather_rows(const RowArgs &a, uint32_t row0, uin
         for (int u = 0; u < 4; ++u) {
             const uint32_t e = e0 + u * blockDim.x;
             if (e < total) {
-                T *dst = reinterpret_cast<T *>(a.dst + (int64_t)(row0 + r[u]) * a.ld_dst + (int64_t)c[u] * VEC);
+                T *dst = reinterpret_cast<T *>(a.dst + (int64_t)(row0 + r[u]) * a.ld_dst + c[u]);
                 if (STREAM || NT_STORE)
                     __builtin_nontemporal_store(val[u], dst);
                 else
@@ -1103,7 +1107,7 @@ __device__ __forceinline__ void aggregate_rows(const RowArgs &a, uint32_t row0, 
     const uint32_t total = rows * a.dimv;
     for (uint32_t e = threadIdx.x; e < total; e += kBlock) {
         const uint32_t r = (uint32_t)(((uint64_t)e * a.inv) >> 32);
-        const uint32_t c = e - r * a.dimv;
+        const uint32_t piece = (e - r * a.dimv) * VEC, c = piece < a.last ? piece : a.last; // the piece's first element
         const uint32_t b = (uint32_t)(s_rp[r] - e_begin);
         uint32_t k = (uint32_t)(s_rp[r + 1] - s_rp[r]);
         if (b + k > e_count) k = b < e_count ? e_count - b : 0;
@@ -1118,7 +1122,7 @@ __device__ __forceinline__ void aggregate_rows(const RowArgs &a, uint32_t row0, 
             for (uint32_t u = 0; u < 8; ++u) {
                 v[u] = VecOf<VEC>::zero();
                 if (cj[u] >= 0) {
-                    const T *src = reinterpret_cast<const T *>(a.src + (int64_t)cj[u] * a.ld_src + (int64_t)c * VEC);
+                    const T *src = reinterpret_cast<const T *>(a.src + (int64_t)cj[u] * a.ld_src + c);
                     v[u] = *src;
                 }
             }
@@ -1129,7 +1133,7 @@ __device__ __forceinline__ void aggregate_rows(const RowArgs &a, uint32_t row0, 
                     if (ONE_PASS) { // the hop's first edge to a new vertex copies the piece into X on the way
                         const int32_t dj = s_dst[b + j0 + u];
                         if (dj >= 0) {
-                            T *xd = reinterpret_cast<T *>(a.x_dst + (int64_t)dj * a.ld_x + (int64_t)c * VEC);
+                            T *xd = reinterpret_cast<T *>(a.x_dst + (int64_t)dj * a.ld_x + c);
                             if (NT)
                                 __builtin_nontemporal_store(v[u], xd);
                             else
@@ -1139,7 +1143,7 @@ __device__ __forceinline__ void aggregate_rows(const RowArgs &a, uint32_t row0, 
                 }
         }
         const T res = k > 0 ? acc / (float)k : VecOf<VEC>::zero();
-        T *out = reinterpret_cast<T *>(a.dst + (int64_t)(row0 + r) * a.ld_dst + (int64_t)c * VEC);
+        T *out = reinterpret_cast<T *>(a.dst + (int64_t)(row0 + r) * a.ld_dst + c);
         if (NT) // (the step does not read the means again either)
             __builtin_nontemporal_store(res, out);
         else
@@ -1408,8 +1412,6 @@ struct zg_plan_s {
 
 namespace {
 
-bool aligned16(const void *p, int64_t ld) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && (ld % 4) == 0; }
-
 RelabelArgs relabel_args(const zg_plan_t *p, int hop, bool present, const zg_plan_t *gate = nullptr)
 {
     RelabelArgs ra;
@@ -1468,13 +1470,11 @@ FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate =
     return fa;
 }
 
-RowArgs gather_args(const zg_plan_t *p, const float *d_feat, int64_t ld, int32_t dim, float *d_out, int64_t ld_out, int hop_rows,
-                    int *vec)
+RowArgs gather_args(const zg_plan_t *p, const float *d_feat, int64_t ld, int32_t dim, float *d_out, int64_t ld_out, int hop_rows)
 {
     RowArgs a;
     std::memset(&a, 0, sizeof(a));
-    const RowTiling t = gather_tiling(dim, *vec == 4);
-    *vec = t.vec;
+    const RowTiling t = gather_tiling(dim);
     a.src = d_feat;
     a.dst = d_out;
     a.S = p->S();
@@ -1483,6 +1483,8 @@ RowArgs gather_args(const zg_plan_t *p, const float *d_feat, int64_t ld, int32_t
     a.ld_dst = ld_out;
     a.inv = t.inv;
     a.dimv = t.dimv;
+    a.last = (uint32_t)(dim - t.vec);
+    a.vec4 = t.vec == 4 ? 1 : 0;
     a.rows = t.rows;
     a.blocks = (uint32_t)((p->lay.node_cap[hop_rows] + t.rows - 1) / t.rows);
     return a;
@@ -1490,12 +1492,11 @@ RowArgs gather_args(const zg_plan_t *p, const float *d_feat, int64_t ld, int32_t
 
 // input rows addressed by `col` (local ids, bounded by n[hop+1]) or, with by_gid, by nbr_gid (global ids into the table)
 RowArgs aggregate_args(const zg_plan_t *p, int hop, const float *d_in, int64_t ld_in, int32_t dim, float *d_out, int64_t ld_out,
-                       bool by_gid, int *vec)
+                       bool by_gid)
 {
     RowArgs a;
     std::memset(&a, 0, sizeof(a));
-    const RowTiling t = aggregate_tiling(dim, *vec == 4);
-    *vec = t.vec;
+    const RowTiling t = aggregate_tiling(dim);
     a.src = d_in;
     a.dst = d_out;
     a.row_ptr = p->row_ptr(hop);
@@ -1507,18 +1508,20 @@ RowArgs aggregate_args(const zg_plan_t *p, int hop, const float *d_in, int64_t l
     a.ld_dst = ld_out;
     a.inv = t.inv;
     a.dimv = t.dimv;
+    a.last = (uint32_t)(dim - t.vec);
+    a.vec4 = t.vec == 4 ? 1 : 0;
     a.rows = t.rows;
     a.max_fanout = (uint32_t)p->lay.fanout[hop];
     a.blocks = (uint32_t)((p->lay.node_cap[hop] + t.rows - 1) / t.rows);
     return a;
 }
 
-int launch_gather(int vec, const RowArgs &gat, const RelabelArgs &ra, hipStream_t st)
+int launch_gather(const RowArgs &gat, const RelabelArgs &ra, hipStream_t st)
 {
     const unsigned grid = gat.blocks + ra.blocks;
     if (grid == 0) return ZG_OK;
     const size_t lds = (size_t)kBlock * 4;
-    if (vec == 4)
+    if (gat.vec4)
         hipLaunchKernelGGL(k_gather<4>, dim3(grid), dim3(kBlock), lds, st, gat, ra);
     else
         hipLaunchKernelGGL(k_gather<1>, dim3(grid), dim3(kBlock), lds, st, gat, ra);
@@ -1526,12 +1529,12 @@ int launch_gather(int vec, const RowArgs &gat, const RelabelArgs &ra, hipStream_
     return ZG_OK;
 }
 
-int launch_aggregate(int vec, const RowArgs &agg, const FinishArgs &fa, hipStream_t st)
+int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, hipStream_t st)
 {
     const unsigned grid = agg.blocks + fa.blocks;
     if (grid == 0) return ZG_OK;
     const size_t lds = agg.blocks ? ((size_t)agg.rows + 1 + (size_t)agg.rows * agg.max_fanout * (agg.x_dst ? 2 : 1)) * 4 : 0;
-    if (vec == 4)
+    if (agg.vec4)
         hipLaunchKernelGGL(k_aggregate<4>, dim3(grid), dim3(kBlock), lds, st, agg, fa);
     else
         hipLaunchKernelGGL(k_aggregate<1>, dim3(grid), dim3(kBlock), lds, st, agg, fa);
@@ -1559,20 +1562,18 @@ MarkTag mark_tag(const zg_plan_t *p)
 // rows from the table, addressed by the sampled global ids (feat[nbr_gid[e]] is the row X[col[e]] holds), and - unless
 // ZG_PLAN_FUSED_INPUT leaves them out - writes the other rows of X, those of the last hop's newly discovered
 // vertices, on the way.
-void step_feature_args(const zg_plan_t *p, RowArgs *gat, RowArgs *agg, int *vec)
+void step_feature_args(const zg_plan_t *p, RowArgs *gat, RowArgs *agg)
 {
     const Layout &L = p->lay;
     const int H = L.num_hops;
-    *vec = aligned16(p->d_feat, p->ld_feat) && aligned16(p->X(), L.ld_out) && aligned16(p->agg(), L.ld_out) ? 4 : 1;
-    int v1 = *vec, v2 = *vec;
     const bool fused = (p->flags & ZG_PLAN_FUSED_INPUT) != 0, one_pass = x_written_by_aggregation(p);
     if (fused || one_pass) {
-        *agg = aggregate_args(p, H - 1, p->d_feat, p->ld_feat, L.feat_dim, p->agg(), L.ld_out, true, &v1);
+        *agg = aggregate_args(p, H - 1, p->d_feat, p->ld_feat, L.feat_dim, p->agg(), L.ld_out, true);
         // the aggregation relabels the last hop's edges itself (it holds their sampled ids anyway): no launch in between
         agg->local_id = p->local_id();
         agg->col_out = p->col(H - 1);
     } else {
-        *agg = aggregate_args(p, H - 1, p->X(), L.ld_out, L.feat_dim, p->agg(), L.ld_out, false, &v1);
+        *agg = aggregate_args(p, H - 1, p->X(), L.ld_out, L.feat_dim, p->agg(), L.ld_out, false);
     }
     if (one_pass) {
         agg->x_dst = p->X();
@@ -1581,9 +1582,7 @@ void step_feature_args(const zg_plan_t *p, RowArgs *gat, RowArgs *agg, int *vec)
         agg->tag = mark_tag(p);
     }
     if (fused || one_pass) agg->nt = 1;
-    *gat = gather_args(p, p->d_feat, p->ld_feat, L.feat_dim, p->X(), L.ld_out, (fused || one_pass) ? H - 1 : H, &v2);
-    *vec = v1; // both tilings take the same vector width for the same dim and alignment
-    gat->vec4 = agg->vec4 = *vec == 4 ? 1 : 0;
+    *gat = gather_args(p, p->d_feat, p->ld_feat, L.feat_dim, p->X(), L.ld_out, (fused || one_pass) ? H - 1 : H);
 }
 
 // whether the step has no gather launch of its own: the frontier's rows are copied by workgroups of the closing hop-kernel
@@ -1631,8 +1630,7 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
     std::memset(&agg, 0, sizeof(agg));
     std::memset(&gat, 0, sizeof(gat));
     std::memset(&no_rows, 0, sizeof(no_rows));
-    int vec = 1;
-    if (feats) step_feature_args(p, &gat, &agg, &vec);
+    if (feats) step_feature_args(p, &gat, &agg);
     for (int l = 0; l <= H; ++l) {
         HopArgs ha;
         std::memset(&ha, 0, sizeof(ha));
@@ -1716,11 +1714,11 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
     // the tail: {gather + relabel of the last hop} - unless both ride along elsewhere -, then {aggregation + end-of-step
     // clean-up}.  (One launch for all four roles was measured: no gain - the two big roles are bound by the same memory fabric.)
     if (!ride) {
-        int rc = launch_gather(vec, gat, relabel_args(p, H - 1, true, gate), st);
+        int rc = launch_gather(gat, relabel_args(p, H - 1, true, gate), st);
         if (rc != ZG_OK) return rc;
     }
     if (probe) probe->error = hipEventRecord(probe->before, st);
-    int rc = launch_aggregate(vec, agg, finish_args(p, true, gate, defer_completed), st);
+    int rc = launch_aggregate(agg, finish_args(p, true, gate, defer_completed), st);
     if (rc == ZG_OK && probe && probe->error == hipSuccess) probe->error = hipEventRecord(probe->after, st);
     return rc;
 }
@@ -1977,11 +1975,10 @@ int zg_plan_replay_features(zg_plan_t *p, int32_t which, void *stream)
     if (!p->d_feat || p->lay.feat_dim <= 0) return fail(ZG_ESTATE, "no feature table is bound to the plan");
     if (which != 0 && which != 1) return fail(ZG_EINVAL, "which must be 0 (gather) or 1 (aggregation)");
     RowArgs gat, agg;
-    int vec = 1;
-    step_feature_args(p, &gat, &agg, &vec);
+    step_feature_args(p, &gat, &agg);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (which == 0) return launch_gather(vec, gat, relabel_args(p, 0, false), st);
-    return launch_aggregate(vec, agg, finish_args(p, false), st);
+    if (which == 0) return launch_gather(gat, relabel_args(p, 0, false), st);
+    return launch_aggregate(agg, finish_args(p, false), st);
 }
 
 int zg_pilot_update(const zg_plan_t *p, int64_t *largest, void *stream)
@@ -2158,9 +2155,8 @@ int zg_gather(zg_plan_t *p, const float *d_feat, int64_t ld, int32_t dim, float 
 {
     if (!p || !d_feat || !d_out) return fail(ZG_EINVAL, "null argument");
     if (dim < 1 || dim > 32768 || ld < dim || ld_out < dim) return fail(ZG_EINVAL, "dim outside 1..32768 or a row stride < dim");
-    int vec = aligned16(d_feat, ld) && aligned16(d_out, ld_out) ? 4 : 1;
-    const RowArgs gat = gather_args(p, d_feat, ld, dim, d_out, ld_out, p->lay.num_hops, &vec);
-    return launch_gather(vec, gat, relabel_args(p, 0, false), static_cast<hipStream_t>(stream));
+    const RowArgs gat = gather_args(p, d_feat, ld, dim, d_out, ld_out, p->lay.num_hops);
+    return launch_gather(gat, relabel_args(p, 0, false), static_cast<hipStream_t>(stream));
 }
 
 int zg_aggregate_mean(zg_plan_t *p, int32_t hop, const float *d_in, int64_t ld_in, int32_t dim, float *d_out, int64_t ld_out,
@@ -2169,9 +2165,8 @@ int zg_aggregate_mean(zg_plan_t *p, int32_t hop, const float *d_in, int64_t ld_i
     if (!p || !d_in || !d_out) return fail(ZG_EINVAL, "null argument");
     if (hop < 0 || hop >= p->lay.num_hops) return fail(ZG_EINVAL, "hop out of range");
     if (dim < 1 || dim > 32768 || ld_in < dim || ld_out < dim) return fail(ZG_EINVAL, "dim outside 1..32768 or a row stride < dim");
-    int vec = aligned16(d_in, ld_in) && aligned16(d_out, ld_out) ? 4 : 1;
-    const RowArgs agg = aggregate_args(p, hop, d_in, ld_in, dim, d_out, ld_out, false, &vec);
-    return launch_aggregate(vec, agg, finish_args(p, false), static_cast<hipStream_t>(stream));
+    const RowArgs agg = aggregate_args(p, hop, d_in, ld_in, dim, d_out, ld_out, false);
+    return launch_aggregate(agg, finish_args(p, false), static_cast<hipStream_t>(stream));
 }
 
 int zg_overflow_flag(const zg_plan_t *p, const uint32_t **d_flag)

@@ -22,19 +22,19 @@ int fail(int status, const std::string &msg)
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-RowTiling gather_tiling(int32_t dim, bool aligned16)
+RowTiling gather_tiling(int32_t dim)
 {
     RowTiling t;
-    t.vec = (aligned16 && dim % 4 == 0) ? 4 : 1;
-    t.dimv = (uint32_t)(dim / t.vec);
+    t.vec = dim >= 4 ? 4 : 1;
+    t.dimv = (uint32_t)((dim + t.vec - 1) / t.vec);
     t.inv = ((1ull << 32) + t.dimv - 1) / t.dimv;
     t.rows = std::max<uint32_t>(1, std::min<uint32_t>(kBlock, 2048u / t.dimv));
     return t;
 }
 
-RowTiling aggregate_tiling(int32_t dim, bool aligned16)
+RowTiling aggregate_tiling(int32_t dim)
 {
-    RowTiling t = gather_tiling(dim, aligned16);
+    RowTiling t = gather_tiling(dim);
     // one (row, piece) pair per lane: small workgroups, many of them, hide the staging of the block's edges best
     // (measured at 128- and 600-float rows: 256 pairs per workgroup 86 / 41 us, 512 pairs 91 / 42, 1024 pairs 101 / 44).
     // Filling the lanes better for widths that leave many idle (five 600-float rows = 750 pairs instead of one = 150 of 256
@@ -342,7 +342,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
     }
     pi.grid_compact = (int32_t)L.rank_tiles[num_hops];
     if (feat_dim > 0) {
-        RowTiling tg = gather_tiling(feat_dim, true), ta = aggregate_tiling(feat_dim, true);
+        RowTiling tg = gather_tiling(feat_dim), ta = aggregate_tiling(feat_dim);
         pi.grid_gather = (int32_t)((L.x_rows + tg.rows - 1) / tg.rows);
         pi.grid_aggregate = (int32_t)((L.node_cap[num_hops - 1] + ta.rows - 1) / ta.rows);
     }

@@ -95,15 +95,15 @@ int compute_layout(const zg_graph_t *g, const int32_t *fanouts, int32_t num_hops
 
 // launch shapes of the feature kernels for a row of `dim` floats
 struct RowTiling {
-    int vec;            // floats per lane access: 4 when rows are 16-byte aligned, else 1
-    uint32_t dimv;      // dim / vec
+    int vec;            // floats per lane access: 4, or 1 for rows of fewer
+    uint32_t dimv;      // accesses per row
     uint64_t inv;       // ceil(2^32 / dimv): e / dimv == (e * inv) >> 32 for the small e used
     uint32_t rows;      // rows per workgroup
 };
 int sample_group_log2(int fanout);
 int64_t sample_tile_nodes(int fanout);
-RowTiling gather_tiling(int32_t dim, bool aligned16);
-RowTiling aggregate_tiling(int32_t dim, bool aligned16);
+RowTiling gather_tiling(int32_t dim);
+RowTiling aggregate_tiling(int32_t dim);
 
 // synchronising device-side check of the CSR arrays (indices in range, rows strictly ascending)
 int validate_graph_device(const zg_graph_t *g);

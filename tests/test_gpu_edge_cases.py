@@ -222,3 +222,39 @@ def test_marks_tiles_and_batches_at_their_edges(oracle, nodes, draws, batch, fan
     for s in range(3):
         plan, _, _ = run_and_compare(oracle, g, feat, pool.batch_for(s).numpy(), fanouts, 900 + s, plan=plan, og=og, replace=replace,
                                      env=zg.make_envelope(zg.ENV_MAX, flags=zg.PLAN_REPLACE if replace else 0, max_tickets=max_tickets))
+
+
+@pytest.mark.parametrize("dim", [3, 4, 5, 7, 75, 102])
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+def test_rows_at_any_float_boundary(oracle, dim, shift):
+    # a table whose rows start at any multiple of four bytes (a column slice of a wider one): pieces of four floats, the last one
+    # reaching back over the one before; through the step (one pass and two) and the stand-alone entry points
+    g = W.rmat_graph(6000, 90_000, 3)
+    feat = W.feature_table(6000, dim, 4)
+    og = to_host_graph(oracle, g)
+    seeds = W.SeedPool(g, 90, 2).batch_for(0).numpy()
+    ref = og.sample_blocks(seeds, (6, 4), 11)
+    wide = torch.full((6000, dim + 5), 1e30, device="cuda")
+    table = wide[:, shift: shift + dim]
+    table.copy_(feat)
+    dg = zg.Graph(g.offsets.cuda(), g.indices.cuda())
+    X_ref = oracle.gather(feat.numpy(), ref.S)
+    for flags in (0, zg.PLAN_X_TWO_PASS, zg.PLAN_FUSED_INPUT):
+        plan = zg.Plan(dg, (6, 4), 90, zg.make_envelope(zg.ENV_MAX, flags=flags), feat_dim=dim)
+        plan.bind_features(table)
+        plan.step(torch.as_tensor(seeds).cuda(), 11)
+        res = plan.read_step()
+        compare_blocks(res, ref, f"flags {flags}")
+        assert np.array_equal(res.X, X_ref[: res.X.shape[0]])
+        agg_ref = oracle.aggregate_mean(ref.row_ptr[-1], ref.col[-1], X_ref)
+        assert agg_error(oracle, res.agg, agg_ref, ref.row_ptr[-1], ref.col[-1], X_ref) <= 1e-5
+    out = torch.full((res.n[2] + 1, dim + 5), -7.0, device="cuda")
+    plan.gather(table, out[:, shift: shift + dim])
+    mean = torch.full((res.n[1] + 1, dim + 5), -7.0, device="cuda")
+    plan.aggregate_mean(1, out[:, shift: shift + dim], mean[:, 3 - shift: 3 - shift + dim])
+    torch.cuda.synchronize()
+    assert np.array_equal(out[: res.n[2], shift: shift + dim].cpu().numpy(), X_ref)
+    for t, c0, rows in ((out, shift, res.n[2]), (mean, 3 - shift, res.n[1])):  # nothing around the rows is touched
+        assert bool((t[:, :c0] == -7.0).all()) and bool((t[:, c0 + dim:] == -7.0).all()) and bool((t[rows:] == -7.0).all())
+    got = mean[: res.n[1], 3 - shift: 3 - shift + dim].cpu().numpy()
+    assert agg_error(oracle, got, agg_ref, ref.row_ptr[-1], ref.col[-1], X_ref) <= 1e-5
