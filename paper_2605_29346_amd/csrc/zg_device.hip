@@ -199,19 +199,44 @@ struct IngestArgs {
 // of the step's dependency chain; when the host runs ahead of the device - the normal case in a training loop - the
 // previous step has already copied this step's slot into the metadata buffer (prefetch_step_inputs) and the read
 // stays in device memory.  Otherwise: the mailbox slot of the device-side step counter.
-__device__ __forceinline__ void read_step_inputs(const Drmb *d, const Drmb *gate, const Mailbox *mailbox, unsigned long long *out)
+__device__ __forceinline__ bool prefetched_inputs(const Drmb *d, const Drmb *gate, unsigned long long *out)
 {
-    // (all of it on its way at once: the branch below would make two round trips of it)
+    // (all of it on its way at once: a branch in between would make two round trips of it)
     const uint32_t valid = d->pre_valid, pre_epoch = d->pre_epoch, epoch = d->epoch;
-    const unsigned long long pre_seeds = d->pre_seeds, pre_key = d->pre_key;
-    if (!gate && valid && pre_epoch == epoch) {
-        out[0] = pre_seeds;
-        out[1] = pre_key;
-        return;
-    }
+    out[0] = d->pre_seeds;
+    out[1] = d->pre_key;
+    return !gate && valid && pre_epoch == epoch;
+}
+
+__device__ __forceinline__ void mailbox_inputs(const Drmb *d, const Drmb *gate, const Mailbox *mailbox, unsigned long long *out)
+{
     const uint32_t slot = (gate ? gate->epoch - 1u : d->epoch) % kMailboxSlots;
     out[0] = __hip_atomic_load(&mailbox->slot[slot].seeds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     out[1] = __hip_atomic_load(&mailbox->slot[slot].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// One lane of a ticket, where nothing was prefetched (the host waits for every step, or this is the first): ticket 0 reads the
+// mailbox and passes the inputs on in device memory.  Reads of host memory queue up: 132 workgroups that each read the
+// slot took 20 us.  Ticket 0's workgroup runs before any other ticket is handed out; a wait that runs out reads the mailbox itself.
+__device__ __forceinline__ void shared_inputs(Drmb *d, const Drmb *gate, const Mailbox *mailbox, uint32_t ticket, unsigned long long *out)
+{
+    const uint32_t tag = d->epoch + 1u;
+    if (ticket != 0u) {
+        for (uint32_t spins = 0; spins < kSpinLimit; ++spins) {
+            if (__hip_atomic_load(&d->cur_epoch, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == tag) {
+                out[0] = __hip_atomic_load(&d->cur_seeds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                out[1] = __hip_atomic_load(&d->cur_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    mailbox_inputs(d, gate, mailbox, out);
+    if (ticket == 0u) {
+        __hip_atomic_store(&d->cur_seeds, out[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&d->cur_key, out[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&d->cur_epoch, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // Step entry ("ingest"): seeds -> D_0 (caller's order), their local ids and "seen" bits; step key and batch size ->
@@ -220,7 +245,7 @@ __device__ __forceinline__ void read_step_inputs(const Drmb *d, const Drmb *gate
 __device__ __forceinline__ void ingest_block(const IngestArgs &a, uint32_t block, unsigned long long *s_in)
 {
     const uint32_t gtid = block * blockDim.x + threadIdx.x;
-    if (threadIdx.x == 0) read_step_inputs(a.drmb, a.gate, a.mailbox, s_in); // one read of the host-resident slot per workgroup
+    if (threadIdx.x == 0 && !prefetched_inputs(a.drmb, a.gate, s_in)) mailbox_inputs(a.drmb, a.gate, a.mailbox, s_in); // (a workgroup per 1024 seeds)
     __syncthreads();
     const int32_t *seeds = reinterpret_cast<const int32_t *>(s_in[0]);
     if (gtid == 0) {
@@ -442,6 +467,7 @@ struct HopShared {
     uint32_t ticket;
     uint32_t base_cnt;
     uint32_t base_edge;
+    bool have_in;
     unsigned long long in[2];
     uint32_t wsum[64];                 // per round of the tile's words and wavefront: new vertices
     uint32_t wk[kHopBlock / 64];
@@ -714,7 +740,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     Drmb *d = a.drmb;
     if (tid == 0) sh.ticket = atomicAdd(&d->ticket[a.launch], 1u);
-    if (FIRST && tid == 64) read_step_inputs(d, a.gate, a.mailbox, sh.in);
+    if (FIRST && tid == 64) sh.have_in = prefetched_inputs(d, a.gate, sh.in);
     const uint32_t n_old = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while the ticket comes back)
     const uint32_t key_lo_d = FIRST ? 0u : d->key_lo, key_hi_d = FIRST ? 0u : d->key_hi;
     __syncthreads();
@@ -727,6 +753,10 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     const uint32_t t_old = (n_old + rows - 1u) / rows;
     const uint32_t n_tickets = t_old + (FIRST ? 0u : a.rank_tiles);
     if (ticket >= n_tickets) return;
+    if (FIRST && !sh.have_in) {
+        if (tid == 0) shared_inputs(d, a.gate, a.mailbox, ticket, sh.in);
+        __syncthreads();
+    }
     const bool old = FIRST || ticket < t_old; // uniform over the workgroup
     const uint32_t key_lo = FIRST ? (uint32_t)(sh.in[1] & 0xFFFFFFFFull) : key_lo_d;
     const uint32_t key_hi = FIRST ? (uint32_t)(sh.in[1] >> 32) : key_hi_d;

@@ -51,6 +51,8 @@ struct Drmb {
     uint32_t active;                   // ZG_PLAN_AUTO_FALLBACK: 1 when the last step's valid outputs are the twin's
     uint32_t pre_valid, pre_epoch;     // the next step's inputs, copied from the host mailbox ahead of time: valid for step pre_epoch
     unsigned long long pre_seeds, pre_key;
+    unsigned long long cur_seeds, cur_key; // this step's inputs, where they had to be read from the mailbox: valid once cur_epoch is the step's number + 1
+    uint32_t cur_epoch;
 };
 
 struct Layout {
