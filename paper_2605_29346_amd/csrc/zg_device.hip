@@ -958,6 +958,162 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     }
 }
 
+// A small step's sampling, all hops of it in one workgroup: what the hop launches do, with the marks and "seen" as bitmaps in
+// LDS and barriers where they have launches and chained scans.  Outputs are the same; the global marks, "seen" and scan state
+// stay zero.  The last hop is relabeled by the launch that follows, the others here.
+struct SmallArgs {
+    HopArgs hop;     // what does not depend on the hop
+    int32_t *row_ptr[ZG_MAX_HOPS], *nbr[ZG_MAX_HOPS], *col[ZG_MAX_HOPS];
+    uint32_t fanout[ZG_MAX_HOPS], edge_cap[ZG_MAX_HOPS];
+    uint32_t cap[ZG_MAX_HOPS + 1];
+    uint32_t words;  // of a bitmap, a multiple of 32
+};
+
+template <typename OffT>
+__global__ __launch_bounds__(kHopBlock) void k_small(SmallArgs s)
+{
+    constexpr int R = kSmallMaxWords / 4 / kHopBlock; // rounds of a bitmap's pieces
+    __shared__ HopShared sh;
+    extern __shared__ __align__(16) uint32_t s_dyn[]; // the sampled ids on their way, the hop's marks, "seen"
+    if (gate_closed(s.hop.gate)) return;
+    HopArgs a = s.hop;
+    int32_t *const s_ids = reinterpret_cast<int32_t *>(s_dyn);
+    uint32_t *const s_marks = s_dyn + a.stage_edges, *const s_seen = s_marks + s.words;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    Drmb *d = a.drmb;
+    if (tid == 0 && !prefetched_inputs(d, a.gate, sh.in)) mailbox_inputs(d, a.gate, a.mailbox, sh.in);
+    for (uint32_t w = tid; w < 2u * s.words; w += (uint32_t)kHopBlock) s_marks[w] = 0u;
+    __syncthreads();
+    const int32_t *seeds = reinterpret_cast<const int32_t *>(sh.in[0]);
+    const uint32_t key_lo = (uint32_t)(sh.in[1] & 0xFFFFFFFFull), key_hi = (uint32_t)(sh.in[1] >> 32);
+    if (tid == 0) {
+        d->n[0] = a.batch;
+        d->n_exact[0] = a.batch;
+        d->key_lo = key_lo;
+        d->key_hi = key_hi;
+    }
+    for (uint32_t i = tid; i < a.batch; i += (uint32_t)kHopBlock) {
+        int32_t v = seeds[i];
+        if ((uint32_t)v >= a.num_nodes) {
+            atomicOr(&d->flags, ZG_FLAG_SEED_RANGE);
+            atomicOr(&d->step_flags, ZG_FLAG_SEED_RANGE);
+            v = -1;
+        } else {
+            const uint32_t bit = 1u << (v & 31);
+            if (atomicOr(&s_seen[(uint32_t)v >> 5], bit) & bit) {
+                atomicOr(&d->flags, ZG_FLAG_SEED_DUP);
+                atomicOr(&d->step_flags, ZG_FLAG_SEED_DUP);
+            }
+            a.local_id[v] = (int32_t)i;
+        }
+        a.S[i] = v;
+    }
+    uint32_t n = a.batch;
+    for (int h = 0; h < a.num_hops; ++h) {
+        a.launch = h;
+        a.fanout = (int32_t)s.fanout[h];
+        a.rows_per_wave = 64u / s.fanout[h];
+        a.inv_fanout = 65536u / s.fanout[h] + 1u;
+        int32_t *const row_ptr = s.row_ptr[h], *const nbr = s.nbr[h];
+        uint8_t *const own = h == a.num_hops - 1 ? a.own : nullptr;
+        const uint32_t rpw = a.rows_per_wave, step = rpw * (uint32_t)(kHopBlock / 64), stage_rows = a.stage_edges / s.fanout[h];
+        uint32_t ebase = 0;
+        for (uint32_t c0 = 0; c0 < n; c0 += kHopRows) {
+            const uint32_t nrows = n - c0 < (uint32_t)kHopRows ? n - c0 : (uint32_t)kHopRows;
+            __syncthreads(); // S is written, the last batch's rows have been read
+            if (tid < nrows) sh.v[tid] = a.S[c0 + tid];
+            const uint32_t k = load_rows<OffT>(a, sh, nrows, (int)tid), kincl = wave_incl_scan(k);
+            if (lane == 63u) sh.wk[wave] = kincl;
+            __syncthreads();
+            const uint32_t wk = lane < (uint32_t)kHopBlock / 64u ? sh.wk[lane] : 0u, wks = wave_incl_scan(wk);
+            const uint32_t batch_edges = lane_value(wks, 63u);
+            if (tid < nrows) {
+                const uint32_t rp = lane_value(wks, wave) - lane_value(wk, wave) + kincl - k;
+                sh.rp[tid] = rp;
+                row_ptr[c0 + tid] = (int32_t)(ebase + rp);
+            }
+            if (tid == 0) sh.rp[nrows] = batch_edges;
+            __syncthreads();
+            for (uint32_t b0 = 0; b0 < nrows; b0 += stage_rows) {
+                const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0], e1 = sh.rp[b1];
+                for (uint32_t row0 = b0 + wave * rpw; row0 < b1; row0 += step) {
+                    const Slot slot = resolve_slot(a, sh, key_lo, key_hi, row0, b1, (int)lane);
+                    if (slot.taken) s_ids[slot.edge - e0] = a.indices[slot.src];
+                }
+                __syncthreads();
+                for (uint32_t e = e0 + tid; e < e1; e += (uint32_t)kHopBlock) {
+                    const uint32_t edge = ebase + e;
+                    if (edge < s.edge_cap[h]) {
+                        const int32_t g = s_ids[e - e0];
+                        nbr[edge] = g;
+                        bool mine = false; // the hop's first edge to reach the vertex: see mark_bit
+                        if ((uint32_t)g < a.num_nodes) {
+                            const uint32_t bit = 1u << (g & 31);
+                            mine = (atomicOr(&s_marks[(uint32_t)g >> 5], bit) & bit) == 0u;
+                        }
+                        if (own) own[edge] = mine ? 1 : 0;
+                    }
+                }
+                if (b1 < nrows) __syncthreads(); // the ids are reused
+            }
+            ebase += batch_edges;
+        }
+        __syncthreads();
+        // rank the hop's new vertices, in ascending id behind D_h
+        uint4 x[R];
+        uint32_t lex[R];
+        const uint32_t np = s.words / 4u, room = s.cap[h + 1] - n;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const uint32_t q = u * (uint32_t)kHopBlock + tid;
+            x[u] = make_uint4(0u, 0u, 0u, 0u);
+            if (q < np) {
+                x[u] = reinterpret_cast<const uint4 *>(s_marks)[q];
+                if (piece_any(x[u])) {
+                    const uint4 sn = reinterpret_cast<const uint4 *>(s_seen)[q];
+                    reinterpret_cast<uint4 *>(s_marks)[q] = make_uint4(0u, 0u, 0u, 0u);
+                    x[u].x &= ~sn.x, x[u].y &= ~sn.y, x[u].z &= ~sn.z, x[u].w &= ~sn.w;
+                }
+            }
+        }
+        const uint32_t m = rank_pieces<kHopBlock, R>(x, lex, sh.wsum, np, wave, lane);
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            uint32_t j = lex[u];
+            const uint32_t w0 = (u * (uint32_t)kHopBlock + tid) * 4u;
+            if (piece_any(x[u]))
+#pragma unroll
+                for (uint32_t c = 0; c < 4u; ++c) {
+                    const uint32_t w = piece_word(x[u], c);
+                    if (w) s_seen[w0 + c] |= j < room ? lowest_set_bits(w, room - j) : 0u; // (vertices beyond the cap are dropped)
+                    for (uint32_t y = w; y; y &= y - 1u, ++j) {
+                        const int32_t gid = (int32_t)(((w0 + c) << 5) + (uint32_t)__ffs((int)y) - 1u);
+                        if (j < room) a.S[n + j] = gid;
+                        a.local_id[gid] = j < room ? (int32_t)(n + j) : -1;
+                    }
+                }
+        }
+        const uint32_t exact = n + m, next = m < room ? exact : s.cap[h + 1];
+        if (tid == 0) {
+            row_ptr[n] = (int32_t)ebase;
+            d->E[h] = ebase;
+            d->n_exact[h + 1] = exact;
+            d->n[h + 1] = next;
+            if (m > room) {
+                atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(h));
+                atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(h));
+            }
+        }
+        n = next;
+        __syncthreads(); // ranks and ids are there for the relabel, the marks for the next hop
+        if (h < a.num_hops - 1)
+            for (uint32_t e = tid; e < ebase && e < s.edge_cap[h]; e += (uint32_t)kHopBlock) {
+                const int32_t g = nbr[e];
+                s.col[h][e] = (uint32_t)g < a.num_nodes ? a.local_id[g] : -1;
+            }
+    }
+}
+
 struct CloseRoles { // the closing launch's other workgroups
     RelabelArgs rel; // the edges of hop H-2
     RowArgs gat;     // the copy of the frontier's feature rows (their ids are final by now), if the step has no gather launch
@@ -1233,8 +1389,15 @@ __global__ __launch_bounds__(kBlock) void k_gather(RowArgs gat, RelabelArgs last
         gather_block<VEC>(gat, blockIdx.x - last.blocks, s_mem);
 }
 
-template <int VEC>
-__global__ __launch_bounds__(kBlock) void k_aggregate(RowArgs agg, FinishArgs fin)
+// (a small step has no closing launch to copy the frontier's rows in: they come first here)
+struct NoCopy {};
+__device__ __forceinline__ uint32_t copy_blocks(const RowArgs &copy) { return copy.blocks; }
+__device__ __forceinline__ uint32_t copy_blocks(const NoCopy &) { return 0u; }
+template <int VEC> __device__ __forceinline__ void copy_block(const RowArgs &copy, uint32_t b, int32_t *s_id) { gather_rows_block<VEC>(copy, b, s_id); }
+template <int VEC> __device__ __forceinline__ void copy_block(const NoCopy &, uint32_t, int32_t *) {}
+
+template <int VEC, class Copy>
+__global__ __launch_bounds__(kBlock) void k_aggregate(RowArgs agg, FinishArgs fin, Copy copy)
 {
     extern __shared__ int32_t s_mem[];
     if (gate_closed(fin.gate)) {
@@ -1243,10 +1406,13 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(RowArgs agg, FinishArgs fi
     }
     // the launch's first workgroup starts early in the launch: its first lane looks whether the next step is already there
     if (blockIdx.x == 0 && threadIdx.x == 0 && fin.blocks && !fin.gate) prefetch_step_inputs(fin.drmb, fin.mailbox);
-    if (blockIdx.x < agg.blocks)
-        aggregate_block<VEC>(agg, blockIdx.x, s_mem);
+    const uint32_t copies = copy_blocks(copy);
+    if (blockIdx.x < copies)
+        copy_block<VEC>(copy, blockIdx.x, s_mem);
+    else if (blockIdx.x - copies < agg.blocks)
+        aggregate_block<VEC>(agg, blockIdx.x - copies, s_mem);
     else
-        finish_block(fin, blockIdx.x - agg.blocks);
+        finish_block(fin, blockIdx.x - copies - agg.blocks);
 }
 
 // The tail of a step without features: relabel of the last hop and end-of-step clean-up, in one launch - neither reads what the
@@ -1588,15 +1754,21 @@ int launch_gather(const RowArgs &gat, const RelabelArgs &ra, hipStream_t st)
     return ZG_OK;
 }
 
-int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, hipStream_t st)
+int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, hipStream_t st, const RowArgs *copy = nullptr)
 {
-    const unsigned grid = agg.blocks + fa.blocks;
+    const unsigned grid = agg.blocks + fa.blocks + (copy ? copy->blocks : 0u);
     if (grid == 0) return ZG_OK;
-    const size_t lds = agg.blocks ? ((size_t)agg.rows + 1 + (size_t)agg.rows * agg.max_fanout * (agg.x_dst ? 2 : 1)) * 4 : 0;
-    if (agg.vec4)
-        hipLaunchKernelGGL(k_aggregate<4>, dim3(grid), dim3(kBlock), lds, st, agg, fa);
+    size_t lds = agg.blocks ? ((size_t)agg.rows + 1 + (size_t)agg.rows * agg.max_fanout * (agg.x_dst ? 2 : 1)) * 4 : 0;
+    if (copy) lds = std::max(lds, (size_t)copy->rows * 4);
+    const dim3 g(grid), b(kBlock);
+    if (copy && agg.vec4)
+        hipLaunchKernelGGL((k_aggregate<4, RowArgs>), g, b, lds, st, agg, fa, *copy);
+    else if (copy)
+        hipLaunchKernelGGL((k_aggregate<1, RowArgs>), g, b, lds, st, agg, fa, *copy);
+    else if (agg.vec4)
+        hipLaunchKernelGGL((k_aggregate<4, NoCopy>), g, b, lds, st, agg, fa, NoCopy());
     else
-        hipLaunchKernelGGL(k_aggregate<1>, dim3(grid), dim3(kBlock), lds, st, agg, fa);
+        hipLaunchKernelGGL((k_aggregate<1, NoCopy>), g, b, lds, st, agg, fa, NoCopy());
     ZG_HIP(hipGetLastError());
     return ZG_OK;
 }
@@ -1674,6 +1846,45 @@ void launch_hop(const HopArgs &ha, const HopRoles &o, unsigned grid, size_t lds,
     }
 }
 
+// the sampling of a small step
+int launch_small(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate)
+{
+    const Layout &L = p->lay;
+    const zg_graph_t *g = p->graph;
+    SmallArgs sa;
+    std::memset(&sa, 0, sizeof(sa));
+    HopArgs &ha = sa.hop;
+    ha.offsets = g->d_offsets;
+    ha.indices = g->d_indices;
+    ha.drmb = p->drmb();
+    ha.gate = gate ? gate->drmb() : nullptr;
+    ha.mailbox = gate ? gate->mailbox_dev : p->mailbox_dev;
+    ha.S = p->S();
+    ha.local_id = p->local_id();
+    ha.own = x_written_by_aggregation(p) ? p->own() : nullptr;
+    ha.num_nodes = (uint32_t)g->num_nodes;
+    ha.num_hops = L.num_hops;
+    ha.replace = (p->flags & ZG_PLAN_REPLACE) ? 1 : 0;
+    ha.batch = (uint32_t)p->batch;
+    ha.stage_edges = (uint32_t)kSmallStage;
+    for (int h = 0; h < L.num_hops; ++h) {
+        sa.row_ptr[h] = p->row_ptr(h);
+        sa.nbr[h] = p->nbr(h);
+        sa.col[h] = p->col(h);
+        sa.fanout[h] = (uint32_t)L.fanout[h];
+        sa.edge_cap[h] = (uint32_t)L.edge_cap[h];
+    }
+    for (int h = 0; h <= L.num_hops; ++h) sa.cap[h] = (uint32_t)L.node_cap[h];
+    sa.words = (uint32_t)(((g->num_nodes + 31) / 32 + 31) / 32 * 32);
+    const size_t lds = (kSmallStage + 2 * (size_t)sa.words) * 4;
+    if (g->offsets_dtype == ZG_I64)
+        hipLaunchKernelGGL(k_small<int64_t>, dim3(1), dim3(kHopBlock), lds, st, sa);
+    else
+        hipLaunchKernelGGL(k_small<int32_t>, dim3(1), dim3(kHopBlock), lds, st, sa);
+    ZG_HIP(hipGetLastError());
+    return ZG_OK;
+}
+
 // a whole step, in order, on one stream (captured once, or issued eagerly): the hop kernel's launches 0..H, then the
 // two feature launches.  With `gate` the kernels are those of gate's worst-case twin `p`, run on gate's inputs and
 // only if gate's step overflowed; `defer_completed` marks a plan whose gated twin follows in the same sequence.
@@ -1690,7 +1901,11 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
     std::memset(&gat, 0, sizeof(gat));
     std::memset(&no_rows, 0, sizeof(no_rows));
     if (feats) step_feature_args(p, &gat, &agg);
-    for (int l = 0; l <= H; ++l) {
+    if (L.small) {
+        const int rc = launch_small(p, st, gate);
+        if (rc != ZG_OK) return rc;
+    }
+    for (int l = 0; l <= H && !L.small; ++l) {
         HopArgs ha;
         std::memset(&ha, 0, sizeof(ha));
         ha.offsets = g->d_offsets;
@@ -1784,7 +1999,7 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         if (rc != ZG_OK) return rc;
     }
     if (probe) probe->error = hipEventRecord(probe->before, st);
-    int rc = launch_aggregate(agg, finish_args(p, true, gate, defer_completed), st);
+    int rc = launch_aggregate(agg, finish_args(p, true, gate, defer_completed), st, L.small && ride ? &gat : nullptr);
     if (rc == ZG_OK && probe && probe->error == hipSuccess) probe->error = hipEventRecord(probe->after, st);
     return rc;
 }

@@ -223,11 +223,15 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
         pi.edge_cap[h] = L.edge_cap[h];
     }
     // byte marks where the hop's edges are many enough for the graph: the caps bound them, and so does the model's frontier size
+    int64_t all_edges = 0;
     for (int h = 0; h < num_hops; ++h) {
         double edges = (double)L.edge_cap[h];
         if (!g->degrees.empty()) edges = std::min(edges, std::ceil(mean[h]) * fanouts[h]);
         L.byte_marks[h] = (double)V <= (double)kByteMarkVerticesPerEdge * edges ? 1 : 0;
+        all_edges += L.edge_cap[h];
     }
+    L.small = all_edges <= kSmallEdgesPerHop * num_hops - kSmallEdgesPerHop / 2 && (V + 31) / 32 <= kSmallMaxWords;
+    if (L.small) std::fill(L.byte_marks, L.byte_marks + num_hops, 0); // (its marks are bits in LDS)
     {
         // Launch l of the hop kernel (l = 0..H) samples hop l for the rows of D_l and, for l > 0, first ranks the vertices
         // hop l-1 discovered.  Rows that were already in D_{l-1} come in tiles of 1024 / G rows, a ticket covering 1..4

@@ -18,6 +18,13 @@ constexpr int kMaxTickets = 480;       // tickets per launch of the hop kernel: 
 constexpr int kHopMaxTpt = 4;           // most consecutive tiles of frontier rows the plan gives a ticket
 constexpr int kHopMaxWordsPerLane = 8;  // bitmap words of a ranking tile per lane of a 1024-lane workgroup
 constexpr size_t kHopLdsBytes = 78 << 10; // LDS of a sampling workgroup: half a compute unit's
+// A step whose edge caps sum up to at most 3840 H - 1920, on a graph whose bitmaps fit into LDS twice, samples all its hops in
+// one workgroup (k_small): two launches instead of H + 2.  Step time against the launches per hop: two hops of 2240 edges
+// 32.9 -> 24.5 us, of 7680 with 2400-byte rows 39.3 -> 37.5 (56 -> 58 where the host waits for each), of 14160 37.8 -> 42.9; three
+// hops of 9460 45.3 -> 39.8; one hop of 3500 26.8 -> 27.1.
+constexpr int64_t kSmallEdgesPerHop = 3840;
+constexpr int kSmallMaxWords = 8192;      // 262144 vertices: 32 KB per bitmap
+constexpr size_t kSmallStage = 8192;      // sampled ids it holds at once
 constexpr size_t kHopMinStage = 4096, kHopMaxStage = 12288; // sampled ids it holds at once
 constexpr int kHopMinTileWords = 32;    // smallest ranking tile: 32 words = 1024 vertices
 constexpr int kHopMaxTileWords = kHopBlock * kHopMaxWordsPerLane; // largest: 8192 words = 262144 vertices
@@ -65,6 +72,7 @@ struct Layout {
     int64_t edge_cap[ZG_MAX_HOPS] = {};
     int32_t fanout[ZG_MAX_HOPS] = {};
     int64_t bitmap_words = 0; // padded to whole ranking tiles of the largest size
+    bool small = false; // all hops in one workgroup (k_small)
     // how hop h records the vertices it reaches: 0 = a bit per vertex (atomicOr), 1 = a byte per vertex (plain stores)
     int32_t byte_marks[ZG_MAX_HOPS] = {};
     // launch l = 0..H of the hop kernel samples hop l (l < H) and ranks the vertices that hop l-1 discovered (l > 0)

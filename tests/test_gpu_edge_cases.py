@@ -258,3 +258,60 @@ def test_rows_at_any_float_boundary(oracle, dim, shift):
         assert bool((t[:, :c0] == -7.0).all()) and bool((t[:, c0 + dim:] == -7.0).all()) and bool((t[rows:] == -7.0).all())
     got = mean[: res.n[1], 3 - shift: 3 - shift + dim].cpu().numpy()
     assert agg_error(oracle, got, agg_ref, ref.row_ptr[-1], ref.col[-1], X_ref) <= 1e-5
+
+
+@pytest.mark.parametrize("nodes,batch,fanouts", [
+    (262_144, 64, (10, 7)),      # 5568 edges and 2^18 vertices: within what one workgroup samples ...
+    (262_145, 64, (10, 7)),      # ... a vertex more
+    (262_144, 64, (10, 8)),      # ... more edges than two hops allow
+    (20_000, 48, (6, 9, 1)),     # three hops
+    (9000, 60, (64, 1)),         # the widest fanout
+    (5000, 1280, (1,)),          # more seeds than lanes
+    (40, 40, (64, 3)),           # every vertex a seed (2680 edges)
+    (1, 1, (2, 2)),
+])
+@pytest.mark.parametrize("flags", [0, zg.PLAN_X_TWO_PASS, zg.PLAN_FUSED_INPUT, zg.PLAN_REPLACE])
+def test_steps_sampled_by_one_workgroup(oracle, nodes, batch, fanouts, flags):
+    g = W.rmat_graph(nodes, 12 * nodes, 21)
+    feat = W.feature_table(nodes, 9, 3)
+    og = to_host_graph(oracle, g)
+    pool = W.SeedPool(g, batch, 4)
+    dg = zg.Graph(g.offsets.cuda(), g.indices.cuda())
+    plan = zg.Plan(dg, fanouts, batch, zg.make_envelope(zg.ENV_MAX, flags=flags), feat_dim=9)
+    plan.bind_features(feat.cuda())
+    for s in range(3):
+        seeds = pool.batch_for(s).numpy()
+        plan.step(torch.as_tensor(seeds).cuda(), 50 + s)
+        res = plan.read_step()
+        ref = og.sample_blocks(seeds, fanouts, 50 + s, with_replacement=bool(flags & zg.PLAN_REPLACE))
+        compare_blocks(res, ref, f"step {s}")
+        X_ref = oracle.gather(feat.numpy(), ref.S)
+        assert np.array_equal(res.X, X_ref[: res.X.shape[0]])
+        agg_ref = oracle.aggregate_mean(ref.row_ptr[-1], ref.col[-1], X_ref)
+        assert agg_error(oracle, res.agg, agg_ref, ref.row_ptr[-1], ref.col[-1], X_ref) <= 1e-5
+
+
+def test_small_step_drops_what_the_caps_cut_and_flags_bad_seeds(oracle):
+    g = W.rmat_graph(9000, 120_000, 2)
+    og = to_host_graph(oracle, g)
+    dg = zg.Graph(g.offsets.cuda(), g.indices.cuda())
+    seeds = W.SeedPool(g, 30, 6).batch_for(1).numpy()
+    ref = og.sample_blocks(seeds, (6, 5), 9)
+    plan = zg.Plan(dg, (6, 5), 30, zg.make_envelope(zg.ENV_EXPLICIT, node_caps=[0, ref.n[1], ref.n[2] - 11]))
+    plan.step(torch.as_tensor(seeds).cuda(), 9)
+    torch.cuda.synchronize()
+    n, E, n_exact, flags = [t.cpu().numpy() for t in plan.view_counts()]
+    assert int(flags[0]) == zg.FLAG_HOP_OVERFLOW(1)
+    assert list(n) == [30, ref.n[1], ref.n[2] - 11] and list(n_exact[1:]) == ref.n[1:] and list(E) == ref.E
+    assert np.array_equal(plan.view_S()[: n[2]].cpu().numpy(), ref.S[: n[2]])
+    col = plan.view_block(1)[2][: E[1]].cpu().numpy()
+    assert np.array_equal(col, np.where(ref.col[1] < n[2], ref.col[1], -1))
+    for bad, flag in (([9000, 1], zg.FLAG_SEED_RANGE), ([5, 5], zg.FLAG_SEED_DUP)):
+        plan.overflow_clear()
+        plan.step(torch.as_tensor(np.concatenate([np.arange(100, 128, dtype=np.int32), np.array(bad, dtype=np.int32)])).cuda(), 3)
+        torch.cuda.synchronize()
+        assert int(plan.view_counts()[3].cpu()[0]) & flag
+    plan.overflow_clear()
+    full = zg.Plan(dg, (6, 5), 30, zg.make_envelope(zg.ENV_MAX))
+    full.step(torch.as_tensor(seeds).cuda(), 9)
+    compare_blocks(full.read_step(), ref, "worst-case caps")
