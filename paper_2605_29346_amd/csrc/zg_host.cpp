@@ -109,9 +109,10 @@ int compute_layout(const zg_graph_t *g, const int32_t *fanouts, int32_t num_hops
         Layout Ls;
         rc = compute_layout_one(g, fanouts, num_hops, batch, &worst, feat_dim, &pis, &Ls);
         if (rc != ZG_OK) return rc;
-        // [plan outputs][twin outputs][scratch, sized for the twin (it has the larger scan state)]
+        // [plan outputs][twin outputs][scratch, sized for the larger of the two: as a rule the twin's, but a saturated worst case
+        // may get by with fewer ranking tiles.  The id maps coincide; everything behind them is zero between steps.]
         const size_t env_t = L.envelope_end, env_s = Ls.envelope_end;
-        const size_t scratch_bytes = Ls.total - Ls.envelope_end;
+        const size_t scratch_bytes = std::max(Ls.total - Ls.envelope_end, L.total - L.envelope_end);
         relocate(L, 0, env_t + env_s);
         relocate(Ls, env_t, env_t + env_s);
         L.total = Ls.total = env_t + env_s + scratch_bytes;

@@ -276,3 +276,19 @@ def test_ranking_tiles_grow_to_16_words_per_lane_only_where_rows_not_the_budget_
     assert info.grid_sample[1] == 4096 // 64 + t16                # fanout 10: 64 old rows per ticket + fat ranking tiles (255 tickets)
     assert info.grid_sample[2] == -(-16_000 // 256) + t8          # fanout 5: two tiles of 128 old rows per ticket, to stay in the budget
     assert info.grid_compact == t8
+
+
+@pytest.mark.parametrize("nodes,deg,fanouts,batch", [
+    (70_000, 10, (25, 5, 5), 4096),   # saturated worst case: its launches need fewer ranking tiles than the plan's own
+    (10_000, 50, (64, 2, 1, 64), 64),
+    (2_000_000, 10, (10, 5), 1000),   # the ordinary case: the twin's scratch is the larger one
+])
+def test_the_shared_scratch_holds_the_larger_of_plan_and_twin(nodes, deg, fanouts, batch):
+    g = zg.Graph.from_degree_histogram([deg, deg + 1], [nodes // 2, nodes - nodes // 2])
+    own = g.plan_query(fanouts, batch, zg.make_envelope(zg.ENV_MODEL)).scratch_bytes
+    worst = g.plan_query(fanouts, batch, zg.make_envelope(zg.ENV_MAX)).scratch_bytes
+    for flag in (zg.PLAN_SAFE_TWIN, zg.PLAN_AUTO_FALLBACK):
+        both = g.plan_query(fanouts, batch, zg.make_envelope(zg.ENV_MODEL, flags=flag))
+        assert both.scratch_bytes == max(own, worst)
+        assert both.workspace_bytes == both.envelope_bytes + both.safe_envelope_bytes + both.scratch_bytes
+    assert (own > worst) == (nodes < 1_000_000)
