@@ -115,11 +115,13 @@ typedef struct {
     double model_sigma[ZG_MAX_HOPS + 1];  /* Lemma 1 sigma of n_h */
     double z;                             /* Phi^-1(confidence^(1/iterations)) */
     int64_t envelope_bytes;               /* step outputs: S, block CSRs, X, agg, metadata */
-    int64_t scratch_bytes;                /* id map over |V|, bitmap, scan state */
+    int64_t scratch_bytes;                /* id map over |V|, mark maps, scan state */
     int64_t workspace_bytes;              /* envelope + scratch + alignment: what zg_plan needs */
     int64_t maxsg_envelope_bytes;         /* envelope_bytes if ZG_ENV_MAX had been used */
     int32_t grid_sample[ZG_MAX_HOPS];     /* launch caps (workgroups) of the fixed launch skeleton: hop kernel launch h
-                                             (samples hop h; for h > 0 it first ranks the vertices hop h-1 discovered) */
+                                             (samples hop h; for h > 0 it first ranks the vertices hop h-1 discovered).  (A plan
+                                             whose edge caps sum up to no more than 3840 num_hops - 1920, on at most 2^18
+                                             vertices, runs these launches and the closing one as a single workgroup.) */
     int32_t grid_compact;                 /* the closing hop-kernel launch (ranks the last hop's vertices, samples nothing) */
     int32_t grid_relabel[ZG_MAX_HOPS];
     int32_t grid_gather;

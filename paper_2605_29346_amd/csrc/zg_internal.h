@@ -31,9 +31,10 @@ constexpr int kHopMaxTileWords = kHopBlock * kHopMaxWordsPerLane; // largest: 81
 constexpr int kHopFatWordsPerLane = 16; // ... 16 in a launch whose tile count is set by its (few) rows, not by the ticket budget
 constexpr int kHopFatTileWords = kHopBlock * kHopFatWordsPerLane; // 16384 words = 524288 vertices
 // A hop that marks E of V vertices: bits cost E device-scope atomics (12-25 G/s on this chip whatever the address pattern, and
-// hubs serialise further), bytes cost E plain stores (50-150 G/s) and a map eight times as large to read back (5 TB/s).  The two
-// break even at V = 290 E at 15 and 60 G/s; the line is drawn below that because E is known from above only.
-constexpr int64_t kByteMarkVerticesPerEdge = 40;
+// hubs serialise further), bytes cost E plain stores (50-150 G/s) and a map eight times as large to read back, by a launch that
+// has other things to read.  Step time with bits / bytes in the last hop: V / E = 8 and 26 (2.4 M vertices, also the hop before)
+// 120.3 / 117.4 us, 32 (8 M) 108.3 / 109.1, 41 (20 M) 182.7 / 187.9, 48 (40 M) 196.6 / 206.7.
+constexpr int64_t kByteMarkVerticesPerEdge = 30;
 constexpr int kSampleHashBits = 11;      // LDS dedup set of a sampling workgroup: 2048 slots for <= 1024 ids
 constexpr int kSampleHashSlots = 1 << kSampleHashBits;
 constexpr uint64_t kGatherStreamBytes = 160ull << 20; // gathered matrices above this size are copied with non-temporal accesses

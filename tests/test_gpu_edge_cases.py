@@ -204,8 +204,8 @@ def test_worked_example_from_the_published_known_answer(oracle):
 
 
 @pytest.mark.parametrize("nodes,draws,batch,fanouts,max_tickets", [
-    (8000, 160_000, 40, (5, 5), 0),          # 200 edges of hop 0: at the line between byte and bit marks ...
-    (8001, 160_000, 40, (5, 5), 0),          # ... and one vertex beyond it (bits, then bytes)
+    (6000, 160_000, 40, (5, 25, 2), 0),      # 200 edges of hop 0: at the line between byte and bit marks ...
+    (6001, 160_000, 40, (5, 25, 2), 0),      # ... and one vertex beyond it (bits, then bytes)
     (33, 400, 2, (3, 2, 2), 0),              # one word and a bit
     (70_000, 1_400_000, 700, (11, 6), 0),    # ranking tiles of 32 k words that are no power of two, groups of 11 and 6 lanes
     (40_000, 2_400_000, 1500, (64, 9), 1),   # one tile holds thousands of rows: several batches of 1024, each its ids in parts
@@ -315,3 +315,33 @@ def test_small_step_drops_what_the_caps_cut_and_flags_bad_seeds(oracle):
     full = zg.Plan(dg, (6, 5), 30, zg.make_envelope(zg.ENV_MAX))
     full.step(torch.as_tensor(seeds).cuda(), 9)
     compare_blocks(full.read_step(), ref, "worst-case caps")
+
+
+@pytest.mark.parametrize("batch,fanouts,dim", [(300, (8, 6), 0), (24, (6, 5), 0), (24, (6, 5), 12), (150, (5, 4), 12)])
+def test_armed_fallback_of_small_and_featureless_steps(oracle, batch, fanouts, dim):
+    # the plan's own step and its twin's may take different routes (one workgroup or a launch per hop, with the tail of a step without
+    # features): about half of the steps overflow and are redone by the gated twin, on shared scratch
+    g = W.rmat_graph(30_000, 600_000, 21)
+    og = to_host_graph(oracle, g)
+    feat = W.feature_table(30_000, dim, 4) if dim else None
+    pool = W.SeedPool(g, batch, 2)
+    seeds = [pool.batch_for(s).numpy() for s in range(10)]
+    refs = [og.sample_blocks(seeds[s], fanouts, 70 + s) for s in range(10)]
+    caps = [0, max(r.n[1] for r in refs), int(np.median([r.n[2] for r in refs]))]
+    env = zg.make_envelope(zg.ENV_EXPLICIT, flags=zg.PLAN_AUTO_FALLBACK, node_caps=caps)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), fanouts, batch, env, feat_dim=dim)
+    if dim:
+        plan.bind_features(feat.cuda())
+    twin, fell_back = plan.safe_view(), 0
+    for s in range(10):
+        plan.step(torch.as_tensor(seeds[s]).cuda(), 70 + s)
+        torch.cuda.synchronize()
+        active = int(plan.view_active().item())
+        assert active == (1 if refs[s].n[2] > caps[2] else 0) and plan.step_status()[0] == s + 1
+        res = (twin if active else plan).read_step()
+        res.flags &= ~zg.FLAG_HOP_OVERFLOW(1)
+        compare_blocks(res, refs[s], f"step {s} active={active}")
+        if dim:
+            assert np.array_equal(res.X, oracle.gather(feat.numpy(), refs[s].S))
+        fell_back += active
+    assert 0 < fell_back < 10
