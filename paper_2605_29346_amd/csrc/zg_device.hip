@@ -1,9 +1,10 @@
 // HIP kernels (gfx950, wave64) and the plan / step entry points of libzg.
 //
-// One step = H+3 launches: the hop kernel's launches 0..H, then {gather + relabel of the last hop} and
-// {aggregate + finish}.  Launch l of the hop kernel samples hop l (l < H) and, for l > 0, first ranks the vertices hop
-// l-1 discovered - they are rows of block l themselves, so ranking and sampling share their chained scans; launch
-// 0 also ingests the seeds and launch l >= 2 relabels the edges of hop l-2 (workgroups of a launch are split by role).
+// One step = H+2 launches: the hop kernel's launches 0..H-1, the closing launch and {aggregate + relabel of the last hop +
+// finish} (H+3 when X is written by a gather launch of its own; a small step's hops are one workgroup's work: 2).  Launch l of
+// the hop kernel samples hop l and, for l > 0, first ranks the vertices hop l-1 discovered - they are rows of block l
+// themselves, so ranking and sampling share their chained scans; launch 0 also ingests the seeds, launch l >= 2 relabels the
+// edges of hop l-2 and the closing launch ranks only (workgroups of a launch are split by role).
 // Every kernel boundary costs about as much as the small kernels themselves at mini-batch sizes, and kernels of
 // different streams do not hide it from each other, so the step is cut into as few launches as its global
 // dependencies allow: "all of hop l-1 sampled" before its vertices can be ranked, and "all vertices ranked" before
@@ -529,7 +530,7 @@ __device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &
 // byte by byte; whichever of several edges' stores lands last, the byte says "reached", and nobody looks before the next
 // launch.  (Stores that write through to memory at once queue up on a hub's byte like atomics: 129 -> 212 us in a launch of
 // 2 M edges, against 81 us; a look at the byte first costs more than it spares, 84 us.)
-// A hop that reaches few of them (a byte map of 110 M vertices takes the next launch 25 us to read) sets a bit, after a hash
+// A hop that reaches few of them (a byte map of 110 M vertices made the closing launch 54 us longer) sets a bit, after a hash
 // set in LDS: each distinct id of the pass reaches the hop's bitmap with at most one device-scope atomic - popular
 // vertices are sampled hundreds of times per hop and same-address atomics serialise at the memory side.
 // Ids that are already in D_l are marked too: the next launch masks them with "seen" (looking every id up in "seen" here was

@@ -44,7 +44,7 @@ RowTiling aggregate_tiling(int32_t dim)
     return t;
 }
 
-// frontier vertices per sampling workgroup: 1024 lanes / (lanes per vertex = power of two >= max(4, fanout))
+// rows of a tile of old rows: 1024 lanes / (a power of two >= max(4, fanout))
 int sample_group_log2(int fanout)
 {
     int g = 2;
