@@ -288,17 +288,20 @@ struct RelabelArgs {
 
 // Hop h, "relabel edges": col[e] = local id of nbr_gid[e] (-1 for a vertex dropped by an overflow).
 // Every sampled id is in S_h, so its map entry was written during this step (by the ingest or a ranking tile).
+// An entry at or beyond n_{h+1} belongs to a vertex that this hop's cap dropped and a later hop found again - ranked
+// by the very launch this role runs in, and on the last hop tagged (MarkTag): the vertex is not in S_h, whichever entry is read.
 // Works for any workgroup size; a workgroup covers kRelabelPerBlock edges.
 __device__ __forceinline__ void relabel_block(const RelabelArgs &a, uint32_t block)
 {
-    const uint32_t E = a.drmb->E[a.hop];
+    const uint32_t E = a.drmb->E[a.hop], n = a.drmb->n[a.hop + 1];
     const uint32_t e0 = block * kRelabelPerBlock;
     if (e0 >= E) return;
     const uint32_t e1 = e0 + kRelabelPerBlock < E ? e0 + kRelabelPerBlock : E;
 #pragma unroll 4
     for (uint32_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
         const int32_t g = a.nbr[e];
-        a.col[e] = (uint32_t)g < a.num_nodes ? a.local_id[g] : -1;
+        const int32_t id = (uint32_t)g < a.num_nodes ? a.local_id[g] : -1;
+        a.col[e] = (uint32_t)id < n ? id : -1;
     }
 }
 

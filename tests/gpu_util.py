@@ -64,3 +64,42 @@ def run_and_compare(oracle, g, feat, seeds, fanouts, key, *, env=None, plan=None
     if feat is not None:
         compare_features(oracle, res, ref, feat.cpu().numpy(), label)
     return plan, res, ref
+
+
+def samples_in_one_workgroup(plan):
+    """Whether the plan's step samples all its hops in one workgroup: the rule zg_plan_info documents beside grid_sample."""
+    H = plan.num_hops
+    return sum(plan.info.edge_cap[h] for h in range(H)) <= 3840 * H - 1920 and plan.graph.num_nodes <= 1 << 18
+
+
+def truncated_blocks(oracle, g, seeds, fanouts, key, caps):
+    """What a step under node caps leaves, built row by row from the checker's sampled positions: a hop's new vertices beyond its
+    cap are dropped (no row, col -1) and may be found again by a later hop.  Returns (n, n_exact, S, per hop (row_ptr, nbr, col))."""
+    off, idx = g.offsets.cpu().numpy().astype(np.int64), g.indices.cpu().numpy()
+    S, n, n_exact, blocks = [int(v) for v in seeds], [len(seeds)], [len(seeds)], []
+    for h, F in enumerate(fanouts):
+        row_ptr, nbr = [0], []
+        for v in S:
+            pos = oracle.sample_positions(key, h, v, int(off[v + 1] - off[v]), F)
+            nbr += [int(idx[off[v] + p]) for p in pos]
+            row_ptr.append(len(nbr))
+        new = sorted(set(nbr) - set(S))
+        n_exact.append(len(S) + len(new))
+        S = S + new[: caps[h + 1] - len(S)]
+        n.append(len(S))
+        at = {v: i for i, v in enumerate(S)}
+        blocks.append((np.array(row_ptr), np.array(nbr, dtype=np.int64), np.array([at.get(v, -1) for v in nbr])))
+    return n, n_exact, np.array(S), blocks
+
+
+def compare_truncated(plan, want, label=""):
+    n, n_exact, S, blocks = want
+    got_n, got_E, got_exact, _ = [t.cpu().numpy().tolist() for t in plan.view_counts()]
+    assert got_n == n and got_exact == n_exact, f"{label}: n {got_n} {n}, exact {got_exact} {n_exact}"
+    assert np.array_equal(plan.view_S()[: n[-1]].cpu().numpy(), S), f"{label}: S"
+    for h, (row_ptr, nbr, col) in enumerate(blocks):
+        got = [t.cpu().numpy() for t in plan.view_block(h)]
+        assert got_E[h] == len(nbr), f"{label}: E[{h}]"
+        assert np.array_equal(got[0][: len(row_ptr)], row_ptr), f"{label}: row_ptr[{h}]"
+        assert np.array_equal(got[1][: len(nbr)], nbr), f"{label}: nbr[{h}]"
+        assert np.array_equal(got[2][: len(nbr)], col), f"{label}: col[{h}]"
