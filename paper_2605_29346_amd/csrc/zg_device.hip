@@ -339,7 +339,8 @@ struct RowArgs {
     int32_t vec4;           // rows are moved in pieces of four floats (else, below four, element by element)
     int32_t nt;             // aggregate inside a step: what it writes (means, rows of X) is stored past the caches (non-temporal)
     const int32_t *local_id; // aggregate that relabels its block's edges itself: the id map ...
-    int32_t *col_out;        // ... and where col[e] = local id of nbr_gid[e] goes
+    int32_t *col_out;        // ... where col[e] = local id of nbr_gid[e] goes ...
+    const uint32_t *n_ids;   // ... and the device address of the number of local ids: an entry beyond it is not of this step (a twin's, see mark_tag)
     uint32_t blocks; // workgroups given to this role (0: role absent)
 };
 
@@ -1349,6 +1350,7 @@ __device__ __forceinline__ void aggregate_block(const RowArgs &a, uint32_t block
     int32_t *s_dst = s_col + a.rows * a.max_fanout; // [rows * max_fanout] when X is written on the way: row of X, or -1
     const uint32_t n = *a.n_rows;
     const uint32_t n_in = a.n_cols ? *a.n_cols : a.col_limit;
+    const uint32_t n_ids = a.col_out ? *a.n_ids : 0u;
     const uint32_t row0 = block * a.rows;
     if (row0 >= n) return;
     const uint32_t rows = n - row0 < a.rows ? n - row0 : a.rows;
@@ -1363,7 +1365,7 @@ __device__ __forceinline__ void aggregate_block(const RowArgs &a, uint32_t block
         s_col[t] = valid ? (int32_t)c : -1;
         if (a.col_out) { // "relabel edges" of this block, done here: c is the sampled global id
             const int32_t entry = valid ? a.local_id[c] : -1;
-            const int32_t lid = a.tag.local_id(entry);
+            const int32_t id = a.tag.local_id(entry), lid = (uint32_t)id < n_ids ? id : -1;
             a.col_out[e_begin + t] = lid;
             // one edge to a vertex writes its row of X, if the vertex is new (the frontier's rows are the gather's)
             if (a.x_dst) s_dst[t] = lid >= (int32_t)n && (a.own ? a.own[e_begin + t] != 0 : a.tag.owns(entry, (uint32_t)(e_begin + (int32_t)t))) ? lid : -1;
@@ -1777,14 +1779,16 @@ int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, hipStream_t st, c
     return ZG_OK;
 }
 
-// how the last hop's new vertices carry their marking edge's tag (all zero: they do not)
+// How the last hop's new vertices carry their marking edge's tag, where that hop marks bytes (all zero: they do not).  A plan and
+// its twin share one id map, and the replayed aggregation of one may meet the other's entries: both read them by one layout, whether
+// their own hop marks bytes (tags) or bits (tag 0).
 MarkTag mark_tag(const zg_plan_t *p)
 {
     const Layout &L = p->lay;
     MarkTag t = {0, 0u};
-    if (!x_written_by_aggregation(p) || !L.byte_marks[L.num_hops - 1]) return t;
+    if (!x_written_by_aggregation(p)) return t;
     int lid_bits = 1;
-    while (lid_bits < 31 && ((int64_t)1 << lid_bits) < L.node_cap[L.num_hops]) ++lid_bits;
+    while (lid_bits < 31 && ((int64_t)1 << lid_bits) < L.id_rows) ++lid_bits;
     const int bits = std::min(7, 31 - lid_bits);
     if (bits <= 0) return t; // no room for a tag: every edge to a new vertex writes its row
     t.shift = 31 - bits;
@@ -1807,6 +1811,7 @@ void step_feature_args(const zg_plan_t *p, RowArgs *gat, RowArgs *agg)
         // the aggregation relabels the last hop's edges itself (it holds their sampled ids anyway): no launch in between
         agg->local_id = p->local_id();
         agg->col_out = p->col(H - 1);
+        agg->n_ids = &p->drmb()->n[H];
     } else {
         *agg = aggregate_args(p, H - 1, p->X(), L.ld_out, L.feat_dim, p->agg(), L.ld_out, false);
     }

@@ -116,6 +116,7 @@ int compute_layout(const zg_graph_t *g, const int32_t *fanouts, int32_t num_hops
         relocate(L, 0, env_t + env_s);
         relocate(Ls, env_t, env_t + env_s);
         L.total = Ls.total = env_t + env_s + scratch_bytes;
+        L.id_rows = Ls.id_rows = std::max(L.id_rows, Ls.id_rows);
         pi.safe_envelope_bytes = (int64_t)env_s;
         pi.scratch_bytes = (int64_t)scratch_bytes;
         pi.workspace_bytes = (int64_t)L.total;
@@ -217,6 +218,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
     L.feat_dim = feat_dim;
     L.ldx = ldx;
     for (int h = 0; h <= num_hops; ++h) L.node_cap[h] = pi.node_cap[h];
+    L.id_rows = L.node_cap[num_hops];
     for (int h = 0; h < num_hops; ++h) {
         L.fanout[h] = fanouts[h];
         L.edge_cap[h] = L.node_cap[h] * fanouts[h];

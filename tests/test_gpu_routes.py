@@ -6,7 +6,7 @@ import torch
 
 from paper_2605_29346_amd import workloads as W
 from paper_2605_29346_amd import zg
-from gpu_util import compare_truncated, samples_in_one_workgroup, to_host_graph, truncated_blocks
+from gpu_util import compare_blocks, compare_truncated, samples_in_one_workgroup, to_host_graph, truncated_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +60,39 @@ def test_a_cap_in_the_middle_leaves_a_consistent_step(oracle, nodes, draws, batc
         torch.cuda.synchronize()
         assert plan.step_status() == (2 * rep + 2, 0)
         compare_truncated(plan, fits, f"after rep {rep}")
+
+
+@pytest.mark.parametrize("nodes,batch,cut,maps_differ", [
+    (300_000, 1130, 0.5, True),   # the plan marks bits, its twin - whose caps allow more edges - bytes
+    (300_000, 1130, 0.95, True),
+    (300_000, 1600, 0.5, False),  # both bytes
+    (100_000, 300, 0.5, False),   # both in one workgroup
+])
+def test_replayed_features_after_the_twins_step(oracle, nodes, batch, cut, maps_differ):
+    # the plan's step is cut at the last hop, the twin redoes it over the shared id map, then the plan's own feature launches run
+    # again: its outputs are rewritten with the same values and nothing else in the workspace changes
+    g = W.rmat_graph(nodes, 20 * nodes, 29)
+    feat = W.feature_table(nodes, 16, 3).cuda()
+    og = to_host_graph(oracle, g)
+    seeds = W.SeedPool(g, batch, 7).batch_for(0)
+    ref = og.sample_blocks(seeds.numpy(), (3, 4), 5)
+    caps = [0, ref.n[1], ref.n[1] + int(cut * (ref.n[2] - ref.n[1]))]
+    dg = zg.Graph(g.offsets.cuda(), g.indices.cuda())
+    plan = zg.Plan(dg, (3, 4), batch, zg.make_envelope(zg.ENV_EXPLICIT, flags=zg.PLAN_SAFE_TWIN, node_caps=caps), feat_dim=16)
+    plan.bind_features(feat)
+    own, worst = (dg.plan_query((3, 4), batch, zg.make_envelope(m, node_caps=caps)).scratch_bytes for m in (zg.ENV_EXPLICIT, zg.ENV_MAX))
+    assert (worst - own > nodes) == maps_differ  # a map of bytes instead of bits
+    plan.step(seeds.cuda(), 5)
+    cut_step = plan.read_step()
+    plan.step_safe(seeds.cuda(), 5)
+    torch.cuda.synchronize()
+    assert cut_step.flags == zg.FLAG_HOP_OVERFLOW(1) and cut_step.n == [batch, caps[1], caps[2]]
+    before = plan.workspace.clone()
+    plan.replay_features(0)
+    plan.replay_features(1)
+    torch.cuda.synchronize()
+    assert torch.equal(plan.workspace, before)
+    again, whole = plan.read_step(), plan.safe_view().read_step()
+    compare_blocks(whole, ref, "twin")
+    for got, want in zip([again.X, again.agg] + again.col, [cut_step.X, cut_step.agg] + cut_step.col):
+        assert np.array_equal(got, want)
