@@ -251,6 +251,7 @@ __device__ __forceinline__ void ingest_block(const IngestArgs &a, uint32_t block
     const int32_t *seeds = reinterpret_cast<const int32_t *>(s_in[0]);
     if (gtid == 0) {
         Drmb *d = a.drmb;
+        d->step = d->epoch;
         d->n[0] = a.batch;
         d->n_exact[0] = a.batch;
         d->key_lo = (uint32_t)(s_in[1] & 0xFFFFFFFFull);
@@ -992,6 +993,7 @@ __global__ __launch_bounds__(kHopBlock) void k_small(SmallArgs s)
     const int32_t *seeds = reinterpret_cast<const int32_t *>(sh.in[0]);
     const uint32_t key_lo = (uint32_t)(sh.in[1] & 0xFFFFFFFFull), key_hi = (uint32_t)(sh.in[1] >> 32);
     if (tid == 0) {
+        d->step = d->epoch;
         d->n[0] = a.batch;
         d->n_exact[0] = a.batch;
         d->key_lo = key_lo;
@@ -1231,10 +1233,11 @@ __device__ __forceinline__ void publish_gate_owner(const FinishArgs &a)
 }
 
 // One lane, early in the step's last launch: if the host has already handed over the next step, its mailbox slot is
-// copied into the metadata buffer, so that the next step starts without a read of host memory.
+// copied into the metadata buffer, so that the next step starts without a read of host memory.  Counted from `step`, not from
+// `epoch`: a finish workgroup of the same launch advances that one, before or after this lane looks.
 __device__ __forceinline__ void prefetch_step_inputs(Drmb *d, const Mailbox *mailbox)
 {
-    const uint32_t next = d->epoch + 1u;
+    const uint32_t next = d->step + 1u;
     const uint32_t issued = __hip_atomic_load(&mailbox->issued, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
     if ((int32_t)(issued - (next + 1u)) >= 0) {
         const uint32_t slot = next % kMailboxSlots;

@@ -96,3 +96,32 @@ def test_replayed_features_after_the_twins_step(oracle, nodes, batch, cut, maps_
     compare_blocks(whole, ref, "twin")
     for got, want in zip([again.X, again.agg] + again.col, [cut_step.X, cut_step.agg] + cut_step.col):
         assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("dim", [0, 8])
+@pytest.mark.parametrize("batch", [300, 24])  # a launch per hop; all hops in one workgroup
+@pytest.mark.parametrize("flags", [0, zg.PLAN_EAGER])
+def test_a_queued_step_finds_its_own_inputs_prefetched(oracle, dim, batch, flags):
+    # The last launch of a step copies the next step's inputs out of host memory if the host is ahead: what it leaves (the two words
+    # behind the fallback word: valid, step number) must name the next step, not the one after it, although the same launch
+    # also advances the step counter.
+    g = W.rmat_graph(30_000, 600_000, 21)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (8, 6), batch, zg.make_envelope(zg.ENV_MAX, flags=flags), feat_dim=dim)
+    assert samples_in_one_workgroup(plan) == (batch == 24)
+    if dim:
+        plan.bind_features(W.feature_table(30_000, dim, 4).cuda())
+    pool, og, steps = W.SeedPool(g, batch, 2), to_host_graph(oracle, g), 40
+    batches = [pool.batch_for(s).cuda() for s in range(steps)]
+    words = plan._view(plan.out.d_active + 4, 2, torch.int32)
+    seen = torch.full((steps, 2), -1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda._sleep(50_000_000)  # the device starts when all steps are queued
+    for s in range(steps):
+        plan.step(batches[s], 600 + s)
+        seen[s].copy_(words)
+    torch.cuda.synchronize()
+    assert seen.cpu().tolist()[:-1] == [[1, s + 1] for s in range(steps - 1)] and int(seen[-1, 0]) == 0
+    log = plan.view_log().cpu().numpy()
+    for s in range(steps):
+        ref = og.sample_blocks(batches[s].cpu().numpy(), (8, 6), 600 + s)
+        assert log[s][0] == s and log[s][1] == 0 and list(log[s][2:5]) == ref.n and list(log[s][5:7]) == ref.E
