@@ -2010,8 +2010,15 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         int rc = launch_gather(gat, relabel_args(p, H - 1, true, gate), st);
         if (rc != ZG_OK) return rc;
     }
+    // a small step's frontier rows are copied by workgroups of the aggregation launch - by a launch of their own, ahead of it, where
+    // the events are to bracket the aggregation alone
+    const bool copy_along = L.small && ride && !probe;
+    if (L.small && ride && probe) {
+        const int rc = launch_gather(gat, relabel_args(p, 0, false), st);
+        if (rc != ZG_OK) return rc;
+    }
     if (probe) probe->error = hipEventRecord(probe->before, st);
-    int rc = launch_aggregate(agg, finish_args(p, true, gate, defer_completed), st, L.small && ride ? &gat : nullptr);
+    int rc = launch_aggregate(agg, finish_args(p, true, gate, defer_completed), st, copy_along ? &gat : nullptr);
     if (rc == ZG_OK && probe && probe->error == hipSuccess) probe->error = hipEventRecord(probe->after, st);
     return rc;
 }

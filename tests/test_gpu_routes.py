@@ -6,7 +6,7 @@ import torch
 
 from paper_2605_29346_amd import workloads as W
 from paper_2605_29346_amd import zg
-from gpu_util import compare_blocks, compare_truncated, samples_in_one_workgroup, to_host_graph, truncated_blocks
+from gpu_util import agg_error, compare_blocks, compare_truncated, samples_in_one_workgroup, to_host_graph, truncated_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -125,3 +125,38 @@ def test_a_queued_step_finds_its_own_inputs_prefetched(oracle, dim, batch, flags
     for s in range(steps):
         ref = og.sample_blocks(batches[s].cpu().numpy(), (8, 6), 600 + s)
         assert log[s][0] == s and log[s][1] == 0 and list(log[s][2:5]) == ref.n and list(log[s][5:7]) == ref.E
+
+
+@pytest.mark.parametrize("flags", [0, zg.PLAN_FUSED_INPUT])
+def test_the_stop_watch_of_a_small_step_is_on_its_aggregation_alone(oracle, flags):
+    # 1900 rows of 32768 floats and next to no edges: the frontier's copy moves twice the bytes of the aggregation
+    nodes, dim, batch = 2000, 32768, 1900
+    g = W.rmat_graph(nodes, 400, 3)
+    feat = W.feature_table(nodes, dim, 4)
+    table = feat.cuda()
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (1,), batch, zg.make_envelope(zg.ENV_MAX, flags=flags), feat_dim=dim)
+    assert samples_in_one_workgroup(plan)
+    plan.bind_features(table)
+    seeds = W.SeedPool(g, batch, 5).batch_for(0)
+    ref = to_host_graph(oracle, g).sample_blocks(seeds.numpy(), (1,), 8)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(), b.record()
+    times = {"step": [], 0: [], 1: []}
+    for rep in range(12):
+        plan.step_timed(seeds.cuda(), 8, a, b)
+        torch.cuda.synchronize()
+        times["step"].append(a.elapsed_time(b))
+        if rep == 0:
+            res = plan.read_step()
+            compare_blocks(res, ref)
+            X_ref = oracle.gather(feat.numpy(), ref.S)
+            assert np.array_equal(res.X, X_ref[: res.X.shape[0]])
+            assert agg_error(oracle, res.agg, oracle.aggregate_mean(ref.row_ptr[0], ref.col[0], X_ref), ref.row_ptr[0], ref.col[0], X_ref) <= 1e-5
+        for which in (0, 1):
+            a.record()
+            plan.replay_features(which)
+            b.record()
+            torch.cuda.synchronize()
+            times[which].append(a.elapsed_time(b))
+    step, copy, mean = (min(times[k]) for k in ("step", 0, 1))
+    assert step < mean + 0.5 * copy, (step, copy, mean)
