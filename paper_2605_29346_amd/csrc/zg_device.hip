@@ -628,7 +628,7 @@ __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
 //
 // Bound by latency: a ticket is a chain of about eight dependent memory accesses, so a launch costs the length of that chain,
 // the code it walks through cold and its slowest ticket.  Hence one instantiation per kind of launch and of marks (one
-// kernel for all spilled 140 scalar and 6 vector registers), wide scans in registers, and a chain of two levels.
+// kernel for all spilled 140 scalar and 6 vector registers) and wide scans in registers.
 
 // The words of a ranking tile, bit b of word w: vertex 32 w + b is marked and not "seen".  A lane holds pieces of four words,
 // piece u NT + tid in round u: 16-byte accesses, consecutive lanes consecutive.
@@ -747,10 +747,14 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     Drmb *d = a.drmb;
     if (tid == 0) sh.ticket = atomicAdd(&d->ticket[a.launch], 1u);
     if (FIRST && tid == 64) sh.have_in = prefetched_inputs(d, a.gate, sh.in);
-    const uint32_t n_old = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while the ticket comes back)
+    const uint32_t n_old_d = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while the ticket comes back)
     const uint32_t key_lo_d = FIRST ? 0u : d->key_lo, key_hi_d = FIRST ? 0u : d->key_hi;
     __syncthreads();
     const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ticket);
+    // A scalar, and with it all that follows from it (rows per ticket, the tile, its address, which kind of ticket this is): kept per lane
+    // these cost a launch that marks bits 7 registers more than its 64, 28 bytes per lane written to scratch - 14 MB in a launch of
+    // 480 tickets, 110 M vertices: 88 + 38 MB read + written and 54 us against 79 + 24 MB, the step 280 -> 274 us.
+    const uint32_t n_old = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_old_d);
     // old rows per ticket: more than the plan's when there are so many that the launch would need a second round of workgroups
     uint32_t rows = a.rows_per_ticket;
     if (!FIRST && rows < 128u) rows = 128u;
