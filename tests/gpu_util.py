@@ -1,5 +1,8 @@
 """Helpers shared by the GPU parity tests: run the HIP path through the C-ABI binding and compare
 every output with the CPU checker on the same seeded inputs."""
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -67,9 +70,12 @@ def run_and_compare(oracle, g, feat, seeds, fanouts, key, *, env=None, plan=None
 
 
 def samples_in_one_workgroup(plan):
-    """Whether the plan's step samples all its hops in one workgroup: the rule zg_plan_info documents beside grid_sample."""
-    H = plan.num_hops
-    return sum(plan.info.edge_cap[h] for h in range(H)) <= 3840 * H - 1920 and plan.graph.num_nodes <= 1 << 18
+    """Whether the plan's step samples all its hops in one workgroup (the rule zg_plan_info documents beside grid_sample, with the
+    planner's own constants): asserted where a test is there for one of the two routes."""
+    src = open(os.path.join(os.path.dirname(zg.__file__), "csrc", "zg_internal.h")).read()
+    const = {k: int(re.search(rf"\b{k} = (\d+);", src).group(1)) for k in ("kSmallEdgesPerHop", "kSmallMaxWords")}
+    H, per_hop = plan.num_hops, const["kSmallEdgesPerHop"]
+    return sum(plan.info.edge_cap[h] for h in range(H)) <= per_hop * H - per_hop // 2 and -(-plan.graph.num_nodes // 32) <= const["kSmallMaxWords"]
 
 
 def truncated_blocks(oracle, g, seeds, fanouts, key, caps):

@@ -1,12 +1,13 @@
-"""GPU parity on the routes a step can take beyond the plain one: steps that the caps cut short, each at the route its sizes lead to
-(marks as bits or bytes, all hops in one workgroup or a launch per hop)."""
+"""GPU parity on each of the routes a step can take (marks as bits or bytes, all hops in one workgroup or a launch per hop): steps that
+the caps cut short, and the degenerate shapes - bad seeds, no edges, ragged words and rows - at sizes that reach the hop launches, with the
+route asserted."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2605_29346_amd import workloads as W
 from paper_2605_29346_amd import zg
-from gpu_util import agg_error, compare_blocks, compare_truncated, samples_in_one_workgroup, to_host_graph, truncated_blocks
+from gpu_util import agg_error, compare_blocks, compare_truncated, run_and_compare, samples_in_one_workgroup, to_host_graph, truncated_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -160,3 +161,122 @@ def test_the_stop_watch_of_a_small_step_is_on_its_aggregation_alone(oracle, flag
             times[which].append(a.elapsed_time(b))
     step, copy, mean = (min(times[k]) for k in ("step", 0, 1))
     assert step < mean + 0.5 * copy, (step, copy, mean)
+
+
+def _plan(g, fanouts, batch, small, feat=None, **more):
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), fanouts, batch, zg.make_envelope(zg.ENV_MAX, **more), feat_dim=0 if feat is None else feat.shape[1])
+    assert samples_in_one_workgroup(plan) == small
+    if feat is not None:
+        plan.bind_features(feat if feat.is_cuda else feat.cuda())
+    return plan
+
+
+@pytest.mark.parametrize("batch,small", [(30, True), (400, False), (1500, False)])  # (the last: two workgroups ingest the seeds)
+def test_bad_seeds_on_either_route(oracle, batch, small):
+    # flags, and no row for an id out of range; the clean step after it is exact
+    g = W.rmat_graph(5000, 80_000, 6)
+    plan, og = _plan(g, (4, 4), batch, small), to_host_graph(oracle, g)
+    good = W.SeedPool(g, batch, 3).batch_for(0).numpy()
+    for at in (0, batch // 2, batch - 1):
+        for bad in (5000, -1, -2**31, 2**31 - 1):
+            seeds = good.copy()
+            seeds[at] = bad
+            plan.step(torch.as_tensor(seeds).cuda(), 1)
+            torch.cuda.synchronize()
+            assert int(plan.view_counts()[3].cpu()[0]) == zg.FLAG_SEED_RANGE
+            row_ptr = plan.view_block(0)[0].cpu().numpy()
+            assert row_ptr[at + 1] == row_ptr[at] and int(plan.view_S()[at].item()) == -1
+            plan.overflow_clear()
+        seeds = good.copy()
+        seeds[at] = good[(at + 1) % batch]
+        plan.step(torch.as_tensor(seeds).cuda(), 1)
+        torch.cuda.synchronize()
+        assert int(plan.view_counts()[3].cpu()[0]) & zg.FLAG_SEED_DUP
+        plan.overflow_clear()
+        plan.step(torch.as_tensor(good).cuda(), 2)
+        compare_blocks(plan.read_step(), og.sample_blocks(good, (4, 4), 2), f"after bad seeds at {at}")
+
+
+def test_a_graph_without_edges_on_the_hop_launches(oracle):
+    n = 1000
+    g = W.Graph(n, torch.zeros(n + 1, dtype=torch.int32), torch.zeros(0, dtype=torch.int32))
+    feat = W.feature_table(n, 8, 1)
+    seeds = np.arange(300, 800, dtype=np.int32)
+    plan = _plan(g, (8, 8), 500, False, feat)
+    _, res, _ = run_and_compare(oracle, g, feat, seeds, (8, 8), 7, plan=plan)
+    assert res.n == [500, 500, 500] and res.E == [0, 0] and np.all(res.agg == 0)
+
+
+def test_a_single_seed_on_the_hop_launches(oracle):
+    g = W.rmat_graph(300_000, 3_000_000, 2)  # (more vertices than one workgroup's bitmaps hold)
+    feat = W.feature_table(300_000, 12, 1)
+    deg = np.diff(g.offsets.numpy())
+    plan, og = _plan(g, (5, 5, 5), 1, False, feat), to_host_graph(oracle, g)
+    for v in (int(np.argmax(deg)), int(np.argmin(deg)), 299_999):
+        run_and_compare(oracle, g, feat, np.array([v], dtype=np.int32), (5, 5, 5), 3, plan=plan, og=og)
+
+
+def test_the_published_known_answer_on_the_hop_launches(oracle):
+    # vertex 0 draws 0xe169c58d6627e8d5 / 2^64 at key 0, hop 0, slot 0 (the all-zero Philox input)
+    n = 300_000
+    for d in (5, 1000):
+        off = np.full(n + 1, d, dtype=np.int64)
+        off[0] = 0
+        g = W.Graph(n, torch.as_tensor(off), torch.arange(1, d + 1, dtype=torch.int32))
+        _, res, _ = run_and_compare(oracle, g, None, np.array([0], dtype=np.int32), (1,), 0, plan=_plan(g, (1,), 1, False))
+        assert res.nbr_gid[0].tolist() == [((0xE169C58D6627E8D5 * d) >> 64) + 1]
+
+
+@pytest.mark.parametrize("nodes,batch,fanouts", [
+    (31, 31, (64,)), (32, 32, (64,)), (33, 33, (64,)),                            # every vertex a seed; one word, a word and a bit
+    (95, 40, (64, 64)), (96, 40, (64, 64)), (97, 40, (64, 64)), (97, 50, (64, 63, 64)),
+    (1023, 900, (5, 2)), (1025, 1025, (4, 2)),                                   # a ranking tile of 32 words, and one bit more
+])
+@pytest.mark.parametrize("flags", [0, zg.PLAN_REPLACE])
+def test_ragged_words_on_the_hop_launches(oracle, nodes, batch, fanouts, flags):
+    g = W.rmat_graph(nodes, 12 * nodes, nodes)
+    feat = W.feature_table(nodes, 5, 1)
+    plan, og = _plan(g, fanouts, batch, False, feat, flags=flags), to_host_graph(oracle, g)
+    for s in range(2):
+        seeds = np.random.RandomState(s).permutation(nodes)[:batch].astype(np.int32)
+        run_and_compare(oracle, g, feat, seeds, fanouts, 11 + s, plan=plan, og=og, replace=bool(flags))
+
+
+def test_more_steps_queued_than_the_mailbox_holds_on_the_hop_launches(oracle):
+    g = W.rmat_graph(30_000, 600_000, 21)
+    plan, og, pool, steps = _plan(g, (8, 4), 160, False), to_host_graph(oracle, g), W.SeedPool(g, 160, 2), 600
+    batches = [pool.batch_for(s).cuda() for s in range(steps)]
+    torch.cuda.synchronize()
+    for s in range(steps):
+        plan.step(batches[s], 9000 + s)
+    torch.cuda.synchronize()
+    assert plan.step_status() == (steps, 0)
+    log = plan.view_log().cpu().numpy()
+    for s in range(steps):
+        ref = og.sample_blocks(batches[s].cpu().numpy(), (8, 4), 9000 + s)
+        assert log[s][0] == s and log[s][1] == 0 and list(log[s][2:5]) == ref.n and list(log[s][5:7]) == ref.E, f"step {s}"
+
+
+@pytest.mark.parametrize("dim", [1, 3, 4, 5, 7, 75, 102, 600])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_ragged_and_shifted_rows_through_the_closing_launchs_copy(oracle, dim, shift):
+    # rows that start at any multiple of four bytes; the frontier's are copied by workgroups of 512 lanes beside the ranking
+    g = W.rmat_graph(6000, 90_000, 3)
+    feat, og = W.feature_table(6000, dim, 4), to_host_graph(oracle, g)
+    seeds = W.SeedPool(g, 200, 2).batch_for(0).numpy()
+    wide = torch.full((6000, dim + 5), 1e30, device="cuda")
+    wide[:, shift: shift + dim] = feat.cuda()
+    ref = og.sample_blocks(seeds, (6, 4), 11)
+    X_ref = oracle.gather(feat.numpy(), ref.S)
+    agg_ref = oracle.aggregate_mean(ref.row_ptr[-1], ref.col[-1], X_ref)
+    for flags in (0, zg.PLAN_X_TWO_PASS, zg.PLAN_FUSED_INPUT):
+        plan = _plan(g, (6, 4), 200, False, wide[:, shift: shift + dim], flags=flags)
+        out = plan.out
+        last = out.d_agg + 4 * ((out.node_cap[1] - 1) * out.ld_agg + (dim + 3) // 4 * 4) - plan.workspace.data_ptr()
+        plan.workspace[last: last + 256] = 0xA5
+        plan.step(torch.as_tensor(seeds).cuda(), 11)
+        res = plan.read_step()
+        compare_blocks(res, ref, f"flags {flags}")
+        assert np.array_equal(res.X, X_ref[: res.X.shape[0]])
+        assert agg_error(oracle, res.agg, agg_ref, ref.row_ptr[-1], ref.col[-1], X_ref) <= 1e-5
+        assert bool((plan.workspace[last: last + 256] == 0xA5).all())
