@@ -115,7 +115,8 @@ typedef struct {
     double model_sigma[ZG_MAX_HOPS + 1];  /* Lemma 1 sigma of n_h */
     double z;                             /* Phi^-1(confidence^(1/iterations)) */
     int64_t envelope_bytes;               /* step outputs: S, block CSRs, X, agg, metadata */
-    int64_t scratch_bytes;                /* id map over |V|, mark maps, scan state */
+    int64_t scratch_bytes;                /* id map over |V| (4 bytes a vertex), scan state, two mark maps: a bit per vertex each,
+                                             or a byte where a hop that fills it samples an edge per 30 vertices or more */
     int64_t workspace_bytes;              /* envelope + scratch + alignment: what zg_plan needs */
     int64_t maxsg_envelope_bytes;         /* envelope_bytes if ZG_ENV_MAX had been used */
     int32_t grid_sample[ZG_MAX_HOPS];     /* launch caps (workgroups) of the fixed launch skeleton: hop kernel launch h

@@ -1,7 +1,7 @@
 // HIP kernels (gfx950, wave64) and the plan / step entry points of libzg.
 //
 // One step = H+2 launches: the hop kernel's launches 0..H-1, the closing launch and {aggregate + relabel of the last hop +
-// finish} (H+3 when X is written by a gather launch of its own; a small step's hops are one workgroup's work: 2).  Launch l of
+// finish} (H+3 when X is written by a gather launch of its own; a small step's hops are one workgroup's work: 2, or 3).  Launch l of
 // the hop kernel samples hop l and, for l > 0, first ranks the vertices hop l-1 discovered - they are rows of block l
 // themselves, so ranking and sampling share their chained scans; launch 0 also ingests the seeds, launch l >= 2 relabels the
 // edges of hop l-2 and the closing launch ranks only (workgroups of a launch are split by role).
@@ -216,9 +216,9 @@ __device__ __forceinline__ void mailbox_inputs(const Drmb *d, const Drmb *gate, 
     out[1] = __hip_atomic_load(&mailbox->slot[slot].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// One lane of a ticket, where nothing was prefetched (the host waits for every step, or this is the first): ticket 0 reads the
-// mailbox and passes the inputs on in device memory.  Reads of host memory queue up: 132 workgroups that each read the
-// slot took 20 us.  Ticket 0's workgroup runs before any other ticket is handed out; a wait that runs out reads the mailbox itself.
+// One lane of a sampling ticket, where nothing was prefetched (the host waits for every step, or this is the first): ticket 0 reads
+// the mailbox and passes the inputs on in device memory.  Reads of host memory queue up: 132 workgroups that each read the
+// slot took 20 us.  (The ingest workgroups of the launch, one per 1024 seeds, read it themselves.)  Ticket 0's workgroup runs before any other ticket is handed out; a wait that runs out reads the mailbox itself.
 __device__ __forceinline__ void shared_inputs(Drmb *d, const Drmb *gate, const Mailbox *mailbox, uint32_t ticket, unsigned long long *out)
 {
     const uint32_t tag = d->epoch + 1u;
@@ -392,12 +392,7 @@ __device__ __forceinline__ void gather_rows(const RowArgs &a, uint32_t row0, uin
     }
 }
 
-// "Gather": X[i,:] = feat[S[i],:].  A workgroup copies `rows` consecutive output rows; lanes walk the rows
-// as one flat run of 16-byte pieces so that rows whose length is not a multiple of the wave width still
-// fill every lane, four loads in flight per lane before the stores.  When the gathered matrix of this step
-// is larger than the caches can hold for the aggregation that follows (decided on the device from the true
-// row count), loads and stores are non-temporal: measured +15 % at 200 MB, -10 % at 90 MB.
-// the same for a launch that copies the frontier's rows only (never large enough for the non-temporal path)
+// the frontier's rows only, beside the closing launch's ranking or ahead of a small step's aggregation
 template <int VEC>
 __device__ __forceinline__ void gather_rows_block(const RowArgs &a, uint32_t block, int32_t *s_id)
 {
@@ -410,6 +405,9 @@ __device__ __forceinline__ void gather_rows_block(const RowArgs &a, uint32_t blo
     gather_rows<VEC, false, true>(a, row0, rows, s_id); // nothing in the step reads these rows of X again: stored past the caches
 }
 
+// a launch of its own.  When the gathered matrix of this step is larger than the caches can hold for the aggregation that
+// follows (decided on the device from the true row count), loads and stores are non-temporal: measured +15 % at 200 MB,
+// -10 % at 90 MB.
 template <int VEC>
 __device__ __forceinline__ void gather_block(const RowArgs &a, uint32_t block, int32_t *s_id)
 {
@@ -753,7 +751,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ticket);
     // A scalar, and with it all that follows from it (rows per ticket, the tile, its address, which kind of ticket this is): kept per lane
     // these cost a launch that marks bits 7 registers more than its 64, 28 bytes per lane written to scratch - 14 MB in a launch of
-    // 480 tickets, 110 M vertices: 88 + 38 MB read + written and 54 us against 79 + 24 MB, the step 280 -> 274 us.
+    // 480 tickets.  (110 M vertices: 88 + 38 MB read + written by that launch, now 79 + 24 MB; the step 280 -> 274 us.)
     const uint32_t n_old = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_old_d);
     // old rows per ticket: more than the plan's when there are so many that the launch would need a second round of workgroups
     uint32_t rows = a.rows_per_ticket;
@@ -2126,8 +2124,8 @@ int zg_plan(zg_plan_t **out, const zg_graph_t *g, const int32_t *fanouts, int32_
     char *ws = static_cast<char *>(d_workspace);
     const bool with_twin = (env->flags & (ZG_PLAN_SAFE_TWIN | ZG_PLAN_AUTO_FALLBACK)) != 0;
     zg_plan_t *p = nullptr;
-    // with a twin the shared scratch is sized through the twin's (larger) layout; each of the two clears the regions of
-    // its own layout (they overlap, but neither covers the other's: the gaps between one's regions are inside the other's)
+    // with a twin both lay their scratch out in the same region, sized for the larger of the two.  The id maps coincide; everything
+    // behind them has to be zero between steps, whichever layout reads it: each of the two clears the regions of its own.
     rc = make_plan_object(&p, g, L, env->flags, batch, ws, st, true);
     if (rc != ZG_OK) return rc;
     if (with_twin) {

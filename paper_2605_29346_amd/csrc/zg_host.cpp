@@ -264,7 +264,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
                 int64_t W = std::max<int64_t>(kHopMinTileWords, (int64_t)align_up((size_t)((words + want - 1) / want), kHopMinTileWords));
                 // A launch that samples for few rows over a very long bitmap (its tile count is set by the rows, not by the
                 // budget) takes tiles of 16 words per lane: half the tickets, each still about one sampling pass of rows.
-                // (At 110 M vertices and 25 k rows: 27.5 us instead of 29.3 us; a launch whose tiles hold several passes of rows
+                // (At 110 M vertices and 25 k rows: the step 271.1 us instead of 272.4; a launch whose tiles hold several passes of rows
                 // each loses more by the longer tickets, 53 -> 57 us with 157 k rows.  A byte-marked tile stays at 256 KB.)
                 const int64_t max_words = l < num_hops && 2 * ((L.node_cap[l] + T - 1) / T) < 3 * budget && !L.byte_marks[l - 1] ? kHopFatTileWords : kHopMaxTileWords;
                 if (W > kHopBlock) { // whole rounds of the workgroup beyond one word per lane

@@ -19,9 +19,9 @@ constexpr int kHopMaxTpt = 4;           // most consecutive tiles of frontier ro
 constexpr int kHopMaxWordsPerLane = 8;  // bitmap words of a ranking tile per lane of a 1024-lane workgroup
 constexpr size_t kHopLdsBytes = 78 << 10; // LDS of a sampling workgroup: half a compute unit's
 // A step whose edge caps sum up to at most 3840 H - 1920, on a graph whose bitmaps fit into LDS twice, samples all its hops in
-// one workgroup (k_small): two launches instead of H + 2.  Step time against the launches per hop: two hops of 2240 edges
-// 32.9 -> 24.5 us, of 7680 with 2400-byte rows 39.3 -> 37.5 (56 -> 58 where the host waits for each), of 14160 37.8 -> 42.9; three
-// hops of 9460 45.3 -> 39.8; one hop of 3500 26.8 -> 27.1.
+// one workgroup (k_small): two launches instead of H + 2 (three instead of H + 3 with ZG_PLAN_X_TWO_PASS).  Step time against the
+// launches per hop: two hops of 2240 edges 32.9 -> 24.6 us, of 7680 with 2400-byte rows 38.1 -> 37.5 (56 -> 58 where the host waits
+// for each), of 14160 37.8 -> 42.9; three hops of 9460 42.4 -> 39.6; one hop of 3500 26.8 -> 27.2.
 constexpr int64_t kSmallEdgesPerHop = 3840;
 constexpr int kSmallMaxWords = 8192;      // 262144 vertices: 32 KB per bitmap
 constexpr size_t kSmallStage = 8192;      // sampled ids it holds at once
@@ -33,7 +33,7 @@ constexpr int kHopFatTileWords = kHopBlock * kHopFatWordsPerLane; // 16384 words
 // A hop that marks E of V vertices: bits cost E device-scope atomics (12-25 G/s on this chip whatever the address pattern, and
 // hubs serialise further), bytes cost E plain stores (50-150 G/s) and a map eight times as large to read back, by a launch that
 // has other things to read.  Step time with bits / bytes in the last hop: V / E = 8 and 26 (2.4 M vertices, also the hop before)
-// 120.3 / 117.4 us, 32 (8 M) 108.3 / 109.1, 41 (20 M) 182.7 / 187.9, 48 (40 M) 196.6 / 206.7.
+// 117.3 / 115.1 us, 30 (8 M) 103.4 / 105.1, 41 (20 M) 176.6 / 183.1, 48 (40 M) 190.6 / 206.5.
 constexpr int64_t kByteMarkVerticesPerEdge = 30;
 constexpr int kSampleHashBits = 11;      // LDS dedup set of a sampling workgroup: 2048 slots for <= 1024 ids
 constexpr int kSampleHashSlots = 1 << kSampleHashBits;
