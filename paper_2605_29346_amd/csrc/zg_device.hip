@@ -323,10 +323,11 @@ struct RowArgs {
     float *dst;
     const int32_t *S;       // gather: global ids of the rows to copy
     const int32_t *row_ptr; // aggregate
-    const int32_t *col;     // aggregate: per edge, the index of its input row (local ids, or global ids: see n_cols)
+    const int32_t *col;     // aggregate: per edge, the index of its input row (local ids, or - where col_out is set - global ids)
     const uint32_t *n_rows; // device address of the row count
-    const uint32_t *n_cols; // aggregate: device address of the number of valid input rows, or null if `col_limit` holds it
-    uint32_t col_limit;     // aggregate: number of valid input rows when n_cols is null (num_nodes for global ids)
+    const uint32_t *n_cols; // aggregate: device address of the block's number of columns: an id at or beyond it is none (where ids come
+                            // from the id map: not of this step but a twin's, see mark_tag)
+    uint32_t col_limit;     // aggregate whose `col` holds global ids: the number of input rows (num_nodes)
     float *x_dst;           // aggregate reading the table: X, whose rows of newly discovered vertices it writes on the way (or null)
     const uint8_t *own;     // ... per edge, whether this edge is the one that writes it (null: the id map's entry carries its tag)
     MarkTag tag;            // ... how the id map's entries carry it
@@ -340,8 +341,7 @@ struct RowArgs {
     int32_t vec4;           // rows are moved in pieces of four floats (else, below four, element by element)
     int32_t nt;             // aggregate inside a step: what it writes (means, rows of X) is stored past the caches (non-temporal)
     const int32_t *local_id; // aggregate that relabels its block's edges itself: the id map ...
-    int32_t *col_out;        // ... where col[e] = local id of nbr_gid[e] goes ...
-    const uint32_t *n_ids;   // ... and the device address of the number of local ids: an entry beyond it is not of this step (a twin's, see mark_tag)
+    int32_t *col_out;        // ... and where col[e] = local id of nbr_gid[e] goes
     uint32_t blocks; // workgroups given to this role (0: role absent)
 };
 
@@ -1354,8 +1354,7 @@ __device__ __forceinline__ void aggregate_block(const RowArgs &a, uint32_t block
     int32_t *s_col = s_mem + a.rows + 1; // [rows * max_fanout]
     int32_t *s_dst = s_col + a.rows * a.max_fanout; // [rows * max_fanout] when X is written on the way: row of X, or -1
     const uint32_t n = *a.n_rows;
-    const uint32_t n_in = a.n_cols ? *a.n_cols : a.col_limit;
-    const uint32_t n_ids = a.col_out ? *a.n_ids : 0u;
+    const uint32_t n_ids = *a.n_cols, n_in = a.col_out ? a.col_limit : n_ids;
     const uint32_t row0 = block * a.rows;
     if (row0 >= n) return;
     const uint32_t rows = n - row0 < a.rows ? n - row0 : a.rows;
@@ -1738,7 +1737,7 @@ RowArgs aggregate_args(const zg_plan_t *p, int hop, const float *d_in, int64_t l
     a.row_ptr = p->row_ptr(hop);
     a.col = by_gid ? p->nbr(hop) : p->col(hop);
     a.n_rows = &p->drmb()->n[hop];
-    a.n_cols = by_gid ? nullptr : &p->drmb()->n[hop + 1];
+    a.n_cols = &p->drmb()->n[hop + 1];
     a.col_limit = (uint32_t)p->graph->num_nodes;
     a.ld_src = ld_in;
     a.ld_dst = ld_out;
@@ -1816,7 +1815,6 @@ void step_feature_args(const zg_plan_t *p, RowArgs *gat, RowArgs *agg)
         // the aggregation relabels the last hop's edges itself (it holds their sampled ids anyway): no launch in between
         agg->local_id = p->local_id();
         agg->col_out = p->col(H - 1);
-        agg->n_ids = &p->drmb()->n[H];
     } else {
         *agg = aggregate_args(p, H - 1, p->X(), L.ld_out, L.feat_dim, p->agg(), L.ld_out, false);
     }
