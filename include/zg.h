@@ -141,7 +141,8 @@ typedef struct {
     const int32_t *d_S;        /* [node_cap[H]] global ids; local id = index */
     const int32_t *d_row_ptr[ZG_MAX_HOPS]; /* [node_cap[h]+1] */
     const int32_t *d_nbr_gid[ZG_MAX_HOPS]; /* [edge_cap[h]] sampled neighbor global ids, slot order */
-    const int32_t *d_col[ZG_MAX_HOPS];     /* [edge_cap[h]] local ids: block h is (row_ptr, col), n_h x n_{h+1} */
+    const int32_t *d_col[ZG_MAX_HOPS];     /* [edge_cap[h]] local ids: block h is (row_ptr, col), n_h x n_{h+1}; -1 where
+                                              the hop's cap dropped the vertex (the step is flagged) */
     int64_t node_cap[ZG_MAX_HOPS + 1];
     int64_t edge_cap[ZG_MAX_HOPS];
     const float *d_X;   /* [x_row_cap, ldx] gathered feature rows of S_{H-1} (NULL if feat_dim == 0) */
@@ -330,7 +331,8 @@ int zg_calibration_copy(const void *d_src, void *d_dst, size_t bytes, void *stre
  * meant for timing the step's dominant kernels one by one.  Errors: ZG_EINVAL, ZG_ESTATE (no features bound), ZG_EHIP. */
 int zg_plan_replay_features(zg_plan_t *p, int32_t which, void *stream);
 /* zg_step with a stop-watch on its dominant kernel: the same step (same outputs, same mailbox and status bookkeeping),
- * its kernels enqueued one by one as a ZG_PLAN_EAGER plan does instead of replaying the captured graph, and the caller's
+ * its kernels enqueued one by one as a ZG_PLAN_EAGER plan does instead of replaying the captured graph - the copy of a
+ * small step's frontier rows, otherwise a part of its aggregation launch, in a launch of its own -, and the caller's
  * two events (hipEvent_t, created with timing enabled) recorded on `stream` right before and right after the
  * aggregation launch (section 2.2, first GraphSAGE aggregation), so that their distance is that launch's duration
  * inside a real step.  Errors: as zg_step; ZG_ESTATE if no feature table is bound; ZG_EHIP if an event could not be
