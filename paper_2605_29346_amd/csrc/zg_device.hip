@@ -458,6 +458,7 @@ struct HopArgs {
     uint32_t edge_cap;        // capacity of E_l
     uint32_t stage_edges;     // ids a workgroup holds in LDS between loading and storing them
     uint32_t words_per_tile;  // ranking tile (a multiple of 32)
+    uint32_t chunk_log2;      // ... of at most a word per lane: a lane ranks 2^chunk_log2 vertices (4 .. 32)
     uint32_t rank_tiles;      // 0 for launch 0
     uint32_t batch;
     uint32_t blocks;          // workgroups of this role (the launch's first ones)
@@ -596,6 +597,15 @@ __device__ __forceinline__ uint32_t load_rows(const HopArgs &a, HopShared &sh, u
     return a.replace ? (deg > 0 ? F : 0u) : (deg < F ? deg : F);
 }
 
+// The same value in a scalar register of its own.  The compiler keeps some values that are the same for the whole workgroup in
+// vector registers, and so all that it computes from them; and what a kernel's head and its tail compute alike it computes once, at the
+// head, and keeps: registers of which k_hop has none to spare (they go to memory).
+__device__ __forceinline__ int32_t own_scalar(int32_t x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 // the lowest q set bits of x
 __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
 {
@@ -718,6 +728,73 @@ __device__ __forceinline__ void expand_piece(const uint4 &x, uint32_t j, uint32_
             if (j - c0 < n) v[j - c0] = (int32_t)(((first_word + c) << 5) + (uint32_t)__ffs((int)w) - 1u);
 }
 
+// A tile of at most a word per lane (the graph is small for its ranking tiles, the tile dense with new vertices): the lane's word
+// of new vertices, also left in s_words.  A word per lane while it is read, and 2^chunk_log2 vertices per lane once it is ranked and
+// expanded (pieces of 128 left 16 lanes of 1024 to walk through a tile of 64 words, up to 128 vertices one after another: a hop launch
+// over 250 k vertices 15.6 -> 14.5 us, with 2.4 M vertices 57 -> 54).  Marks are cleared where they are read, 16 bytes per lane, unless
+// their tags are still needed.
+template <int NT, bool BYTES, bool JOIN>
+__device__ __forceinline__ uint32_t load_words(const HopArgs &a, size_t tile0, uint32_t words, uint32_t tid, uint32_t *s_words)
+{
+    const bool tagged = BYTES && !JOIN && a.tag.shift != 0;
+    uint32_t sn = 0u, w = 0u;
+    if (tid < words) sn = a.seen[tile0 + tid];
+    if (BYTES) {
+        uint4 *src = reinterpret_cast<uint4 *>(a.marks_prev) + tile0 * 2u;
+        uint16_t *half = reinterpret_cast<uint16_t *>(s_words);
+#pragma unroll 2
+        for (uint32_t q = tid; q < 2u * words; q += (uint32_t)NT) {
+            const uint4 y = src[q];
+            half[q] = (uint16_t)(marks4(y.x) | (marks4(y.y) << 4) | (marks4(y.z) << 8) | (marks4(y.w) << 12));
+            if (!tagged && piece_any(y)) src[q] = make_uint4(0u, 0u, 0u, 0u);
+        }
+        __syncthreads();
+        if (tid < words) w = s_words[tid];
+    } else if (tid < words) {
+        w = a.marks_prev[tile0 + tid];
+        if (w) a.marks_prev[tile0 + tid] = 0u;
+    }
+    const uint32_t fresh = w & ~sn;
+    if (JOIN && fresh) a.seen[tile0 + tid] = sn | fresh;
+    if (tagged && w) { // a new vertex's byte stays until its tag has been read
+        uint4 *b = reinterpret_cast<uint4 *>(a.marks_prev) + (tile0 + tid) * 2u; // the word's 32 bytes
+        if (fresh == 0u)
+            b[0] = b[1] = make_uint4(0u, 0u, 0u, 0u);
+        else
+            for (uint32_t old = w & ~fresh; old; old &= old - 1u) reinterpret_cast<uint8_t *>(b)[__ffs((int)old) - 1] = 0;
+    }
+    if (tid < words) s_words[tid] = fresh;
+    return fresh;
+}
+
+// ... and its ranks: the lane's chunk of the tile's words (in s_words: barriers before the first and after the last use are in
+// here), `before` = new vertices ahead of it.  Returns their number.  `wsum` holds a count per wavefront.
+template <int NT>
+__device__ __forceinline__ uint32_t rank_chunks(uint32_t word, uint32_t chunk_log2, uint32_t words, const uint32_t *s_words, uint32_t *wsum, uint32_t tid,
+                                                uint32_t &chunk, uint32_t &before)
+{
+    const uint32_t lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    __syncthreads();
+    chunk = word;
+    if (chunk_log2 < 5u) {
+        const uint32_t at = tid << chunk_log2, w = at >> 5;
+        chunk = w < words ? (s_words[w] >> (at & 31u)) & ((1u << (1u << chunk_log2)) - 1u) : 0u;
+    }
+    const uint32_t c = __popc(chunk), incl = wave_incl_scan(c);
+    if (lane == 63u) wsum[wave] = incl;
+    __syncthreads();
+    const uint32_t e = lane < (uint32_t)NT / 64u ? wsum[lane] : 0u, sum = wave_incl_scan(e);
+    before = lane_value(sum, wave) - lane_value(e, wave) + incl - c;
+    return lane_value(sum, 63u);
+}
+
+// the new vertices number c0 .. c0 + n - 1 of the tile into v: those of one chunk, the first of which is vertex `first`
+__device__ __forceinline__ void expand_chunk(uint32_t chunk, uint32_t before, uint32_t first, uint32_t c0, uint32_t n, int32_t *v)
+{
+    for (uint32_t j = before - c0; chunk; chunk &= chunk - 1u, ++j)
+        if (j < n) v[j] = (int32_t)(first + (uint32_t)__ffs((int)chunk) - 1u);
+}
+
 struct HopRoles { // the other workgroups of launches 0 .. H-1
     RelabelArgs rel; // launches 2 ..
     IngestArgs ing;  // launch 0
@@ -771,37 +848,58 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
 
     // ---- what this ticket's rows are: m old rows from r0 on, or the tile's m new vertices
     uint32_t m;
-    uint32_t lex[R];
-    const uint32_t r0 = ticket * rows, tile = ticket - t_old;
+    const uint32_t r0 = ticket * rows, tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ticket - t_old));
     const uint32_t np = a.words_per_tile / 4u; // the tile's pieces
     const size_t tile0 = (size_t)tile * a.words_per_tile;
     uint4 *const s_piece = reinterpret_cast<uint4 *>(s_words);
+    const bool by_chunks = a.words_per_tile <= (uint32_t)kHopBlock;
+    uint32_t chunk = 0u, before_chunk = 0u;
+    auto expand_pieces = [&](const uint4 (&x)[R], const uint32_t (&lex)[R], uint32_t c0) {
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (u * (uint32_t)kHopBlock + tid < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kHopBlock + tid) * 4u, c0, kHopRows, sh.v);
+    };
+    // the tile's words as they were ranked, out of LDS, and their ranks once more (a tile of several batches of rows, or cut by the cap)
+    auto pieces_again = [&](uint4 (&x)[R], uint32_t (&lex)[R]) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) x[u] = u * (uint32_t)kHopBlock + tid < np ? s_piece[u * kHopBlock + tid] : make_uint4(0u, 0u, 0u, 0u);
+        (void)rank_pieces<kHopBlock, R>(x, lex, sh.wsum, np, wave, lane);
+    };
     if (old) {
         m = n_old - r0 < rows ? n_old - r0 : rows;
+    } else if (by_chunks) {
+        const uint32_t word = load_words<kHopBlock, PREV_BYTES, true>(a, tile0, a.words_per_tile, tid, s_words);
+        m = rank_chunks<kHopBlock>(word, a.chunk_log2, a.words_per_tile, s_words, sh.wsum, tid, chunk, before_chunk);
+        if (tid == 0) chain_publish(a.status_cnt, tile, m);
     } else {
         uint4 x[R];
+        uint32_t lex[R];
         load_tile<kHopBlock, R, PREV_BYTES, true>(a, tile0, np, tid, x, s_words);
         m = rank_pieces<kHopBlock, R>(x, lex, sh.wsum, np, wave, lane);
+        if (tid == 0) chain_publish(a.status_cnt, tile, m);
+        expand_pieces(x, lex, 0u);
 #pragma unroll
         for (int u = 0; u < R; ++u)
             if (u * (uint32_t)kHopBlock + tid < np) s_piece[u * kHopBlock + tid] = x[u]; // (read back by this lane only)
-        if (tid == 0) chain_publish(a.status_cnt, tile, m);
     }
 
     // rows c0 .. c0 + 1023 of the ticket into sh.v: old rows from the frontier list (launch 0: the seeds, an
-    // out-of-range one becoming -1, a vertex without neighbors), new vertices expanded from the lane's words
-    auto fill_rows = [&](uint32_t c0) {
+    // out-of-range one becoming -1, a vertex without neighbors), new vertices expanded from the lane's words (`first`: a tile
+    // ranked by pieces has its first batch there already)
+    auto fill_rows = [&](uint32_t c0, bool first) {
         if (old) {
             if (tid < m) {
                 int32_t v = FIRST ? reinterpret_cast<const int32_t *>(sh.in[0])[r0 + tid] : a.S[r0 + tid];
                 if (FIRST && (uint32_t)v >= a.num_nodes) v = -1;
                 sh.v[tid] = v;
             }
-        } else {
-#pragma unroll
-            for (int u = 0; u < R; ++u)
-                if (u * (uint32_t)kHopBlock + tid < np)
-                    expand_piece(s_piece[u * kHopBlock + tid], lex[u], (uint32_t)tile0 + (u * (uint32_t)kHopBlock + tid) * 4u, c0, kHopRows, sh.v);
+        } else if (by_chunks) {
+            expand_chunk(chunk, before_chunk, ((uint32_t)tile0 << 5) + (tid << a.chunk_log2), c0, kHopRows, sh.v);
+        } else if (!first) {
+            uint4 x[R];
+            uint32_t lex[R];
+            pieces_again(x, lex);
+            expand_pieces(x, lex, c0);
         }
         __syncthreads();
     };
@@ -813,7 +911,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         uint32_t before = 0; // earlier batches
         for (uint32_t q = 0; q < supers; ++q) {
             const uint32_t c0 = q * kHopRows;
-            fill_rows(c0);
+            fill_rows(c0, q == 0);
             before += lane_value(kincl, 63u);
             k = load_rows<OffT>(a, sh, m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows, tid);
             kincl = wave_incl_scan(k);
@@ -854,7 +952,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         const uint32_t nrows = m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows;
         if (supers > 1) {
             if (q) __syncthreads(); // the last batch's rows have been read
-            fill_rows(c0);
+            fill_rows(c0, false);
             k = load_rows<OffT>(a, sh, nrows, tid);
             kincl = wave_incl_scan(k);
             if (lane == 63u) sh.wk[wave] = kincl;
@@ -929,14 +1027,17 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
 
     if (m > room) {
         // ---- the cap cuts into this tile: the vertices dropped leave "seen" again
+        uint4 x[R];
+        uint32_t lex[R];
+        __syncthreads();
+        pieces_again(x, lex);
 #pragma unroll
         for (int u = 0; u < R; ++u)
             if (u * (uint32_t)kHopBlock + tid < np) {
-                const uint4 x = s_piece[u * kHopBlock + tid];
                 uint32_t j = lex[u];
 #pragma unroll
                 for (uint32_t c = 0; c < 4u; ++c) {
-                    const uint32_t w = piece_word(x, c), pc = __popc(w);
+                    const uint32_t w = piece_word(x[u], c), pc = __popc(w);
                     const uint32_t kept = j < room ? lowest_set_bits(w, room - j) : 0u;
                     if (kept != w) a.seen[tile0 + (u * (uint32_t)kHopBlock + tid) * 4u + c] &= ~(w & ~kept);
                     j += pc;
@@ -947,20 +1048,21 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     // ---- end of the block: the tile in which the cap falls closes a truncated block; the last ticket publishes the
     // hop's sizes and, when everything fitted, closes the block
     if (tid == 0) {
+        const int32_t launch = own_scalar(a.launch);
         if (rank0 <= a.cap_rows && (uint64_t)rank0 + m > a.cap_rows) {
             a.row_ptr[a.cap_rows] = (int32_t)ebase;
-            d->E[a.launch] = ebase;
+            d->E[launch] = ebase;
         }
         if (ticket == n_tickets - 1u) {
             const uint64_t exact = (uint64_t)rank0 + m;
-            d->n_exact[a.launch] = (uint32_t)exact;
-            d->n[a.launch] = exact < a.cap_rows ? (uint32_t)exact : a.cap_rows;
+            d->n_exact[launch] = (uint32_t)exact;
+            d->n[launch] = exact < a.cap_rows ? (uint32_t)exact : a.cap_rows;
             if (exact > a.cap_rows) {
-                atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
-                atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
+                atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(launch - 1));
+                atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(launch - 1));
             } else {
                 a.row_ptr[exact] = (int32_t)ebase;
-                d->E[a.launch] = ebase;
+                d->E[launch] = ebase;
             }
         }
     }
@@ -1132,15 +1234,16 @@ struct CloseRoles { // the closing launch's other workgroups
 // first in the grid: chains of dependent accesses, they all start at once and leave most of the chip to the copy, which is
 // bound by bandwidth and runs beside them.  Measured at 110 M vertices, 433 k new ones and a copy of 157 k rows of 512 bytes
 // (160 MB, 34 us alone): 54 us; 1024 lanes per ticket, tickets and copy alternating in the grid: 56 us.  Without a copy,
-// 2.4 M vertices and 668 k new ones: 31 us; 137 k new: 21 us, with 1024 lanes 26 us.
+// 2.4 M vertices and 668 k new ones: 20.6 us (31 us when a workgroup expanded 1024 of its 2800 vertices at a time, in pieces of 128 per
+// lane); 137 k new, with a copy of 25 MB: 21 us, with 1024 lanes 26 us.
 template <bool BYTES>
-__global__ __launch_bounds__(kCloseBlock) void k_close(HopArgs a, CloseRoles o)
+__global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles o)
 {
     constexpr int R = kHopMaxTileWords / 4 / kCloseBlock;
-    constexpr uint32_t kBatch = 1024; // vertices expanded at a time
+    constexpr uint32_t kBatch = kCloseBatch; // vertices expanded at a time
     __shared__ uint32_t s_ticket, s_base, s_wsum[64];
     __shared__ int32_t s_v[kBatch];
-    extern __shared__ __align__(16) uint32_t s_words[]; // byte marks: the tile's words
+    extern __shared__ __align__(16) uint32_t s_words[]; // the tile's words (bit marks: of a tile of at most a word per lane)
     if (gate_closed(a.gate)) return;
     if (blockIdx.x >= a.blocks) {
         uint32_t b = blockIdx.x - a.blocks;
@@ -1165,8 +1268,15 @@ __global__ __launch_bounds__(kCloseBlock) void k_close(HopArgs a, CloseRoles o)
     const size_t tile0 = (size_t)tile * a.words_per_tile;
     uint4 x[R];
     uint32_t lex[R];
-    load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
-    const uint32_t m = rank_pieces<kCloseBlock, R>(x, lex, s_wsum, np, wave, lane);
+    uint32_t m, chunk = 0u, before_chunk = 0u;
+    const bool by_chunks = a.words_per_tile <= (uint32_t)kCloseBlock;
+    if (by_chunks) {
+        const uint32_t word = load_words<kCloseBlock, BYTES, false>(a, tile0, a.words_per_tile, tid, s_words);
+        m = rank_chunks<kCloseBlock>(word, a.chunk_log2, a.words_per_tile, s_words, s_wsum, tid, chunk, before_chunk);
+    } else {
+        load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
+        m = rank_pieces<kCloseBlock, R>(x, lex, s_wsum, np, wave, lane);
+    }
     if (wave == 0u) {
         if (lane == 0) chain_publish(a.status_cnt, tile, m);
         const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane);
@@ -1177,17 +1287,21 @@ __global__ __launch_bounds__(kCloseBlock) void k_close(HopArgs a, CloseRoles o)
     uint8_t *const bytes = reinterpret_cast<uint8_t *>(a.marks_prev);
     for (uint32_t c0 = 0; c0 == 0 || c0 < m; c0 += kBatch) {
         if (c0) __syncthreads(); // the last batch has been read
+        if (by_chunks) {
+            expand_chunk(chunk, before_chunk, ((uint32_t)tile0 << 5) + (tid << a.chunk_log2), c0, kBatch, s_v);
+        } else {
 #pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (u * (uint32_t)kCloseBlock + tid < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + tid) * 4u, c0, kBatch, s_v);
+            for (int u = 0; u < R; ++u)
+                if (u * (uint32_t)kCloseBlock + tid < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + tid) * 4u, c0, kBatch, s_v);
+        }
         __syncthreads();
         rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_base);
         room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;
-#pragma unroll
-        for (uint32_t i = 0; i < kBatch; i += kCloseBlock) {
-            const uint32_t j = c0 + i + tid;
-            if (j < m) {
-                const int32_t gid = s_v[i + tid];
+#pragma unroll 2
+        for (uint32_t i = tid; i < kBatch && c0 + i < m; i += kCloseBlock) {
+            const uint32_t j = c0 + i;
+            {
+                const int32_t gid = s_v[i];
                 uint32_t mark = 0u;
                 if (tagged) {
                     mark = bytes[gid];
@@ -1199,12 +1313,13 @@ __global__ __launch_bounds__(kCloseBlock) void k_close(HopArgs a, CloseRoles o)
         }
     }
     if (tid == 0 && tile == a.rank_tiles - 1u) { // the last ticket publishes the hop's size
+        const int32_t launch = own_scalar(a.launch);
         const uint64_t exact = (uint64_t)rank0 + m;
-        d->n_exact[a.launch] = (uint32_t)exact;
-        d->n[a.launch] = exact < a.cap_rows ? (uint32_t)exact : a.cap_rows;
+        d->n_exact[launch] = (uint32_t)exact;
+        d->n[launch] = exact < a.cap_rows ? (uint32_t)exact : a.cap_rows;
         if (exact > a.cap_rows) {
-            atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
-            atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(a.launch - 1));
+            atomicOr(&d->flags, ZG_FLAG_HOP_OVERFLOW(launch - 1));
+            atomicOr(&d->step_flags, ZG_FLAG_HOP_OVERFLOW(launch - 1));
         }
     }
 }
@@ -1953,6 +2068,8 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         ha.cap_rows = (uint32_t)L.node_cap[l];
         ha.edge_cap = l < H ? (uint32_t)L.edge_cap[l] : 0u;
         ha.words_per_tile = l > 0 ? (uint32_t)L.tile_words[l] : (uint32_t)kHopMinTileWords;
+        ha.chunk_log2 = 5; // as few vertices per lane as the workgroup has lanes for
+        while (ha.chunk_log2 > 2 && ((uint64_t)ha.words_per_tile << (6 - ha.chunk_log2)) <= (uint64_t)(l < H ? kHopBlock : kCloseBlock)) --ha.chunk_log2;
         ha.rank_tiles = (uint32_t)L.rank_tiles[l];
         ha.batch = (uint32_t)p->batch;
         ha.blocks = (uint32_t)(L.old_tickets[l] + L.rank_tiles[l]);
@@ -1980,7 +2097,7 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
             if (ha.bytes_prev)
                 hipLaunchKernelGGL(k_close<true>, grid, block, (size_t)ha.words_per_tile * 4, st, ha, roles);
             else
-                hipLaunchKernelGGL(k_close<false>, grid, block, 0, st, ha, roles);
+                hipLaunchKernelGGL(k_close<false>, grid, block, ha.words_per_tile <= (uint32_t)kCloseBlock ? (size_t)ha.words_per_tile * 4 : 0, st, ha, roles);
         } else {
             const HopRoles roles = {ra, ia};
             const unsigned grid = ha.blocks + ra.blocks + ia.blocks;

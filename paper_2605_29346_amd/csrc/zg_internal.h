@@ -14,6 +14,7 @@ namespace zg {
 constexpr int kBlock = 256;             // threads per workgroup (4 wavefronts of 64)
 constexpr int kHopBlock = 1024;         // threads per workgroup of the hop kernel's sampling launches
 constexpr int kCloseBlock = 512;        // ... and of the closing launch, which only ranks
+constexpr uint32_t kCloseBatch = 4096;  // new vertices one of its workgroups holds at a time
 constexpr int kMaxTickets = 480;       // tickets per launch of the hop kernel: what 256 compute units hold at once (2 x 1024 lanes each), less a margin
 constexpr int kHopMaxTpt = 4;           // most consecutive tiles of frontier rows the plan gives a ticket
 constexpr int kHopMaxWordsPerLane = 8;  // bitmap words of a ranking tile per lane of a 1024-lane workgroup

@@ -345,3 +345,26 @@ def test_armed_fallback_of_small_and_featureless_steps(oracle, batch, fanouts, d
             assert np.array_equal(res.X, oracle.gather(feat.numpy(), refs[s].S))
         fell_back += active
     assert 0 < fell_back < 10
+
+
+@pytest.mark.parametrize("nodes", [
+    1000,             # one tile of 32 words, four vertices per lane
+    512 * 32,         # a word per lane of the closing launch ...
+    512 * 32 + 1,     # ... and a word more: pieces of 128 vertices there, a word per lane in the hop launch
+    1024 * 32 - 5,    # a word per lane of the hop launch ...
+    1024 * 32 + 1,    # ... and pieces
+])
+@pytest.mark.parametrize("dim", [0, 4])  # mark bytes cleared where they are read; new vertices' bytes kept for their tags
+def test_one_ranking_tile_on_either_side_of_a_word_per_lane(oracle, nodes, dim):
+    # every launch ranks the whole graph in one tile, most of it new: up to 30 k vertices, many batches of 1024 (hop launch) or 4096
+    # (closing launch)
+    g = W.rmat_graph(nodes, 30 * nodes, 6)
+    feat = W.feature_table(nodes, dim, 3) if dim else None
+    og = to_host_graph(oracle, g)
+    batch = min(nodes // 2, 3000)
+    pool = W.SeedPool(g, batch, 9)
+    plan = None
+    for s in range(2):
+        plan, _, ref = run_and_compare(oracle, g, feat, pool.batch_for(s).numpy(), (7, 11), 50 + s, plan=plan, og=og,
+                                       env=zg.make_envelope(zg.ENV_MAX, max_tickets=1))
+    assert plan.info.grid_compact == 1 and ref.n[-1] > nodes // 3
