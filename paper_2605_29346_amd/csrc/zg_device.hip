@@ -120,20 +120,32 @@ __device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, u
     return excl;
 }
 
+// a * b in one instruction (the compiler makes two products of it, low half and high half)
+__device__ __forceinline__ uint64_t product(uint32_t a, uint32_t b)
+{
+    uint64_t p;
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p) : "v"(a), "s"(b) : "vcc");
+    return p;
+}
+
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
 // Philox4x32-10 (Salmon et al., SC'11) for counter (node, slot, hop, 0) and the 64-bit step key;
-// returns the first two output words as one 64-bit draw.
+// returns the first two output words as one 64-bit draw.  A sampling pass computes this more than anything else: 36
+// products and as many pairs of xors took 114 ns per wavefront with 8 of them on a SIMD, 20 whole products and three-way xors
+// take 73 ns.
 __device__ __forceinline__ uint64_t philox_draw(uint32_t key_lo, uint32_t key_hi, uint32_t hop, uint32_t node, uint32_t slot)
 {
     uint32_t c0 = node, c1 = slot, c2 = hop, c3 = 0u;
     uint32_t k0 = key_lo, k1 = key_hi;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t h0 = __umulhi(0xD2511F53u, c0), l0 = 0xD2511F53u * c0;
-        const uint32_t h1 = __umulhi(0xCD9E8D57u, c2), l1 = 0xCD9E8D57u * c2;
-        c0 = h1 ^ c1 ^ k0;
-        c1 = l1;
-        c2 = h0 ^ c3 ^ k1;
-        c3 = l0;
+        const uint64_t p0 = product(c0, 0xD2511F53u);
+        const uint64_t p1 = r == 0 ? (uint64_t)0xCD9E8D57u * c2 : product(c2, 0xCD9E8D57u); // (the first one is the hop's: a scalar)
+        c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        c1 = (uint32_t)p1;
+        c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+        c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -147,13 +159,37 @@ __device__ __forceinline__ uint32_t scale_draw(uint64_t x, uint32_t b)
 }
 
 // The F consecutive lanes of a wavefront that hold the slots of one frontier vertex, as the group interface of
-// floyd_position (zg_floyd.h): slot j of the group sits in lane gbase + j.
+// floyd_settle (zg_floyd.h): slot j of the group sits in lane gbase + j.  A flag is looked up in the wavefront's mask of them.
 struct WaveGroup {
-    int gbase;
-    __device__ __forceinline__ uint32_t candidate_of(uint32_t j, uint32_t mine) const { return __shfl(mine, gbase + (int)j, 64); }
-    __device__ __forceinline__ bool flag_of(uint32_t j, bool mine) const { return __shfl((int)mine, gbase + (int)j, 64) != 0; }
+    uint32_t gbase;
+    __device__ __forceinline__ bool flag_of(uint32_t j, bool mine) const { return (__ballot(mine) >> (gbase + j)) & 1ull; }
     __device__ __forceinline__ bool any(bool b) const { return __any(b) != 0; }
 };
+
+// Whether an earlier slot of the lane's group holds the same candidate: groups of F consecutive lanes, `group` the number of
+// the lane's; all of the wavefront's lanes active.  The candidates travel one lane up per round as a register move, three
+// instructions a round (a look through LDS per slot, ds_bpermute, is a round trip each, and F - 1 of them one after another).  What
+// comes from the group before differs in the top bit, which no candidate has; what comes from before lane 0 is zero, which
+// none of them is.
+__device__ __forceinline__ bool drawn_before(uint32_t cand, uint32_t group, uint32_t F)
+{
+    const uint32_t mine = (cand + 1u) | (group << 31); // (cand < a row's length < 2^31)
+    uint32_t x = mine, nearest = 0xFFFFFFFFu;
+    auto round = [&]() {
+        x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, true); // wave_shr:1
+        const uint32_t t = x ^ mine;
+        nearest = t < nearest ? t : nearest;
+    };
+    uint32_t left = F - 1u;
+    for (; left >= 4u; left -= 4u) {
+        round();
+        round();
+        round();
+        round();
+    }
+    for (; left; --left) round();
+    return nearest == 0u;
+}
 
 // =================================================================================================
 // kernels
@@ -517,8 +553,8 @@ __device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &
         if (__any(floyd)) {
             uint32_t cand = gl;
             if (floyd) cand = scale_draw(philox_draw(key_lo, key_hi, (uint32_t)a.launch, (uint32_t)tv, gl), tdeg - F + gl + 1u);
-            WaveGroup grp{(int)(sub * F)};
-            pos = floyd_position(grp, gl, F, tdeg, floyd, cand);
+            WaveGroup grp{sub * F};
+            pos = floyd_settle(grp, gl, F, tdeg, floyd, cand, drawn_before(cand, sub, F));
         }
     }
     Slot r;
@@ -526,6 +562,27 @@ __device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &
     r.taken = slot;
     r.src = sh.off[tl] + pos;
     return r;
+}
+
+// The neighbor ids of rows row0, row0 + step, .. (64/F rows at a time) below row_end into s_ids, by edge, edge e0 first; one wavefront.
+// An id is stored only when the next slots have been worked out: its load is out for that long.
+// A pass is bound by instruction issue (2 M edges: seven passes of 32 wavefronts per compute unit, 3 us each, the ids' loads 1 us of it):
+// whole products in Philox, register moves instead of ds_bpermute in drawn_before and the loads' overlap took the hop launches from 23.4
+// to 19.0 us (430 k edges), 18.0 to 16.3 (240 k), 14.5 to 14.0 (130 k); 54 us stay 54 at 2 M, where the random loads take over.
+__device__ __forceinline__ void load_ids(const HopArgs &a, const HopShared &sh, uint32_t key_lo, uint32_t key_hi, uint32_t row0, uint32_t row_end,
+                                         uint32_t step, int lane, uint32_t e0, int32_t *s_ids)
+{
+    int32_t id = 0;
+    uint32_t at = 0;
+    bool out = false; // a load is out, its id goes to s_ids[at]
+    for (; row0 < row_end; row0 += step) {
+        const Slot slot = resolve_slot(a, sh, key_lo, key_hi, row0, row_end, lane);
+        if (out) s_ids[at] = id;
+        out = slot.taken;
+        at = slot.edge - e0;
+        if (out) id = a.indices[slot.src];
+    }
+    if (out) s_ids[at] = id;
 }
 
 // Marks.  A hop that reaches many of the graph's vertices (bytes_next) stores a byte per sampled edge: idempotent stores
@@ -967,10 +1024,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         uint32_t keep = 0;
         for (uint32_t b0 = 0; b0 < nrows; b0 += stage_rows) {
             const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0];
-            for (uint32_t row0 = b0 + wave * rpw; row0 < b1; row0 += step) {
-                const Slot slot = resolve_slot(a, sh, key_lo, key_hi, row0, b1, lane);
-                if (slot.taken) s_ids[slot.edge - e0] = a.indices[slot.src];
-            }
+            load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
             if (!chained)
                 take_prefixes();
             else
@@ -1147,10 +1201,7 @@ __global__ __launch_bounds__(kHopBlock) void k_small(SmallArgs s)
             __syncthreads();
             for (uint32_t b0 = 0; b0 < nrows; b0 += stage_rows) {
                 const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0], e1 = sh.rp[b1];
-                for (uint32_t row0 = b0 + wave * rpw; row0 < b1; row0 += step) {
-                    const Slot slot = resolve_slot(a, sh, key_lo, key_hi, row0, b1, (int)lane);
-                    if (slot.taken) s_ids[slot.edge - e0] = a.indices[slot.src];
-                }
+                load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
                 __syncthreads();
                 for (uint32_t e = e0 + tid; e < e1; e += (uint32_t)kHopBlock) {
                     const uint32_t edge = ebase + e;

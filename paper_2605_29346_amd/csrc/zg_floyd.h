@@ -11,7 +11,8 @@
 // The rule is written against a small group interface so that the sampling kernel (lanes of a wavefront,
 // shuffles) and a host-side lockstep harness (a CPU test that enumerates every candidate sequence) run the
 // very same code:
-//   candidate_of(j, mine)  the candidate of the group's slot j (every lane passes its own)
+//   candidate_of(j, mine)  the candidate of the group's slot j (every lane passes its own); floyd_position only: the kernel finds
+//                          the repeated candidates its own way and starts at floyd_settle
 //   flag_of(j, mine)       the boolean `mine` of the group's slot j
 //   any(b)                 true if b holds for any lane that takes part in the same exchange
 #pragma once
@@ -28,17 +29,14 @@ namespace zg {
 
 // Position taken by slot `slot` of a vertex with `deg` neighbors and fanout F.  `active` lanes are slots of a
 // vertex with deg > F (cand = their draw, in [0, deg-F+slot]); the other lanes of the group pass through with
-// position = slot, and take part in the exchanges only as partners.
+// position = slot, and take part in the exchanges only as partners.  `dup`: an earlier slot drew the same candidate
+// (means nothing where not active).
 template <class Group>
-ZG_FLOYD_FN uint32_t floyd_position(Group &grp, uint32_t slot, uint32_t F, uint32_t deg, bool active, uint32_t cand)
+ZG_FLOYD_FN uint32_t floyd_settle(Group &grp, uint32_t slot, uint32_t F, uint32_t deg, bool active, uint32_t cand, bool dup)
 {
     const uint32_t tail0 = deg - F; // candidates >= tail0 coincide with the fallback position of slot cand - tail0
-    bool dup = false;
-    for (uint32_t j = 0; j + 1 < F; ++j) {
-        const uint32_t cj = grp.candidate_of(j, cand);
-        dup = dup || (j < slot && cj == cand);
-    }
     dup = dup && active;
+    if (!grp.any(dup)) return active ? cand : slot; // nobody collides
     const uint32_t a = cand - tail0; // meaningful only when cand >= tail0
     const bool chase = active && cand >= tail0 && a < slot;
     bool collide = dup;
@@ -50,6 +48,18 @@ ZG_FLOYD_FN uint32_t floyd_position(Group &grp, uint32_t slot, uint32_t F, uint3
         if (!grp.any(changed)) break;
     }
     return active ? (collide ? tail0 + slot : cand) : slot;
+}
+
+// ... with the repeated candidates found by asking for every earlier slot's
+template <class Group>
+ZG_FLOYD_FN uint32_t floyd_position(Group &grp, uint32_t slot, uint32_t F, uint32_t deg, bool active, uint32_t cand)
+{
+    bool dup = false;
+    for (uint32_t j = 0; j + 1 < F; ++j) {
+        const uint32_t cj = grp.candidate_of(j, cand);
+        dup = dup || (j < slot && cj == cand);
+    }
+    return floyd_settle(grp, slot, F, deg, active, cand, dup);
 }
 
 } // namespace zg

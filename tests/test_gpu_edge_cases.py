@@ -368,3 +368,19 @@ def test_one_ranking_tile_on_either_side_of_a_word_per_lane(oracle, nodes, dim):
         plan, _, ref = run_and_compare(oracle, g, feat, pool.batch_for(s).numpy(), (7, 11), 50 + s, plan=plan, og=og,
                                        env=zg.make_envelope(zg.ENV_MAX, max_tickets=1))
     assert plan.info.grid_compact == 1 and ref.n[-1] > nodes // 3
+
+
+@pytest.mark.parametrize("fanout", [1, 2, 3, 4, 5, 6, 9, 25, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("batch", [2500, 16])  # a launch per hop; all hops in one workgroup (up to 30 edges a row)
+def test_repeated_draws_in_groups_of_any_width(oracle, fanout, batch):
+    # rows of fanout to fanout + 3 neighbors, so that nearly every row draws some candidate twice and many chase a collision, next
+    # to rows of one neighbor and long ones in the same wavefront; position 0 among the candidates
+    n = 4000
+    rnd = np.random.RandomState(fanout)
+    rows = {v: np.sort(rnd.choice(n, size=(fanout + v % 4, 1, 700, fanout + 1)[v % 7 % 4], replace=False)).tolist() for v in range(n)}
+    g = _csr(rows, n)
+    og = to_host_graph(oracle, g)
+    plan = None
+    for s in range(2):
+        seeds = rnd.permutation(n)[:batch].astype(np.int32)
+        plan, _, _ = run_and_compare(oracle, g, None, seeds, (fanout,), 60 + s, plan=plan, og=og)
