@@ -1642,6 +1642,9 @@ __global__ void k_validate(const OffT *off, const int32_t *idx, int64_t num_node
 // probability (1 - q_v) * prod over its in-neighbors u of (1 - q_u r_u).  One sweep over the edges per hop.
 // Sums are kept as 64-bit fixed point (2^-32) so that the result does not depend on the order of the atomics.
 constexpr double kFix = 4294967296.0; // 2^32
+constexpr int kModelBinBlock = 512, kModelWindow = 4096; // threads of a workgroup of k_model_bin, edges it looks at together
+constexpr int kModelAddBlock = 512;
+constexpr uint32_t kModelMaxBins = 32768;                // a counter each in LDS
 
 __global__ void k_model_init(float *q, unsigned long long *ell, const float *seed_prob, float uniform, int64_t n)
 {
@@ -1653,7 +1656,22 @@ __global__ void k_model_init(float *q, unsigned long long *ell, const float *see
     }
 }
 
-// one wave per source vertex: every neighbor v of u receives -log(1 - q_u r_u)
+// -log(1 - q_u r_u) in fixed point: what a vertex u of `deg` neighbors adds to each of them (at most 9e10: 37 bits)
+__device__ __forceinline__ unsigned long long model_term(float qu, int64_t deg, int32_t fanout, int32_t replace)
+{
+    if (qu <= 0.0f || deg <= 0) return 0ull;
+    double r;
+    if (replace)
+        r = -expm1((double)fanout * log1p(-1.0 / (double)deg));
+    else
+        r = deg <= fanout ? 1.0 : (double)fanout / (double)deg;
+    double x = (double)qu * r;
+    if (x > 1.0 - 1e-9) x = 1.0 - 1e-9;
+    return (unsigned long long)(-log1p(-x) * kFix);
+}
+
+// The sweep with nothing but the two arrays over the vertices: one wave per source vertex, one 64-bit atomic per edge.  Bound by
+// those: 16 G/s here, whatever their scope - the L2s pass every atomic on to memory (7 ms per hop at 120 M edges).
 template <typename OffT>
 __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const int32_t *idx, const float *q, unsigned long long *ell,
                                                        int64_t n, int32_t fanout, int32_t replace)
@@ -1662,22 +1680,228 @@ __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const in
     const int64_t wave0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
     const int64_t waves = ((int64_t)gridDim.x * kBlock) >> 6;
     for (int64_t u = wave0; u < n; u += waves) {
-        const float qu = q[u];
-        if (qu <= 0.0f) continue;
         const int64_t b = (int64_t)off[u], e = (int64_t)off[u + 1];
-        const int64_t deg = e - b;
-        if (deg <= 0) continue;
-        double r;
-        if (replace)
-            r = -expm1((double)fanout * log1p(-1.0 / (double)deg));
-        else
-            r = deg <= fanout ? 1.0 : (double)fanout / (double)deg;
-        double x = (double)qu * r;
-        if (x > 1.0 - 1e-9) x = 1.0 - 1e-9;
-        const unsigned long long c = (unsigned long long)(-log1p(-x) * kFix);
+        const unsigned long long c = model_term(q[u], e - b, fanout, replace);
         if (c == 0ull) continue;
         for (int64_t p = b + lane; p < e; p += 64) atomicAdd(&ell[idx[p]], c);
     }
+}
+
+// The sweep with room for 8 bytes per edge: no atomic leaves a compute unit.  The vertices are cut into bins of 2^log2.  Once per
+// call the edges are counted by chunk and bin (k_model_count) and the counts turned into places (k_model_places, k_model_starts); in
+// each hop every edge's term is written to its bin behind those of earlier chunks (k_model_bin: the term, and the vertex within the
+// bin in the low bits), and a workgroup per bin adds it up in LDS (k_model_add).  The terms are integers: the same sums as above.
+// Three hops at 2.4 M vertices and 115 M edges: 22.8 -> 3.2 ms, k_model_bin 0.59 ms per hop (0.46 GB read, 0.92 GB written in pieces of 8
+// bytes), k_model_add 0.34 ms (2.7 TB/s), the places 0.17 ms once; 40 M vertices and 350 M edges 61 -> 15 ms.  (A window's entries put in
+// the order of their bins in LDS first, so that they leave in runs: 0.56 ms instead of 0.59, 1.06 instead of 1.27 with 1831 bins;
+// left out for its length.)
+struct ModelBins {
+    const int32_t *idx;
+    int64_t num_edges, num_nodes;
+    uint32_t log2, bins;
+    uint32_t chunk, chunks;    // edges of a chunk, a multiple of kModelWindow
+    uint32_t *place;           // [chunks][bins]: edges of the chunk that lead into the bin; then how many of earlier chunks do
+    uint32_t *start;           // [bins + 1]: where the bin's entries begin
+    unsigned long long *entry; // [num_edges]
+};
+
+__global__ __launch_bounds__(1024) void k_model_count(ModelBins m)
+{
+    extern __shared__ uint32_t s_count[];
+    for (uint32_t b = threadIdx.x; b < m.bins; b += 1024u) s_count[b] = 0u;
+    __syncthreads();
+    const int64_t e0 = (int64_t)blockIdx.x * m.chunk, e1 = e0 + m.chunk < m.num_edges ? e0 + m.chunk : m.num_edges;
+    typedef int32_t v4i __attribute__((ext_vector_type(4), aligned(4)));
+    auto count = [&](int32_t id) {
+        const uint32_t g = (uint32_t)id;
+        if ((int64_t)g < m.num_nodes) atomicAdd(&s_count[g >> m.log2], 1u);
+    };
+    const int64_t e4 = e0 + (e1 - e0) / 4 * 4;
+#pragma unroll 4
+    for (int64_t e = e0 + 4 * (int64_t)threadIdx.x; e < e4; e += 4096) {
+        const v4i x = *reinterpret_cast<const v4i *>(m.idx + e);
+        count(x[0]);
+        count(x[1]);
+        count(x[2]);
+        count(x[3]);
+    }
+    if (e4 + threadIdx.x < e1) count(m.idx[e4 + threadIdx.x]);
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < m.bins; b += 1024u) m.place[(size_t)blockIdx.x * m.bins + b] = s_count[b];
+}
+
+// 64 bins per workgroup, a lane per bin, a sixteenth of the chunks per wavefront: the running sums over the chunks; start[b] = the bin's total
+__global__ __launch_bounds__(1024) void k_model_places(ModelBins m)
+{
+    __shared__ uint32_t s_sum[16][64];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, b = blockIdx.x * 64u + lane;
+    const uint32_t each = (m.chunks + 15u) / 16u, c0 = wave * each, c1 = c0 + each < m.chunks ? c0 + each : m.chunks;
+    uint32_t sum = 0;
+    if (b < m.bins) {
+#pragma unroll 8
+        for (uint32_t c = c0; c < c1; ++c) sum += m.place[(size_t)c * m.bins + b];
+    }
+    s_sum[wave][lane] = sum;
+    __syncthreads();
+    if (b >= m.bins) return;
+    uint32_t run = 0;
+    for (uint32_t w = 0; w < wave; ++w) run += s_sum[w][lane];
+    for (uint32_t c = c0; c < c1; c += 8u) {
+        uint32_t x[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8u; ++u) x[u] = c + u < c1 ? m.place[(size_t)(c + u) * m.bins + b] : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < 8u; ++u)
+            if (c + u < c1) {
+                m.place[(size_t)(c + u) * m.bins + b] = run;
+                run += x[u];
+            }
+    }
+    if (wave == 15u) m.start[b] = run;
+}
+
+// one workgroup: the bins' totals into their starts
+__global__ __launch_bounds__(1024) void k_model_starts(ModelBins m)
+{
+    __shared__ uint32_t s_sum[16];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, each = (m.bins + 1023u) / 1024u;
+    const uint32_t b0 = threadIdx.x * each, b1 = b0 + each < m.bins ? b0 + each : m.bins;
+    uint32_t sum = 0;
+    for (uint32_t b = b0; b < b1; ++b) sum += m.start[b];
+    const uint32_t incl = wave_incl_scan(sum);
+    if (lane == 63u) s_sum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+    for (uint32_t w = 0; w < wave; ++w) run += s_sum[w];
+    for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t x = m.start[b];
+        m.start[b] = run;
+        run += x;
+    }
+    if (threadIdx.x == 1023u) m.start[m.bins] = run; // (threads without bins carry the total on)
+}
+
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
+{
+    auto up = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    v = up(v, dpp_or_zero<0x111, 0xF>(v));
+    v = up(v, dpp_or_zero<0x112, 0xF>(v));
+    v = up(v, dpp_or_zero<0x114, 0xF>(v));
+    v = up(v, dpp_or_zero<0x118, 0xF>(v));
+    v = up(v, dpp_or_zero<0x142, 0xA>(v));
+    v = up(v, dpp_or_zero<0x143, 0xC>(v));
+    return v;
+}
+
+// A workgroup goes through a chunk of the edges in windows: the rows that begin in the window leave their number at their first
+// edge, a running maximum tells every edge its row, and the row's term - worked out once, by a thread per row - goes to the edge's bin.
+template <typename OffT>
+__global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, const OffT *off, const float *q, int32_t fanout, int32_t replace)
+{
+    constexpr uint32_t kEach = kModelWindow / kModelBinBlock, NW = kModelBinBlock / 64;
+    typedef int32_t v4i __attribute__((ext_vector_type(4), aligned(4)));
+    __shared__ __align__(16) uint16_t s_row[kModelWindow]; // at a row's first edge in the window: the row, counted from the window's first
+    __shared__ unsigned long long s_term[kModelBinBlock];
+    __shared__ unsigned long long s_last;
+    __shared__ uint32_t s_max[NW];
+    extern __shared__ uint32_t s_next[]; // where the bin's next entry goes
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const int64_t n = m.num_nodes;
+    for (uint32_t b = tid; b < m.bins; b += (uint32_t)kModelBinBlock) s_next[b] = m.start[b] + m.place[(size_t)blockIdx.x * m.bins + b];
+    int64_t e = (int64_t)blockIdx.x * m.chunk;
+    const int64_t e1 = e + m.chunk < m.num_edges ? e + m.chunk : m.num_edges;
+    // the row that holds edge e: off[row] <= e < off[row + 1], a thread per probe
+    int64_t row = 0, hi = n;
+    while (hi - row > 1) {
+        const int64_t step = (hi - row + kModelBinBlock - 1) / kModelBinBlock, p = row + ((int64_t)tid + 1) * step;
+        row += (int64_t)__syncthreads_count(p < hi && (int64_t)off[p] <= e) * step;
+        if (row + step < hi) hi = row + step;
+    }
+    // this thread's edges, and the rows row .. row + kModelBinBlock - 1, one per thread: loaded a window ahead
+    v4i v_next[kEach / 4];
+    int64_t o0_next, o1_next;
+    float q_next;
+    auto load_window = [&]() {
+#pragma unroll
+        for (uint32_t u = 0; u < kEach / 4; ++u) {
+            const int64_t p = e + (int64_t)tid * kEach + 4 * u;
+            if (p + 4 <= e1) {
+                v_next[u] = *reinterpret_cast<const v4i *>(m.idx + p);
+            } else {
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) v_next[u][i] = p + i < e1 ? m.idx[p + i] : -1;
+            }
+        }
+        const int64_t r = row + tid;
+        o0_next = (int64_t)off[r < n ? r : n];
+        o1_next = (int64_t)off[r + 1 < n ? r + 1 : n];
+        q_next = r < n ? q[r] : 0.0f;
+    };
+    load_window();
+    while (e < e1) {
+        v4i v[kEach / 4];
+#pragma unroll
+        for (uint32_t u = 0; u < kEach / 4; ++u) v[u] = v_next[u];
+        const int64_t mine = e + (int64_t)tid * kEach, o0 = o0_next, o1 = o1_next, r = row + tid, e_now = e;
+        const float qr = q_next;
+        if (tid == kModelBinBlock - 1) s_last = (unsigned long long)o1;
+#pragma unroll
+        for (uint32_t u = 0; u < kEach / 4; ++u) reinterpret_cast<uint2 *>(s_row)[tid * (kEach / 4) + u] = make_uint2(0u, 0u);
+        __syncthreads();
+        int64_t w1 = e + kModelWindow < e1 ? e + kModelWindow : e1; // the window's end; earlier if it has more rows than there are threads
+        if ((int64_t)s_last < w1) w1 = (int64_t)s_last;
+        row += __syncthreads_count(r < n && o1 <= w1);
+        e = w1;
+        if (e < e1) load_window();
+        if (o1 > o0 && o1 > e_now && o0 < w1) {
+            s_row[o0 > e_now ? o0 - e_now : 0] = (uint16_t)tid;
+            s_term[tid] = model_term(qr, o1 - o0, fanout, replace);
+        }
+        __syncthreads();
+        uint32_t at[kEach], top = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < kEach; ++u) {
+            const uint32_t x = s_row[tid * kEach + u];
+            top = x > top ? x : top;
+            at[u] = top;
+        }
+        const uint32_t incl = wave_incl_max(top);
+        uint32_t before = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x138, 0xF, 0xF, true); // (the lane before: wave_shr:1)
+        if (lane == 63u) s_max[wave] = incl;
+        __syncthreads();
+        const uint32_t others = lane_value(wave_incl_max(lane < wave ? s_max[lane] : 0u), 63u);
+        before = before > others ? before : others;
+#pragma unroll
+        for (uint32_t u = 0; u < kEach; ++u) {
+            const uint32_t g = (uint32_t)v[u / 4][u % 4];
+            if (mine + u < w1 && (int64_t)g < n)
+                m.entry[atomicAdd(&s_next[g >> m.log2], 1u)] = (s_term[at[u] > before ? at[u] : before] << m.log2) | (g & ((1u << m.log2) - 1u));
+        }
+    }
+}
+
+// a workgroup per bin
+__global__ __launch_bounds__(kModelAddBlock) void k_model_add(ModelBins m, unsigned long long *ell)
+{
+    extern __shared__ unsigned long long s_ell[];
+    typedef unsigned long long v2u __attribute__((ext_vector_type(2), aligned(8)));
+    const uint32_t size = 1u << m.log2, mask = size - 1u, e0 = m.start[blockIdx.x], e1 = m.start[blockIdx.x + 1];
+    for (uint32_t i = threadIdx.x; i < size; i += (uint32_t)kModelAddBlock) s_ell[i] = 0ull;
+    __syncthreads();
+    const uint32_t pairs = (e1 - e0) / 2u;
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < pairs; i += (uint32_t)kModelAddBlock) {
+        const v2u x = *reinterpret_cast<const v2u *>(m.entry + e0 + 2u * (size_t)i);
+        atomicAdd(&s_ell[(uint32_t)x[0] & mask], x[0] >> m.log2);
+        atomicAdd(&s_ell[(uint32_t)x[1] & mask], x[1] >> m.log2);
+    }
+    if (threadIdx.x == 0 && ((e1 - e0) & 1u)) {
+        const unsigned long long x = m.entry[e1 - 1u];
+        atomicAdd(&s_ell[(uint32_t)x & mask], x >> m.log2);
+    }
+    __syncthreads();
+    const int64_t v0 = (int64_t)blockIdx.x << m.log2;
+    for (uint32_t i = threadIdx.x; i < size && v0 + i < m.num_nodes; i += (uint32_t)kModelAddBlock) ell[v0 + i] = s_ell[i];
 }
 
 // q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v).  Vertices kModelStride apart are added in
@@ -1739,6 +1963,77 @@ constexpr size_t kStaticEllBytes = (size_t)ZG_STATIC_MODEL_MAX_NODES * 8;
 constexpr size_t kStaticQBytes = (size_t)ZG_STATIC_MODEL_MAX_NODES * 4;
 constexpr size_t kStaticSumsBytes = 2 * ZG_MAX_HOPS * 8;
 static __device__ __align__(256) unsigned char scratch[kStaticEllBytes + kStaticQBytes + kStaticSumsBytes];
+
+// How the sweep's edges are binned, laid out behind `used` bytes of the caller's buffer; bins == 0: they are not.  About 256 to 512
+// bins, of up to 8192 vertices (64 KB of sums: two workgroups to a compute unit; bins of 4096 at 2.4 M vertices: k_model_bin 0.70 instead of
+// 0.58 ms, k_model_add 0.31 instead of 0.34; one bin per compute unit at 62 bins: k_model_add 0.77 ms instead of 0.24), beyond 16 M vertices
+// of 16384; a thousand chunks, of at most 65536 edges unless their counters would be more than a byte per edge.  Below
+// ZG_MODEL_BIN_EDGES edges the launches cost more than the atomics: 102 k edges 121 us with atomics, 152 binned; 290 k 169 / 153; 2 M 485 / 192.
+ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_bytes)
+{
+    ModelBins m;
+    std::memset(&m, 0, sizeof(m));
+    const int64_t n = g->num_nodes, E = g->num_edges;
+    if (E < ZG_MODEL_BIN_EDGES || E >= ((int64_t)1 << 32)) return m;
+    uint32_t log2 = 8;
+    while (log2 < 13 && (n >> log2) >= 512) ++log2;
+    while (log2 < 14 && (n >> log2) >= 2048) ++log2;
+    const int64_t bins = (n + ((int64_t)1 << log2) - 1) >> log2;
+    if (bins > (int64_t)kModelMaxBins) return m;
+    const int64_t want = std::max<int64_t>(4 * bins, std::min<int64_t>(65536, E / 1024));
+    const int64_t chunk = (want + kModelWindow - 1) / kModelWindow * kModelWindow, chunks = (E + chunk - 1) / chunk;
+    auto place = [&](size_t bytes) {
+        const size_t at = (used + kAlign - 1) / kAlign * kAlign;
+        used = at + bytes;
+        return static_cast<char *>(temp) + at;
+    };
+    m.entry = reinterpret_cast<unsigned long long *>(place((size_t)E * 8));
+    m.place = reinterpret_cast<uint32_t *>(place((size_t)(bins * chunks) * 4));
+    m.start = reinterpret_cast<uint32_t *>(place((size_t)(bins + 1) * 4));
+    if (used > temp_bytes) return m;
+    m.idx = g->d_indices;
+    m.num_edges = E;
+    m.num_nodes = n;
+    m.log2 = log2;
+    m.chunk = (uint32_t)chunk;
+    m.chunks = (uint32_t)chunks;
+    m.bins = (uint32_t)bins;
+    return m;
+}
+
+// once per call: places for the edges' terms
+void enqueue_model_places(const ModelBins &m, hipStream_t st)
+{
+    if (!m.bins) return;
+    hipLaunchKernelGGL(k_model_count, dim3(m.chunks), dim3(1024), (size_t)m.bins * 4, st, m);
+    hipLaunchKernelGGL(k_model_places, dim3((m.bins + 63u) / 64u), dim3(1024), 0, st, m);
+    hipLaunchKernelGGL(k_model_starts, dim3(1), dim3(1024), 0, st, m);
+}
+
+// one hop of the size model: the sweep over the edges and the update of the probabilities
+void enqueue_model_hop(const zg_graph_t *g, const ModelBins &m, float *q, unsigned long long *ell, unsigned long long *sums, int32_t fanout, int32_t replace,
+                       hipStream_t st)
+{
+    const int64_t n = g->num_nodes;
+    const bool wide = g->offsets_dtype == ZG_I64;
+    if (m.bins) {
+        const dim3 grid(m.chunks), block(kModelBinBlock);
+        const size_t lds = (size_t)m.bins * 4;
+        if (wide)
+            hipLaunchKernelGGL(k_model_bin<int64_t>, grid, block, lds, st, m, (const int64_t *)g->d_offsets, q, fanout, replace);
+        else
+            hipLaunchKernelGGL(k_model_bin<int32_t>, grid, block, lds, st, m, (const int32_t *)g->d_offsets, q, fanout, replace);
+        hipLaunchKernelGGL(k_model_add, dim3(m.bins), dim3(kModelAddBlock), (size_t)8 << m.log2, st, m, ell);
+    } else {
+        const dim3 grid((unsigned)std::min<int64_t>(1 << 16, (n + (kBlock / 64) - 1) / (kBlock / 64)));
+        if (wide)
+            hipLaunchKernelGGL(k_model_push<int64_t>, grid, dim3(kBlock), 0, st, (const int64_t *)g->d_offsets, g->d_indices, q, ell, n, fanout, replace);
+        else
+            hipLaunchKernelGGL(k_model_push<int32_t>, grid, dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, q, ell, n, fanout, replace);
+    }
+    hipLaunchKernelGGL(k_model_update, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell, n,
+                       sums);
+}
 
 #define ZG_HIP(call)                                                                                         \
     do {                                                                                                     \
@@ -2503,21 +2798,16 @@ int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t
     at += (size_t)n * 4;
     at = (at + kAlign - 1) / kAlign * kAlign;
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(base + at); // [2] per hop, reused
+    const ModelBins bins = model_bins(g, d_temp, at + 64, temp_bytes);
+    enqueue_model_places(bins, st);
     const int grid = (int)std::min<int64_t>(1 << 16, (n + kBlock - 1) / kBlock);
-    const int grid_push = (int)std::min<int64_t>(1 << 16, (n + (kBlock / 64) - 1) / (kBlock / 64));
     hipLaunchKernelGGL(k_model_init, dim3(grid), dim3(kBlock), 0, st, q, ell, d_seed_prob, (float)((double)batch / (double)n), n);
     ZG_HIP(hipGetLastError());
     mean[0] = (double)batch;
     sigma[0] = 0.0;
     for (int h = 0; h < num_hops; ++h) {
         hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)4);
-        if (g->offsets_dtype == ZG_I64)
-            hipLaunchKernelGGL(k_model_push<int64_t>, dim3(grid_push), dim3(kBlock), 0, st, (const int64_t *)g->d_offsets, g->d_indices, q,
-                               ell, n, fanouts[h], with_replacement);
-        else
-            hipLaunchKernelGGL(k_model_push<int32_t>, dim3(grid_push), dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, q,
-                               ell, n, fanouts[h], with_replacement);
-        hipLaunchKernelGGL(k_model_update, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell, n, sums);
+        enqueue_model_hop(g, bins, q, ell, sums, fanouts[h], with_replacement, st);
         ZG_HIP(hipGetLastError());
         unsigned long long host[2] = {0, 0};
         ZG_HIP(hipMemcpyAsync(host, sums, sizeof(host), hipMemcpyDeviceToHost, st));
@@ -2570,21 +2860,16 @@ int zg_envelope_model_graph_static(const zg_graph_t *g, const int32_t *fanouts, 
     unsigned long long *ell = reinterpret_cast<unsigned long long *>(base);
     float *q = reinterpret_cast<float *>(base + kStaticEllBytes);
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(base + kStaticEllBytes + kStaticQBytes);
+    ModelBins bins; // (no room for any)
+    std::memset(&bins, 0, sizeof(bins));
     const int grid = (int)std::min<int64_t>(1 << 16, (n + kBlock - 1) / kBlock);
-    const int grid_push = (int)std::min<int64_t>(1 << 16, (n + (kBlock / 64) - 1) / (kBlock / 64));
     // the array keeps the last call's contents: the per-hop sums restart at zero here (a fill kernel, not a memset
     // node, so that the sequence may be captured), q and ell are overwritten for the first n vertices by the first kernel
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)(4 * ZG_MAX_HOPS));
     hipLaunchKernelGGL(k_model_init, dim3(grid), dim3(kBlock), 0, st, q, ell, d_seed_prob, (float)((double)batch / (double)n), n);
     ZG_HIP(hipGetLastError());
     for (int h = 0; h < num_hops; ++h) {
-        if (g->offsets_dtype == ZG_I64)
-            hipLaunchKernelGGL(k_model_push<int64_t>, dim3(grid_push), dim3(kBlock), 0, st, (const int64_t *)g->d_offsets, g->d_indices, q,
-                               ell, n, fanouts[h], with_replacement);
-        else
-            hipLaunchKernelGGL(k_model_push<int32_t>, dim3(grid_push), dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, q,
-                               ell, n, fanouts[h], with_replacement);
-        hipLaunchKernelGGL(k_model_update, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell, n, sums + 2 * h);
+        enqueue_model_hop(g, bins, q, ell, sums + 2 * h, fanouts[h], with_replacement, st);
         ZG_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_model_finish, dim3(1), dim3(64), 0, st, sums, num_hops, batch, d_mean_sigma);

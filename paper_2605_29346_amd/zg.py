@@ -11,6 +11,7 @@ from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
 MAX_HOPS = 8
+MODEL_BIN_EDGES = 1 << 18  # ZG_MODEL_BIN_EDGES
 MAX_FANOUT = 64
 LOG_STRIDE = 32
 
@@ -213,7 +214,14 @@ def graph_model(graph: "Graph", fanouts: Sequence[int], batch: int, *, with_repl
     mean = (C.c_double * (MAX_HOPS + 1))()
     sigma = (C.c_double * (MAX_HOPS + 1))()
     nbytes = 12 * graph.num_nodes + 576
-    temp = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+    edges = graph.indices.numel() if graph.indices is not None else 0
+    if edges >= MODEL_BIN_EDGES:  # with 9 bytes per edge on top no atomic leaves a compute unit; without them the call works as well
+        nbytes += 9 * edges + (1 << 20)
+    try:
+        temp = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        nbytes = 12 * graph.num_nodes + 576
+        temp = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
     base = (temp.data_ptr() + 255) // 256 * 256
     sp = None
     if seed_prob is not None:

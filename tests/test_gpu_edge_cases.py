@@ -1,6 +1,7 @@
 """GPU parity on the degenerate and extreme shapes of the method: no edges at all, a single seed, every
 vertex a seed, the maximum number of hops, fanout 64 on a six-figure degree, vertex counts that are not a
 multiple of 32, and every tile-size variant of the chained-scan kernels (forced through the envelope's max_tickets knob)."""
+import ctypes as C
 import os
 
 import numpy as np
@@ -384,3 +385,36 @@ def test_repeated_draws_in_groups_of_any_width(oracle, fanout, batch):
     for s in range(2):
         seeds = rnd.permutation(n)[:batch].astype(np.int32)
         plan, _, _ = run_and_compare(oracle, g, None, seeds, (fanout,), 60 + s, plan=plan, og=og)
+
+
+@pytest.mark.parametrize("nodes,edges,i64", [
+    (60_000, zg.MODEL_BIN_EDGES - 1, False),      # atomics either way
+    (60_000, zg.MODEL_BIN_EDGES, False),          # bins, the first time; the last window and the last bin are ragged
+    (256 * 512 + 1, 4096 * 300, True),            # a bin of one vertex, whole windows
+    (300_000, 3_000_001, False),
+    (8192 * 2048 + 5, 700_000, True),             # bins of 16384 vertices; thousands of empty rows in a window
+])
+@pytest.mark.parametrize("replace", [False, True])
+def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, replace):
+    # one row that many windows long, stretches of empty rows longer than a window has threads, a popular neighbor; the sums are
+    # integers, so the two sweeps agree to the last bit (the one with atomics is checked against its reference elsewhere)
+    gen = torch.Generator(device="cuda").manual_seed(nodes)
+    weight = torch.rand(nodes, generator=gen, device="cuda").pow_(6)
+    weight[nodes // 3: nodes // 2] = 0
+    deg = (weight * (0.9 * edges / float(weight.sum()))).long()
+    rest = edges - int(deg.sum())
+    assert 0 < rest
+    deg[nodes // 2 + 7] += rest  # the long row
+    offsets = torch.zeros(nodes + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(deg, 0)
+    idx = torch.randint(0, nodes, (edges,), generator=gen, device="cuda", dtype=torch.int32)
+    idx[::5] = 11
+    idx[::7] = nodes - 1
+    dg = zg.Graph(offsets if i64 else offsets.int(), idx)
+    fan, batch = (9, 4), 300
+    binned = zg.graph_model(dg, fan, batch, with_replacement=replace)
+    f, mean, sigma = (C.c_int32 * 2)(*fan), (C.c_double * 9)(), (C.c_double * 9)()
+    temp = torch.empty(12 * nodes + 576 + 256, dtype=torch.uint8, device="cuda")
+    base = (temp.data_ptr() + 255) // 256 * 256
+    assert zg.lib().zg_envelope_model_graph(dg._h, f, 2, batch, int(replace), None, base, 12 * nodes + 576, None, mean, sigma) == zg.OK
+    assert binned == (list(mean[:3]), list(sigma[:3]))
