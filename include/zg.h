@@ -72,6 +72,9 @@ enum zg_dtype { ZG_I32 = 0, ZG_I64 = 1 };
                                  what a plan does by default; the flag is kept for callers that state it */
 #define ZG_PLAN_X_TWO_PASS 64u /* the gather copies every row of S_{H-1}; the aggregation reads X.  Results are the same
                                  bytes either way */
+#define ZG_PLAN_IMPATIENT 128u /* for tests: a workgroup that needs another one's total before it is there works it out at once instead
+                                 of after a quarter of a millisecond (what it does when kernels of other streams keep that
+                                 workgroup from starting).  Results are the same, steps slower */
 
 /* bits of the sticky device status word (zg_overflow_flag) */
 #define ZG_FLAG_HOP_OVERFLOW(h) (1u << (h)) /* |S_h| exceeded its cap at hop h: outputs of the step invalid */

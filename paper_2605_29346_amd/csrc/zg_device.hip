@@ -41,7 +41,8 @@ typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr uint64_t kStAggregate = 1ull << 62; // status word of a ticket: its total published ...
 constexpr uint64_t kStPrefix = 2ull << 62;    // ... or its inclusive prefix
-constexpr uint32_t kSpinLimit = 1u << 22;     // bounded wait: polls before giving up with ZG_FLAG_INTERNAL
+constexpr uint32_t kPatience = 256;           // polls, about a microsecond each, before a workgroup does what it waits for itself
+constexpr uint32_t kSpinLimit = 1u << 22;     // ... where its predecessors are known to run: before it gives up with ZG_FLAG_INTERNAL
 
 // value of the lane a DPP control names, 0 where there is none
 template <int CTRL, int ROWS>
@@ -76,23 +77,34 @@ __device__ __forceinline__ uint64_t st_load(uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Single-pass chained scan across workgroups: ticket t (tickets are handed out in start order, so every predecessor is
-// already running) publishes its total, and later looks back over the predecessors' status words until it meets a
+// Single-pass chained scan across workgroups, in the order of their tickets (a ticket: one workgroup's share of a launch, by
+// workgroup index).  Ticket t publishes its total, and later looks back over the predecessors' status words until it meets a
 // published inclusive prefix.  A status word carries state and value together, so one relaxed 64-bit access is enough.  One
 // wavefront looks back, 64 predecessors per round.  (Measured and not kept: sharing a look-back among eight wavefronts -
 // the wait is for the predecessors to publish, not for the rounds; a second level of one word per 32 tickets that each
 // ticket adds to and every later ticket polls - the polls of one line queue up behind each other, launches of 400
-// tickets took twice as long.)  The wait is bounded; when it runs out the step is flagged invalid (sticky and per-step word)
-// and what is there is used.  Values are taken modulo 2^32: more than that is only reached beyond a cap, by dropped rows.
+// tickets took twice as long.)
+// Whether a predecessor is running while a workgroup waits for it depends on what a ticket is (see k_hop).  Drawn from a counter, in
+// the order in which workgroups start: all of them are, and the lowest unfinished one never waits.  The workgroup's index: kernels of
+// other streams may hold the compute units it needs, and wait in turn for workgroups that this kernel keeps out.  So a wait ends after `patience` polls:
+// `missing(t)` then works out ticket t's total from what the launch found - which t changes only after its totals are published
+// (publish_done), so that what was read stands if they still are not.  No wait depends on another workgroup's progress, and no wait changes
+// the result.  Where the marks are changed before the totals are published, and tickets always drawn, the wait is bounded all the same
+// (kSpinLimit): when it runs out the step is flagged invalid (sticky and per-step word) and what is there is used.
+// Values are taken modulo 2^32: more than that is only reached beyond a cap, by dropped rows.
 __device__ __forceinline__ void chain_publish(uint64_t *status, uint32_t t, uint32_t total)
 {
     st_store(&status[t], (t == 0u ? kStPrefix : kStAggregate) | total);
 }
 
+// the publishing wavefront's stores have been performed; behind a barrier the workgroup may change what its totals were taken from
+__device__ __forceinline__ void publish_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // all 64 lanes of one wavefront: the sum of the totals of tickets 0 .. t-1, after this ticket's own was published
-__device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, uint32_t total, Drmb *d, int lane)
+template <class Missing>
+__device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, uint32_t total, Drmb *d, int lane, uint32_t patience, const Missing &missing)
 {
-    uint32_t excl = 0, spins = 0;
+    uint32_t excl = 0, polls = 0;
     if (t == 0u) return 0u;
     for (int64_t base = (int64_t)t - 1;; base -= 64) {
         // the 64 status words base, base-1, .. base-63 (indices below zero count as an inclusive prefix of zero)
@@ -100,12 +112,24 @@ __device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, u
         uint64_t st;
         for (;;) {
             st = idx >= 0 ? st_load(&status[idx]) : kStPrefix;
-            const bool invalid = (st >> 62) == 0;
-            if (!__any(invalid)) break;
-            if (++spins > kSpinLimit) {
-                if (lane == 0) { // the step's outputs are invalid: both the sticky and the per-step word say so
-                    atomicOr(&d->flags, ZG_FLAG_INTERNAL);
-                    atomicOr(&d->step_flags, ZG_FLAG_INTERNAL);
+            unsigned long long none = __ballot((st >> 62) == 0);
+            if (!none) break;
+            if (++polls > patience) {
+                if (patience == kSpinLimit) { // drawn tickets: the step's outputs are invalid, both the sticky and the per-step word say so
+                    if (lane == 0) {
+                        atomicOr(&d->flags, ZG_FLAG_INTERNAL);
+                        atomicOr(&d->step_flags, ZG_FLAG_INTERNAL);
+                    }
+                    break;
+                }
+                for (; none; none &= none - 1ull) {
+                    const int l = __ffsll((long long)none) - 1;
+                    const uint32_t v = missing((uint32_t)(base - l));
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // read before the second look
+                    if (lane == l) {
+                        st = st_load(&status[idx]);
+                        if ((st >> 62) == 0) st = kStAggregate | v;
+                    }
                 }
                 break;
             }
@@ -114,7 +138,7 @@ __device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, u
         const unsigned long long pm = __ballot((st >> 62) == 2);
         const int last = pm ? __ffsll((long long)pm) - 1 : 63;
         excl += wave_sum(lane <= last ? (uint32_t)st : 0u);
-        if (pm || base < 64 || spins > kSpinLimit) break;
+        if (pm || base < 64 || polls > kSpinLimit) break;
     }
     if (lane == 0) st_store(&status[t], kStPrefix | (uint32_t)(excl + total));
     return excl;
@@ -254,12 +278,13 @@ __device__ __forceinline__ void mailbox_inputs(const Drmb *d, const Drmb *gate, 
 
 // One lane of a sampling ticket, where nothing was prefetched (the host waits for every step, or this is the first): ticket 0 reads
 // the mailbox and passes the inputs on in device memory.  Reads of host memory queue up: 132 workgroups that each read the
-// slot took 20 us.  (The ingest workgroups of the launch, one per 1024 seeds, read it themselves.)  Ticket 0's workgroup runs before any other ticket is handed out; a wait that runs out reads the mailbox itself.
-__device__ __forceinline__ void shared_inputs(Drmb *d, const Drmb *gate, const Mailbox *mailbox, uint32_t ticket, unsigned long long *out)
+// slot took 20 us.  (The ingest workgroups of the launch, one per 1024 seeds, read it themselves.)  A wait that runs out - ticket 0 need
+// not be running yet - reads the mailbox itself.
+__device__ __forceinline__ void shared_inputs(Drmb *d, const Drmb *gate, const Mailbox *mailbox, uint32_t ticket, uint32_t patience, unsigned long long *out)
 {
     const uint32_t tag = d->epoch + 1u;
     if (ticket != 0u) {
-        for (uint32_t spins = 0; spins < kSpinLimit; ++spins) {
+        for (uint32_t polls = 0; polls < patience; ++polls) {
             if (__hip_atomic_load(&d->cur_epoch, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == tag) {
                 out[0] = __hip_atomic_load(&d->cur_seeds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 out[1] = __hip_atomic_load(&d->cur_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -497,6 +522,8 @@ struct HopArgs {
     uint32_t chunk_log2;      // ... of at most a word per lane: a lane ranks 2^chunk_log2 vertices (4 .. 32)
     uint32_t rank_tiles;      // 0 for launch 0
     uint32_t batch;
+    int32_t draw;             // tickets are drawn from a counter instead of being the workgroups' indices
+    uint32_t patience;        // polls before a wait ends
     uint32_t blocks;          // workgroups of this role (the launch's first ones)
 };
 
@@ -505,7 +532,7 @@ struct HopArgs {
 // bits, and a ranking tile's words
 constexpr int kHopRows = kHopBlock; // one row per lane
 struct HopShared {
-    uint32_t ticket;
+    uint32_t drawn;
     uint32_t base_cnt;
     uint32_t base_edge;
     bool have_in;
@@ -633,6 +660,12 @@ __device__ __forceinline__ void mark_bit(const HopArgs &a, uint32_t *set, uint32
     if (a.own) a.own[edge] = mine ? 1 : 0;
 }
 
+__device__ __forceinline__ uint32_t row_length(const HopArgs &a, uint32_t deg)
+{
+    const uint32_t F = (uint32_t)a.fanout;
+    return a.replace ? (deg > 0 ? F : 0u) : (deg < F ? deg : F);
+}
+
 // "Row lengths" of the workgroup's LDS rows: lane t takes the vertex sh.v[t] (none beyond `nrows`), loads its two offsets, and
 // leaves degree and first edge offset in LDS.  Returns this lane's k = min(F, deg) (F whenever deg > 0 with replacement).
 template <typename OffT>
@@ -650,8 +683,15 @@ __device__ __forceinline__ uint32_t load_rows(const HopArgs &a, HopShared &sh, u
     }
     sh.deg[tid] = deg;
     sh.off[tid] = off0;
-    const uint32_t F = (uint32_t)a.fanout;
-    return a.replace ? (deg > 0 ? F : 0u) : (deg < F ? deg : F);
+    return row_length(a, deg);
+}
+
+// the same of any one vertex, the length alone
+template <typename OffT>
+__device__ __forceinline__ uint32_t vertex_length(const HopArgs &a, int32_t v)
+{
+    const OffT *off = (const OffT *)a.offsets;
+    return row_length(a, (uint32_t)(off[v + 1] - off[v]));
 }
 
 // The same value in a scalar register of its own.  The compiler keeps some values that are the same for the whole workgroup in
@@ -660,6 +700,13 @@ __device__ __forceinline__ uint32_t load_rows(const HopArgs &a, HopShared &sh, u
 __device__ __forceinline__ int32_t own_scalar(int32_t x)
 {
     asm volatile("" : "+s"(x));
+    return x;
+}
+
+// ... and a vector register
+__device__ __forceinline__ uint32_t own_vector(uint32_t x)
+{
+    asm volatile("" : "+v"(x));
     return x;
 }
 
@@ -676,8 +723,7 @@ __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
     return out;
 }
 
-// The hop kernel's launches 0 .. H-1 (k_hop) and the closing launch H (k_close).  A workgroup takes a ticket; tickets are
-// handed out in start order, so every ticket a workgroup ever waits for belongs to a workgroup that already runs.  In ticket
+// The hop kernel's launches 0 .. H-1 (k_hop) and the closing launch H (k_close).  Every workgroup has a ticket; in ticket
 // order a launch's work is the row order of block l:
 //   tickets 0 .. t_old-1   rows that were already in D_{l-1} (launch 0: the seeds);
 //   then the ranking tiles of hop l-1's marks, 32 W vertices each, in ascending vertex id: those marked and not "seen"
@@ -689,7 +735,15 @@ __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
 // scan") and samples its rows, F lanes per row ("sample").  New vertices join "seen", consumed marks are cleared.  Vertices
 // ranked beyond the cap are dropped (no row, local id -1, not "seen") and the hop's overflow bit is raised; the rows kept are
 // a prefix of the row order, so the block stays consistent up to the cap.  Launch H ranks only.  The launch's surplus
-// workgroups (the grid is sized by the caps) find no ticket and return.
+// workgroups (the grid is sized by the caps) have no ticket and return.
+//
+// A ticket is the workgroup's index, or drawn from a counter (HopArgs.draw).  Drawing costs: the counter answers once per 13 ns, so the
+// last of 240 workgroups has its ticket 5.7 us into the launch, the last of 470 after 9.4 (large launches with one plan 20.3 -> 16.5 us, 53.7 -> 46,
+// launch 0 12.4 -> 8.1 with 128 of them).  It pays where the chip is shared: a workgroup that starts late, because another stream's kernels
+// hold its place, gets a late ticket, while a late index keeps all those behind it waiting in places that others could use (110 M
+// vertices, four plans: 217 us per step drawn, 235 by index; 2.4 M vertices 74 / 78; one plan 251-270 / 250-260 and 102 / 95).  So: launch 0 never; tiles
+// that are ranked by pieces of 128 vertices (of more than a word per lane: long launches) always; else where the plan has company - its
+// graph had another plan when it was made.
 //
 // Bound by latency: a ticket is a chain of about eight dependent memory accesses, so a launch costs the length of that chain,
 // the code it walks through cold and its slowest ticket.  Hence one instantiation per kind of launch and of marks (one
@@ -699,6 +753,14 @@ __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
 // piece u NT + tid in round u: 16-byte accesses, consecutive lanes consecutive.
 __device__ __forceinline__ uint32_t piece_word(const uint4 &x, uint32_t c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; }
 __device__ __forceinline__ uint32_t piece_any(const uint4 &x) { return x.x | x.y | x.z | x.w; }
+
+// the marks of one word's 32 bytes
+__device__ __forceinline__ uint32_t marks32(const uint4 *b)
+{
+    const uint4 y = b[0], z = b[1];
+    return marks4(y.x) | (marks4(y.y) << 4) | (marks4(y.z) << 8) | (marks4(y.w) << 12) | (marks4(z.x) << 16) | (marks4(z.y) << 20) | (marks4(z.z) << 24) |
+           (marks4(z.w) << 28);
+}
 
 // Reads a tile's marks, masks them with "seen", and clears them for the hop after next (tagged: a new vertex's byte stays until
 // its tag has been read).  Mark bytes become words in LDS first, 16 bytes per lane.  With JOIN the new vertices join
@@ -751,6 +813,41 @@ __device__ __forceinline__ void load_tile(const HopArgs &a, size_t tile0, uint32
         }
 }
 
+// Clears a word's mark bytes for the hop after next; where tags are still needed (`tagged`) a new vertex's byte stays until its tag has
+// been read.
+__device__ __forceinline__ void clear_bytes(uint4 *b, uint32_t marked, uint32_t fresh, bool tagged)
+{
+    if (!tagged || fresh == 0u)
+        b[0] = b[1] = make_uint4(0u, 0u, 0u, 0u);
+    else
+        for (uint32_t old = marked & ~fresh; old; old &= old - 1u) reinterpret_cast<uint8_t *>(b)[__ffs((int)old) - 1] = 0;
+}
+
+// a word of a tile, whoever's it is: marked and not "seen" (rarely needed, and in few registers)
+template <bool BYTES>
+__device__ __forceinline__ uint32_t new_vertices(const HopArgs &a, uint32_t word)
+{
+    uint32_t w = 0u;
+    if (BYTES) {
+#pragma unroll 1
+        for (uint32_t c = 0; c < 8u; ++c) w |= marks4(a.marks_prev[(size_t)word * 8u + c]) << (4u * c);
+    } else {
+        w = a.marks_prev[word];
+    }
+    return w & ~a.seen[word];
+}
+
+// a tile's total, worked out by one wavefront of another workgroup (see chain_prefix)
+template <bool BYTES>
+__device__ __forceinline__ uint32_t missing_vertices(const HopArgs &a, uint32_t tile, uint32_t lane)
+{
+    const uint32_t w0 = tile * a.words_per_tile;
+    uint32_t c = 0;
+#pragma unroll 1
+    for (uint32_t w = lane; w < a.words_per_tile; w += 64u) c += __popc(new_vertices<BYTES>(a, w0 + w));
+    return wave_sum(c);
+}
+
 // Ranks within the tile: lex[u] = new vertices before the lane's piece of round u.  Returns their number.  `wsum` holds a count
 // per round and wavefront (64 at most); one barrier.
 template <int NT, int R>
@@ -788,40 +885,43 @@ __device__ __forceinline__ void expand_piece(const uint4 &x, uint32_t j, uint32_
 // A tile of at most a word per lane (the graph is small for its ranking tiles, the tile dense with new vertices): the lane's word
 // of new vertices, also left in s_words.  A word per lane while it is read, and 2^chunk_log2 vertices per lane once it is ranked and
 // expanded (pieces of 128 left 16 lanes of 1024 to walk through a tile of 64 words, up to 128 vertices one after another: a hop launch
-// over 250 k vertices 15.6 -> 14.5 us, with 2.4 M vertices 57 -> 54).  Marks are cleared where they are read, 16 bytes per lane, unless
-// their tags are still needed.
-template <int NT, bool BYTES, bool JOIN>
+// over 250 k vertices 15.6 -> 14.5 us, with 2.4 M vertices 57 -> 54).
+template <int NT, bool BYTES>
 __device__ __forceinline__ uint32_t load_words(const HopArgs &a, size_t tile0, uint32_t words, uint32_t tid, uint32_t *s_words)
 {
-    const bool tagged = BYTES && !JOIN && a.tag.shift != 0;
-    uint32_t sn = 0u, w = 0u;
+    uint32_t sn = 0u, marked = 0u;
     if (tid < words) sn = a.seen[tile0 + tid];
     if (BYTES) {
-        uint4 *src = reinterpret_cast<uint4 *>(a.marks_prev) + tile0 * 2u;
+        const uint4 *src = reinterpret_cast<const uint4 *>(a.marks_prev) + tile0 * 2u;
         uint16_t *half = reinterpret_cast<uint16_t *>(s_words);
 #pragma unroll 2
         for (uint32_t q = tid; q < 2u * words; q += (uint32_t)NT) {
             const uint4 y = src[q];
             half[q] = (uint16_t)(marks4(y.x) | (marks4(y.y) << 4) | (marks4(y.z) << 8) | (marks4(y.w) << 12));
-            if (!tagged && piece_any(y)) src[q] = make_uint4(0u, 0u, 0u, 0u);
         }
         __syncthreads();
-        if (tid < words) w = s_words[tid];
+        if (tid < words) marked = s_words[tid];
     } else if (tid < words) {
-        w = a.marks_prev[tile0 + tid];
-        if (w) a.marks_prev[tile0 + tid] = 0u;
+        marked = a.marks_prev[tile0 + tid];
     }
-    const uint32_t fresh = w & ~sn;
-    if (JOIN && fresh) a.seen[tile0 + tid] = sn | fresh;
-    if (tagged && w) { // a new vertex's byte stays until its tag has been read
-        uint4 *b = reinterpret_cast<uint4 *>(a.marks_prev) + (tile0 + tid) * 2u; // the word's 32 bytes
-        if (fresh == 0u)
-            b[0] = b[1] = make_uint4(0u, 0u, 0u, 0u);
-        else
-            for (uint32_t old = w & ~fresh; old; old &= old - 1u) reinterpret_cast<uint8_t *>(b)[__ffs((int)old) - 1] = 0;
-    }
-    if (tid < words) s_words[tid] = fresh;
-    return fresh;
+    if (tid < words) s_words[tid] = marked & ~sn;
+    return marked & ~sn;
+}
+
+// ... and what changes once the tile's totals are published: its marks are cleared - read again: no register holds them that long -
+// and, with JOIN, its new vertices join "seen".
+template <bool BYTES, bool JOIN>
+__device__ __forceinline__ void settle_word(const HopArgs &a, size_t tile0, uint32_t words, uint32_t tid, const uint32_t *s_words)
+{
+    if (tid >= words) return;
+    uint4 *const bytes = reinterpret_cast<uint4 *>(a.marks_prev) + (tile0 + tid) * 2u;
+    const uint32_t marked = BYTES ? marks32(bytes) : a.marks_prev[tile0 + tid], fresh = s_words[tid];
+    if (JOIN && fresh) a.seen[tile0 + tid] |= fresh;
+    if (marked == 0u) return;
+    if (BYTES)
+        clear_bytes(bytes, marked, fresh, !JOIN && a.tag.shift != 0);
+    else
+        a.marks_prev[tile0 + tid] = 0u;
 }
 
 // ... and its ranks: the lane's chunk of the tile's words (in s_words: barriers before the first and after the last use are in
@@ -877,12 +977,15 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     uint32_t *const s_words = s_set + (NEXT_BYTES ? 0 : kSampleHashSlots);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     Drmb *d = a.drmb;
-    if (tid == 0) sh.ticket = atomicAdd(&d->ticket[a.launch], 1u);
     if (FIRST && tid == 64) sh.have_in = prefetched_inputs(d, a.gate, sh.in);
-    const uint32_t n_old_d = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while the ticket comes back)
+    if (!FIRST && a.draw && tid == 0) sh.drawn = atomicAdd(&d->ticket[a.launch], 1u);
+    const uint32_t n_old_d = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while a drawn ticket comes back)
     const uint32_t key_lo_d = FIRST ? 0u : d->key_lo, key_hi_d = FIRST ? 0u : d->key_hi;
-    __syncthreads();
-    const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.ticket);
+    uint32_t ticket = blockIdx.x;
+    if (FIRST || a.draw) {
+        __syncthreads();
+        if (!FIRST) ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.drawn);
+    }
     // A scalar, and with it all that follows from it (rows per ticket, the tile, its address, which kind of ticket this is): kept per lane
     // these cost a launch that marks bits 7 registers more than its 64, 28 bytes per lane written to scratch - 14 MB in a launch of
     // 480 tickets.  (110 M vertices: 88 + 38 MB read + written by that launch, now 79 + 24 MB; the step 280 -> 274 us.)
@@ -892,11 +995,11 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     if (!FIRST && rows < 128u) rows = 128u;
     if (!FIRST)
         while (rows < (uint32_t)kHopRows / 2u + 1u && (n_old + rows - 1u) / rows + a.rank_tiles > a.max_tickets) rows *= 2u;
-    const uint32_t t_old = (n_old + rows - 1u) / rows;
+    const uint32_t t_old = (uint32_t)__builtin_amdgcn_readfirstlane((int)((n_old + rows - 1u) / rows));
     const uint32_t n_tickets = t_old + (FIRST ? 0u : a.rank_tiles);
     if (ticket >= n_tickets) return;
     if (FIRST && !sh.have_in) {
-        if (tid == 0) shared_inputs(d, a.gate, a.mailbox, ticket, sh.in);
+        if (tid == 0) shared_inputs(d, a.gate, a.mailbox, ticket, a.patience, sh.in);
         __syncthreads();
     }
     const bool old = FIRST || ticket < t_old; // uniform over the workgroup
@@ -910,53 +1013,76 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     const size_t tile0 = (size_t)tile * a.words_per_tile;
     uint4 *const s_piece = reinterpret_cast<uint4 *>(s_words);
     const bool by_chunks = a.words_per_tile <= (uint32_t)kHopBlock;
-    uint32_t chunk = 0u, before_chunk = 0u;
-    auto expand_pieces = [&](const uint4 (&x)[R], const uint32_t (&lex)[R], uint32_t c0) {
+    auto rank_and_expand = [&](uint32_t word, uint32_t c0, bool publish) { // by chunks
+        uint32_t chunk, before;
+        const uint32_t t = own_vector(tid);
+        const uint32_t n = rank_chunks<kHopBlock>(word, a.chunk_log2, a.words_per_tile, s_words, sh.wsum, t, chunk, before);
+        if (publish && tid == 0) chain_publish(a.status_cnt, tile, n);
+        expand_chunk(chunk, before, ((uint32_t)tile0 << 5) + (t << a.chunk_log2), c0, kHopRows, sh.v);
+        return n;
+    };
+    auto expand_pieces = [&](const uint4 (&x)[R], const uint32_t (&lex)[R], uint32_t c0, uint32_t t) {
 #pragma unroll
         for (int u = 0; u < R; ++u)
-            if (u * (uint32_t)kHopBlock + tid < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kHopBlock + tid) * 4u, c0, kHopRows, sh.v);
+            if (u * (uint32_t)kHopBlock + t < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kHopBlock + t) * 4u, c0, kHopRows, sh.v);
     };
-    // the tile's words as they were ranked, out of LDS, and their ranks once more (a tile of several batches of rows, or cut by the cap)
-    auto pieces_again = [&](uint4 (&x)[R], uint32_t (&lex)[R]) {
+    // the tile's words as they were ranked, out of LDS, and their ranks once more: no register holds them (a tile of several batches of
+    // rows, or cut by the cap)
+    auto pieces_again = [&](uint4 (&x)[R], uint32_t (&lex)[R], uint32_t t) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) x[u] = u * (uint32_t)kHopBlock + tid < np ? s_piece[u * kHopBlock + tid] : make_uint4(0u, 0u, 0u, 0u);
+        for (int u = 0; u < R; ++u) x[u] = u * (uint32_t)kHopBlock + t < np ? s_piece[u * kHopBlock + t] : make_uint4(0u, 0u, 0u, 0u);
         (void)rank_pieces<kHopBlock, R>(x, lex, sh.wsum, np, wave, lane);
     };
     if (old) {
         m = n_old - r0 < rows ? n_old - r0 : rows;
     } else if (by_chunks) {
-        const uint32_t word = load_words<kHopBlock, PREV_BYTES, true>(a, tile0, a.words_per_tile, tid, s_words);
-        m = rank_chunks<kHopBlock>(word, a.chunk_log2, a.words_per_tile, s_words, sh.wsum, tid, chunk, before_chunk);
-        if (tid == 0) chain_publish(a.status_cnt, tile, m);
+        m = rank_and_expand(load_words<kHopBlock, PREV_BYTES>(a, tile0, a.words_per_tile, tid, s_words), 0u, true);
     } else {
         uint4 x[R];
         uint32_t lex[R];
         load_tile<kHopBlock, R, PREV_BYTES, true>(a, tile0, np, tid, x, s_words);
         m = rank_pieces<kHopBlock, R>(x, lex, sh.wsum, np, wave, lane);
         if (tid == 0) chain_publish(a.status_cnt, tile, m);
-        expand_pieces(x, lex, 0u);
+        expand_pieces(x, lex, 0u, tid);
 #pragma unroll
         for (int u = 0; u < R; ++u)
             if (u * (uint32_t)kHopBlock + tid < np) s_piece[u * kHopBlock + tid] = x[u]; // (read back by this lane only)
     }
+    auto old_row = [&](uint32_t r) { // a row of the frontier (launch 0: a seed, an out-of-range one becoming -1, a vertex without neighbors)
+        const int32_t v = FIRST ? reinterpret_cast<const int32_t *>(sh.in[0])[r] : a.S[r];
+        return FIRST && (uint32_t)v >= a.num_nodes ? -1 : v;
+    };
+    auto missing_edges = [&](uint32_t t) { // another ticket's edges, worked out by this wavefront (see chain_prefix)
+        uint32_t k = 0;
+        if (t < t_old) {
+#pragma unroll 1
+            for (uint32_t i = lane; i < rows && t * rows + i < n_old; i += 64u) {
+                const int32_t v = old_row(t * rows + i);
+                if (v >= 0) k += vertex_length<OffT>(a, v);
+            }
+        } else if (!FIRST) {
+            const uint32_t w0 = (t - t_old) * a.words_per_tile;
+#pragma unroll 1
+            for (uint32_t w = lane; w < a.words_per_tile; w += 64u)
+#pragma unroll 1
+                for (uint32_t x = new_vertices<PREV_BYTES>(a, w0 + w); x; x &= x - 1u) k += vertex_length<OffT>(a, (int32_t)((w0 + w) * 32u) + __ffs((int)x) - 1);
+        }
+        return wave_sum(k);
+    };
 
-    // rows c0 .. c0 + 1023 of the ticket into sh.v: old rows from the frontier list (launch 0: the seeds, an
-    // out-of-range one becoming -1, a vertex without neighbors), new vertices expanded from the lane's words (`first`: a tile
-    // ranked by pieces has its first batch there already)
+    // rows c0 .. c0 + 1023 of the ticket into sh.v: old rows from the frontier list, new vertices expanded from the tile's words
+    // (`first`: a tile's first batch has been there since it was ranked)
     auto fill_rows = [&](uint32_t c0, bool first) {
         if (old) {
-            if (tid < m) {
-                int32_t v = FIRST ? reinterpret_cast<const int32_t *>(sh.in[0])[r0 + tid] : a.S[r0 + tid];
-                if (FIRST && (uint32_t)v >= a.num_nodes) v = -1;
-                sh.v[tid] = v;
-            }
-        } else if (by_chunks) {
-            expand_chunk(chunk, before_chunk, ((uint32_t)tile0 << 5) + (tid << a.chunk_log2), c0, kHopRows, sh.v);
+            if (tid < m) sh.v[tid] = old_row(r0 + tid);
+        } else if (!first && by_chunks) {
+            (void)rank_and_expand(tid < a.words_per_tile ? s_words[tid] : 0u, c0, false);
         } else if (!first) {
             uint4 x[R];
             uint32_t lex[R];
-            pieces_again(x, lex);
-            expand_pieces(x, lex, c0);
+            const uint32_t t = own_vector(tid);
+            pieces_again(x, lex, t);
+            expand_pieces(x, lex, c0, t);
         }
         __syncthreads();
     };
@@ -991,20 +1117,21 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     bool chained = false;
     auto take_prefixes = [&]() { // wavefront 0 sums up the new vertices before this tile, wavefront 1 the edges before this ticket
         if (wave == 0u && !old) {
-            const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane);
+            publish_done();
+            const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane, a.patience, [&](uint32_t t) { return missing_vertices<PREV_BYTES>(a, t, lane); });
             if (lane == 0) sh.base_cnt = c;
         }
         if (wave == 1u) {
-            const uint32_t e = chain_prefix(a.status_edge, ticket, ticket_edges, d, (int)lane);
+            const uint32_t e = chain_prefix(a.status_edge, ticket, ticket_edges, d, (int)lane, a.patience, missing_edges);
             if (lane == 0) sh.base_edge = e;
         }
         __syncthreads();
         if (!old) rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.base_cnt); // row index of the ticket's first row
-        room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;                                   // how many of its rows fit (old rows: all)
+        room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;                                  // how many of its rows fit (old rows: all)
         ebase = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.base_edge);
         chained = true;
     };
-    for (uint32_t q = 0; q < supers; ++q) {
+    for (uint32_t q = 0; q == 0u || q < supers; ++q) { // (a tile without a new vertex: once, for the prefixes)
         const uint32_t c0 = q * kHopRows;
         const uint32_t nrows = m - c0 < (uint32_t)kHopRows ? m - c0 : (uint32_t)kHopRows;
         if (supers > 1) {
@@ -1022,7 +1149,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         if (tid == 0) sh.rp[nrows] = batch_edges;
         __syncthreads();
         uint32_t keep = 0;
-        for (uint32_t b0 = 0; b0 < nrows; b0 += stage_rows) {
+        for (uint32_t b0 = 0; b0 == 0u || b0 < nrows; b0 += stage_rows) {
             const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0];
             load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
             if (!chained)
@@ -1069,8 +1196,6 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         }
         ebase += sh.rp[keep];
     }
-    if (!chained) take_prefixes(); // (a tile without a new vertex)
-
     if (old) {
         if (FIRST && ticket == t_old - 1u && tid == 0) { // launch 0 has no ranking tiles: the block ends with these rows
             a.row_ptr[n_old] = (int32_t)ebase;
@@ -1079,21 +1204,24 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         return;
     }
 
+    const uint32_t tid_end = own_vector(tid);
+    if (by_chunks) settle_word<PREV_BYTES, true>(a, tile0, a.words_per_tile, tid_end, s_words);
+
     if (m > room) {
         // ---- the cap cuts into this tile: the vertices dropped leave "seen" again
         uint4 x[R];
         uint32_t lex[R];
         __syncthreads();
-        pieces_again(x, lex);
+        pieces_again(x, lex, tid_end);
 #pragma unroll
         for (int u = 0; u < R; ++u)
-            if (u * (uint32_t)kHopBlock + tid < np) {
+            if (u * (uint32_t)kHopBlock + tid_end < np) {
                 uint32_t j = lex[u];
 #pragma unroll
                 for (uint32_t c = 0; c < 4u; ++c) {
                     const uint32_t w = piece_word(x[u], c), pc = __popc(w);
                     const uint32_t kept = j < room ? lowest_set_bits(w, room - j) : 0u;
-                    if (kept != w) a.seen[tile0 + (u * (uint32_t)kHopBlock + tid) * 4u + c] &= ~(w & ~kept);
+                    if (kept != w) a.seen[tile0 + (u * (uint32_t)kHopBlock + tid_end) * 4u + c] &= ~(w & ~kept);
                     j += pc;
                 }
             }
@@ -1292,7 +1420,7 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
 {
     constexpr int R = kHopMaxTileWords / 4 / kCloseBlock;
     constexpr uint32_t kBatch = kCloseBatch; // vertices expanded at a time
-    __shared__ uint32_t s_ticket, s_base, s_wsum[64];
+    __shared__ uint32_t s_drawn, s_base, s_wsum[64];
     __shared__ int32_t s_v[kBatch];
     extern __shared__ __align__(16) uint32_t s_words[]; // the tile's words (bit marks: of a tile of at most a word per lane)
     if (gate_closed(a.gate)) return;
@@ -1311,10 +1439,13 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
     }
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     Drmb *d = a.drmb;
-    if (tid == 0) s_ticket = atomicAdd(&d->ticket[a.launch], 1u);
     const uint32_t n_old = d->n[a.launch - 1];
-    __syncthreads();
-    const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_ticket); // (the grid holds no more tickets than tiles)
+    uint32_t tile = blockIdx.x;
+    if (a.draw) {
+        if (tid == 0) s_drawn = atomicAdd(&d->ticket[a.launch], 1u);
+        __syncthreads();
+        tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_drawn);
+    }
     const uint32_t np = a.words_per_tile / 4u;
     const size_t tile0 = (size_t)tile * a.words_per_tile;
     uint4 x[R];
@@ -1322,7 +1453,7 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
     uint32_t m, chunk = 0u, before_chunk = 0u;
     const bool by_chunks = a.words_per_tile <= (uint32_t)kCloseBlock;
     if (by_chunks) {
-        const uint32_t word = load_words<kCloseBlock, BYTES, false>(a, tile0, a.words_per_tile, tid, s_words);
+        const uint32_t word = load_words<kCloseBlock, BYTES>(a, tile0, a.words_per_tile, tid, s_words);
         m = rank_chunks<kCloseBlock>(word, a.chunk_log2, a.words_per_tile, s_words, s_wsum, tid, chunk, before_chunk);
     } else {
         load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
@@ -1330,7 +1461,8 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
     }
     if (wave == 0u) {
         if (lane == 0) chain_publish(a.status_cnt, tile, m);
-        const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane);
+        publish_done();
+        const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane, a.patience, [&](uint32_t t) { return missing_vertices<BYTES>(a, t, lane); });
         if (lane == 0) s_base = c;
     }
     uint32_t rank0 = 0, room = 0;
@@ -1341,9 +1473,10 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
         if (by_chunks) {
             expand_chunk(chunk, before_chunk, ((uint32_t)tile0 << 5) + (tid << a.chunk_log2), c0, kBatch, s_v);
         } else {
+            const uint32_t t = own_vector(tid);
 #pragma unroll
             for (int u = 0; u < R; ++u)
-                if (u * (uint32_t)kCloseBlock + tid < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + tid) * 4u, c0, kBatch, s_v);
+                if (u * (uint32_t)kCloseBlock + t < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + t) * 4u, c0, kBatch, s_v);
         }
         __syncthreads();
         rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_base);
@@ -1363,6 +1496,7 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
             }
         }
     }
+    if (by_chunks) settle_word<BYTES, false>(a, tile0, a.words_per_tile, own_vector(tid), s_words);
     if (tid == 0 && tile == a.rank_tiles - 1u) { // the last ticket publishes the hop's size
         const int32_t launch = own_scalar(a.launch);
         const uint64_t exact = (uint64_t)rank0 + m;
@@ -2084,6 +2218,8 @@ struct zg_plan_s {
     uint32_t issued = 0;            // steps enqueued so far (mod 2^32, like the device-side step counter)
     hipStream_t last_stream = nullptr; // stream of the last enqueued step (what zg_plan_destroy waits for)
     bool stepped = false;
+    bool in_company = false;        // there were other plans on the graph when this one was made: they are meant to run side by side
+    std::shared_ptr<std::atomic<int>> company; // ... and the count of them that this one is part of
     zg_plan_s *twin = nullptr;      // worst-case twin (ZG_PLAN_SAFE_TWIN): own outputs, metadata and mailbox, shared scratch
     hipStream_t capture_stream = nullptr;
     hipGraph_t graph_obj = nullptr;
@@ -2418,6 +2554,10 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         while (ha.chunk_log2 > 2 && ((uint64_t)ha.words_per_tile << (6 - ha.chunk_log2)) <= (uint64_t)(l < H ? kHopBlock : kCloseBlock)) --ha.chunk_log2;
         ha.rank_tiles = (uint32_t)L.rank_tiles[l];
         ha.batch = (uint32_t)p->batch;
+        // Tickets: see k_hop.  A tile ranked by pieces changes its marks before its totals are out: nobody else can work them out.
+        const bool by_pieces = l > 0 && L.tile_words[l] > (l < H ? kHopBlock : kCloseBlock);
+        ha.draw = l > 0 && (by_pieces || p->in_company);
+        ha.patience = by_pieces ? kSpinLimit : (p->flags & ZG_PLAN_IMPATIENT) ? 0u : kPatience;
         ha.blocks = (uint32_t)(L.old_tickets[l] + L.rank_tiles[l]);
         // the edges of hop l-2 can be relabeled now: launch l-1 ranked the last vertices they point to
         const RelabelArgs ra = relabel_args(p, l - 2, l >= 2);
@@ -2527,7 +2667,7 @@ int build_graph(zg_plan_t *p)
 extern "C" {
 
 static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &L, uint32_t flags, int32_t batch,
-                            char *ws, hipStream_t st, bool init_scratch)
+                            char *ws, hipStream_t st, bool init_scratch, bool in_company)
 {
     zg_plan_t *p = new (std::nothrow) zg_plan_t();
     if (!p) return fail(ZG_ENOMEM, "out of host memory");
@@ -2536,6 +2676,7 @@ static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &
     p->ws = ws;
     p->flags = flags;
     p->batch = batch;
+    p->in_company = in_company;
     auto bail = [&](int code) {
         zg_plan_destroy(p);
         return code;
@@ -2587,10 +2728,13 @@ int zg_plan(zg_plan_t **out, const zg_graph_t *g, const int32_t *fanouts, int32_
     zg_plan_t *p = nullptr;
     // with a twin both lay their scratch out in the same region, sized for the larger of the two.  The id maps coincide; everything
     // behind them has to be zero between steps, whichever layout reads it: each of the two clears the regions of its own.
-    rc = make_plan_object(&p, g, L, env->flags, batch, ws, st, true);
+    const bool in_company = g->plans->load(std::memory_order_relaxed) > 0;
+    rc = make_plan_object(&p, g, L, env->flags, batch, ws, st, true, in_company);
     if (rc != ZG_OK) return rc;
+    p->company = g->plans;
+    p->company->fetch_add(1, std::memory_order_relaxed);
     if (with_twin) {
-        rc = make_plan_object(&p->twin, g, Ls, env->flags & ~(ZG_PLAN_SAFE_TWIN | ZG_PLAN_AUTO_FALLBACK), batch, ws, st, true);
+        rc = make_plan_object(&p->twin, g, Ls, env->flags & ~(ZG_PLAN_SAFE_TWIN | ZG_PLAN_AUTO_FALLBACK), batch, ws, st, true, in_company);
         if (rc == ZG_OK && (env->flags & ZG_PLAN_AUTO_FALLBACK)) rc = build_graph(p); // again, now with the twin's kernels behind
         if (rc != ZG_OK) {
             zg_plan_destroy(p);
@@ -2632,6 +2776,7 @@ int zg_plan_destroy(zg_plan_t *p)
     drop_graph(p);
     if (p->capture_stream) (void)hipStreamDestroy(p->capture_stream);
     if (p->mailbox) (void)hipHostFree(p->mailbox);
+    if (p->company) p->company->fetch_sub(1, std::memory_order_relaxed);
     delete p;
     return ZG_OK;
 }

@@ -238,7 +238,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
     {
         // Launch l of the hop kernel (l = 0..H) samples hop l for the rows of D_l and, for l > 0, first ranks the vertices
         // hop l-1 discovered.  Rows that were already in D_{l-1} come in tiles of 1024 / G rows, a ticket covering 1..4
-        // tiles or more (every ticket is one atomic on a shared counter, about 13 ns each on MI355X, hence the budget).
+        // tiles or more (a drawn ticket is one atomic on a shared counter, about 13 ns each on MI355X, hence the budget).
         // The discovered vertices come in ranking tiles: W consecutive words (32 vertices each) of the hop's marks per
         // workgroup, so many that a tile holds about one sampling pass (1024 / G vertices) of new rows at the cap, within
         // the ticket budget and between 32 and 8192 words.
@@ -252,7 +252,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
             const int64_t T = l < num_hops ? sample_tile_nodes(fanouts[l]) : 256;
             if (l > 0) {
                 // New and old rows share the budget in proportion.  Within it a sampling pass of rows per tile up to 160 tiles,
-                // then 320 rows per tile: a ticket costs 13 ns of the shared counter and a share of the look-backs, its rows only
+                // then 320 rows per tile: a drawn ticket costs 13 ns of the shared counter, and every one a share of the look-backs, its rows only
                 // time of their own while there are few.  (15 k new rows: 245 tiles 18.4 us, 139 tiles 17.0 us; 33 k: 390 tiles
                 // 22.5 us, 204 tiles 19.8 us; 285 k: 256 tickets 79 us, 480 tickets 57 us.)  The closing launch only
                 // ranks: half the budget.  (137 k new vertices: 469 tickets 25 us, 235 tickets 21 us.)

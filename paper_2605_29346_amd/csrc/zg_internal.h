@@ -3,7 +3,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -56,7 +58,7 @@ struct Drmb {
     uint32_t last_flags;               // step_flags of the step that finished last (step_flags itself restarts at 0)
     uint32_t epoch;                    // steps run so far
     uint32_t key_lo, key_hi;           // step key
-    uint32_t ticket[ZG_MAX_HOPS + 1];  // tile tickets of the hop kernel's launches 0..H
+    uint32_t ticket[ZG_MAX_HOPS + 1];  // tickets drawn in the hop kernel's launches 0..H
     uint32_t active;                   // ZG_PLAN_AUTO_FALLBACK: 1 when the last step's valid outputs are the twin's
     uint32_t pre_valid, pre_epoch;     // the next step's inputs, copied from the host mailbox ahead of time: valid for step pre_epoch
     unsigned long long pre_seeds, pre_key;
@@ -132,4 +134,6 @@ struct zg_graph_s {
     bool stats_only = false;
     int device = -1;
     std::vector<int64_t> degrees, counts; // distinct degree values (ascending) and how many vertices have each
+    // plans made from the handle and not destroyed yet (shared with them: nothing but this outlives the handle)
+    std::shared_ptr<std::atomic<int>> plans = std::make_shared<std::atomic<int>>(0);
 };

@@ -20,6 +20,7 @@ I32, I64 = 0, 1
 GRAPH_VALIDATE = 1
 PLAN_EAGER, PLAN_REPLACE, PLAN_SAFE_TWIN, PLAN_FUSED_INPUT, PLAN_AUTO_FALLBACK = 1, 2, 4, 8, 16
 PLAN_X_ONE_PASS, PLAN_X_TWO_PASS = 32, 64
+PLAN_IMPATIENT = 128
 ENV_MAX, ENV_MODEL, ENV_EXPLICIT, ENV_GRAPH = 0, 1, 2, 3
 FLAG_SEED_RANGE, FLAG_SEED_DUP, FLAG_INTERNAL = 1 << 16, 1 << 17, 1 << 18
 

@@ -418,3 +418,25 @@ def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, repla
     base = (temp.data_ptr() + 255) // 256 * 256
     assert zg.lib().zg_envelope_model_graph(dg._h, f, 2, batch, int(replace), None, base, 12 * nodes + 576, None, mean, sigma) == zg.OK
     assert binned == (list(mean[:3]), list(sigma[:3]))
+
+
+@pytest.mark.parametrize("nodes,draws,batch,fanouts,max_tickets", [
+    (20_000, 500_000, 256, (6, 5, 4), 0),        # bytes, tiles of at most a word per lane
+    (3_000_000, 12_000_000, 256, (8, 5, 3), 0),  # bits, a few hundred words per tile
+    (3_000_000, 12_000_000, 900, (8, 5), 20),    # bits, pieces of 128 vertices
+    (600_000, 6_000_000, 3000, (9, 7), 8),       # bytes, pieces, several batches of rows per ticket
+    (70_000, 1_400_000, 3000, (11, 6), 300),
+])
+@pytest.mark.parametrize("replace", [False, True])
+def test_totals_worked_out_instead_of_waited_for(oracle, nodes, draws, batch, fanouts, max_tickets, replace):
+    # no workgroup waits for another one: totals that are not there at the first look are worked out from the marks, the rows and the
+    # offsets, whether their owner has not begun, is at it or has just published
+    g = W.rmat_graph(nodes, draws, 5)
+    feat = W.feature_table(nodes, 8, 3)
+    og = to_host_graph(oracle, g)
+    pool = W.SeedPool(g, batch, 9)
+    flags = zg.PLAN_IMPATIENT | (zg.PLAN_REPLACE if replace else 0)
+    plan = None
+    for s in range(3):
+        plan, _, _ = run_and_compare(oracle, g, feat, pool.batch_for(s).numpy(), fanouts, 70 + s, plan=plan, og=og, replace=replace,
+                                     env=zg.make_envelope(zg.ENV_MAX, flags=flags, max_tickets=max_tickets))
