@@ -1779,6 +1779,8 @@ constexpr double kFix = 4294967296.0; // 2^32
 constexpr int kModelBinBlock = 512, kModelWindow = 4096; // threads of a workgroup of k_model_bin, edges it looks at together
 constexpr int kModelAddBlock = 512;
 constexpr uint32_t kModelMaxBins = 32768;                // a counter each in LDS
+constexpr uint32_t kModelNoShare = 0xFFFFFFFFu;
+constexpr int64_t kModelMinPart = 16384;
 
 __global__ void k_model_init(float *q, unsigned long long *ell, const float *seed_prob, float uniform, int64_t n)
 {
@@ -1824,7 +1826,7 @@ __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const in
 // The sweep with room for 8 bytes per edge: no atomic leaves a compute unit.  The vertices are cut into bins of 2^log2.  Once per
 // call the edges are counted by chunk and bin (k_model_count) and the counts turned into places (k_model_places, k_model_starts); in
 // each hop every edge's term is written to its bin behind those of earlier chunks (k_model_bin: the term, and the vertex within the
-// bin in the low bits), and a workgroup per bin adds it up in LDS (k_model_add).  The terms are integers: the same sums as above.
+// bin in the low bits), and a workgroup per bin, or several, adds it up in LDS (k_model_add).  The terms are integers: the same sums as above.
 // Three hops at 2.4 M vertices and 115 M edges: 22.8 -> 3.2 ms, k_model_bin 0.59 ms per hop (0.46 GB read, 0.92 GB written in pieces of 8
 // bytes), k_model_add 0.34 ms (2.7 TB/s), the places 0.17 ms once; 40 M vertices and 350 M edges 61 -> 15 ms.  (A window's entries put in
 // the order of their bins in LDS first, so that they leave in runs: 0.56 ms instead of 0.59, 1.06 instead of 1.27 with 1831 bins;
@@ -1834,8 +1836,10 @@ struct ModelBins {
     int64_t num_edges, num_nodes;
     uint32_t log2, bins;
     uint32_t chunk, chunks;    // edges of a chunk, a multiple of kModelWindow
+    uint32_t part, parts;      // most entries a workgroup of k_model_add takes, and how many such parts there are at most
     uint32_t *place;           // [chunks][bins]: edges of the chunk that lead into the bin; then how many of earlier chunks do
     uint32_t *start;           // [bins + 1]: where the bin's entries begin
+    uint32_t *share;           // [parts]: a bin, and above its 15 bits which part of it; kModelNoShare behind the last one
     unsigned long long *entry; // [num_edges]
 };
 
@@ -1894,25 +1898,40 @@ __global__ __launch_bounds__(1024) void k_model_places(ModelBins m)
     if (wave == 15u) m.start[b] = run;
 }
 
-// one workgroup: the bins' totals into their starts
+__device__ __forceinline__ uint32_t model_parts(const ModelBins &m, uint32_t entries) { return entries ? (entries - 1u) / m.part + 1u : 1u; }
+
+// one workgroup: the bins' totals into their starts, and the bins into parts of at most m.part entries
 __global__ __launch_bounds__(1024) void k_model_starts(ModelBins m)
 {
-    __shared__ uint32_t s_sum[16];
+    __shared__ uint32_t s_sum[2][16];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, each = (m.bins + 1023u) / 1024u;
-    const uint32_t b0 = threadIdx.x * each, b1 = b0 + each < m.bins ? b0 + each : m.bins;
-    uint32_t sum = 0;
-    for (uint32_t b = b0; b < b1; ++b) sum += m.start[b];
-    const uint32_t incl = wave_incl_scan(sum);
-    if (lane == 63u) s_sum[wave] = incl;
-    __syncthreads();
-    uint32_t run = incl - sum;
-    for (uint32_t w = 0; w < wave; ++w) run += s_sum[w];
+    const uint32_t b0 = threadIdx.x * each < m.bins ? threadIdx.x * each : m.bins, b1 = b0 + each < m.bins ? b0 + each : m.bins;
+    uint32_t sum = 0, parts = 0;
     for (uint32_t b = b0; b < b1; ++b) {
-        const uint32_t x = m.start[b];
+        sum += m.start[b];
+        parts += model_parts(m, m.start[b]);
+    }
+    const uint32_t incl = wave_incl_scan(sum), incl_parts = wave_incl_scan(parts);
+    if (lane == 63u) {
+        s_sum[0][wave] = incl;
+        s_sum[1][wave] = incl_parts;
+    }
+    __syncthreads();
+    uint32_t run = incl - sum, at = incl_parts - parts;
+    for (uint32_t w = 0; w < wave; ++w) {
+        run += s_sum[0][w];
+        at += s_sum[1][w];
+    }
+    for (uint32_t b = b0; b < b1; ++b) {
+        const uint32_t x = m.start[b], p = model_parts(m, x);
         m.start[b] = run;
         run += x;
+        for (uint32_t i = 0; i < p; ++i) m.share[at++] = b | (i << 15);
     }
-    if (threadIdx.x == 1023u) m.start[m.bins] = run; // (threads without bins carry the total on)
+    if (threadIdx.x == 1023u) { // (threads without bins carry the totals on)
+        m.start[m.bins] = run;
+        for (; at < m.parts; ++at) m.share[at] = kModelNoShare;
+    }
 }
 
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
@@ -2014,12 +2033,19 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
     }
 }
 
-// a workgroup per bin
+// A workgroup per bin, or per part of a bin that holds more than twice its share of the edges (hubs, ids in the order of their
+// popularity): the parts' sums meet in `ell`, which is zero before.  One workgroup went through such a bin at an entry per clock: three
+// hops at 2.4 M vertices and 115 M edges 64.4 ms with ids in the order of a power law's ranks, 147 ms with half of the edges into
+// one vertex; in parts 3.1 and 4.1 ms (3.0 with even bins).  Parts of one share cut every bin in two, and with them all sums go through
+// atomics (2.4 M more per hop); fewer than 256 bins are cut as if they were 256.
 __global__ __launch_bounds__(kModelAddBlock) void k_model_add(ModelBins m, unsigned long long *ell)
 {
     extern __shared__ unsigned long long s_ell[];
     typedef unsigned long long v2u __attribute__((ext_vector_type(2), aligned(8)));
-    const uint32_t size = 1u << m.log2, mask = size - 1u, e0 = m.start[blockIdx.x], e1 = m.start[blockIdx.x + 1];
+    const uint32_t share = m.share[blockIdx.x];
+    if (share == kModelNoShare) return;
+    const uint32_t bin = share & (kModelMaxBins - 1u), size = 1u << m.log2, mask = size - 1u;
+    const uint32_t b0 = m.start[bin], b1 = m.start[bin + 1u], e0 = b0 + (share >> 15) * m.part, e1 = b1 - e0 < m.part ? b1 : e0 + m.part;
     for (uint32_t i = threadIdx.x; i < size; i += (uint32_t)kModelAddBlock) s_ell[i] = 0ull;
     __syncthreads();
     const uint32_t pairs = (e1 - e0) / 2u;
@@ -2034,8 +2060,15 @@ __global__ __launch_bounds__(kModelAddBlock) void k_model_add(ModelBins m, unsig
         atomicAdd(&s_ell[(uint32_t)x & mask], x >> m.log2);
     }
     __syncthreads();
-    const int64_t v0 = (int64_t)blockIdx.x << m.log2;
-    for (uint32_t i = threadIdx.x; i < size && v0 + i < m.num_nodes; i += (uint32_t)kModelAddBlock) ell[v0 + i] = s_ell[i];
+    const int64_t v0 = (int64_t)bin << m.log2;
+    const bool alone = b1 - b0 <= m.part;
+    for (uint32_t i = threadIdx.x; i < size && v0 + i < m.num_nodes; i += (uint32_t)kModelAddBlock) {
+        const unsigned long long x = s_ell[i];
+        if (alone)
+            ell[v0 + i] = x;
+        else if (x)
+            atomicAdd(&ell[v0 + i], x);
+    }
 }
 
 // q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v).  Vertices kModelStride apart are added in
@@ -2124,6 +2157,8 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
     m.entry = reinterpret_cast<unsigned long long *>(place((size_t)E * 8));
     m.place = reinterpret_cast<uint32_t *>(place((size_t)(bins * chunks) * 4));
     m.start = reinterpret_cast<uint32_t *>(place((size_t)(bins + 1) * 4));
+    const int64_t part = std::max<int64_t>(kModelMinPart, 2 * E / std::max<int64_t>(bins, 256)), parts = bins + E / part;
+    m.share = reinterpret_cast<uint32_t *>(place((size_t)parts * 4));
     if (used > temp_bytes) return m;
     m.idx = g->d_indices;
     m.num_edges = E;
@@ -2131,6 +2166,8 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
     m.log2 = log2;
     m.chunk = (uint32_t)chunk;
     m.chunks = (uint32_t)chunks;
+    m.part = (uint32_t)part;
+    m.parts = (uint32_t)parts;
     m.bins = (uint32_t)bins;
     return m;
 }
@@ -2157,7 +2194,7 @@ void enqueue_model_hop(const zg_graph_t *g, const ModelBins &m, float *q, unsign
             hipLaunchKernelGGL(k_model_bin<int64_t>, grid, block, lds, st, m, (const int64_t *)g->d_offsets, q, fanout, replace);
         else
             hipLaunchKernelGGL(k_model_bin<int32_t>, grid, block, lds, st, m, (const int32_t *)g->d_offsets, q, fanout, replace);
-        hipLaunchKernelGGL(k_model_add, dim3(m.bins), dim3(kModelAddBlock), (size_t)8 << m.log2, st, m, ell);
+        hipLaunchKernelGGL(k_model_add, dim3(m.parts), dim3(kModelAddBlock), (size_t)8 << m.log2, st, m, ell);
     } else {
         const dim3 grid((unsigned)std::min<int64_t>(1 << 16, (n + (kBlock / 64) - 1) / (kBlock / 64)));
         if (wide)

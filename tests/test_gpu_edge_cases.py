@@ -420,6 +420,25 @@ def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, repla
     assert binned == (list(mean[:3]), list(sigma[:3]))
 
 
+def test_size_model_bins_in_parts():
+    # 2^18 edges: parts of 16384.  Bins of 256 vertices that hold a whole part, an entry more, two parts, an entry more, nothing and the
+    # rest; the last one is ragged
+    nodes, edges = 5 * 256 + 44, 1 << 18
+    held = [16384, 16385, 32768, 32769, 0]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    parts = [torch.randint(256 * b, 256 * b + 256, (k,), generator=gen, device="cuda") for b, k in enumerate(held)]
+    parts.append(torch.randint(256 * 5, nodes, (edges - sum(held),), generator=gen, device="cuda"))
+    idx = torch.cat(parts)[torch.randperm(edges, generator=gen, device="cuda")].int()
+    offsets = torch.linspace(0, edges, nodes + 1, dtype=torch.float64, device="cuda").long()
+    dg = zg.Graph(offsets, idx)
+    fan, batch = (9, 4), 100
+    f, mean, sigma = (C.c_int32 * 2)(*fan), (C.c_double * 9)(), (C.c_double * 9)()
+    temp = torch.empty(12 * nodes + 576 + 256, dtype=torch.uint8, device="cuda")
+    base = (temp.data_ptr() + 255) // 256 * 256
+    assert zg.lib().zg_envelope_model_graph(dg._h, f, 2, batch, 0, None, base, 12 * nodes + 576, None, mean, sigma) == zg.OK
+    assert zg.graph_model(dg, fan, batch) == (list(mean[:3]), list(sigma[:3]))
+
+
 @pytest.mark.parametrize("nodes,draws,batch,fanouts,max_tickets", [
     (20_000, 500_000, 256, (6, 5, 4), 0),        # bytes, tiles of at most a word per lane
     (3_000_000, 12_000_000, 256, (8, 5, 3), 0),  # bits, a few hundred words per tile
