@@ -211,12 +211,12 @@ int zg_envelope_model(const int64_t *degrees, const int64_t *counts, int64_t n_d
  * `stream` (plan time, once).  d_seed_prob: per-vertex probability of being a seed, fp32 [num_nodes] in device
  * memory, or NULL for uniform seeds (batch / num_nodes).  d_temp: caller's device scratch, 256-byte aligned, at
  * least 12 * num_nodes + 576 bytes; contents undefined afterwards.  With 9 * num_edges + 2^20 bytes more, and from
- * ZG_MODEL_BIN_EDGES edges on, a sweep writes every edge's term to a bin of its neighbor instead of adding it with an
- * atomic, several times faster.  The result is deterministic (integer sums) and the same either way.
+ * ZG_MODEL_BIN_EDGES edges on, a sweep in which most edges have a term writes each to a bin of its neighbor instead of adding it
+ * with an atomic, several times faster.  The result is deterministic (integer sums) and the same either way.
  * Turn it into caps with ZG_ENV_GRAPH: copy mean / sigma into zg_envelope.model_mean / model_sigma; the planner
  * applies the cap formula of section 4.3 / Lemma 1 (margin and z) to them.
  * Errors: ZG_EINVAL (arguments, buffer), ZG_ESTATE (statistics-only handle, other device), ZG_EHIP. */
-#define ZG_MODEL_BIN_EDGES (1 << 18)
+#define ZG_MODEL_BIN_EDGES (1 << 19)
 int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t num_hops, int32_t batch,
                             int32_t with_replacement, const float *d_seed_prob, void *d_temp, size_t temp_bytes,
                             void *stream, double *mean, double *sigma);

@@ -1781,15 +1781,61 @@ constexpr int kModelAddBlock = 512;
 constexpr uint32_t kModelMaxBins = 32768;                // a counter each in LDS
 constexpr uint32_t kModelNoShare = 0xFFFFFFFFu;
 constexpr int64_t kModelMinPart = 16384;
+constexpr int kModelBlock = 1024, kModelGrid = 512; // the sweeps over the vertices
+constexpr int64_t kModelPushWaves = 16384;          // twice what the chip holds at once
+constexpr int64_t kModelRowWork = 2;                // a row of a sweep by atomics, in edges
 
-__global__ void k_model_init(float *q, unsigned long long *ell, const float *seed_prob, float uniform, int64_t n)
+// What a sweep by atomics has to do for a vertex that may be in D_h, in edges: the graph's offsets, where that is summed up
+struct ModelRows {
+    const void *off;
+    int32_t wide;
+    __device__ __forceinline__ unsigned long long work(int64_t v) const
+    {
+        const int64_t deg = wide ? ((const int64_t *)off)[v + 1] - ((const int64_t *)off)[v] : (int64_t)(((const int32_t *)off)[v + 1] - ((const int32_t *)off)[v]);
+        return deg > 0 ? (unsigned long long)(deg + kModelRowWork) : 0ull;
+    }
+};
+
+// ... and what depends on the sum: a kernel of the first hop that may not be meant to run (see zg_envelope_model_graph)
+struct ModelGate {
+    const unsigned long long *work; // null: always
+    unsigned long long below;
+    __device__ __forceinline__ bool closed() const { return work != nullptr && *work >= below; }
+};
+
+// the workgroup's sums of x[0 .. N-1] into out[0 .. N-1] (all lanes; one instruction: atomics queue up at 13 ns)
+template <int NT, int N>
+__device__ __forceinline__ void add_sums(unsigned long long *out, unsigned long long (&x)[N])
 {
+    __shared__ unsigned long long s_sum[N][NT / 64];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] += __shfl_xor(x[i], d, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int i = 0; i < N; ++i) s_sum[i][threadIdx.x >> 6] = x[i];
+    __syncthreads();
+    if (threadIdx.x < N) {
+        unsigned long long sum = 0ull;
+        for (int w = 0; w < NT / 64; ++w) sum += s_sum[threadIdx.x][w];
+        atomicAdd(&out[threadIdx.x], sum);
+    }
+}
+
+template <bool COUNT>
+__global__ __launch_bounds__(COUNT ? kModelBlock : kBlock) void k_model_init(float *q, unsigned long long *ell, const float *seed_prob, float uniform, int64_t n,
+                                                                             ModelRows rows, unsigned long long *work)
+{
+    unsigned long long sum[1] = {0ull};
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         float p = seed_prob ? seed_prob[v] : uniform;
         p = p < 0.0f ? 0.0f : (p > 1.0f ? 1.0f : p);
         q[v] = p;
         ell[v] = 0ull;
+        if (COUNT && p > 0.0f) sum[0] += rows.work(v);
     }
+    if (COUNT) add_sums<kModelBlock>(work, sum);
 }
 
 // -log(1 - q_u r_u) in fixed point: what a vertex u of `deg` neighbors adds to each of them (at most 9e10: 37 bits)
@@ -1806,20 +1852,45 @@ __device__ __forceinline__ unsigned long long model_term(float qu, int64_t deg, 
     return (unsigned long long)(-log1p(-x) * kFix);
 }
 
-// The sweep with nothing but the two arrays over the vertices: one wave per source vertex, one 64-bit atomic per edge.  Bound by
-// those: 16 G/s here, whatever their scope - the L2s pass every atomic on to memory (7 ms per hop at 120 M edges).
+// The sweep with nothing but the two arrays over the vertices: one 64-bit atomic per edge that has a term, a wave per source
+// vertex.  Bound by the atomics: 16 G/s here, whatever their scope - the L2s pass every one on to memory (7 ms per hop at 120 M edges).
+// Where few vertices can be in D_h the rest have to be passed by quickly: a wave looks at `rows` vertices at a time, a lane each (a power of
+// two; as many as leave enough waves).  One vertex at a time took 75 ps each: 2.4 M vertices and 115 M edges, 1 % of the vertices as
+// seeds, 213 -> 106 us for the call.  (Where that is one vertex, the plain loop: 15.5 instead of 16.8 us at 30 k vertices and 2^18 edges.)
 template <typename OffT>
 __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const int32_t *idx, const float *q, unsigned long long *ell,
-                                                       int64_t n, int32_t fanout, int32_t replace)
+                                                       int64_t n, int32_t fanout, int32_t replace, int32_t rows, ModelGate gate)
 {
+    if (gate.closed()) return;
     const int lane = threadIdx.x & 63;
     const int64_t wave0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
     const int64_t waves = ((int64_t)gridDim.x * kBlock) >> 6;
-    for (int64_t u = wave0; u < n; u += waves) {
+    for (int64_t u = wave0; rows == 1 && u < n; u += waves) {
         const int64_t b = (int64_t)off[u], e = (int64_t)off[u + 1];
         const unsigned long long c = model_term(q[u], e - b, fanout, replace);
         if (c == 0ull) continue;
         for (int64_t p = b + lane; p < e; p += 64) atomicAdd(&ell[idx[p]], c);
+    }
+    if (rows == 1) return;
+    for (int64_t u0 = wave0 * rows; u0 < n; u0 += waves * rows) {
+        const int64_t u = u0 + lane;
+        float qu = 0.0f;
+        int64_t b = 0, e = 0;
+        if (lane < rows && u < n) {
+            qu = q[u];
+            if (rows < 64 || qu > 0.0f) { // (a small graph's offsets are not worth waiting for q)
+                b = (int64_t)off[u];
+                e = (int64_t)off[u + 1];
+            }
+        }
+        const unsigned long long c = model_term(qu, e - b, fanout, replace);
+        for (unsigned long long some = __ballot(c != 0ull); some; some &= some - 1ull) {
+            const uint32_t l = (uint32_t)__ffsll((long long)some) - 1u;
+            auto of = [&](unsigned long long x) { return (unsigned long long)lane_value((uint32_t)(x >> 32), l) << 32 | lane_value((uint32_t)x, l); };
+            const int64_t first = (int64_t)of((unsigned long long)b), end = (int64_t)of((unsigned long long)e);
+            const unsigned long long term = of(c);
+            for (int64_t p = first + lane; p < end; p += 64) atomicAdd(&ell[idx[p]], term);
+        }
     }
 }
 
@@ -1898,7 +1969,7 @@ __global__ __launch_bounds__(1024) void k_model_places(ModelBins m)
     if (wave == 15u) m.start[b] = run;
 }
 
-__device__ __forceinline__ uint32_t model_parts(const ModelBins &m, uint32_t entries) { return entries ? (entries - 1u) / m.part + 1u : 1u; }
+__device__ __forceinline__ uint32_t model_parts(const ModelBins &m, uint32_t entries) { return entries > m.part ? (entries - 1u) / m.part + 1u : 1u; }
 
 // one workgroup: the bins' totals into their starts, and the bins into parts of at most m.part entries
 __global__ __launch_bounds__(1024) void k_model_starts(ModelBins m)
@@ -1917,21 +1988,20 @@ __global__ __launch_bounds__(1024) void k_model_starts(ModelBins m)
         s_sum[1][wave] = incl_parts;
     }
     __syncthreads();
-    uint32_t run = incl - sum, at = incl_parts - parts;
-    for (uint32_t w = 0; w < wave; ++w) {
-        run += s_sum[0][w];
-        at += s_sum[1][w];
+    uint32_t run = incl - sum, at = incl_parts - parts, end = 0;
+    for (uint32_t w = 0; w < 16u; ++w) {
+        if (w < wave) run += s_sum[0][w];
+        if (w < wave) at += s_sum[1][w];
+        end += s_sum[1][w];
     }
+    for (uint32_t i = end + threadIdx.x; i < m.parts; i += 1024u) m.share[i] = kModelNoShare;
     for (uint32_t b = b0; b < b1; ++b) {
         const uint32_t x = m.start[b], p = model_parts(m, x);
         m.start[b] = run;
         run += x;
         for (uint32_t i = 0; i < p; ++i) m.share[at++] = b | (i << 15);
     }
-    if (threadIdx.x == 1023u) { // (threads without bins carry the totals on)
-        m.start[m.bins] = run;
-        for (; at < m.parts; ++at) m.share[at] = kModelNoShare;
-    }
+    if (threadIdx.x == 1023u) m.start[m.bins] = run; // (threads without bins carry the total on)
 }
 
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
@@ -2071,15 +2141,16 @@ __global__ __launch_bounds__(kModelAddBlock) void k_model_add(ModelBins m, unsig
     }
 }
 
-// q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v).  Vertices kModelStride apart are added in
+// q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v); with COUNT, sums[2] += the next sweep's work.  Vertices kModelStride apart are added in
 // double, everything else as integers, so the sums do not depend on the launch.  One pair of atomics per workgroup of at most
 // 512: a pair per wavefront queued up on the two words (2.4 M vertices: 905 us, now 16 us).
 constexpr int64_t kModelStride = (int64_t)65536 * kBlock;
-constexpr int kModelBlock = 1024, kModelGrid = 512;
-__global__ __launch_bounds__(kModelBlock) void k_model_update(float *q, unsigned long long *ell, int64_t n, unsigned long long *sums)
+template <bool COUNT>
+__global__ __launch_bounds__(kModelBlock) void k_model_update(float *q, unsigned long long *ell, int64_t n, unsigned long long *sums, ModelGate gate,
+                                                              ModelRows rows)
 {
-    __shared__ unsigned long long s_sum[2][kModelBlock / 64];
-    unsigned long long fa = 0ull, fb = 0ull;
+    if (gate.closed()) return;
+    unsigned long long sum[COUNT ? 3 : 2] = {};
     for (int64_t t = (int64_t)blockIdx.x * kModelBlock + threadIdx.x; t < n && t < kModelStride; t += (int64_t)gridDim.x * kModelBlock) {
         double a = 0.0, b = 0.0;
         for (int64_t v = t; v < n; v += kModelStride) {
@@ -2090,25 +2161,12 @@ __global__ __launch_bounds__(kModelBlock) void k_model_update(float *q, unsigned
             ell[v] = 0ull;
             a += q1;
             b += q1 * (1.0 - q1);
+            if (COUNT && q1 > 0.0) sum[COUNT ? 2 : 0] += rows.work(v);
         }
-        fa += (unsigned long long)(a * kFix);
-        fb += (unsigned long long)(b * kFix);
+        sum[0] += (unsigned long long)(a * kFix);
+        sum[1] += (unsigned long long)(b * kFix);
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        fa += __shfl_xor(fa, d, 64);
-        fb += __shfl_xor(fb, d, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        s_sum[0][threadIdx.x >> 6] = fa;
-        s_sum[1][threadIdx.x >> 6] = fb;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        unsigned long long x = 0ull;
-        for (int w = 0; w < kModelBlock / 64; ++w) x += s_sum[threadIdx.x][w];
-        atomicAdd(&sums[threadIdx.x], x);
-    }
+    add_sums<kModelBlock>(sums, sum);
 }
 
 // results of the size model left on the device: out[0..H] = mean, out[H+1..2H+1] = sigma (sums: per hop {sum q, sum q(1-q)} in 2^-32 units)
@@ -2135,7 +2193,7 @@ static __device__ __align__(256) unsigned char scratch[kStaticEllBytes + kStatic
 // bins, of up to 8192 vertices (64 KB of sums: two workgroups to a compute unit; bins of 4096 at 2.4 M vertices: k_model_bin 0.70 instead of
 // 0.58 ms, k_model_add 0.31 instead of 0.34; one bin per compute unit at 62 bins: k_model_add 0.77 ms instead of 0.24), beyond 16 M vertices
 // of 16384; a thousand chunks, of at most 65536 edges unless their counters would be more than a byte per edge.  Below
-// ZG_MODEL_BIN_EDGES edges the launches cost more than the atomics: 102 k edges 121 us with atomics, 152 binned; 290 k 169 / 153; 2 M 485 / 192.
+// ZG_MODEL_BIN_EDGES edges never (see model_bins_work).
 ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_bytes)
 {
     ModelBins m;
@@ -2172,38 +2230,78 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
     return m;
 }
 
+// Work of a sweep by atomics, in edges (46 ps each; a row with a term is two more), that takes as long as the same sweep by bins, with
+// `hops` sweeps to share the price of the places.  A sweep by bins takes 9 ps per edge, 12 us, and 4 us for every 512 vertices that a
+// workgroup passes by; the places take 24 us.  Atomics and bins in us, uniform seeds, 1 / 3 hops: 4 k vertices and 2^18 edges 44 / 123 and
+// 62 / 140; 30 k and 2^19 59 / 167 and 66 / 153; 30 k and 2^20 84 / 242 and 76 / 167; 1 M and 2^19 93 / 268 and 120 / 305; 1 M and 2^20 108 / 307
+// and 105 / 248; 8 M and 2^20 206 / 577 and 286 / 769; 8 M and 2^21 284 / 809 and 231 / 600.  2.4 M vertices and 115 M edges, one hop: 1.1 ms by
+// bins; by atomics 0.11, 0.55, 0.94, 1.3 ms with 1, 10, 18, 25 % of the vertices as seeds, 5.6 with all; three hops from 1 % 2.2 ms, not 3.0.
+int64_t model_bins_work(const ModelBins &m, int hops)
+{
+    return m.num_edges / 5 + (1 << 18) + (1 << 19) / hops + 160 * m.num_nodes / m.chunks;
+}
+
 // once per call: places for the edges' terms
 void enqueue_model_places(const ModelBins &m, hipStream_t st)
 {
-    if (!m.bins) return;
     hipLaunchKernelGGL(k_model_count, dim3(m.chunks), dim3(1024), (size_t)m.bins * 4, st, m);
     hipLaunchKernelGGL(k_model_places, dim3((m.bins + 63u) / 64u), dim3(1024), 0, st, m);
     hipLaunchKernelGGL(k_model_starts, dim3(1), dim3(1024), 0, st, m);
 }
 
-// one hop of the size model: the sweep over the edges and the update of the probabilities
-void enqueue_model_hop(const zg_graph_t *g, const ModelBins &m, float *q, unsigned long long *ell, unsigned long long *sums, int32_t fanout, int32_t replace,
-                       hipStream_t st)
+// the sweep over the vertices that starts the size model
+void enqueue_model_init(const zg_graph_t *g, float *q, unsigned long long *ell, const float *seed_prob, int32_t batch, const ModelRows &rows, unsigned long long *work,
+                        hipStream_t st)
+{
+    const int64_t n = g->num_nodes;
+    const float uniform = (float)((double)batch / (double)n);
+    if (rows.off)
+        hipLaunchKernelGGL(k_model_init<true>, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell,
+                           seed_prob, uniform, n, rows, work);
+    else
+        hipLaunchKernelGGL(k_model_init<false>, dim3((unsigned)std::min<int64_t>(1 << 16, (n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, q, ell, seed_prob, uniform,
+                           n, rows, work);
+}
+
+// one hop of it: the sweep over the edges and the update of the probabilities
+struct ModelHop {
+    float *q;
+    unsigned long long *ell, *sums;
+    int32_t fanout, replace;
+    bool binned;
+    ModelGate gate;
+    ModelRows rows; // `off` not null: sums[2] is the work of the next hop
+};
+
+void enqueue_model_hop(const zg_graph_t *g, const ModelBins &m, const ModelHop &a, hipStream_t st)
 {
     const int64_t n = g->num_nodes;
     const bool wide = g->offsets_dtype == ZG_I64;
-    if (m.bins) {
+    if (a.binned) {
         const dim3 grid(m.chunks), block(kModelBinBlock);
         const size_t lds = (size_t)m.bins * 4;
         if (wide)
-            hipLaunchKernelGGL(k_model_bin<int64_t>, grid, block, lds, st, m, (const int64_t *)g->d_offsets, q, fanout, replace);
+            hipLaunchKernelGGL(k_model_bin<int64_t>, grid, block, lds, st, m, (const int64_t *)g->d_offsets, a.q, a.fanout, a.replace);
         else
-            hipLaunchKernelGGL(k_model_bin<int32_t>, grid, block, lds, st, m, (const int32_t *)g->d_offsets, q, fanout, replace);
-        hipLaunchKernelGGL(k_model_add, dim3(m.parts), dim3(kModelAddBlock), (size_t)8 << m.log2, st, m, ell);
+            hipLaunchKernelGGL(k_model_bin<int32_t>, grid, block, lds, st, m, (const int32_t *)g->d_offsets, a.q, a.fanout, a.replace);
+        hipLaunchKernelGGL(k_model_add, dim3(m.parts), dim3(kModelAddBlock), (size_t)8 << m.log2, st, m, a.ell);
     } else {
-        const dim3 grid((unsigned)std::min<int64_t>(1 << 16, (n + (kBlock / 64) - 1) / (kBlock / 64)));
+        int32_t rows = 1;
+        while (rows < 64 && n / (2 * rows) >= kModelPushWaves) rows *= 2;
+        const int64_t waves = (n + rows - 1) / rows;
+        const dim3 grid((unsigned)std::min<int64_t>(1 << 16, (waves + (kBlock / 64) - 1) / (kBlock / 64)));
         if (wide)
-            hipLaunchKernelGGL(k_model_push<int64_t>, grid, dim3(kBlock), 0, st, (const int64_t *)g->d_offsets, g->d_indices, q, ell, n, fanout, replace);
+            hipLaunchKernelGGL(k_model_push<int64_t>, grid, dim3(kBlock), 0, st, (const int64_t *)g->d_offsets, g->d_indices, a.q, a.ell, n, a.fanout, a.replace,
+                               rows, a.gate);
         else
-            hipLaunchKernelGGL(k_model_push<int32_t>, grid, dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, q, ell, n, fanout, replace);
+            hipLaunchKernelGGL(k_model_push<int32_t>, grid, dim3(kBlock), 0, st, (const int32_t *)g->d_offsets, g->d_indices, a.q, a.ell, n, a.fanout, a.replace,
+                               rows, a.gate);
     }
-    hipLaunchKernelGGL(k_model_update, dim3((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock)), dim3(kModelBlock), 0, st, q, ell, n,
-                       sums);
+    const dim3 sweep((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock));
+    if (a.rows.off)
+        hipLaunchKernelGGL(k_model_update<true>, sweep, dim3(kModelBlock), 0, st, a.q, a.ell, n, a.sums, a.gate, a.rows);
+    else
+        hipLaunchKernelGGL(k_model_update<false>, sweep, dim3(kModelBlock), 0, st, a.q, a.ell, n, a.sums, a.gate, a.rows);
 }
 
 #define ZG_HIP(call)                                                                                         \
@@ -2979,23 +3077,60 @@ int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t
     float *q = reinterpret_cast<float *>(base + at);
     at += (size_t)n * 4;
     at = (at + kAlign - 1) / kAlign * kAlign;
-    unsigned long long *sums = reinterpret_cast<unsigned long long *>(base + at); // [2] per hop, reused
+    unsigned long long *sums = reinterpret_cast<unsigned long long *>(base + at); // q and q (1 - q) of a hop, the next one's work; the first one's
     const ModelBins bins = model_bins(g, d_temp, at + 64, temp_bytes);
-    enqueue_model_places(bins, st);
-    const int grid = (int)std::min<int64_t>(1 << 16, (n + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_model_init, dim3(grid), dim3(kBlock), 0, st, q, ell, d_seed_prob, (float)((double)batch / (double)n), n);
+    // Which hops go by bins: those where the atomics would take longer.  With seeds given, a hop's terms may come from few of the edges:
+    // the first hop's of a training set, all hops' of a handful of seeds.  A hop's work is counted by the update before it and known with
+    // that one's sums; a probability never falls, so once by bins, always.  The first hop's is known to the device alone: it is
+    // enqueued as if it was little, behind a gate; where it is not, nothing has happened but a look from the host.
+    const int64_t all = g->num_edges + kModelRowWork * std::min(n, g->num_edges);
+    auto by_bins = [&](int h, uint64_t work) { return bins.bins && work >= (uint64_t)model_bins_work(bins, num_hops - h); };
+    bool binned = by_bins(0, (uint64_t)all), placed = false;
+    ModelHop hop;
+    std::memset(&hop, 0, sizeof(hop));
+    hop.q = q;
+    hop.ell = ell;
+    hop.sums = sums;
+    hop.replace = with_replacement;
+    if (binned && d_seed_prob) {
+        hop.rows.off = g->d_offsets;
+        hop.rows.wide = g->offsets_dtype == ZG_I64;
+        hop.gate.work = &sums[3];
+        hop.gate.below = (uint64_t)model_bins_work(bins, num_hops);
+        binned = false;
+    }
+    auto clear_sums = [&]() { hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)8); };
+    if (binned) { // (the longest launches first: the host is ahead of the device from here on)
+        enqueue_model_places(bins, st);
+        placed = true;
+    }
+    clear_sums();
+    enqueue_model_init(g, q, ell, d_seed_prob, batch, hop.rows, &sums[3], st);
     ZG_HIP(hipGetLastError());
     mean[0] = (double)batch;
     sigma[0] = 0.0;
-    for (int h = 0; h < num_hops; ++h) {
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)4);
-        enqueue_model_hop(g, bins, q, ell, sums, fanouts[h], with_replacement, st);
+    for (int h = 0; h < num_hops;) {
+        if (binned && !placed) enqueue_model_places(bins, st);
+        placed = binned;
+        hop.fanout = fanouts[h];
+        hop.binned = binned;
+        if (binned || h + 1 == num_hops) hop.rows.off = nullptr;
+        enqueue_model_hop(g, bins, hop, st);
         ZG_HIP(hipGetLastError());
-        unsigned long long host[2] = {0, 0};
+        unsigned long long host[4] = {0, 0, 0, 0};
         ZG_HIP(hipMemcpyAsync(host, sums, sizeof(host), hipMemcpyDeviceToHost, st));
         ZG_HIP(hipStreamSynchronize(st));
+        const bool gated = hop.gate.work != nullptr;
+        hop.gate.work = nullptr;
+        if (gated && host[3] >= hop.gate.below) { // the gate was closed
+            binned = true;
+            continue;
+        }
         mean[h + 1] = (double)host[0] / kFix;
         sigma[h + 1] = std::sqrt((double)host[1] / kFix);
+        if (++h == num_hops) break;
+        binned = binned || (hop.rows.off && by_bins(h, host[2]));
+        clear_sums();
     }
     return ZG_OK;
 }
@@ -3044,14 +3179,20 @@ int zg_envelope_model_graph_static(const zg_graph_t *g, const int32_t *fanouts, 
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(base + kStaticEllBytes + kStaticQBytes);
     ModelBins bins; // (no room for any)
     std::memset(&bins, 0, sizeof(bins));
-    const int grid = (int)std::min<int64_t>(1 << 16, (n + kBlock - 1) / kBlock);
+    ModelHop hop;
+    std::memset(&hop, 0, sizeof(hop));
+    hop.q = q;
+    hop.ell = ell;
+    hop.replace = with_replacement;
     // the array keeps the last call's contents: the per-hop sums restart at zero here (a fill kernel, not a memset
     // node, so that the sequence may be captured), q and ell are overwritten for the first n vertices by the first kernel
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)(4 * ZG_MAX_HOPS));
-    hipLaunchKernelGGL(k_model_init, dim3(grid), dim3(kBlock), 0, st, q, ell, d_seed_prob, (float)((double)batch / (double)n), n);
+    enqueue_model_init(g, q, ell, d_seed_prob, batch, hop.rows, nullptr, st);
     ZG_HIP(hipGetLastError());
     for (int h = 0; h < num_hops; ++h) {
-        enqueue_model_hop(g, bins, q, ell, sums + 2 * h, fanouts[h], with_replacement, st);
+        hop.sums = sums + 2 * h;
+        hop.fanout = fanouts[h];
+        enqueue_model_hop(g, bins, hop, st);
         ZG_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_model_finish, dim3(1), dim3(64), 0, st, sums, num_hops, batch, d_mean_sigma);

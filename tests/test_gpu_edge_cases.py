@@ -387,15 +387,17 @@ def test_repeated_draws_in_groups_of_any_width(oracle, fanout, batch):
         plan, _, _ = run_and_compare(oracle, g, None, seeds, (fanout,), 60 + s, plan=plan, og=og)
 
 
-@pytest.mark.parametrize("nodes,edges,i64", [
-    (60_000, zg.MODEL_BIN_EDGES - 1, False),      # atomics either way
-    (60_000, zg.MODEL_BIN_EDGES, False),          # bins, the first time; the last window and the last bin are ragged
-    (256 * 512 + 1, 4096 * 300, True),            # a bin of one vertex, whole windows
-    (300_000, 3_000_001, False),
-    (8192 * 2048 + 5, 700_000, True),             # bins of 16384 vertices; thousands of empty rows in a window
+@pytest.mark.parametrize("nodes,edges,i64,by_bins", [
+    (60_000, zg.MODEL_BIN_EDGES - 1, False, False),
+    (60_000, zg.MODEL_BIN_EDGES, False, True),    # bins, the first time; the last window and the last bin are ragged
+    (4_000, zg.MODEL_BIN_EDGES, False, False),    # the places would take longer than the atomics
+    (256 * 512 + 1, 4096 * 300, True, True),      # a bin of one vertex, whole windows
+    (300_000, 3_000_001, False, True),
+    (8192 * 2048 + 5, 700_000, True, False),      # 190 k vertices to every workgroup of the sweep by bins
+    (8192 * 2048 + 5, 12_000_000, True, True),    # bins of 16384 vertices; thousands of empty rows in a window
 ])
 @pytest.mark.parametrize("replace", [False, True])
-def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, replace):
+def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, by_bins, replace):
     # one row that many windows long, stretches of empty rows longer than a window has threads, a popular neighbor; the sums are
     # integers, so the two sweeps agree to the last bit (the one with atomics is checked against its reference elsewhere)
     gen = torch.Generator(device="cuda").manual_seed(nodes)
@@ -411,19 +413,52 @@ def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, repla
     idx[::5] = 11
     idx[::7] = nodes - 1
     dg = zg.Graph(offsets if i64 else offsets.int(), idx)
-    fan, batch = (9, 4), 300
-    binned = zg.graph_model(dg, fan, batch, with_replacement=replace)
-    f, mean, sigma = (C.c_int32 * 2)(*fan), (C.c_double * 9)(), (C.c_double * 9)()
-    temp = torch.empty(12 * nodes + 576 + 256, dtype=torch.uint8, device="cuda")
-    base = (temp.data_ptr() + 255) // 256 * 256
-    assert zg.lib().zg_envelope_model_graph(dg._h, f, 2, batch, int(replace), None, base, 12 * nodes + 576, None, mean, sigma) == zg.OK
-    assert binned == (list(mean[:3]), list(sigma[:3]))
+    fan, batch = (9, 4, 3), 300
+    want, _ = _size_model(dg, fan, batch, edges, replace=replace, large=False)
+    got, used = _size_model(dg, fan, batch, edges, replace=replace, large=True)
+    assert got == want and used == by_bins
+    assert zg.graph_model(dg, fan, batch, with_replacement=replace) == (want[0][:4], want[1][:4])
+
+
+def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
+    """(mean, sigma) from a scratch buffer with or without room for bins, and whether anything was written behind the smaller one."""
+    small = 12 * dg.num_nodes + 576
+    nbytes = small + (9 * edges + (1 << 20) if large else 0)
+    temp = torch.full((nbytes + 512,), 0xAB, dtype=torch.uint8, device="cuda")
+    at = (-temp.data_ptr()) % 256
+    f, mean, sigma = (C.c_int32 * len(fan))(*fan), (C.c_double * 9)(), (C.c_double * 9)()
+    rc = zg.lib().zg_envelope_model_graph(dg._h, f, len(fan), batch, int(replace), prob.data_ptr() if prob is not None else None, temp.data_ptr() + at, nbytes,
+                                          None, mean, sigma)
+    assert rc == zg.OK and bool((temp[:at] == 0xAB).all()) and bool((temp[at + nbytes:] == 0xAB).all())
+    return (list(mean), list(sigma)), large and bool((temp[at + small: at + nbytes] != 0xAB).any())
+
+
+@pytest.mark.parametrize("share,hops,binned", [
+    (0.01, 1, False),   # a hundredth of the edges have a term
+    (0.01, 3, True),    # ... and about a tenth of them in the second hop, most in the third: that one goes by bins
+    (0.51, 1, False),   # on either side of the line (0.521: work of a row 2 + 10, of all 2.4 M; by bins 1.252 M)
+    (0.53, 1, True),
+    (1.0, 2, True),
+    (0.0, 2, False),
+])
+@pytest.mark.parametrize("replace", [False, True])
+def test_size_model_sweeps_few_edges_with_atomics(share, hops, binned, replace):
+    nodes, edges = 200_000, 2_000_000
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    offsets = torch.arange(0, edges + 1, 10, device="cuda").int()
+    idx = torch.randint(0, nodes, (edges,), generator=gen, device="cuda", dtype=torch.int32)
+    dg = zg.Graph(offsets, idx)
+    prob = torch.zeros(nodes, device="cuda")
+    prob[torch.randperm(nodes, generator=gen, device="cuda")[: int(share * nodes)]] = 0.25
+    want, _ = _size_model(dg, (9, 6, 4)[:hops], 300, edges, replace=replace, prob=prob, large=False)
+    got, used = _size_model(dg, (9, 6, 4)[:hops], 300, edges, replace=replace, prob=prob, large=True)
+    assert got == want and used == binned
 
 
 def test_size_model_bins_in_parts():
-    # 2^18 edges: parts of 16384.  Bins of 256 vertices that hold a whole part, an entry more, two parts, an entry more, nothing and the
+    # 2^20 edges: parts of 16384.  Bins of 256 vertices that hold a whole part, an entry more, two parts, an entry more, nothing and the
     # rest; the last one is ragged
-    nodes, edges = 5 * 256 + 44, 1 << 18
+    nodes, edges = 5 * 256 + 44, 1 << 20
     held = [16384, 16385, 32768, 32769, 0]
     gen = torch.Generator(device="cuda").manual_seed(5)
     parts = [torch.randint(256 * b, 256 * b + 256, (k,), generator=gen, device="cuda") for b, k in enumerate(held)]
@@ -432,11 +467,9 @@ def test_size_model_bins_in_parts():
     offsets = torch.linspace(0, edges, nodes + 1, dtype=torch.float64, device="cuda").long()
     dg = zg.Graph(offsets, idx)
     fan, batch = (9, 4), 100
-    f, mean, sigma = (C.c_int32 * 2)(*fan), (C.c_double * 9)(), (C.c_double * 9)()
-    temp = torch.empty(12 * nodes + 576 + 256, dtype=torch.uint8, device="cuda")
-    base = (temp.data_ptr() + 255) // 256 * 256
-    assert zg.lib().zg_envelope_model_graph(dg._h, f, 2, batch, 0, None, base, 12 * nodes + 576, None, mean, sigma) == zg.OK
-    assert zg.graph_model(dg, fan, batch) == (list(mean[:3]), list(sigma[:3]))
+    want, _ = _size_model(dg, fan, batch, edges, large=False)
+    got, used = _size_model(dg, fan, batch, edges, large=True)
+    assert got == want and used
 
 
 @pytest.mark.parametrize("nodes,draws,batch,fanouts,max_tickets", [
