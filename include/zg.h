@@ -152,7 +152,8 @@ typedef struct {
     int64_t ldx;
     const float *d_agg; /* [node_cap[H-1], ld_agg] mean of block H-1 over X */
     int64_t ld_agg;
-    const uint32_t *d_log; /* ring of ZG_LOG_STRIDE-word records, one per step: epoch, flags, n[0..H], E[0..H-1], n_exact[1..H] */
+    const uint32_t *d_log; /* ring of ZG_LOG_STRIDE-word records, one per step: epoch, flags, n[0..H], E[0..H-1],
+                            n_exact[1..H]; in the last word how many workgroups drew their share of a launch from its counter */
     int32_t log_capacity;  /* records in the ring; record of step e sits at (e % log_capacity) */
     const uint32_t *d_epoch; /* number of steps run on this plan */
     int64_t x_row_cap;       /* rows of d_X: node_cap[H], or node_cap[H-1] with ZG_PLAN_FUSED_INPUT (rows i < n_{H-1} are valid) */

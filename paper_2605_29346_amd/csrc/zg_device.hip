@@ -741,9 +741,13 @@ __device__ __forceinline__ uint32_t lowest_set_bits(uint32_t x, uint32_t q)
 // last of 240 workgroups has its ticket 5.7 us into the launch, the last of 470 after 9.4 (large launches with one plan 20.3 -> 16.5 us, 53.7 -> 46,
 // launch 0 12.4 -> 8.1 with 128 of them).  It pays where the chip is shared: a workgroup that starts late, because another stream's kernels
 // hold its place, gets a late ticket, while a late index keeps all those behind it waiting in places that others could use (110 M
-// vertices, four plans: 217 us per step drawn, 235 by index; 2.4 M vertices 74 / 78; one plan 251-270 / 250-260 and 102 / 95).  So: launch 0 never; tiles
-// that are ranked by pieces of 128 vertices (of more than a word per lane: long launches) always; else where the plan has company - its
-// graph had another plan when it was made.
+// vertices, four plans: 217 us per step drawn, 235 by index; one plan 251-270 / 250-260).  With smaller graphs it pays little or nothing even
+// there.  us per step drawn / by index: 2.4 M vertices and 115 M edges, three hops, one plan 102.6 / 94.9, two on two streams 80.9 /
+// 78.3, four 85.6 / 84.0, beside a matrix product on another stream 219 / 213, beside a copy 226 / 221; sampling alone 120.7 / 112.7, 98.0 /
+// 95.7, 103.1 / 100.5, 227 / 219, 209 / 205; 1 M vertices and hubs 100.1 / 96.4, 91.4 / 89.5, 92.3 / 91.1; the benchmark's smaller workloads, four
+// plans: 52.3 / 52.6 (large_sparse), 68.4 / 68.9 (medium_dense), 62.6 / 64.3 (envelope_stress), and 87.9 / 83.8, 95.1 / 93.5, 87.2 / 83.6 with one.  So tiles
+// that are ranked by pieces of 128 vertices (of more than a word per lane: long launches, with nobody who could work out a missing
+// total) draw, and no other launch does.
 //
 // Bound by latency: a ticket is a chain of about eight dependent memory accesses, so a launch costs the length of that chain,
 // the code it walks through cold and its slowest ticket.  Hence one instantiation per kind of launch and of marks (one
@@ -1563,6 +1567,8 @@ __device__ __forceinline__ void finish_block(const FinishArgs &a, uint32_t block
     for (uint64_t w = i; w < a.status_words; w += (uint64_t)a.blocks * kBlock) a.status[w] = 0ull;
     if (i == 0) {
         Drmb *d = a.drmb;
+        uint32_t drawn = 0u;
+        for (int l = 0; l <= a.num_hops; ++l) drawn += d->ticket[l];
         for (int l = 0; l <= a.num_hops; ++l) d->ticket[l] = 0u;
         const uint32_t epoch = d->epoch;
         uint32_t *rec = a.log + (size_t)(epoch % kLogCapacity) * ZG_LOG_STRIDE;
@@ -1572,6 +1578,7 @@ __device__ __forceinline__ void finish_block(const FinishArgs &a, uint32_t block
         for (int h = 0; h <= a.num_hops; ++h) rec[p++] = d->n[h];
         for (int h = 0; h < a.num_hops; ++h) rec[p++] = d->E[h];
         for (int h = 1; h <= a.num_hops; ++h) rec[p++] = d->n_exact[h];
+        rec[ZG_LOG_STRIDE - 1] = drawn;
         d->epoch = epoch + 1;
         const uint32_t step_flags = d->step_flags;
         d->last_flags = step_flags;
@@ -2353,8 +2360,6 @@ struct zg_plan_s {
     uint32_t issued = 0;            // steps enqueued so far (mod 2^32, like the device-side step counter)
     hipStream_t last_stream = nullptr; // stream of the last enqueued step (what zg_plan_destroy waits for)
     bool stepped = false;
-    bool in_company = false;        // there were other plans on the graph when this one was made: they are meant to run side by side
-    std::shared_ptr<std::atomic<int>> company; // ... and the count of them that this one is part of
     zg_plan_s *twin = nullptr;      // worst-case twin (ZG_PLAN_SAFE_TWIN): own outputs, metadata and mailbox, shared scratch
     hipStream_t capture_stream = nullptr;
     hipGraph_t graph_obj = nullptr;
@@ -2691,7 +2696,7 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         ha.batch = (uint32_t)p->batch;
         // Tickets: see k_hop.  A tile ranked by pieces changes its marks before its totals are out: nobody else can work them out.
         const bool by_pieces = l > 0 && L.tile_words[l] > (l < H ? kHopBlock : kCloseBlock);
-        ha.draw = l > 0 && (by_pieces || p->in_company);
+        ha.draw = by_pieces;
         ha.patience = by_pieces ? kSpinLimit : (p->flags & ZG_PLAN_IMPATIENT) ? 0u : kPatience;
         ha.blocks = (uint32_t)(L.old_tickets[l] + L.rank_tiles[l]);
         // the edges of hop l-2 can be relabeled now: launch l-1 ranked the last vertices they point to
@@ -2802,7 +2807,7 @@ int build_graph(zg_plan_t *p)
 extern "C" {
 
 static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &L, uint32_t flags, int32_t batch,
-                            char *ws, hipStream_t st, bool init_scratch, bool in_company)
+                            char *ws, hipStream_t st, bool init_scratch)
 {
     zg_plan_t *p = new (std::nothrow) zg_plan_t();
     if (!p) return fail(ZG_ENOMEM, "out of host memory");
@@ -2811,7 +2816,6 @@ static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &
     p->ws = ws;
     p->flags = flags;
     p->batch = batch;
-    p->in_company = in_company;
     auto bail = [&](int code) {
         zg_plan_destroy(p);
         return code;
@@ -2863,13 +2867,10 @@ int zg_plan(zg_plan_t **out, const zg_graph_t *g, const int32_t *fanouts, int32_
     zg_plan_t *p = nullptr;
     // with a twin both lay their scratch out in the same region, sized for the larger of the two.  The id maps coincide; everything
     // behind them has to be zero between steps, whichever layout reads it: each of the two clears the regions of its own.
-    const bool in_company = g->plans->load(std::memory_order_relaxed) > 0;
-    rc = make_plan_object(&p, g, L, env->flags, batch, ws, st, true, in_company);
+    rc = make_plan_object(&p, g, L, env->flags, batch, ws, st, true);
     if (rc != ZG_OK) return rc;
-    p->company = g->plans;
-    p->company->fetch_add(1, std::memory_order_relaxed);
     if (with_twin) {
-        rc = make_plan_object(&p->twin, g, Ls, env->flags & ~(ZG_PLAN_SAFE_TWIN | ZG_PLAN_AUTO_FALLBACK), batch, ws, st, true, in_company);
+        rc = make_plan_object(&p->twin, g, Ls, env->flags & ~(ZG_PLAN_SAFE_TWIN | ZG_PLAN_AUTO_FALLBACK), batch, ws, st, true);
         if (rc == ZG_OK && (env->flags & ZG_PLAN_AUTO_FALLBACK)) rc = build_graph(p); // again, now with the twin's kernels behind
         if (rc != ZG_OK) {
             zg_plan_destroy(p);
@@ -2911,7 +2912,6 @@ int zg_plan_destroy(zg_plan_t *p)
     drop_graph(p);
     if (p->capture_stream) (void)hipStreamDestroy(p->capture_stream);
     if (p->mailbox) (void)hipHostFree(p->mailbox);
-    if (p->company) p->company->fetch_sub(1, std::memory_order_relaxed);
     delete p;
     return ZG_OK;
 }

@@ -3,9 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cstdint>
-#include <memory>
 #include <string>
 #include <vector>
 
@@ -134,6 +132,4 @@ struct zg_graph_s {
     bool stats_only = false;
     int device = -1;
     std::vector<int64_t> degrees, counts; // distinct degree values (ascending) and how many vertices have each
-    // plans made from the handle and not destroyed yet (shared with them: nothing but this outlives the handle)
-    std::shared_ptr<std::atomic<int>> plans = std::make_shared<std::atomic<int>>(0);
 };

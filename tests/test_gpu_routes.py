@@ -280,3 +280,21 @@ def test_ragged_and_shifted_rows_through_the_closing_launchs_copy(oracle, dim, s
         assert np.array_equal(res.X, X_ref[: res.X.shape[0]])
         assert agg_error(oracle, res.agg, agg_ref, ref.row_ptr[-1], ref.col[-1], X_ref) <= 1e-5
         assert bool((plan.workspace[last: last + 256] == 0xA5).all())
+
+
+@pytest.mark.parametrize("nodes,draws,max_tickets,draw", [(70_000, 1_400_000, 0, False), (3_000_000, 12_000_000, 20, True)])
+@pytest.mark.parametrize("flags", [0, zg.PLAN_EAGER, zg.PLAN_AUTO_FALLBACK])
+def test_the_kind_of_the_tickets_does_not_depend_on_other_plans(oracle, nodes, draws, max_tickets, draw, flags):
+    # drawn where a tile is longer than a word per lane, whichever plan was made first and on whatever handle
+    g = W.rmat_graph(nodes, draws, 8)
+    og = to_host_graph(oracle, g)
+    off, idx = g.offsets.cuda(), g.indices.cuda()
+    fanouts, batch = (7, 5), 2000
+    pool = W.SeedPool(g, batch, 3)
+    graphs = [zg.Graph(off, idx), zg.Graph(off, idx)]
+    plans = [zg.Plan(graphs[k], fanouts, batch, zg.make_envelope(zg.ENV_MAX, flags=flags, max_tickets=max_tickets)) for k in (0, 0, 1)]
+    assert not samples_in_one_workgroup(plans[0])
+    for s in range(3):
+        for plan in plans[1:]:  # (the first one does nothing)
+            run_and_compare(oracle, g, None, pool.batch_for(s).numpy(), fanouts, 90 + s, plan=plan, og=og)
+            assert (int(plan.view_log()[s][zg.LOG_STRIDE - 1]) > 0) == draw
