@@ -88,7 +88,9 @@ __device__ __forceinline__ uint64_t st_load(uint64_t *p)
 // the order in which workgroups start: all of them are, and the lowest unfinished one never waits.  The workgroup's index: kernels of
 // other streams may hold the compute units it needs, and wait in turn for workgroups that this kernel keeps out.  So a wait ends after `patience` polls:
 // `missing(t)` then works out ticket t's total from what the launch found - which t changes only after its totals are published
-// (publish_done), so that what was read stands if they still are not.  No wait depends on another workgroup's progress, and no wait changes
+// (publish_done), so that what was read stands if they still are not.  It does so for the nearest ticket, then looks at all of them again,
+// and asks for none beyond the nearest prefix.  (All that were missing at the first look, one after another: steps with no patience
+// at all took 454 us where patient ones take 113, now 120; 370 where 96, now 102.)  No wait depends on another workgroup's progress, and no wait changes
 // the result.  Where the marks are changed before the totals are published, and tickets always drawn, the wait is bounded all the same
 // (kSpinLimit): when it runs out the step is flagged invalid (sticky and per-step word) and what is there is used.
 // Values are taken modulo 2^32: more than that is only reached beyond a cap, by dropped rows.
@@ -110,9 +112,13 @@ __device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, u
         // the 64 status words base, base-1, .. base-63 (indices below zero count as an inclusive prefix of zero)
         const int64_t idx = base - lane;
         uint64_t st;
+        uint32_t worked_out = 0;             // this lane's ticket's total, ...
+        unsigned long long known = 0ull, pm; // ... where it had to be; the lanes whose ticket's prefix is there
         for (;;) {
             st = idx >= 0 ? st_load(&status[idx]) : kStPrefix;
-            unsigned long long none = __ballot((st >> 62) == 0);
+            if ((st >> 62) == 0 && ((known >> lane) & 1ull)) st = kStAggregate | worked_out;
+            pm = __ballot((st >> 62) == 2);
+            const unsigned long long none = __ballot((st >> 62) == 0) & (pm ? (pm & (0ull - pm)) - 1ull : ~0ull); // (none beyond the nearest prefix)
             if (!none) break;
             if (++polls > patience) {
                 if (patience == kSpinLimit) { // drawn tickets: the step's outputs are invalid, both the sticky and the per-step word say so
@@ -122,20 +128,16 @@ __device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, u
                     }
                     break;
                 }
-                for (; none; none &= none - 1ull) {
-                    const int l = __ffsll((long long)none) - 1;
-                    const uint32_t v = missing((uint32_t)(base - l));
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // read before the second look
-                    if (lane == l) {
-                        st = st_load(&status[idx]);
-                        if ((st >> 62) == 0) st = kStAggregate | v;
-                    }
-                }
-                break;
+                // the nearest one; then another look at all of them: the others, or a prefix, may be there by now
+                const int l = __ffsll((long long)none) - 1;
+                const uint32_t v = missing((uint32_t)(base - l));
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // read before that look
+                if (lane == l) worked_out = v;
+                known |= 1ull << l;
+                continue;
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        const unsigned long long pm = __ballot((st >> 62) == 2);
         const int last = pm ? __ffsll((long long)pm) - 1 : 63;
         excl += wave_sum(lane <= last ? (uint32_t)st : 0u);
         if (pm || base < 64 || polls > kSpinLimit) break;

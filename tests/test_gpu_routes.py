@@ -298,3 +298,29 @@ def test_the_kind_of_the_tickets_does_not_depend_on_other_plans(oracle, nodes, d
         for plan in plans[1:]:  # (the first one does nothing)
             run_and_compare(oracle, g, None, pool.batch_for(s).numpy(), fanouts, 90 + s, plan=plan, og=og)
             assert (int(plan.view_log()[s][zg.LOG_STRIDE - 1]) > 0) == draw
+
+
+@pytest.mark.parametrize("nodes,draws,hop", [(20_000, 500_000, 0), (20_000, 500_000, 1), (200_000, 4_000_000, 1)])
+def test_totals_worked_out_where_a_cap_cuts_the_step(oracle, nodes, draws, hop):
+    # two plans on two streams, every total that is not there at a look worked out: the tile in which the cap falls and those behind it too
+    g = W.rmat_graph(nodes, draws, 23)
+    og = to_host_graph(oracle, g)
+    batch, fanouts = 256, (6, 5, 4)
+    pool = W.SeedPool(g, batch, 7)
+    batches = [pool.batch_for(s).numpy() for s in range(2)]
+    caps = [og.sample_blocks(b, fanouts, 31).n for b in batches]
+    for c in caps:
+        c[hop + 1] = (c[hop] + c[hop + 1]) // 2
+    want = [truncated_blocks(oracle, g, b, fanouts, 31, c) for b, c in zip(batches, caps)]
+    dg, streams = zg.Graph(g.offsets.cuda(), g.indices.cuda()), [zg.new_stream() for _ in batches]
+    plans = [zg.Plan(dg, fanouts, batch, zg.make_envelope(zg.ENV_EXPLICIT, node_caps=c, flags=zg.PLAN_IMPATIENT)) for c in caps]
+    seeds = [torch.as_tensor(b).cuda() for b in batches]
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for _ in range(4):
+            for plan, s, st in zip(plans, seeds, streams):
+                plan.step(s, 31, st)
+        torch.cuda.synchronize()
+        for plan, w in zip(plans, want):
+            assert plan.step_status() == (4 * rep + 4, zg.FLAG_HOP_OVERFLOW(hop))
+            compare_truncated(plan, w, f"rep {rep}")
