@@ -208,7 +208,12 @@ def _stream_ptr(stream) -> int:
 
 def graph_model(graph: "Graph", fanouts: Sequence[int], batch: int, *, with_replacement: bool = False, seed_prob=None,
                 stream=None):
-    """Mean and sigma of n_h from the graph-aware size model (computed on the device, synchronises)."""
+    """Mean and sigma of n_h from the graph-aware size model (computed on the device, synchronises).
+
+    Takes scratch from torch's allocator for the time of the call, which keeps it in its cache afterwards: 12 bytes per vertex, and
+    from MODEL_BIN_EDGES edges on 9 bytes per edge and 1 MB more (115 M edges: 1.0 GB, several times faster).  Where that does not fit, torch
+    first gives its cached blocks back, as it does for any allocation, and the call goes on with the smaller amount.  To choose, call
+    zg_envelope_model_graph with a buffer of your own."""
     import torch
     H = len(fanouts)
     f = (C.c_int32 * H)(*fanouts)
