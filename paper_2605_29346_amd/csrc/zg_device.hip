@@ -184,38 +184,14 @@ __device__ __forceinline__ uint32_t scale_draw(uint64_t x, uint32_t b)
     return (uint32_t)(((x >> 32) * b + (((x & 0xFFFFFFFFull) * b) >> 32)) >> 32);
 }
 
-// The F consecutive lanes of a wavefront that hold the slots of one frontier vertex, as the group interface of
-// floyd_settle (zg_floyd.h): slot j of the group sits in lane gbase + j.  A flag is looked up in the wavefront's mask of them.
+// The wavefront as the interface of floyd_position (zg_floyd.h): F consecutive lanes from gbase on hold the slots of this lane's frontier
+// vertex.  A flag is looked up in the wavefront's mask of them.
 struct WaveGroup {
     uint32_t gbase;
+    __device__ __forceinline__ uint32_t up(uint32_t x) const { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, true); } // wave_shr:1
     __device__ __forceinline__ bool flag_of(uint32_t j, bool mine) const { return (__ballot(mine) >> (gbase + j)) & 1ull; }
     __device__ __forceinline__ bool any(bool b) const { return __any(b) != 0; }
 };
-
-// Whether an earlier slot of the lane's group holds the same candidate: groups of F consecutive lanes, `group` the number of
-// the lane's; all of the wavefront's lanes active.  The candidates travel one lane up per round as a register move, three
-// instructions a round (a look through LDS per slot, ds_bpermute, is a round trip each, and F - 1 of them one after another).  What
-// comes from the group before differs in the top bit, which no candidate has; what comes from before lane 0 is zero, which
-// none of them is.
-__device__ __forceinline__ bool drawn_before(uint32_t cand, uint32_t group, uint32_t F)
-{
-    const uint32_t mine = (cand + 1u) | (group << 31); // (cand < a row's length < 2^31)
-    uint32_t x = mine, nearest = 0xFFFFFFFFu;
-    auto round = [&]() {
-        x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, true); // wave_shr:1
-        const uint32_t t = x ^ mine;
-        nearest = t < nearest ? t : nearest;
-    };
-    uint32_t left = F - 1u;
-    for (; left >= 4u; left -= 4u) {
-        round();
-        round();
-        round();
-        round();
-    }
-    for (; left; --left) round();
-    return nearest == 0u;
-}
 
 // =================================================================================================
 // kernels
@@ -583,7 +559,7 @@ __device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &
             uint32_t cand = gl;
             if (floyd) cand = scale_draw(philox_draw(key_lo, key_hi, (uint32_t)a.launch, (uint32_t)tv, gl), tdeg - F + gl + 1u);
             WaveGroup grp{sub * F};
-            pos = floyd_settle(grp, gl, F, tdeg, floyd, cand, drawn_before(cand, sub, F));
+            pos = floyd_position(grp, sub, gl, F, tdeg, floyd, cand);
         }
     }
     Slot r;
@@ -596,7 +572,7 @@ __device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &
 // The neighbor ids of rows row0, row0 + step, .. (64/F rows at a time) below row_end into s_ids, by edge, edge e0 first; one wavefront.
 // An id is stored only when the next slots have been worked out: its load is out for that long.
 // A pass is bound by instruction issue (2 M edges: seven passes of 32 wavefronts per compute unit, 3 us each, the ids' loads 1 us of it):
-// whole products in Philox, register moves instead of ds_bpermute in drawn_before and the loads' overlap took the hop launches from 23.4
+// whole products in Philox, register moves instead of ds_bpermute in floyd_drawn_before and the loads' overlap took the hop launches from 23.4
 // to 19.0 us (430 k edges), 18.0 to 16.3 (240 k), 14.5 to 14.0 (130 k); 54 us stay 54 at 2 M, where the random loads take over.
 __device__ __forceinline__ void load_ids(const HopArgs &a, const HopShared &sh, uint32_t key_lo, uint32_t key_hi, uint32_t row0, uint32_t row_end,
                                          uint32_t step, int lane, uint32_t e0, int32_t *s_ids)

@@ -36,14 +36,20 @@ def test_parallel_rule_equals_sequential_floyd_on_every_candidate_sequence(harne
     assert cases == expect and bad == 0
 
 
-def test_harness_notices_a_wrong_rule(harness, tmp_path):
-    # the same harness over a deliberately broken copy of the rule (the chase clause dropped) must report mismatches:
+@pytest.mark.parametrize("right,wrong", [
+    ("const bool nc = dup || (chase && ca);", "const bool nc = dup;"),                      # the chase clause dropped
+    ("(cand + 1u) | (group << 31)", "(cand + 1u)"),                                        # the group before taken for one's own
+    ("uint32_t left = F - 1u;", "uint32_t left = F - 2u;"),                                # the first slot never reaches the last
+    ("(cand + 1u) | (group << 31)", "cand | (group << 31)"),                               # candidate 0 taken for nothing, nothing for it
+])
+def test_harness_notices_a_wrong_rule(harness, tmp_path, right, wrong):
+    # the same harness over a deliberately broken copy of the rule must report mismatches:
     # otherwise agreement above would prove nothing
     src = open(os.path.join(ROOT, "paper_2605_29346_amd", "csrc", "zg_floyd.h")).read()
-    assert "const bool nc = dup || (chase && ca);" in src
+    assert right in src
     inc = tmp_path / "inc"
     inc.mkdir()
-    (inc / "zg_floyd.h").write_text(src.replace("const bool nc = dup || (chase && ca);", "const bool nc = dup;"))
+    (inc / "zg_floyd.h").write_text(src.replace(right, wrong))
     obj = tmp_path / "o.o"
     exe = tmp_path / "broken"
     subprocess.run(["gcc", "-std=c11", "-O2", "-c", os.path.join(ROOT, "oracle", "zg_oracle.c"), "-I", os.path.join(ROOT, "oracle"),
