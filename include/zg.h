@@ -74,7 +74,8 @@ enum zg_dtype { ZG_I32 = 0, ZG_I64 = 1 };
                                  bytes either way */
 #define ZG_PLAN_IMPATIENT 128u /* for tests: a workgroup that needs another one's total before it is there works it out at once instead
                                  of after a quarter of a millisecond (what it does when kernels of other streams keep that
-                                 workgroup from starting).  Results are the same, steps slower */
+                                 workgroup from starting).  Without effect on a launch whose ranking tiles have more than a word per lane:
+                                 there nobody else can work it out (see d_log).  Results are the same, steps slower */
 
 /* bits of the sticky device status word (zg_overflow_flag) */
 #define ZG_FLAG_HOP_OVERFLOW(h) (1u << (h)) /* |S_h| exceeded its cap at hop h: outputs of the step invalid */
@@ -101,9 +102,8 @@ typedef struct {
     int64_t node_caps[ZG_MAX_HOPS + 1]; /* ZG_ENV_EXPLICIT: cap of n_h for h = 1..H ([0] ignored); clamped to the worst case */
     double model_mean[ZG_MAX_HOPS + 1];  /* ZG_ENV_GRAPH: mean of n_h, h = 1..H ([0] ignored) */
     double model_sigma[ZG_MAX_HOPS + 1]; /* ZG_ENV_GRAPH: sigma of n_h */
-    int32_t max_tickets; /* tuning knob, <= 0 selects 480: how many workgroups of one launch take a tile id from a shared
-                            atomic counter (tiles grow to stay below it; the default is what an MI355X holds at once).
-                            Results do not depend on it. */
+    int32_t max_tickets; /* tuning knob, <= 0 selects 480: how many workgroups share the rows and ranking tiles of one launch (tiles
+                            grow to stay below it; the default is what an MI355X holds at once).  Results do not depend on it. */
     int32_t reserved;
 } zg_envelope;
 
@@ -153,7 +153,8 @@ typedef struct {
     const float *d_agg; /* [node_cap[H-1], ld_agg] mean of block H-1 over X */
     int64_t ld_agg;
     const uint32_t *d_log; /* ring of ZG_LOG_STRIDE-word records, one per step: epoch, flags, n[0..H], E[0..H-1],
-                            n_exact[1..H]; in the last word how many workgroups drew their share of a launch from its counter */
+                            n_exact[1..H]; in the last word how many workgroups drew their share of a launch from its counter (those of
+                            launches whose ranking tiles have more than a word per lane: 512 words in the last one, else 1024) */
     int32_t log_capacity;  /* records in the ring; record of step e sits at (e % log_capacity) */
     const uint32_t *d_epoch; /* number of steps run on this plan */
     int64_t x_row_cap;       /* rows of d_X: node_cap[H], or node_cap[H-1] with ZG_PLAN_FUSED_INPUT (rows i < n_{H-1} are valid) */

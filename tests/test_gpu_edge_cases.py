@@ -473,10 +473,10 @@ def test_size_model_bins_in_parts():
 
 
 @pytest.mark.parametrize("nodes,draws,batch,fanouts,max_tickets", [
-    (20_000, 500_000, 256, (6, 5, 4), 0),        # bytes, tiles of at most a word per lane
-    (3_000_000, 12_000_000, 256, (8, 5, 3), 0),  # bits, a few hundred words per tile
-    (3_000_000, 12_000_000, 900, (8, 5), 20),    # bits, pieces of 128 vertices
-    (600_000, 6_000_000, 3000, (9, 7), 8),       # bytes, pieces, several batches of rows per ticket
+    (20_000, 500_000, 256, (6, 5, 4), 0),        # bytes, a word or two per tile
+    (1_500_000, 12_000_000, 900, (8, 5), 0),     # bits, hundreds of words per tile
+    (1_500_000, 12_000_000, 900, (8, 5, 3), 0),  # bits, then bytes
+    (70_000, 1_400_000, 3000, (11, 6), 16),      # bytes, several batches of rows per ticket
     (70_000, 1_400_000, 3000, (11, 6), 300),
 ])
 @pytest.mark.parametrize("replace", [False, True])
@@ -492,3 +492,4 @@ def test_totals_worked_out_instead_of_waited_for(oracle, nodes, draws, batch, fa
     for s in range(3):
         plan, _, _ = run_and_compare(oracle, g, feat, pool.batch_for(s).numpy(), fanouts, 70 + s, plan=plan, og=og, replace=replace,
                                      env=zg.make_envelope(zg.ENV_MAX, flags=flags, max_tickets=max_tickets))
+        assert int(plan.view_log()[s][zg.LOG_STRIDE - 1]) == 0  # (a launch that ranks by pieces would draw its tickets, and not come this way)
