@@ -218,7 +218,7 @@ int zg_envelope_model(const int64_t *degrees, const int64_t *counts, int64_t n_d
  * Turn it into caps with ZG_ENV_GRAPH: copy mean / sigma into zg_envelope.model_mean / model_sigma; the planner
  * applies the cap formula of section 4.3 / Lemma 1 (margin and z) to them.
  * Errors: ZG_EINVAL (arguments, buffer), ZG_ESTATE (statistics-only handle, other device), ZG_EHIP. */
-#define ZG_MODEL_BIN_EDGES (1 << 19)
+#define ZG_MODEL_BIN_EDGES (1 << 18)
 int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t num_hops, int32_t batch,
                             int32_t with_replacement, const float *d_seed_prob, void *d_temp, size_t temp_bytes,
                             void *stream, double *mean, double *sigma);

@@ -1396,7 +1396,9 @@ struct CloseRoles { // the closing launch's other workgroups
 // bound by bandwidth and runs beside them.  Measured at 110 M vertices, 433 k new ones and a copy of 157 k rows of 512 bytes
 // (160 MB, 34 us alone): 54 us; 1024 lanes per ticket, tickets and copy alternating in the grid: 56 us.  Without a copy,
 // 2.4 M vertices and 668 k new ones: 20.6 us (31 us when a workgroup expanded 1024 of its 2800 vertices at a time, in pieces of 128 per
-// lane); 137 k new, with a copy of 25 MB: 21 us, with 1024 lanes 26 us.
+// lane); 137 k new, with a copy of 25 MB: 21 us, with 1024 lanes 26 us.  A byte-marked tile of 8192 words needs 49 KB of LDS with batches
+// of 4096 vertices, which leaves a compute unit room for three such workgroups, not four as with 1024: faster all the same, 66.2 -> 60.0 us (40 M
+// vertices, 2 M edges in the last hop, a copy of 64 floats a row) and 125.7 -> 124.9 (100 M, 6 M edges, 32 floats).
 template <bool BYTES>
 __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles o)
 {
@@ -1768,7 +1770,7 @@ constexpr uint32_t kModelNoShare = 0xFFFFFFFFu;
 constexpr int64_t kModelMinPart = 16384;
 constexpr int kModelBlock = 1024, kModelGrid = 512; // the sweeps over the vertices
 constexpr int64_t kModelPushWaves = 16384;          // twice what the chip holds at once
-constexpr int64_t kModelRowWork = 2;                // a row of a sweep by atomics, in edges
+constexpr int64_t kModelRowWork = 1;                // a row of a sweep by atomics, in edges
 
 // What a sweep by atomics has to do for a vertex that may be in D_h, in edges: the graph's offsets, where that is summed up
 struct ModelRows {
@@ -2215,15 +2217,17 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
     return m;
 }
 
-// Work of a sweep by atomics, in edges (46 ps each; a row with a term is two more), that takes as long as the same sweep by bins, with
-// `hops` sweeps to share the price of the places.  A sweep by bins takes 9 ps per edge, 12 us, and 4 us for every 512 vertices that a
-// workgroup passes by; the places take 24 us.  Atomics and bins in us, uniform seeds, 1 / 3 hops: 4 k vertices and 2^18 edges 44 / 123 and
-// 62 / 140; 30 k and 2^19 59 / 167 and 66 / 153; 30 k and 2^20 84 / 242 and 76 / 167; 1 M and 2^19 93 / 268 and 120 / 305; 1 M and 2^20 108 / 307
-// and 105 / 248; 8 M and 2^20 206 / 577 and 286 / 769; 8 M and 2^21 284 / 809 and 231 / 600.  2.4 M vertices and 115 M edges, one hop: 1.1 ms by
-// bins; by atomics 0.11, 0.55, 0.94, 1.3 ms with 1, 10, 18, 25 % of the vertices as seeds, 5.6 with all; three hops from 1 % 2.2 ms, not 3.0.
+// Work of a sweep by atomics, in edges (46 ps each where they spread over the graph, up to 110 on a power law's hubs: 65 here; a row with a
+// term is one more), that takes as long as the same sweep by bins, with `hops` sweeps to share the price of the places.  A sweep by bins takes
+// 9 ps per edge, 12 us, and 4 us for every 512 vertices that a workgroup passes by; the places take 24 us.  Atomics / bins in us, uniform
+// seeds.  Even graphs, one hop and three: 4 k vertices and 2^18 edges 44 / 62, 123 / 140; 30 k and 2^19 59 / 66, 167 / 153; 30 k and 2^20 84 / 76,
+// 242 / 167; 1 M and 2^19 93 / 120, 268 / 305; 1 M and 2^20 108 / 105, 307 / 248; 8 M and 2^20 206 / 286, 577 / 769; 8 M and 2^21 284 / 231, 809 / 600.
+// Power laws of skew 0.65: 40 k and 316 k edges 52 / 73, 148 / 149; 40 k and 473 k 66 / 73, 188 / 146; 10 k and 482 k 73 / 75, 209 / 152; 80 k and 0.6 M
+// 78 / 74, 224 / 160.  2.4 M vertices and 115 M edges, one hop: 1.1 ms by bins; by atomics 0.11, 0.55, 0.94, 1.3 ms with 1, 10, 18, 25 % of the
+// vertices as seeds, 5.6 with all; three hops from 1 % 2.2 ms, 3.0 all by bins.
 int64_t model_bins_work(const ModelBins &m, int hops)
 {
-    return m.num_edges / 5 + (1 << 18) + (1 << 19) / hops + 160 * m.num_nodes / m.chunks;
+    return m.num_edges / 7 + 180000 + 360000 / hops + 120 * m.num_nodes / m.chunks;
 }
 
 // once per call: places for the edges' terms

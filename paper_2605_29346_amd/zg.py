@@ -11,7 +11,7 @@ from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
 MAX_HOPS = 8
-MODEL_BIN_EDGES = 1 << 19  # ZG_MODEL_BIN_EDGES
+MODEL_BIN_EDGES = 1 << 18  # ZG_MODEL_BIN_EDGES
 MAX_FANOUT = 64
 LOG_STRIDE = 32
 

@@ -388,9 +388,8 @@ def test_repeated_draws_in_groups_of_any_width(oracle, fanout, batch):
 
 
 @pytest.mark.parametrize("nodes,edges,i64,by_bins", [
-    (60_000, zg.MODEL_BIN_EDGES - 1, False, False),
-    (60_000, zg.MODEL_BIN_EDGES, False, True),    # bins, the first time; the last window and the last bin are ragged
-    (4_000, zg.MODEL_BIN_EDGES, False, False),    # the places would take longer than the atomics
+    (60_000, zg.MODEL_BIN_EDGES, False, False),   # the places would take longer than the atomics
+    (60_001, 2 * zg.MODEL_BIN_EDGES + 1, False, True), # the last window and the last bin are ragged
     (256 * 512 + 1, 4096 * 300, True, True),      # a bin of one vertex, whole windows
     (300_000, 3_000_001, False, True),
     (8192 * 2048 + 5, 700_000, True, False),      # 190 k vertices to every workgroup of the sweep by bins
@@ -436,8 +435,8 @@ def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
 @pytest.mark.parametrize("share,hops,binned", [
     (0.01, 1, False),   # a hundredth of the edges have a term
     (0.01, 3, True),    # ... and about a tenth of them in the second hop, most in the third: that one goes by bins
-    (0.51, 1, False),   # on either side of the line (0.521: work of a row 2 + 10, of all 2.4 M; by bins 1.252 M)
-    (0.53, 1, True),
+    (0.39, 1, False),   # on either side of the line (0.398: work of a row 1 + 10, of all 2.2 M; by bins 875 k)
+    (0.405, 1, True),
     (1.0, 2, True),
     (0.0, 2, False),
 ])
