@@ -2128,8 +2128,8 @@ __global__ __launch_bounds__(kModelAddBlock) void k_model_add(ModelBins m, unsig
     }
 }
 
-// q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v); with COUNT, sums[2] += the next sweep's work.  Vertices kModelStride apart are added in
-// double, everything else as integers, so the sums do not depend on the launch.  One pair of atomics per workgroup of at most
+// q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v); with COUNT, sums[2] += the next sweep's
+// work.  Vertices kModelStride apart are added in double, everything else as integers, so the sums do not depend on the launch.  One pair of atomics per workgroup of at most
 // 512: a pair per wavefront queued up on the two words (2.4 M vertices: 905 us, now 16 us).
 constexpr int64_t kModelStride = (int64_t)65536 * kBlock;
 template <bool COUNT>

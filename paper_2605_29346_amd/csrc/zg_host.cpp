@@ -194,7 +194,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
 
     const int64_t ldx = feat_dim > 0 ? (int64_t)align_up((size_t)feat_dim, 4) : 0;
     const bool fused = (env->flags & ZG_PLAN_FUSED_INPUT) != 0;
-    // tuning knob: upper bound on the tickets (workgroups taking a tile id from one atomic counter) per kernel
+    // tuning knob: upper bound on the tickets (workgroups that share a launch's rows and ranking tiles)
     const int64_t max_tickets = env->max_tickets > 0 ? env->max_tickets : kMaxTickets;
     auto envelope_bytes_for = [&](const int64_t *node_cap) -> int64_t {
         size_t b = align_up(sizeof(Drmb), kAlign) + kGuard + align_up((size_t)kLogCapacity * ZG_LOG_STRIDE * 4, kAlign) + kGuard;
