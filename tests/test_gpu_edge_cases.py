@@ -440,11 +440,12 @@ def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
     (1.0, 2, True),
     (0.0, 2, False),
 ])
-@pytest.mark.parametrize("replace", [False, True])
-def test_size_model_sweeps_few_edges_with_atomics(share, hops, binned, replace):
+@pytest.mark.parametrize("replace,i64", [(False, False), (True, False), (False, True)])
+def test_size_model_sweeps_few_edges_with_atomics(share, hops, binned, replace, i64):
     nodes, edges = 200_000, 2_000_000
     gen = torch.Generator(device="cuda").manual_seed(3)
-    offsets = torch.arange(0, edges + 1, 10, device="cuda").int()
+    offsets = torch.arange(0, edges + 1, 10, device="cuda")
+    offsets = offsets if i64 else offsets.int()
     idx = torch.randint(0, nodes, (edges,), generator=gen, device="cuda", dtype=torch.int32)
     dg = zg.Graph(offsets, idx)
     prob = torch.zeros(nodes, device="cuda")
