@@ -3,7 +3,7 @@
 
 One "step" = one pass of the hot path (sample -> dedup/relabel -> block CSR -> gather -> mean
 aggregation) over one synthetic mini-batch, issued through the C-ABI library as one ingest kernel
-plus one hipGraph replay, with no host synchronisation between steps.  Prints ONE JSON line.
+plus the step's kernel launches, with no host synchronisation between steps.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload very_large] [--env model|max|graph] [--extras]
 
@@ -132,20 +132,23 @@ def summarize_pmc(argv) -> None:
 
 
 def summarize_hipapi(argv) -> None:
-    """The HIP API calls the host makes between the first and the last timed step (every step is one
-    hipGraphLaunch): shows that the steady-state loop holds no synchronising call, no copy and no allocation."""
+    """The HIP API calls the host makes between the first and the last timed step (every step is the same number of
+    kernel launches): shows that the steady-state loop holds no synchronising call, no copy and no allocation."""
     ap = argparse.ArgumentParser(prog="bench.py --summarize hipapi")
     ap.add_argument("trace_csv")
     ap.add_argument("--warmup", type=int, default=10)
+    ap.add_argument("--steps", type=int, default=100)
+    ap.add_argument("--launches", type=int, default=5, help="kernel launches of a step")
     ap.add_argument("--cmd", default="")
     args = ap.parse_args(argv)
     rows = sorted(csv.DictReader(open(args.trace_csv)), key=lambda r: int(r["Start_Timestamp"]))
-    launches = [i for i, r in enumerate(rows) if r["Function"] == "hipGraphLaunch"]
+    launches = [i for i, r in enumerate(rows) if r["Function"] == "hipLaunchKernel"]
+    first, launches = launches, launches[-args.launches * (args.warmup + args.steps)::args.launches]  # the steps' first ones: the loop's are the run's last
     print("# rocprofv3 --hip-trace summary: host API calls inside the timed loop")
     if args.cmd:
         print(f"\ncommand: `{args.cmd}`")
-    print(f"\nhipGraphLaunch calls in the run: {len(launches)} ({args.warmup} warm-up steps left out below)")
-    a, b = launches[args.warmup], launches[-1]
+    print(f"\nsteps: {len(launches)} of {args.launches} kernel launches each ({args.warmup} warm-up steps left out below)")
+    a, b = launches[args.warmup], first[-1]
     inside = defaultdict(int)
     for r in rows[a:b + 1]:
         inside[r["Function"]] += 1
@@ -243,8 +246,8 @@ def main():
     ap.add_argument("--env", default="model", choices=["model", "max", "graph"],
                     help="envelope of the plans: the paper's Lemma 1 from the degree histogram (default), the worst case, or "
                          "the lemma's cap formula on the graph-aware size model")
-    ap.add_argument("--eager", action="store_true", help="plans launch their kernels one by one instead of replaying a hipGraph "
-                    "(a comparison; the default and the reported configuration is the captured graph)")
+    ap.add_argument("--eager", action="store_true", help="plans with ZG_PLAN_AUTO_FALLBACK launch their kernels one by one too, "
+                    "instead of replaying a hipGraph (a comparison)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-seconds", type=float, default=12.0)
     ap.add_argument("--kernel-reps", type=int, default=20)
@@ -573,7 +576,7 @@ def main():
         "dtype": "int32 ids / f32 features", "data": "synthetic",
         "config": {"workload": cfg.name, "graph": f"{cfg.kind} |V|={g.num_nodes} |E|={g.num_edges}",
                    "offsets": str(g.offsets.dtype).replace("torch.", ""), "feat_dim": cfg.dim, "batch": cfg.batch,
-                   "fanouts": list(cfg.fanouts), "envelope": env_mode, "launch": ("kernels launched one by one (--eager)" if args.eager else "1 hipGraph replay per step"),
+                   "fanouts": list(cfg.fanouts), "envelope": env_mode, "launch": "the step's kernels, one by one",
                    "pipeline": f"{pipeline} plan(s) on {pipeline} stream(s), steps issued round-robin",
                    "host_syncs_in_timed_region": 1},
         "single_stream": {"value": K / wall_single, "ms_per_step": wall_single / K * 1e3},

@@ -6,8 +6,8 @@
  * CSR, the feature-row gather and a GraphSAGE mean aggregation.  Every count and offset the
  * step produces stays in a device-resident metadata buffer (section 4.1); all kernels run with
  * launch shapes fixed by a capacity envelope provisioned once (sections 4.2, 4.3) and read the
- * true sizes on the device; the step is a captured hipGraph replayed without any host
- * synchronisation (section 4.4).
+ * true sizes on the device; a step is the same fixed sequence of launches every time, enqueued without any host
+ * synchronisation (section 4.4), as one captured hipGraph where the safe plan's launches stand behind it.
  *
  * Conventions
  *  - Plain C ABI.  Every function returns 0 (ZG_OK) or a negative zg_status; nothing throws.
@@ -51,7 +51,7 @@ enum zg_dtype { ZG_I32 = 0, ZG_I64 = 1 };
 #define ZG_GRAPH_VALIDATE 1u /* synchronising check: indices in range, rows ascending (hence duplicate-free) */
 
 /* zg_envelope.flags */
-#define ZG_PLAN_EAGER 1u   /* launch the step's kernels one by one instead of replaying a hipGraph */
+#define ZG_PLAN_EAGER 1u   /* launch the step's kernels one by one with ZG_PLAN_AUTO_FALLBACK too, instead of replaying a hipGraph */
 #define ZG_PLAN_REPLACE 2u /* sample with replacement (the setting of the paper's Lemma 1) */
 #define ZG_PLAN_FUSED_INPUT 8u /* X holds the rows of the frontier D_{H-1} only and the aggregation reads its input rows
                                  straight from the feature table; the rows that only feed the mean are never written out.
@@ -254,8 +254,8 @@ int zg_plan_query(const zg_graph_t *g, const int32_t *fanouts, int32_t num_hops,
                   int32_t feat_dim, zg_plan_info *out);
 /* Sections 4.1-4.4: lays the device-resident metadata buffer and every step buffer out at fixed addresses
  * inside d_workspace (device memory, 256-byte aligned, >= zg_plan_query's workspace_bytes), initialises the
- * scratch state on `stream`, and captures the step - a fixed launch skeleton sized by the caps - into a
- * hipGraph.  May synchronise.  The workspace belongs to the plan until zg_plan_destroy; the graph handle
+ * scratch state on `stream`, fixes the step - a launch skeleton sized by the caps - and, with ZG_PLAN_AUTO_FALLBACK,
+ * captures it into a hipGraph.  May synchronise.  The workspace belongs to the plan until zg_plan_destroy; the graph handle
  * must outlive the plan; the current device must be the graph's.
  * Errors: those of zg_plan_query, ZG_EINVAL (workspace null or misaligned), ZG_ENOMEM (workspace too small,
  * pinned host memory), ZG_ESTATE (statistics-only graph handle, other device), ZG_EHIP.  *p is NULL on failure. */
@@ -267,7 +267,7 @@ int zg_plan(zg_plan_t **p, const zg_graph_t *g, const int32_t *fanouts, int32_t 
 int zg_plan_destroy(zg_plan_t *p);
 /* Makes gather + aggregation (section 2.2, "feature copy" and the first GraphSAGE aggregation) part of the
  * step: d_feat is the [num_nodes, ld] fp32 table in device memory (row stride ld elements, >= feat_dim),
- * borrowed until the plan is destroyed or another table is bound.  Rebuilds the captured graph: call it
+ * borrowed until the plan is destroyed or another table is bound.  Rebuilds the captured graph, if there is one: call it
  * between steps (nothing of this plan in flight).  Errors: ZG_ESTATE (plan made with feat_dim = 0),
  * ZG_EINVAL (null table, ld < feat_dim), ZG_EHIP. */
 int zg_plan_bind_features(zg_plan_t *p, const float *d_feat, int64_t ld);
@@ -276,17 +276,19 @@ int zg_plan_outputs(const zg_plan_t *p, zg_outputs *out);
 
 /* ---- per step ---------------------------------------------------------------------------------
  * One mini-batch: d_seeds = `batch` distinct vertex ids in device memory (or pinned host memory the
- * device can read), read when the step runs on `stream`; they must stay valid until then.  The call
- * writes (d_seeds, rng_key) into a slot of a small ring in pinned host memory that the step's first
- * kernel reads, and enqueues exactly ONE hipGraph launch - nothing else.  It never synchronises with
- * the device and never allocates; only when 255 earlier steps of this plan are still unfinished does
+ * device can read), read when the step runs on `stream`; they must stay valid until then.  The call enqueues
+ * the step's kernels - H + 2 or H + 3, 2 or 3 of a small step - and nothing else; with ZG_PLAN_AUTO_FALLBACK exactly ONE
+ * hipGraph launch, whose first kernel reads (d_seeds, rng_key) out of a slot of a small ring in pinned host memory.  It
+ * never synchronises with the device and never allocates; only when 255 earlier steps of this plan are still unfinished does
  * it wait, on the host, for the oldest one (a counter the device publishes in the same pinned ring); that
  * wait is bounded: after 30 s without progress the call returns ZG_ESTATE and enqueues nothing.
  * Results are in the plan's output buffers once `stream` reaches this point.  Steps of one plan must be
  * stream-ordered one after another and issued from one host thread at a time.  Invalid seeds do not fault:
  * they raise ZG_FLAG_SEED_* bits in the device status word and make the step's outputs undefined.
- * Errors: ZG_EINVAL (null), ZG_ESTATE (no captured graph; device made no progress for 30 s), ZG_EHIP (launch
- * failed; nothing was enqueued). */
+ * On a stream that is being captured the kernels become part of the caller's graph: each of its replays is a step with these
+ * seeds and this key (not with ZG_PLAN_AUTO_FALLBACK, whose graph launch is not recorded).
+ * Errors: ZG_EINVAL (null), ZG_ESTATE (no captured graph; device made no progress for 30 s), ZG_EHIP (a launch
+ * failed; if it was not the step's first one the plan takes no more steps: ZG_ESTATE). */
 int zg_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, void *stream);
 /* Stand-alone feature gather (section 2.2, "feature copy") for the vertex list the plan's last step left
  * on the device: d_out[i,:] = d_feat[S[i],:], i < n_H (n_H is read on the device); rows >= n_H of d_out are
@@ -339,7 +341,7 @@ int zg_calibration_copy(const void *d_src, void *d_dst, size_t bytes, void *stre
  * meant for timing the step's dominant kernels one by one.  Errors: ZG_EINVAL, ZG_ESTATE (no features bound), ZG_EHIP. */
 int zg_plan_replay_features(zg_plan_t *p, int32_t which, void *stream);
 /* zg_step with a stop-watch on its dominant kernel: the same step (same outputs, same mailbox and status bookkeeping),
- * its kernels enqueued one by one as a ZG_PLAN_EAGER plan does instead of replaying the captured graph - the copy of a
+ * its kernels enqueued one by one also where zg_step replays a captured graph - the copy of a
  * small step's frontier rows, otherwise a part of its aggregation launch, in a launch of its own -, and the caller's
  * two events (hipEvent_t, created with timing enabled) recorded on `stream` right before and right after the
  * aggregation launch (section 2.2, first GraphSAGE aggregation), so that their distance is that launch's duration

@@ -11,8 +11,9 @@
 // the features move.
 // Every kernel is launched with a grid fixed by the plan's capacity envelope, reads the true sizes
 // from the device-resident metadata buffer and lets surplus workgroups return at once (paper
-// sections 4.1-4.3).  The whole step is one hipGraph (section 4.4); the step's seeds pointer and key reach it
-// through a mailbox in pinned host memory.
+// sections 4.1-4.3).  The launches are the same for every step but for the seeds pointer and the key, which its first one
+// takes as arguments; with a twin behind it the step is one hipGraph (section 4.4) and takes them through a mailbox in pinned
+// host memory (see issue_step).
 // A plan may carry a worst-case twin (the paper's "cached safe graph", section 4.3) that replays a mini-batch
 // whose sizes overflowed the envelope, on the host's request or - its kernels appended to the step's graph
 // behind a device-side gate - by itself.
@@ -222,7 +223,14 @@ __device__ __forceinline__ bool gate_closed(const Drmb *gate)
     return gate != nullptr && (gate->last_flags & kHopOverflowMask) == 0u;
 }
 
+// The step's inputs as arguments of its first launch (seeds == null: a captured graph's arguments are frozen, they come through the mailbox)
+struct StepInputs {
+    const int32_t *seeds;
+    unsigned long long key;
+};
+
 struct IngestArgs {
+    StepInputs in;
     Drmb *drmb;
     const Drmb *gate;       // gated twin: the step's inputs are those of the gate owner's step that has just finished
     const Mailbox *mailbox; // the mailbox the inputs are read from (the gate owner's when gated)
@@ -285,7 +293,14 @@ __device__ __forceinline__ void shared_inputs(Drmb *d, const Drmb *gate, const M
 __device__ __forceinline__ void ingest_block(const IngestArgs &a, uint32_t block, unsigned long long *s_in)
 {
     const uint32_t gtid = block * blockDim.x + threadIdx.x;
-    if (threadIdx.x == 0 && !prefetched_inputs(a.drmb, a.gate, s_in)) mailbox_inputs(a.drmb, a.gate, a.mailbox, s_in); // (a workgroup per 1024 seeds)
+    if (threadIdx.x == 0) {
+        if (a.in.seeds) {
+            s_in[0] = reinterpret_cast<unsigned long long>(a.in.seeds);
+            s_in[1] = a.in.key;
+        } else if (!prefetched_inputs(a.drmb, a.gate, s_in)) {
+            mailbox_inputs(a.drmb, a.gate, a.mailbox, s_in); // (a workgroup per 1024 seeds)
+        }
+    }
     __syncthreads();
     const int32_t *seeds = reinterpret_cast<const int32_t *>(s_in[0]);
     if (gtid == 0) {
@@ -469,7 +484,8 @@ struct HopArgs {
     const int32_t *indices;
     Drmb *drmb;
     const Drmb *gate;
-    const Mailbox *mailbox;   // launch 0 reads the step's inputs itself (the gate owner's mailbox when gated)
+    StepInputs in;            // launch 0: the step's inputs ...
+    const Mailbox *mailbox;   // ... or where it reads them itself (the gate owner's mailbox when gated)
     int32_t *S;
     int32_t *local_id;
     uint32_t *marks_prev;    // launches 1..H: the bitmap hop l-1 filled; ranked, consumed and cleared here
@@ -959,12 +975,13 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     uint32_t *const s_words = s_set + (NEXT_BYTES ? 0 : kSampleHashSlots);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     Drmb *d = a.drmb;
-    if (FIRST && tid == 64) sh.have_in = prefetched_inputs(d, a.gate, sh.in);
+    const bool by_mail = FIRST && !a.in.seeds;
+    if (by_mail && tid == 64) sh.have_in = prefetched_inputs(d, a.gate, sh.in);
     if (!FIRST && a.draw && tid == 0) sh.drawn = atomicAdd(&d->ticket[a.launch], 1u);
     const uint32_t n_old_d = FIRST ? a.batch : d->n[a.launch - 1]; // (in flight while a drawn ticket comes back)
     const uint32_t key_lo_d = FIRST ? 0u : d->key_lo, key_hi_d = FIRST ? 0u : d->key_hi;
     uint32_t ticket = blockIdx.x;
-    if (FIRST || a.draw) {
+    if (by_mail || (!FIRST && a.draw)) {
         __syncthreads();
         if (!FIRST) ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.drawn);
     }
@@ -980,13 +997,14 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     const uint32_t t_old = (uint32_t)__builtin_amdgcn_readfirstlane((int)((n_old + rows - 1u) / rows));
     const uint32_t n_tickets = t_old + (FIRST ? 0u : a.rank_tiles);
     if (ticket >= n_tickets) return;
-    if (FIRST && !sh.have_in) {
+    if (by_mail && !sh.have_in) {
         if (tid == 0) shared_inputs(d, a.gate, a.mailbox, ticket, a.patience, sh.in);
         __syncthreads();
     }
+    const unsigned long long seeds_at = by_mail ? sh.in[0] : (unsigned long long)a.in.seeds, key = by_mail ? sh.in[1] : a.in.key; // (launch 0)
     const bool old = FIRST || ticket < t_old; // uniform over the workgroup
-    const uint32_t key_lo = FIRST ? (uint32_t)(sh.in[1] & 0xFFFFFFFFull) : key_lo_d;
-    const uint32_t key_hi = FIRST ? (uint32_t)(sh.in[1] >> 32) : key_hi_d;
+    const uint32_t key_lo = FIRST ? (uint32_t)(key & 0xFFFFFFFFull) : key_lo_d;
+    const uint32_t key_hi = FIRST ? (uint32_t)(key >> 32) : key_hi_d;
 
     // ---- what this ticket's rows are: m old rows from r0 on, or the tile's m new vertices
     uint32_t m;
@@ -1031,7 +1049,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
             if (u * (uint32_t)kHopBlock + tid < np) s_piece[u * kHopBlock + tid] = x[u]; // (read back by this lane only)
     }
     auto old_row = [&](uint32_t r) { // a row of the frontier (launch 0: a seed, an out-of-range one becoming -1, a vertex without neighbors)
-        const int32_t v = FIRST ? reinterpret_cast<const int32_t *>(sh.in[0])[r] : a.S[r];
+        const int32_t v = FIRST ? reinterpret_cast<const int32_t *>(seeds_at)[r] : a.S[r];
         return FIRST && (uint32_t)v >= a.num_nodes ? -1 : v;
     };
     auto missing_edges = [&](uint32_t t) { // another ticket's edges, worked out by this wavefront (see chain_prefix)
@@ -1255,11 +1273,12 @@ __global__ __launch_bounds__(kHopBlock) void k_small(SmallArgs s)
     uint32_t *const s_marks = s_dyn + a.stage_edges, *const s_seen = s_marks + s.words;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     Drmb *d = a.drmb;
-    if (tid == 0 && !prefetched_inputs(d, a.gate, sh.in)) mailbox_inputs(d, a.gate, a.mailbox, sh.in);
+    if (!a.in.seeds && tid == 0 && !prefetched_inputs(d, a.gate, sh.in)) mailbox_inputs(d, a.gate, a.mailbox, sh.in);
     for (uint32_t w = tid; w < 2u * s.words; w += (uint32_t)kHopBlock) s_marks[w] = 0u;
     __syncthreads();
-    const int32_t *seeds = reinterpret_cast<const int32_t *>(sh.in[0]);
-    const uint32_t key_lo = (uint32_t)(sh.in[1] & 0xFFFFFFFFull), key_hi = (uint32_t)(sh.in[1] >> 32);
+    const int32_t *seeds = a.in.seeds ? a.in.seeds : reinterpret_cast<const int32_t *>(sh.in[0]);
+    const unsigned long long key = a.in.seeds ? a.in.key : sh.in[1];
+    const uint32_t key_lo = (uint32_t)(key & 0xFFFFFFFFull), key_hi = (uint32_t)(key >> 32);
     if (tid == 0) {
         d->step = d->epoch;
         d->n[0] = a.batch;
@@ -1505,7 +1524,8 @@ struct FinishArgs {
     uint64_t *status;       // the chained scans' status words of every launch: back to zero for the next step
     uint64_t status_words;
     int32_t num_hops;
-    uint32_t blocks; // workgroups given to this role (0: role absent)
+    uint32_t prefetch; // the launch's workgroup that looks for the next step's inputs
+    uint32_t blocks;   // workgroups given to this role (0: role absent)
 };
 
 // End of step: the "seen" words of this step's frontier vertices (everything in D_{H-1}: the seeds and
@@ -1518,8 +1538,8 @@ __device__ __forceinline__ void publish_gate_owner(const FinishArgs &a)
     __hip_atomic_store(&a.gate_mailbox->completed, a.gate->epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// One lane, early in the step's last launch: if the host has already handed over the next step, its mailbox slot is
-// copied into the metadata buffer, so that the next step starts without a read of host memory.  Counted from `step`, not from
+// One lane of the step's last launch: if the host has already handed over the next step, its mailbox slot is
+// copied into the metadata buffer, so that the next step, if it takes its inputs from there, starts without a read of host memory.  Counted from `step`, not from
 // `epoch`: a finish workgroup of the same launch advances that one, before or after this lane looks.
 __device__ __forceinline__ void prefetch_step_inputs(Drmb *d, const Mailbox *mailbox)
 {
@@ -1701,8 +1721,7 @@ __global__ __launch_bounds__(kBlock) void k_aggregate(RowArgs agg, FinishArgs fi
         if (blockIdx.x == 0 && threadIdx.x == 0) publish_gate_owner(fin);
         return;
     }
-    // the launch's first workgroup starts early in the launch: its first lane looks whether the next step is already there
-    if (blockIdx.x == 0 && threadIdx.x == 0 && fin.blocks && !fin.gate) prefetch_step_inputs(fin.drmb, fin.mailbox);
+    if (blockIdx.x == fin.prefetch && threadIdx.x == 0 && fin.blocks && !fin.gate) prefetch_step_inputs(fin.drmb, fin.mailbox);
     const uint32_t copies = copy_blocks(copy);
     if (blockIdx.x < copies)
         copy_block<VEC>(copy, blockIdx.x, s_mem);
@@ -1720,7 +1739,7 @@ __global__ __launch_bounds__(kBlock) void k_tail(RelabelArgs last, FinishArgs fi
         if (blockIdx.x == 0 && threadIdx.x == 0) publish_gate_owner(fin);
         return;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && !fin.gate) prefetch_step_inputs(fin.drmb, fin.mailbox);
+    if (blockIdx.x == fin.prefetch && threadIdx.x == 0 && !fin.gate) prefetch_step_inputs(fin.drmb, fin.mailbox);
     if (blockIdx.x < last.blocks)
         relabel_block(last, blockIdx.x);
     else
@@ -2342,9 +2361,10 @@ struct zg_plan_s {
     uint32_t issued = 0;            // steps enqueued so far (mod 2^32, like the device-side step counter)
     hipStream_t last_stream = nullptr; // stream of the last enqueued step (what zg_plan_destroy waits for)
     bool stepped = false;
+    bool broken = false;            // a step was enqueued in part
     zg_plan_s *twin = nullptr;      // worst-case twin (ZG_PLAN_SAFE_TWIN): own outputs, metadata and mailbox, shared scratch
-    hipStream_t capture_stream = nullptr;
-    hipGraph_t graph_obj = nullptr;
+    hipStream_t own_stream = nullptr;
+    hipGraph_t graph_obj = nullptr; // (plans that replay one: see issue_step)
     hipGraphExec_t graph_exec = nullptr;
 
     Drmb *drmb() const { return reinterpret_cast<Drmb *>(ws + lay.off_drmb); }
@@ -2403,7 +2423,8 @@ bool x_written_by_aggregation(const zg_plan_t *p)
 // non-temporal 183 / 215 us (X rows of new vertices only: 191 / 222 us), loads cached and stores non-temporal 174 / 214 us,
 // both cached 194 / 242 us.
 
-FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate = nullptr, bool defer_completed = false)
+// (`blocks_before` of the last launch do something else)
+FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate = nullptr, bool defer_completed = false, uint32_t blocks_before = 0)
 {
     FinishArgs fa;
     std::memset(&fa, 0, sizeof(fa));
@@ -2421,6 +2442,9 @@ FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate =
     fa.status_words = p->lay.status_words;
     fa.num_hops = H;
     fa.blocks = (uint32_t)((p->lay.node_cap[H - 1] + kBlock - 1) / kBlock);
+    // A read of host memory: in the first workgroup, where others are still to come when it has ended; in a launch that the chip holds at once, in
+    // the last one, which has little else to do.
+    fa.prefetch = blocks_before < 1024u ? blocks_before + fa.blocks - 1u : 0u;
     return fa;
 }
 
@@ -2470,36 +2494,41 @@ RowArgs aggregate_args(const zg_plan_t *p, int hop, const float *d_in, int64_t l
     return a;
 }
 
-int launch_gather(const RowArgs &gat, const RelabelArgs &ra, hipStream_t st)
+// zg_step_timed: events to record right before and right after the aggregation launch of the plan's own step
+struct StepProbe {
+    hipEvent_t before, after;
+    hipError_t error; // what recording them returned (the step is enqueued either way)
+};
+
+// Where a step's launches go, and how many of them have gone there.  (What a launch returned, and not hipGetLastError: that may be an earlier
+// error of the caller's own.)
+struct Queue {
+    hipStream_t st;
+    int launched = 0;
+    template <class... P> int launch(void (*kernel)(P...), unsigned grid, unsigned block, size_t lds, P... a)
+    {
+        void *args[] = {&a...};
+        ZG_HIP(hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block), args, lds, st));
+        ++launched;
+        return ZG_OK;
+    }
+};
+
+int launch_gather(const RowArgs &gat, const RelabelArgs &ra, Queue &q)
 {
     const unsigned grid = gat.blocks + ra.blocks;
     if (grid == 0) return ZG_OK;
-    const size_t lds = (size_t)kBlock * 4;
-    if (gat.vec4)
-        hipLaunchKernelGGL(k_gather<4>, dim3(grid), dim3(kBlock), lds, st, gat, ra);
-    else
-        hipLaunchKernelGGL(k_gather<1>, dim3(grid), dim3(kBlock), lds, st, gat, ra);
-    ZG_HIP(hipGetLastError());
-    return ZG_OK;
+    return q.launch(gat.vec4 ? k_gather<4> : k_gather<1>, grid, kBlock, (size_t)kBlock * 4, gat, ra);
 }
 
-int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, hipStream_t st, const RowArgs *copy = nullptr)
+int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, Queue &q, const RowArgs *copy = nullptr)
 {
     const unsigned grid = agg.blocks + fa.blocks + (copy ? copy->blocks : 0u);
     if (grid == 0) return ZG_OK;
     size_t lds = agg.blocks ? ((size_t)agg.rows + 1 + (size_t)agg.rows * agg.max_fanout * (agg.x_dst ? 2 : 1)) * 4 : 0;
     if (copy) lds = std::max(lds, (size_t)copy->rows * 4);
-    const dim3 g(grid), b(kBlock);
-    if (copy && agg.vec4)
-        hipLaunchKernelGGL((k_aggregate<4, RowArgs>), g, b, lds, st, agg, fa, *copy);
-    else if (copy)
-        hipLaunchKernelGGL((k_aggregate<1, RowArgs>), g, b, lds, st, agg, fa, *copy);
-    else if (agg.vec4)
-        hipLaunchKernelGGL((k_aggregate<4, NoCopy>), g, b, lds, st, agg, fa, NoCopy());
-    else
-        hipLaunchKernelGGL((k_aggregate<1, NoCopy>), g, b, lds, st, agg, fa, NoCopy());
-    ZG_HIP(hipGetLastError());
-    return ZG_OK;
+    if (copy) return q.launch(agg.vec4 ? k_aggregate<4, RowArgs> : k_aggregate<1, RowArgs>, grid, kBlock, lds, agg, fa, *copy);
+    return q.launch(agg.vec4 ? k_aggregate<4, NoCopy> : k_aggregate<1, NoCopy>, grid, kBlock, lds, agg, fa, NoCopy());
 }
 
 // How the last hop's new vertices carry their marking edge's tag, where that hop marks bytes (all zero: they do not).  A plan and
@@ -2554,31 +2583,17 @@ bool features_ride_along(const zg_plan_t *p)
     return p->d_feat && p->lay.feat_dim > 0 && ((p->flags & ZG_PLAN_FUSED_INPUT) || x_written_by_aggregation(p));
 }
 
-// zg_step_timed: events to record right before and right after the aggregation launch of the plan's own step
-struct StepProbe {
-    hipEvent_t before, after;
-    hipError_t error; // what recording them returned (the step is enqueued either way)
-};
-
 template <typename OffT>
-void launch_hop(const HopArgs &ha, const HopRoles &o, unsigned grid, size_t lds, hipStream_t st)
+int launch_hop(const HopArgs &ha, const HopRoles &o, unsigned grid, size_t lds, Queue &q)
 {
-    const dim3 g(grid), b(kHopBlock);
     const bool prev = ha.bytes_prev != 0, next = ha.bytes_next != 0;
-    if (ha.launch == 0) {
-        if (next) hipLaunchKernelGGL((k_hop<OffT, true, false, true>), g, b, lds, st, ha, o);
-        else hipLaunchKernelGGL((k_hop<OffT, true, false, false>), g, b, lds, st, ha, o);
-    } else if (prev) {
-        if (next) hipLaunchKernelGGL((k_hop<OffT, false, true, true>), g, b, lds, st, ha, o);
-        else hipLaunchKernelGGL((k_hop<OffT, false, true, false>), g, b, lds, st, ha, o);
-    } else {
-        if (next) hipLaunchKernelGGL((k_hop<OffT, false, false, true>), g, b, lds, st, ha, o);
-        else hipLaunchKernelGGL((k_hop<OffT, false, false, false>), g, b, lds, st, ha, o);
-    }
+    if (ha.launch == 0) return q.launch(next ? k_hop<OffT, true, false, true> : k_hop<OffT, true, false, false>, grid, kHopBlock, lds, ha, o);
+    if (prev) return q.launch(next ? k_hop<OffT, false, true, true> : k_hop<OffT, false, true, false>, grid, kHopBlock, lds, ha, o);
+    return q.launch(next ? k_hop<OffT, false, false, true> : k_hop<OffT, false, false, false>, grid, kHopBlock, lds, ha, o);
 }
 
 // the sampling of a small step
-int launch_small(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate)
+int launch_small(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_plan_t *gate)
 {
     const Layout &L = p->lay;
     const zg_graph_t *g = p->graph;
@@ -2589,6 +2604,7 @@ int launch_small(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate)
     ha.indices = g->d_indices;
     ha.drmb = p->drmb();
     ha.gate = gate ? gate->drmb() : nullptr;
+    ha.in = in;
     ha.mailbox = gate ? gate->mailbox_dev : p->mailbox_dev;
     ha.S = p->S();
     ha.local_id = p->local_id();
@@ -2608,18 +2624,13 @@ int launch_small(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate)
     for (int h = 0; h <= L.num_hops; ++h) sa.cap[h] = (uint32_t)L.node_cap[h];
     sa.words = (uint32_t)(((g->num_nodes + 31) / 32 + 31) / 32 * 32);
     const size_t lds = (kSmallStage + 2 * (size_t)sa.words) * 4;
-    if (g->offsets_dtype == ZG_I64)
-        hipLaunchKernelGGL(k_small<int64_t>, dim3(1), dim3(kHopBlock), lds, st, sa);
-    else
-        hipLaunchKernelGGL(k_small<int32_t>, dim3(1), dim3(kHopBlock), lds, st, sa);
-    ZG_HIP(hipGetLastError());
-    return ZG_OK;
+    return q.launch(g->offsets_dtype == ZG_I64 ? k_small<int64_t> : k_small<int32_t>, 1u, kHopBlock, lds, sa);
 }
 
-// a whole step, in order, on one stream (captured once, or issued eagerly): the hop kernel's launches 0..H, then the
+// a whole step, in order, on one stream (a step's launches, or - captured once - those of a graph): the hop kernel's launches 0..H, then the
 // two feature launches.  With `gate` the kernels are those of gate's worst-case twin `p`, run on gate's inputs and
 // only if gate's step overflowed; `defer_completed` marks a plan whose gated twin follows in the same sequence.
-int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nullptr, bool defer_completed = false,
+int enqueue_body(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_plan_t *gate = nullptr, bool defer_completed = false,
                  StepProbe *probe = nullptr)
 {
     const Layout &L = p->lay;
@@ -2633,7 +2644,7 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
     std::memset(&no_rows, 0, sizeof(no_rows));
     if (feats) step_feature_args(p, &gat, &agg);
     if (L.small) {
-        const int rc = launch_small(p, st, gate);
+        const int rc = launch_small(p, q, in, gate);
         if (rc != ZG_OK) return rc;
     }
     for (int l = 0; l <= H && !L.small; ++l) {
@@ -2643,6 +2654,7 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         ha.indices = g->d_indices;
         ha.drmb = p->drmb();
         ha.gate = gate ? gate->drmb() : nullptr;
+        ha.in = in;
         ha.mailbox = gate ? gate->mailbox_dev : p->mailbox_dev;
         ha.S = p->S();
         ha.local_id = p->local_id();
@@ -2681,11 +2693,13 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
         ha.draw = by_pieces;
         ha.patience = by_pieces ? kSpinLimit : (p->flags & ZG_PLAN_IMPATIENT) ? 0u : kPatience;
         ha.blocks = (uint32_t)(L.old_tickets[l] + L.rank_tiles[l]);
+        int rc;
         // the edges of hop l-2 can be relabeled now: launch l-1 ranked the last vertices they point to
         const RelabelArgs ra = relabel_args(p, l - 2, l >= 2);
         IngestArgs ia;
         std::memset(&ia, 0, sizeof(ia));
         if (l == 0) {
+            ia.in = in;
             ia.drmb = p->drmb();
             ia.gate = ha.gate;
             ia.mailbox = ha.mailbox;
@@ -2701,11 +2715,8 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
             CloseRoles roles = {ra, ride ? gat : no_rows};
             roles.gat.rows *= kCloseBlock / kBlock;
             roles.gat.blocks = ride ? (uint32_t)((L.node_cap[H - 1] + roles.gat.rows - 1) / roles.gat.rows) : 0u;
-            const dim3 grid(ha.blocks + ra.blocks + roles.gat.blocks), block(kCloseBlock);
-            if (ha.bytes_prev)
-                hipLaunchKernelGGL(k_close<true>, grid, block, (size_t)ha.words_per_tile * 4, st, ha, roles);
-            else
-                hipLaunchKernelGGL(k_close<false>, grid, block, ha.words_per_tile <= (uint32_t)kCloseBlock ? (size_t)ha.words_per_tile * 4 : 0, st, ha, roles);
+            const size_t lds = ha.bytes_prev || ha.words_per_tile <= (uint32_t)kCloseBlock ? (size_t)ha.words_per_tile * 4 : 0;
+            rc = q.launch(ha.bytes_prev ? k_close<true> : k_close<false>, ha.blocks + ra.blocks + roles.gat.blocks, kCloseBlock, lds, ha, roles);
         } else {
             const HopRoles roles = {ra, ia};
             const unsigned grid = ha.blocks + ra.blocks + ia.blocks;
@@ -2715,45 +2726,41 @@ int enqueue_body(const zg_plan_t *p, hipStream_t st, const zg_plan_t *gate = nul
             const size_t room = kHopLdsBytes / 4 - sizeof(HopShared) / 4;
             ha.stage_edges = (uint32_t)std::min<size_t>(kHopMaxStage, room > words + kHopMinStage ? (room - words) / 64 * 64 : kHopMinStage);
             const size_t lds = (ha.stage_edges + words) * 4u;
-            if (g->offsets_dtype == ZG_I64)
-                launch_hop<int64_t>(ha, roles, grid, lds, st);
-            else
-                launch_hop<int32_t>(ha, roles, grid, lds, st);
+            rc = g->offsets_dtype == ZG_I64 ? launch_hop<int64_t>(ha, roles, grid, lds, q) : launch_hop<int32_t>(ha, roles, grid, lds, q);
         }
-        ZG_HIP(hipGetLastError());
+        if (rc != ZG_OK) return rc;
     }
     // the tail: {gather + relabel of the last hop} - unless both ride along elsewhere -, then {aggregation + end-of-step
     // clean-up}.  (One launch for all four roles was measured: no gain - the two big roles are bound by the same memory fabric.)
     if (!feats) {
         const RelabelArgs ra = relabel_args(p, H - 1, true, gate);
-        const FinishArgs fa = finish_args(p, true, gate, defer_completed);
-        hipLaunchKernelGGL(k_tail, dim3(ra.blocks + fa.blocks), dim3(kBlock), 0, st, ra, fa);
-        ZG_HIP(hipGetLastError());
-        return ZG_OK;
+        const FinishArgs fa = finish_args(p, true, gate, defer_completed, ra.blocks);
+        return q.launch(k_tail, ra.blocks + fa.blocks, kBlock, 0, ra, fa);
     }
     if (!ride) {
-        int rc = launch_gather(gat, relabel_args(p, H - 1, true, gate), st);
+        int rc = launch_gather(gat, relabel_args(p, H - 1, true, gate), q);
         if (rc != ZG_OK) return rc;
     }
     // a small step's frontier rows are copied by workgroups of the aggregation launch - by a launch of their own, ahead of it, where
     // the events are to bracket the aggregation alone
     const bool copy_along = L.small && ride && !probe;
     if (L.small && ride && probe) {
-        const int rc = launch_gather(gat, relabel_args(p, 0, false), st);
+        const int rc = launch_gather(gat, relabel_args(p, 0, false), q);
         if (rc != ZG_OK) return rc;
     }
-    if (probe) probe->error = hipEventRecord(probe->before, st);
-    int rc = launch_aggregate(agg, finish_args(p, true, gate, defer_completed), st, copy_along ? &gat : nullptr);
-    if (rc == ZG_OK && probe && probe->error == hipSuccess) probe->error = hipEventRecord(probe->after, st);
+    if (probe) probe->error = hipEventRecord(probe->before, q.st);
+    const FinishArgs fa = finish_args(p, true, gate, defer_completed, agg.blocks + (copy_along ? gat.blocks : 0u));
+    int rc = launch_aggregate(agg, fa, q, copy_along ? &gat : nullptr);
+    if (rc == ZG_OK && probe && probe->error == hipSuccess) probe->error = hipEventRecord(probe->after, q.st);
     return rc;
 }
 
 // the plan's step, followed - with ZG_PLAN_AUTO_FALLBACK - by its twin's step behind the device-side gate
-int enqueue_step(const zg_plan_t *p, hipStream_t st, StepProbe *probe = nullptr)
+int enqueue_step(const zg_plan_t *p, Queue &q, const StepInputs &in, StepProbe *probe = nullptr)
 {
     const bool autofb = (p->flags & ZG_PLAN_AUTO_FALLBACK) && p->twin;
-    int rc = enqueue_body(p, st, nullptr, autofb, probe);
-    if (rc == ZG_OK && autofb) rc = enqueue_body(p->twin, st, p, false);
+    int rc = enqueue_body(p, q, in, nullptr, autofb, probe);
+    if (rc == ZG_OK && autofb) rc = enqueue_body(p->twin, q, in, p, false);
     return rc;
 }
 
@@ -2765,15 +2772,17 @@ void drop_graph(zg_plan_t *p)
     p->graph_obj = nullptr;
 }
 
+bool replays_graph(const zg_plan_t *p) { return (p->flags & ZG_PLAN_AUTO_FALLBACK) && !(p->flags & ZG_PLAN_EAGER); }
+
 int build_graph(zg_plan_t *p)
 {
     drop_graph(p);
-    if (p->flags & ZG_PLAN_EAGER) return ZG_OK;
-    if (!p->capture_stream) ZG_HIP(hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking));
-    ZG_HIP(hipStreamBeginCapture(p->capture_stream, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_step(p, p->capture_stream);
+    if (!replays_graph(p) || !p->twin) return ZG_OK;
+    ZG_HIP(hipStreamBeginCapture(p->own_stream, hipStreamCaptureModeThreadLocal));
+    Queue q{p->own_stream};
+    int rc = enqueue_step(p, q, StepInputs{nullptr, 0ull});
     hipGraph_t gobj = nullptr;
-    hipError_t e = hipStreamEndCapture(p->capture_stream, &gobj);
+    hipError_t e = hipStreamEndCapture(p->own_stream, &gobj);
     if (rc != ZG_OK) {
         if (gobj) (void)hipGraphDestroy(gobj);
         return rc;
@@ -2813,6 +2822,11 @@ static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &
         if (hipHostGetDevicePointer(&dev, host, 0) != hipSuccess) return bail(fail(ZG_EHIP, "hipHostGetDevicePointer failed"));
         p->mailbox_dev = static_cast<Mailbox *>(dev);
     }
+    // A stream of the plan's own, for the capture of a graph - and where there is none all the same: the runtime spreads a process's streams over
+    // four hardware queues as they are made, and callers with a stream per plan and the default one have five.  (110 M vertices, four plans on
+    // four streams: two of them shared a queue, 908 to 945 us for a step of each; 858 with these streams in between.)
+    if (!(flags & ZG_PLAN_EAGER) && hipStreamCreateWithFlags(&p->own_stream, hipStreamNonBlocking) != hipSuccess)
+        return bail(fail(ZG_EHIP, "hipStreamCreateWithFlags failed"));
     // initial state: metadata, log, both bitmaps and the scan state zero (the id map needs no initial value:
     // an entry is only read for a vertex whose entry was written earlier in the same step)
     hipError_t e = hipMemsetAsync(p->ws + L.off_drmb, 0, sizeof(Drmb), st);
@@ -2825,8 +2839,6 @@ static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return bail(fail(ZG_EHIP, std::string("initialising the workspace: ") + hipGetErrorString(e)));
-    int rc = build_graph(p);
-    if (rc != ZG_OK) return bail(rc);
     *out = p;
     return ZG_OK;
 }
@@ -2853,7 +2865,7 @@ int zg_plan(zg_plan_t **out, const zg_graph_t *g, const int32_t *fanouts, int32_
     if (rc != ZG_OK) return rc;
     if (with_twin) {
         rc = make_plan_object(&p->twin, g, Ls, env->flags & ~(ZG_PLAN_SAFE_TWIN | ZG_PLAN_AUTO_FALLBACK), batch, ws, st, true);
-        if (rc == ZG_OK && (env->flags & ZG_PLAN_AUTO_FALLBACK)) rc = build_graph(p); // again, now with the twin's kernels behind
+        if (rc == ZG_OK) rc = build_graph(p);
         if (rc != ZG_OK) {
             zg_plan_destroy(p);
             return rc;
@@ -2892,7 +2904,7 @@ int zg_plan_destroy(zg_plan_t *p)
     }
     if (p->twin) zg_plan_destroy(p->twin);
     drop_graph(p);
-    if (p->capture_stream) (void)hipStreamDestroy(p->capture_stream);
+    if (p->own_stream) (void)hipStreamDestroy(p->own_stream);
     if (p->mailbox) (void)hipHostFree(p->mailbox);
     delete p;
     return ZG_OK;
@@ -2942,40 +2954,46 @@ int zg_plan_outputs(const zg_plan_t *p, zg_outputs *o)
     return ZG_OK;
 }
 
-// zg_step and zg_step_timed: fill the next mailbox slot, then replay the captured graph - or, for an eager plan and for
-// the timed variant, enqueue the step's kernels one by one
+// zg_step and zg_step_timed.  The step's launches go into the stream one by one, the inputs with the first of them: the next step's first kernel
+// starts when this one's last has ended, where the replay of a captured graph leaves the stream idle for 8 us, it reads its inputs from nowhere, and
+// a launch costs the host 1.5 to 2 us where a replay costs it 15 to 25.  us per step replayed / launched, one plan: two hops of 717 edges 23.8 / 18.6, 2.4 M
+// vertices, three hops and 250 k edges 113 / 108, two hops and 102 k edges 61.2 / 57.1, 110 M vertices 270 / 266; four plans on four streams, 64 seeds each: 26.6 / 7.1.
+// A step with its twin's launches behind it (ZG_PLAN_AUTO_FALLBACK) is replayed: twice the launches gain little (107.4 / 104.1, the
+// host 30 / 35), and that it is one graph launch is part of its contract.  (The mailbox slot is filled for every step: a step
+// that is replayed may follow one that is not.)
 static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, void *stream, StepProbe *probe)
 {
     if (!p || !d_seeds) return fail(ZG_EINVAL, "null argument");
-    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (p->broken) return fail(ZG_ESTATE, "an earlier step of this plan was enqueued in part: its scratch state is undefined");
+    Queue q{static_cast<hipStream_t>(stream)};
     // back-pressure without touching the device: wait (host only) while every mailbox slot is taken by a
     // step that has not finished yet
     if ((uint32_t)(p->issued - p->mailbox->completed) >= (uint32_t)kMailboxSlots - 1u &&
         !wait_completed(p, p->issued - ((uint32_t)kMailboxSlots - 2u), kHostWaitSeconds))
         return fail(ZG_ESTATE, "the device finished no step of this plan for 30 s while 255 are queued; nothing was enqueued");
+    if (!probe && replays_graph(p) && !p->graph_exec) return fail(ZG_ESTATE, "plan has no captured graph");
     const uint32_t slot = p->issued % kMailboxSlots;
     p->mailbox->slot[slot].seeds = reinterpret_cast<unsigned long long>(d_seeds);
     p->mailbox->slot[slot].key = rng_key;
     std::atomic_thread_fence(std::memory_order_seq_cst);
+    if (!probe && replays_graph(p)) {
+        ZG_HIP(hipGraphLaunch(p->graph_exec, q.st));
+    } else {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (q.st) ZG_HIP(hipStreamIsCapturing(q.st, &capture));
+        const int rc = enqueue_step(p, q, StepInputs{d_seeds, rng_key}, probe);
+        if (capture != hipStreamCaptureStatusNone) return rc; // recorded into the caller's graph: it runs, and counts as a step, when that is replayed
+        if (rc != ZG_OK) {
+            p->broken = q.launched > 0; // (else nothing was enqueued: the slot is free again)
+            return rc;
+        }
+    }
+    // only now may an earlier step copy the slot ahead of time: a slot whose launch failed is filled again later
     p->issued += 1;
-    int rc = ZG_OK;
-    if (probe || (p->flags & ZG_PLAN_EAGER)) {
-        rc = enqueue_step(p, st, probe);
-    } else if (!p->graph_exec) {
-        rc = fail(ZG_ESTATE, "plan has no captured graph");
-    } else {
-        hipError_t e = hipGraphLaunch(p->graph_exec, st);
-        if (e != hipSuccess) rc = fail(ZG_EHIP, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
-    }
-    if (rc != ZG_OK) {
-        p->issued -= 1; // nothing was enqueued: the slot is free again
-    } else {
-        // only now may an earlier step copy the slot ahead of time: a slot whose launch failed is filled again later
-        reinterpret_cast<std::atomic<uint32_t> *>(&p->mailbox->issued)->store(p->issued, std::memory_order_release);
-        p->last_stream = st;
-        p->stepped = true;
-    }
-    return rc;
+    reinterpret_cast<std::atomic<uint32_t> *>(&p->mailbox->issued)->store(p->issued, std::memory_order_release);
+    p->last_stream = q.st;
+    p->stepped = true;
+    return ZG_OK;
 }
 
 int zg_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, void *stream)
@@ -3001,9 +3019,9 @@ int zg_plan_replay_features(zg_plan_t *p, int32_t which, void *stream)
     if (which != 0 && which != 1) return fail(ZG_EINVAL, "which must be 0 (gather) or 1 (aggregation)");
     RowArgs gat, agg;
     step_feature_args(p, &gat, &agg);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (which == 0) return launch_gather(gat, relabel_args(p, 0, false), st);
-    return launch_aggregate(agg, finish_args(p, false), st);
+    Queue q{static_cast<hipStream_t>(stream)};
+    if (which == 0) return launch_gather(gat, relabel_args(p, 0, false), q);
+    return launch_aggregate(agg, finish_args(p, false), q);
 }
 
 int zg_pilot_update(const zg_plan_t *p, int64_t *largest, void *stream)
@@ -3214,7 +3232,8 @@ int zg_gather(zg_plan_t *p, const float *d_feat, int64_t ld, int32_t dim, float 
     if (!p || !d_feat || !d_out) return fail(ZG_EINVAL, "null argument");
     if (dim < 1 || dim > 32768 || ld < dim || ld_out < dim) return fail(ZG_EINVAL, "dim outside 1..32768 or a row stride < dim");
     const RowArgs gat = gather_args(p, d_feat, ld, dim, d_out, ld_out, p->lay.num_hops);
-    return launch_gather(gat, relabel_args(p, 0, false), static_cast<hipStream_t>(stream));
+    Queue q{static_cast<hipStream_t>(stream)};
+    return launch_gather(gat, relabel_args(p, 0, false), q);
 }
 
 int zg_aggregate_mean(zg_plan_t *p, int32_t hop, const float *d_in, int64_t ld_in, int32_t dim, float *d_out, int64_t ld_out,
@@ -3224,7 +3243,8 @@ int zg_aggregate_mean(zg_plan_t *p, int32_t hop, const float *d_in, int64_t ld_i
     if (hop < 0 || hop >= p->lay.num_hops) return fail(ZG_EINVAL, "hop out of range");
     if (dim < 1 || dim > 32768 || ld_in < dim || ld_out < dim) return fail(ZG_EINVAL, "dim outside 1..32768 or a row stride < dim");
     const RowArgs agg = aggregate_args(p, hop, d_in, ld_in, dim, d_out, ld_out, false);
-    return launch_aggregate(agg, finish_args(p, false), static_cast<hipStream_t>(stream));
+    Queue q{static_cast<hipStream_t>(stream)};
+    return launch_aggregate(agg, finish_args(p, false), q);
 }
 
 int zg_overflow_flag(const zg_plan_t *p, const uint32_t **d_flag)

@@ -359,7 +359,7 @@ class StepResult:
 
 
 class Plan:
-    """A provisioned execution envelope + captured step for (graph, fanouts, batch)."""
+    """A provisioned execution envelope and its step for (graph, fanouts, batch)."""
 
     def __init__(self, graph: Graph, fanouts: Sequence[int], batch: int, env: Optional[Envelope] = None,
                  feat_dim: int = 0, stream=None, workspace_slack: int = 0):

@@ -7,7 +7,7 @@ import torch
 
 from paper_2605_29346_amd import workloads as W
 from paper_2605_29346_amd import zg
-from gpu_util import agg_error, compare_blocks, compare_truncated, run_and_compare, samples_in_one_workgroup, to_host_graph, truncated_blocks
+from gpu_util import agg_error, compare_blocks, compare_features, compare_truncated, run_and_compare, samples_in_one_workgroup, to_host_graph, truncated_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -324,3 +324,35 @@ def test_totals_worked_out_where_a_cap_cuts_the_step(oracle, nodes, draws, hop):
         for plan, w in zip(plans, want):
             assert plan.step_status() == (4 * rep + 4, zg.FLAG_HOP_OVERFLOW(hop))
             compare_truncated(plan, w, f"rep {rep}")
+
+
+@pytest.mark.parametrize("dim", [0, 8])
+@pytest.mark.parametrize("batch", [300, 24])  # a launch per hop; all hops in one workgroup
+def test_a_step_recorded_into_the_callers_graph(oracle, dim, batch):
+    # replays, each a step of the plan, between steps that are enqueued; one recording is never replayed and counts for nothing
+    g = W.rmat_graph(30_000, 600_000, 21)
+    feat = W.feature_table(30_000, 8, 4)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (8, 6), batch, zg.make_envelope(zg.ENV_MAX), feat_dim=dim)
+    assert samples_in_one_workgroup(plan) == (batch == 24)
+    if dim:
+        plan.bind_features(feat.cuda())
+    pool, og, stream = W.SeedPool(g, batch, 2), to_host_graph(oracle, g), torch.cuda.Stream()
+    batches = [pool.batch_for(s).cuda() for s in range(3)]
+    torch.cuda.synchronize()
+    recorded = [torch.cuda.CUDAGraph() for _ in range(2)]
+    for s, rec in enumerate(recorded):
+        with torch.cuda.graph(rec, stream=stream):
+            plan.step(batches[s], 70 + s, stream)
+    assert plan.step_status() == (0, 0)
+    steps = 0
+    for r in range(4):
+        for s in (1, 2):
+            recorded[1].replay() if s == 1 else plan.step(batches[2], 72)
+            steps += 1
+            res = plan.read_step()
+            ref = og.sample_blocks(batches[s].cpu().numpy(), (8, 6), 70 + s)
+            compare_blocks(res, ref, f"replay {r}, batch {s}")
+            if dim:
+                compare_features(oracle, res, ref, feat.numpy(), f"replay {r}, batch {s}")
+            assert plan.step_status() == (steps, 0) and plan.epoch() == steps
+    plan.close()  # (waits for nothing that was not replayed)
