@@ -100,49 +100,68 @@ __device__ __forceinline__ void chain_publish(uint64_t *status, uint32_t t, uint
     st_store(&status[t], (t == 0u ? kStPrefix : kStAggregate) | total);
 }
 
-// the publishing wavefront's stores have been performed; behind a barrier the workgroup may change what its totals were taken from
+// the publishing wavefront's stores have been performed; behind a barrier the workgroup may change what its totals were taken from (the wavefront
+// that publishes is one that looks back: chain_prefix ends with this)
 __device__ __forceinline__ void publish_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// all 64 lanes of one wavefront: the sum of the totals of tickets 0 .. t-1, after this ticket's own was published
-template <class Missing>
+// all 64 lanes of one wavefront: the sum of the totals of tickets 0 .. t-1, after this ticket's own was published.  A look goes
+// back WINDOWS windows of 64 tickets, all their status words on the way at once.  Four in launch 0 and for the closing launch's tiles of words, whose tickets publish at
+// about the same time and find no prefix nearby: with a window per look, a microsecond each, the last of 235 tickets had its sum 6 us
+// after the last total was published, now 2 us.  One where what is waited for is other tickets' loads (a launch of 2 M edges 47.2 us, with
+// four 49.4).
+template <int WINDOWS, class Missing>
 __device__ __forceinline__ uint32_t chain_prefix(uint64_t *status, uint32_t t, uint32_t total, Drmb *d, int lane, uint32_t patience, const Missing &missing)
 {
     uint32_t excl = 0, polls = 0;
-    if (t == 0u) return 0u;
-    for (int64_t base = (int64_t)t - 1;; base -= 64) {
-        // the 64 status words base, base-1, .. base-63 (indices below zero count as an inclusive prefix of zero)
-        const int64_t idx = base - lane;
-        uint64_t st;
-        uint32_t worked_out = 0;             // this lane's ticket's total, ...
-        unsigned long long known = 0ull, pm; // ... where it had to be; the lanes whose ticket's prefix is there
-        for (;;) {
-            st = idx >= 0 ? st_load(&status[idx]) : kStPrefix;
-            if ((st >> 62) == 0 && ((known >> lane) & 1ull)) st = kStAggregate | worked_out;
-            pm = __ballot((st >> 62) == 2);
-            const unsigned long long none = __ballot((st >> 62) == 0) & (pm ? (pm & (0ull - pm)) - 1ull : ~0ull); // (none beyond the nearest prefix)
-            if (!none) break;
-            if (++polls > patience) {
-                if (patience == kSpinLimit) { // drawn tickets: the step's outputs are invalid, both the sticky and the per-step word say so
-                    if (lane == 0) {
-                        atomicOr(&d->flags, ZG_FLAG_INTERNAL);
-                        atomicOr(&d->step_flags, ZG_FLAG_INTERNAL);
-                    }
-                    break;
-                }
-                // the nearest one; then another look at all of them: the others, or a prefix, may be there by now
-                const int l = __ffsll((long long)none) - 1;
-                const uint32_t v = missing((uint32_t)(base - l));
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // read before that look
-                if (lane == l) worked_out = v;
-                known |= 1ull << l;
-                continue;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        const int last = pm ? __ffsll((long long)pm) - 1 : 63;
-        excl += wave_sum(lane <= last ? (uint32_t)st : 0u);
-        if (pm || base < 64 || polls > kSpinLimit) break;
+    if (t == 0u) {
+        publish_done();
+        return 0u;
     }
+    uint32_t worked_out = 0;         // this lane's ticket's total in the first window, ...
+    unsigned long long known = 0ull; // ... where it had to be
+    for (int64_t base = (int64_t)t - 1;;) {
+        // window w: the status words base - 64 w, .. of 64 tickets (indices below zero count as an inclusive prefix of zero)
+        uint64_t st[WINDOWS];
+#pragma unroll
+        for (int w = 0; w < WINDOWS; ++w) {
+            const int64_t idx = base - 64 * w - lane;
+            st[w] = idx >= 0 ? st_load(&status[idx]) : kStPrefix;
+        }
+        if ((st[0] >> 62) == 0 && ((known >> lane) & 1ull)) st[0] = kStAggregate | worked_out;
+        unsigned long long none = 0ull, pm = 0ull; // of the last window looked at: tickets whose total is not there, those whose prefix is
+#pragma unroll
+        for (int w = 0; w < WINDOWS; ++w) {
+            if (none || pm) break;
+            pm = __ballot((st[w] >> 62) == 2);
+            none = __ballot((st[w] >> 62) == 0) & (pm ? (pm & (0ull - pm)) - 1ull : ~0ull); // (none beyond the nearest prefix)
+            if (none) break;
+            excl += wave_sum(lane <= (pm ? __ffsll((long long)pm) - 1 : 63) ? (uint32_t)st[w] : 0u);
+            base -= 64;
+            known = 0ull;
+        }
+        if (!none) {
+            if (pm) break;
+            continue;
+        }
+        if (++polls > patience) {
+            if (patience == kSpinLimit) { // drawn tickets: the step's outputs are invalid, both the sticky and the per-step word say so
+                if (lane == 0) {
+                    atomicOr(&d->flags, ZG_FLAG_INTERNAL);
+                    atomicOr(&d->step_flags, ZG_FLAG_INTERNAL);
+                }
+                break;
+            }
+            // the nearest one; then another look at all of them: the others, or a prefix, may be there by now
+            const int l = __ffsll((long long)none) - 1;
+            const uint32_t v = missing((uint32_t)(base - l));
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // read before that look
+            if (lane == l) worked_out = v;
+            known |= 1ull << l;
+            continue;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    publish_done(); // (with the looks behind it nothing is left to wait for)
     if (lane == 0) st_store(&status[t], kStPrefix | (uint32_t)(excl + total));
     return excl;
 }
@@ -590,20 +609,24 @@ __device__ __forceinline__ Slot resolve_slot(const HopArgs &a, const HopShared &
 // A pass is bound by instruction issue (2 M edges: seven passes of 32 wavefronts per compute unit, 3 us each, the ids' loads 1 us of it):
 // whole products in Philox, register moves instead of ds_bpermute in floyd_drawn_before and the loads' overlap took the hop launches from 23.4
 // to 19.0 us (430 k edges), 18.0 to 16.3 (240 k), 14.5 to 14.0 (130 k); 54 us stay 54 at 2 M, where the random loads take over.
-__device__ __forceinline__ void load_ids(const HopArgs &a, const HopShared &sh, uint32_t key_lo, uint32_t key_hi, uint32_t row0, uint32_t row_end,
+struct IdOut { // a load that is out: its id goes to s_ids[at]
+    int32_t id;
+    uint32_t at;
+    bool out;
+};
+
+__device__ __forceinline__ IdOut load_ids(const HopArgs &a, const HopShared &sh, uint32_t key_lo, uint32_t key_hi, uint32_t row0, uint32_t row_end,
                                          uint32_t step, int lane, uint32_t e0, int32_t *s_ids)
 {
-    int32_t id = 0;
-    uint32_t at = 0;
-    bool out = false; // a load is out, its id goes to s_ids[at]
+    IdOut x = {0, 0u, false};
     for (; row0 < row_end; row0 += step) {
         const Slot slot = resolve_slot(a, sh, key_lo, key_hi, row0, row_end, lane);
-        if (out) s_ids[at] = id;
-        out = slot.taken;
-        at = slot.edge - e0;
-        if (out) id = a.indices[slot.src];
+        if (x.out) s_ids[x.at] = x.id;
+        x.out = slot.taken;
+        x.at = slot.edge - e0;
+        if (x.out) x.id = a.indices[slot.src];
     }
-    if (out) s_ids[at] = id;
+    return x;
 }
 
 // Marks.  A hop that reaches many of the graph's vertices (bytes_next) stores a byte per sampled edge: idempotent stores
@@ -811,14 +834,22 @@ __device__ __forceinline__ void load_tile(const HopArgs &a, size_t tile0, uint32
         }
 }
 
-// Clears a word's mark bytes for the hop after next; where tags are still needed (`tagged`) a new vertex's byte stays until its tag has
-// been read.
-__device__ __forceinline__ void clear_bytes(uint4 *b, uint32_t marked, uint32_t fresh, bool tagged)
+// a word of a tile: its marks, and those of new vertices
+struct TileWord {
+    uint32_t marked, fresh;
+};
+
+// Clears a word's marks for the hop after next; where tags are still needed (`tagged`) a new vertex's byte stays until its tag has been read.
+template <bool BYTES>
+__device__ __forceinline__ void clear_marks(const HopArgs &a, size_t word, TileWord x, bool tagged)
 {
-    if (!tagged || fresh == 0u)
-        b[0] = b[1] = make_uint4(0u, 0u, 0u, 0u);
+    uint4 *const bytes = reinterpret_cast<uint4 *>(a.marks_prev) + word * 2u;
+    if (!BYTES)
+        a.marks_prev[word] = 0u;
+    else if (!tagged || x.fresh == 0u)
+        bytes[0] = bytes[1] = make_uint4(0u, 0u, 0u, 0u);
     else
-        for (uint32_t old = marked & ~fresh; old; old &= old - 1u) reinterpret_cast<uint8_t *>(b)[__ffs((int)old) - 1] = 0;
+        for (uint32_t old = x.marked & ~x.fresh; old; old &= old - 1u) reinterpret_cast<uint8_t *>(bytes)[__ffs((int)old) - 1] = 0;
 }
 
 // a word of a tile, whoever's it is: marked and not "seen" (rarely needed, and in few registers)
@@ -881,11 +912,11 @@ __device__ __forceinline__ void expand_piece(const uint4 &x, uint32_t j, uint32_
 }
 
 // A tile of at most a word per lane (the graph is small for its ranking tiles, the tile dense with new vertices): the lane's word
-// of new vertices, also left in s_words.  A word per lane while it is read, and 2^chunk_log2 vertices per lane once it is ranked and
+// of marks and of new vertices, the latter also left in s_words.  A word per lane while it is read, and 2^chunk_log2 vertices per lane once it is ranked and
 // expanded (pieces of 128 left 16 lanes of 1024 to walk through a tile of 64 words, up to 128 vertices one after another: a hop launch
 // over 250 k vertices 15.6 -> 14.5 us, with 2.4 M vertices 57 -> 54).
 template <int NT, bool BYTES>
-__device__ __forceinline__ uint32_t load_words(const HopArgs &a, size_t tile0, uint32_t words, uint32_t tid, uint32_t *s_words)
+__device__ __forceinline__ TileWord load_words(const HopArgs &a, size_t tile0, uint32_t words, uint32_t tid, uint32_t *s_words)
 {
     uint32_t sn = 0u, marked = 0u;
     if (tid < words) sn = a.seen[tile0 + tid];
@@ -903,23 +934,18 @@ __device__ __forceinline__ uint32_t load_words(const HopArgs &a, size_t tile0, u
         marked = a.marks_prev[tile0 + tid];
     }
     if (tid < words) s_words[tid] = marked & ~sn;
-    return marked & ~sn;
+    return {marked, marked & ~sn};
 }
 
-// ... and what changes once the tile's totals are published: its marks are cleared - read again: no register holds them that long -
-// and, with JOIN, its new vertices join "seen".
-template <bool BYTES, bool JOIN>
+// ... and what changes once the tile's totals are published: its marks are cleared - read again: no register of k_hop holds them that long -
+// and its new vertices join "seen".
+template <bool BYTES>
 __device__ __forceinline__ void settle_word(const HopArgs &a, size_t tile0, uint32_t words, uint32_t tid, const uint32_t *s_words)
 {
     if (tid >= words) return;
-    uint4 *const bytes = reinterpret_cast<uint4 *>(a.marks_prev) + (tile0 + tid) * 2u;
-    const uint32_t marked = BYTES ? marks32(bytes) : a.marks_prev[tile0 + tid], fresh = s_words[tid];
-    if (JOIN && fresh) a.seen[tile0 + tid] |= fresh;
-    if (marked == 0u) return;
-    if (BYTES)
-        clear_bytes(bytes, marked, fresh, !JOIN && a.tag.shift != 0);
-    else
-        a.marks_prev[tile0 + tid] = 0u;
+    const uint32_t marked = BYTES ? marks32(reinterpret_cast<uint4 *>(a.marks_prev) + (tile0 + tid) * 2u) : a.marks_prev[tile0 + tid], fresh = s_words[tid];
+    if (fresh) a.seen[tile0 + tid] |= fresh;
+    if (marked) clear_marks<BYTES>(a, tile0 + tid, {marked, fresh}, false);
 }
 
 // ... and its ranks: the lane's chunk of the tile's words (in s_words: barriers before the first and after the last use are in
@@ -1036,7 +1062,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     if (old) {
         m = n_old - r0 < rows ? n_old - r0 : rows;
     } else if (by_chunks) {
-        m = rank_and_expand(load_words<kHopBlock, PREV_BYTES>(a, tile0, a.words_per_tile, tid, s_words), 0u, true);
+        m = rank_and_expand(load_words<kHopBlock, PREV_BYTES>(a, tile0, a.words_per_tile, tid, s_words).fresh, 0u, true);
     } else {
         uint4 x[R];
         uint32_t lex[R];
@@ -1117,15 +1143,15 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     bool chained = false;
     auto take_prefixes = [&]() { // wavefront 0 sums up the new vertices before this tile, wavefront 1 the edges before this ticket
         if (wave == 0u && !old) {
-            publish_done();
-            const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane, a.patience, [&](uint32_t t) { return missing_vertices<PREV_BYTES>(a, t, lane); });
+            const uint32_t c = chain_prefix<FIRST ? 4 : 1>(a.status_cnt, tile, m, d, (int)lane, a.patience, [&](uint32_t t) { return missing_vertices<PREV_BYTES>(a, t, lane); });
             if (lane == 0) sh.base_cnt = c;
         }
         if (wave == 1u) {
-            const uint32_t e = chain_prefix(a.status_edge, ticket, ticket_edges, d, (int)lane, a.patience, missing_edges);
+            const uint32_t e = chain_prefix<FIRST ? 4 : 1>(a.status_edge, ticket, ticket_edges, d, (int)lane, a.patience, missing_edges);
             if (lane == 0) sh.base_edge = e;
         }
-        __syncthreads();
+    };
+    auto use_prefixes = [&]() {
         if (!old) rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.base_cnt); // row index of the ticket's first row
         room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;                                  // how many of its rows fit (old rows: all)
         ebase = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.base_edge);
@@ -1151,11 +1177,11 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
         uint32_t keep = 0;
         for (uint32_t b0 = 0; b0 == 0u || b0 < nrows; b0 += stage_rows) {
             const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0];
-            load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
-            if (!chained)
-                take_prefixes();
-            else
-                __syncthreads();
+            const IdOut last = load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
+            if (!chained) take_prefixes(); // (while the last id is on its way)
+            if (last.out) s_ids[last.at] = last.id;
+            __syncthreads();
+            if (!chained) use_prefixes();
             keep = room > c0 ? (room - c0 < nrows ? room - c0 : nrows) : 0u; // dropped rows sample nothing
             const uint32_t e1 = keep > b0 ? sh.rp[keep < b1 ? keep : b1] : e0;
             if (NEXT_BYTES) {
@@ -1205,7 +1231,7 @@ __global__ __launch_bounds__(kHopBlock, 8) void k_hop(HopArgs a, HopRoles o)
     }
 
     const uint32_t tid_end = own_vector(tid);
-    if (by_chunks) settle_word<PREV_BYTES, true>(a, tile0, a.words_per_tile, tid_end, s_words);
+    if (by_chunks) settle_word<PREV_BYTES>(a, tile0, a.words_per_tile, tid_end, s_words);
 
     if (m > room) {
         // ---- the cap cuts into this tile: the vertices dropped leave "seen" again
@@ -1330,7 +1356,8 @@ __global__ __launch_bounds__(kHopBlock) void k_small(SmallArgs s)
             __syncthreads();
             for (uint32_t b0 = 0; b0 < nrows; b0 += stage_rows) {
                 const uint32_t b1 = b0 + stage_rows < nrows ? b0 + stage_rows : nrows, e0 = sh.rp[b0], e1 = sh.rp[b1];
-                load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
+                const IdOut last = load_ids(a, sh, key_lo, key_hi, b0 + wave * rpw, b1, step, (int)lane, e0, s_ids);
+                if (last.out) s_ids[last.at] = last.id;
                 __syncthreads();
                 for (uint32_t e = e0 + tid; e < e1; e += (uint32_t)kHopBlock) {
                     const uint32_t edge = ebase + e;
@@ -1414,8 +1441,9 @@ struct CloseRoles { // the closing launch's other workgroups
 // first in the grid: chains of dependent accesses, they all start at once and leave most of the chip to the copy, which is
 // bound by bandwidth and runs beside them.  Measured at 110 M vertices, 433 k new ones and a copy of 157 k rows of 512 bytes
 // (160 MB, 34 us alone): 54 us; 1024 lanes per ticket, tickets and copy alternating in the grid: 56 us.  Without a copy,
-// 2.4 M vertices and 668 k new ones: 20.6 us (31 us when a workgroup expanded 1024 of its 2800 vertices at a time, in pieces of 128 per
-// lane); 137 k new, with a copy of 25 MB: 21 us, with 1024 lanes 26 us.  A byte-marked tile of 8192 words needs 49 KB of LDS with batches
+// 2.4 M vertices and 662 k new ones: 18.1 us (21.0 with a word's vertices one after another in a lane and one window of tickets per look:
+// the last lane had its up to 28 written 3.3 us after the tile was ranked, and the last tile its prefix 6 us after the last total was out); 72 k
+// new, with a copy of 28 MB: 11.2 us (12.8); 142 k new, with a copy of 48 MB: 20 us, with 1024 lanes 26 us.  A byte-marked tile of 8192 words needs 49 KB of LDS with batches
 // of 4096 vertices, which leaves a compute unit room for three such workgroups, not four as with 1024: faster all the same, 66.2 -> 60.0 us (40 M
 // vertices, 2 M edges in the last hop, a copy of 64 floats a row) and 125.7 -> 124.9 (100 M, 6 M edges, 32 floats).
 template <bool BYTES>
@@ -1424,8 +1452,8 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
     constexpr int R = kHopMaxTileWords / 4 / kCloseBlock;
     constexpr uint32_t kBatch = kCloseBatch; // vertices expanded at a time
     __shared__ uint32_t s_drawn, s_base, s_wsum[64];
-    __shared__ int32_t s_v[kBatch];
-    extern __shared__ __align__(16) uint32_t s_words[]; // the tile's words (bit marks: of a tile of at most a word per lane)
+    extern __shared__ __align__(16) uint32_t s_dyn[]; // see close_lds
+    int32_t *const s_v = reinterpret_cast<int32_t *>(s_dyn);
     if (gate_closed(a.gate)) return;
     if (blockIdx.x >= a.blocks) {
         uint32_t b = blockIdx.x - a.blocks;
@@ -1449,57 +1477,98 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
         __syncthreads();
         tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_drawn);
     }
-    const uint32_t np = a.words_per_tile / 4u;
     const size_t tile0 = (size_t)tile * a.words_per_tile;
-    uint4 x[R];
-    uint32_t lex[R];
-    uint32_t m, chunk = 0u, before_chunk = 0u;
-    const bool by_chunks = a.words_per_tile <= (uint32_t)kCloseBlock;
-    if (by_chunks) {
-        const uint32_t word = load_words<kCloseBlock, BYTES>(a, tile0, a.words_per_tile, tid, s_words);
-        m = rank_chunks<kCloseBlock>(word, a.chunk_log2, a.words_per_tile, s_words, s_wsum, tid, chunk, before_chunk);
-    } else {
-        load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
-        m = rank_pieces<kCloseBlock, R>(x, lex, s_wsum, np, wave, lane);
-    }
-    if (wave == 0u) {
-        if (lane == 0) chain_publish(a.status_cnt, tile, m);
-        publish_done();
-        const uint32_t c = chain_prefix(a.status_cnt, tile, m, d, (int)lane, a.patience, [&](uint32_t t) { return missing_vertices<BYTES>(a, t, lane); });
-        if (lane == 0) s_base = c;
-    }
-    uint32_t rank0 = 0, room = 0;
     const bool tagged = BYTES && a.tag.shift != 0;
     uint8_t *const bytes = reinterpret_cast<uint8_t *>(a.marks_prev);
-    for (uint32_t c0 = 0; c0 == 0 || c0 < m; c0 += kBatch) {
-        if (c0) __syncthreads(); // the last batch has been read
-        if (by_chunks) {
-            expand_chunk(chunk, before_chunk, ((uint32_t)tile0 << 5) + (tid << a.chunk_log2), c0, kBatch, s_v);
-        } else {
-            const uint32_t t = own_vector(tid);
-#pragma unroll
-            for (int u = 0; u < R; ++u)
-                if (u * (uint32_t)kCloseBlock + t < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + t) * 4u, c0, kBatch, s_v);
+    uint32_t m, rank0 = 0, room = 0;
+    const bool by_words = a.words_per_tile <= (uint32_t)kCloseBlock;
+    auto take_prefix = [&]() { // the new vertices before this tile
+        if (wave == 0u) {
+            auto missing = [&](uint32_t t) { return missing_vertices<BYTES>(a, t, lane); };
+            const uint32_t c = by_words ? chain_prefix<4>(a.status_cnt, tile, m, d, (int)lane, a.patience, missing)
+                                        : chain_prefix<1>(a.status_cnt, tile, m, d, (int)lane, a.patience, missing);
+            if (lane == 0) s_base = c;
         }
-        __syncthreads();
+    };
+    auto use_prefix = [&]() {
         rank0 = n_old + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_base);
         room = rank0 < a.cap_rows ? a.cap_rows - rank0 : 0u;
+    };
+    auto write_out = [&](int32_t gid, uint32_t j, uint32_t mark) { // the tile's new vertex number j
+        if (j < room) a.S[rank0 + j] = gid;
+        a.local_id[gid] = j < room ? a.tag.entry(rank0 + j, mark) : -1;
+    };
+    if (by_words) {
+        const uint32_t words = a.words_per_tile;
+        uint32_t *const s_words = s_dyn + kBatch;
+        uint2 *const s_rank = reinterpret_cast<uint2 *>(s_words + words); // a word's new vertices, and those before them
+        const TileWord word = load_words<kCloseBlock, BYTES>(a, tile0, words, tid, s_words);
+        uint32_t chunk, before;
+        m = rank_chunks<kCloseBlock>(word.fresh, a.chunk_log2, words, s_words, s_wsum, tid, chunk, before);
+        if (tid == 0) chain_publish(a.status_cnt, tile, m);
+        // a whole word is too long a walk for a lane: a vertex per lane
+        const bool by_vertex = a.chunk_log2 == 5u;
+        if (by_vertex) {
+            if (tid < words) s_rank[tid] = make_uint2(chunk, before);
+            __syncthreads();
+        }
+        const uint32_t first = (uint32_t)tile0 << 5;
+        for (uint32_t c0 = 0; c0 == 0 || c0 < m; c0 += kBatch) {
+            if (c0) __syncthreads(); // the last batch has been read
+            if (by_vertex) {
+#pragma unroll 4
+                for (uint32_t i = tid; i < 32u * words; i += (uint32_t)kCloseBlock) {
+                    const uint2 x = s_rank[i >> 5];
+                    const uint32_t j = x.y + __popc(x.x & ((1u << (i & 31u)) - 1u)) - c0;
+                    if (((x.x >> (i & 31u)) & 1u) && j < kBatch) s_v[j] = (int32_t)(first + i);
+                }
+            } else {
+                expand_chunk(chunk, before, first + (tid << a.chunk_log2), c0, kBatch, s_v);
+            }
+            if (c0 == 0) take_prefix();
+            __syncthreads();
+            use_prefix();
 #pragma unroll 2
-        for (uint32_t i = tid; i < kBatch && c0 + i < m; i += kCloseBlock) {
-            const uint32_t j = c0 + i;
-            {
+            for (uint32_t i = tid; i < kBatch && c0 + i < m; i += kCloseBlock) {
                 const int32_t gid = s_v[i];
                 uint32_t mark = 0u;
                 if (tagged) {
                     mark = bytes[gid];
                     bytes[gid] = 0;
                 }
-                if (j < room) a.S[rank0 + j] = gid;
-                a.local_id[gid] = j < room ? a.tag.entry(rank0 + j, mark) : -1;
+                write_out(gid, c0 + i, mark);
+            }
+        }
+        if (tid < words && word.marked) clear_marks<BYTES>(a, tile0 + tid, word, tagged);
+    } else {
+        uint32_t *const s_words = s_dyn + kBatch;
+        const uint32_t np = a.words_per_tile / 4u;
+        uint4 x[R];
+        uint32_t lex[R];
+        load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
+        m = rank_pieces<kCloseBlock, R>(x, lex, s_wsum, np, wave, lane);
+        if (tid == 0) chain_publish(a.status_cnt, tile, m);
+        for (uint32_t c0 = 0; c0 == 0 || c0 < m; c0 += kBatch) {
+            if (c0) __syncthreads(); // the last batch has been read
+            const uint32_t t = own_vector(tid);
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (u * (uint32_t)kCloseBlock + t < np) expand_piece(x[u], lex[u], (uint32_t)tile0 + (u * (uint32_t)kCloseBlock + t) * 4u, c0, kBatch, s_v);
+            if (c0 == 0) take_prefix();
+            __syncthreads();
+            use_prefix();
+#pragma unroll 2
+            for (uint32_t i = tid; i < kBatch && c0 + i < m; i += kCloseBlock) {
+                const int32_t gid = s_v[i];
+                uint32_t mark = 0u;
+                if (tagged) {
+                    mark = bytes[gid];
+                    bytes[gid] = 0;
+                }
+                write_out(gid, c0 + i, mark);
             }
         }
     }
-    if (by_chunks) settle_word<BYTES, false>(a, tile0, a.words_per_tile, own_vector(tid), s_words);
     if (tid == 0 && tile == a.rank_tiles - 1u) { // the last ticket publishes the hop's size
         const int32_t launch = own_scalar(a.launch);
         const uint64_t exact = (uint64_t)rank0 + m;
@@ -2627,6 +2696,14 @@ int launch_small(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_pl
     return q.launch(g->offsets_dtype == ZG_I64 ? k_small<int64_t> : k_small<int32_t>, 1u, kHopBlock, lds, sa);
 }
 
+// LDS of a ranking workgroup of the closing launch: the vertices expanded, the tile's words, and these with their ranks; of a tile of more
+// than a word per lane no ranks, and the words only out of mark bytes
+size_t close_lds(const HopArgs &a)
+{
+    const size_t words = a.words_per_tile;
+    return (size_t)kCloseBatch * 4 + (words <= (size_t)kCloseBlock ? words * 12 : a.bytes_prev ? words * 4 : 0);
+}
+
 // a whole step, in order, on one stream (a step's launches, or - captured once - those of a graph): the hop kernel's launches 0..H, then the
 // two feature launches.  With `gate` the kernels are those of gate's worst-case twin `p`, run on gate's inputs and
 // only if gate's step overflowed; `defer_completed` marks a plan whose gated twin follows in the same sequence.
@@ -2715,7 +2792,7 @@ int enqueue_body(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_pl
             CloseRoles roles = {ra, ride ? gat : no_rows};
             roles.gat.rows *= kCloseBlock / kBlock;
             roles.gat.blocks = ride ? (uint32_t)((L.node_cap[H - 1] + roles.gat.rows - 1) / roles.gat.rows) : 0u;
-            const size_t lds = ha.bytes_prev || ha.words_per_tile <= (uint32_t)kCloseBlock ? (size_t)ha.words_per_tile * 4 : 0;
+            const size_t lds = std::max(close_lds(ha), ride ? (size_t)roles.gat.rows * 4 : 0);
             rc = q.launch(ha.bytes_prev ? k_close<true> : k_close<false>, ha.blocks + ra.blocks + roles.gat.blocks, kCloseBlock, lds, ha, roles);
         } else {
             const HopRoles roles = {ra, ia};

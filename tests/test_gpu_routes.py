@@ -356,3 +356,22 @@ def test_a_step_recorded_into_the_callers_graph(oracle, dim, batch):
                 compare_features(oracle, res, ref, feat.numpy(), f"replay {r}, batch {s}")
             assert plan.step_status() == (steps, 0) and plan.epoch() == steps
     plan.close()  # (waits for nothing that was not replayed)
+
+
+@pytest.mark.parametrize("nodes,tickets", [
+    (32 * 64 * 2, 4),        # closing tiles of 64 words: a lane expands 4 vertices
+    (32 * 256 * 2, 4),       # ... 16
+    (32 * 257 * 2 - 5, 4),   # 288 words: a vertex per lane, the last word ragged
+    (32 * 512 * 2, 4),       # a word per lane, several batches of vertices to a tile
+    (32 * 64 * 300 + 1, 0),  # 235 tiles at most: several looks back
+])
+@pytest.mark.parametrize("dim", [0, 8])  # marks without and with tags
+def test_closing_tiles_of_any_width(oracle, nodes, tickets, dim):
+    g = W.rmat_graph(nodes, nodes * 30, 31)
+    feat = W.feature_table(nodes, dim, 4) if dim else None
+    env, plan = zg.make_envelope(zg.ENV_MAX, max_tickets=tickets), None
+    og = to_host_graph(oracle, g)
+    for s in range(3):  # (marks a step leaves behind show in the next)
+        seeds = np.random.RandomState(s).permutation(nodes)[:600].astype(np.int32)
+        plan, res, _ = run_and_compare(oracle, g, feat, seeds, (9, 20), 40 + s, env=env, plan=plan, og=og, label=f"step {s}")
+    assert not samples_in_one_workgroup(plan)
