@@ -349,12 +349,29 @@ __device__ __forceinline__ void ingest_block(const IngestArgs &a, uint32_t block
     }
 }
 
+// The last hop's new vertices carry, in the top bits of their id-map entry, the tag of the edge whose mark was the last to
+// land on the vertex's byte: that edge - and the odd other edge to the vertex with the same tag, which stores the same bytes -
+// writes the vertex's row of X.  As many tag bits as the node cap leaves of an int32's 31 (at most 7); with none left every
+// edge to a new vertex writes its row.
+// In a step whose frontier has `reach_rows` vertices or more, those of them that the last hop reaches again carry a tag too, and their rows are
+// written the same way instead of being copied (see gather_unreached_block).
+struct MarkTag {
+    int32_t shift; // tag = entry >> shift; 0: entries are plain local ids
+    uint32_t mask; // tag bits in use
+    uint32_t reach_rows;
+    __device__ __forceinline__ int32_t entry(uint32_t lid, uint32_t mark) const { return shift ? (int32_t)(lid | ((mark & mask) << shift)) : (int32_t)lid; }
+    __device__ __forceinline__ int32_t local_id(int32_t e) const { return shift && e >= 0 ? e & (int32_t)((1u << shift) - 1u) : e; }
+    __device__ __forceinline__ bool owns(int32_t e, uint32_t edge) const { return shift == 0 || ((uint32_t)e >> shift) == (edge & mask); }
+    __device__ __forceinline__ bool reaches(uint32_t frontier) const { return frontier >= reach_rows; }
+};
+
 struct RelabelArgs {
     const Drmb *drmb;
     const Drmb *gate; // consulted by the gather launch (the hop kernel has its own)
     const int32_t *nbr;
     const int32_t *local_id;
     int32_t *col;
+    MarkTag tag; // closing launch: how entries carry it, where other workgroups of the launch are adding it
     uint32_t num_nodes;
     int32_t hop;
     uint32_t blocks; // workgroups given to this role (0: role absent)
@@ -374,22 +391,10 @@ __device__ __forceinline__ void relabel_block(const RelabelArgs &a, uint32_t blo
 #pragma unroll 4
     for (uint32_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
         const int32_t g = a.nbr[e];
-        const int32_t id = (uint32_t)g < a.num_nodes ? a.local_id[g] : -1;
+        const int32_t id = a.tag.local_id((uint32_t)g < a.num_nodes ? a.local_id[g] : -1);
         a.col[e] = (uint32_t)id < n ? id : -1;
     }
 }
-
-// The last hop's new vertices carry, in the top bits of their id-map entry, the tag of the edge whose mark was the last to
-// land on the vertex's byte: that edge - and the odd other edge to the vertex with the same tag, which stores the same bytes -
-// writes the vertex's row of X.  As many tag bits as the node cap leaves of an int32's 31 (at most 7); with none left every
-// edge to a new vertex writes its row.
-struct MarkTag {
-    int32_t shift; // tag = entry >> shift; 0: entries are plain local ids
-    uint32_t mask; // tag bits in use
-    __device__ __forceinline__ int32_t entry(uint32_t lid, uint32_t mark) const { return shift ? (int32_t)(lid | ((mark & mask) << shift)) : (int32_t)lid; }
-    __device__ __forceinline__ int32_t local_id(int32_t e) const { return shift && e >= 0 ? e & (int32_t)((1u << shift) - 1u) : e; }
-    __device__ __forceinline__ bool owns(int32_t e, uint32_t edge) const { return shift == 0 || ((uint32_t)e >> shift) == (edge & mask); }
-};
 
 struct RowArgs {
     const float *src;       // gather: feature table; aggregate: input rows
@@ -431,8 +436,9 @@ template <> struct VecOf<1> {
 // "Gather": X[i,:] = feat[S[i],:].  A workgroup copies `rows` consecutive output rows; lanes walk the rows
 // as one flat run of 16-byte pieces so that rows whose length is not a multiple of the wave width still
 // fill every lane, four loads in flight per lane before the stores.
+// (`s_row`: which of the workgroup's rows these are, if not all)
 template <int VEC, bool STREAM, bool NT_STORE = false>
-__device__ __forceinline__ void gather_rows(const RowArgs &a, uint32_t row0, uint32_t rows, const int32_t *s_id)
+__device__ __forceinline__ void gather_rows(const RowArgs &a, uint32_t row0, uint32_t rows, const int32_t *s_id, const int32_t *s_row = nullptr)
 {
     typedef typename VecOf<VEC>::type T;
     const uint32_t total = rows * a.dimv;
@@ -455,7 +461,7 @@ __device__ __forceinline__ void gather_rows(const RowArgs &a, uint32_t row0, uin
         for (int u = 0; u < 4; ++u) {
             const uint32_t e = e0 + u * blockDim.x;
             if (e < total) {
-                T *dst = reinterpret_cast<T *>(a.dst + (int64_t)(row0 + r[u]) * a.ld_dst + c[u]);
+                T *dst = reinterpret_cast<T *>(a.dst + (int64_t)(row0 + (s_row ? (uint32_t)s_row[r[u]] : r[u])) * a.ld_dst + c[u]);
                 if (STREAM || NT_STORE)
                     __builtin_nontemporal_store(val[u], dst);
                 else
@@ -476,6 +482,40 @@ __device__ __forceinline__ void gather_rows_block(const RowArgs &a, uint32_t blo
     if (threadIdx.x < rows) s_id[threadIdx.x] = a.S[row0 + threadIdx.x];
     __syncthreads();
     gather_rows<VEC, false, true>(a, row0, rows, s_id); // nothing in the step reads these rows of X again: stored past the caches
+}
+
+// ... without those the last hop reaches again, where its marks are bytes with tags: an edge to such a vertex reads its row for the mean and writes it
+// into X on the way, as for a new vertex.  The vertex's entry gets the tag; its mark is this workgroup's to clear (the ranking
+// tiles clear new vertices').  Saves reading the row, and costs the aggregation what it costs to write it (4.2 TB/s): worth it where the copy is longer than the
+// ranking beside it by more than that, which both are bounds of.  us of the closing launch and the aggregation, all rows copied / these
+// left out: 216 k rows of 2400 bytes 930 / 857, 706 k of 512 629 / 601, 722 k of 400 476 / 465, 622 k of 300 377 / 363, 125 k of 1 KB 185 / 175, 28 k
+// of 2400 166 / 163, 33 k of 1 KB 80.2 / 78.0, 15 k of 2400 105.8 / 105.7; but 188 k rows of 400 bytes 156 / 163, 194 k of 256 115 / 117, 60 k of 400
+// 67 / 70.  Hence from 96 MB of frontier rows on (kReachBytes), from 32 MB where they are 1 KB or longer; by the step's own size.
+template <int VEC>
+__device__ __forceinline__ void gather_unreached_block(const RowArgs &a, uint32_t block, uint8_t *marks, int32_t *local_id, const MarkTag &tag, int32_t *s_mem)
+{
+    const uint32_t n = *a.n_rows;
+    const uint32_t row0 = block * a.rows;
+    if (row0 >= n) return;
+    const uint32_t rows = n - row0 < a.rows ? n - row0 : a.rows;
+    int32_t *const s_id = s_mem, *const s_row = s_mem + a.rows;
+    uint32_t *const s_left = reinterpret_cast<uint32_t *>(s_row + a.rows);
+    if (threadIdx.x == 0) *s_left = 0u;
+    __syncthreads();
+    if (threadIdx.x < rows) {
+        const int32_t g = a.S[row0 + threadIdx.x];
+        const uint32_t mark = g >= 0 ? marks[g] : 0u;
+        if (mark) {
+            marks[g] = 0;
+            local_id[g] = tag.entry(row0 + threadIdx.x, mark);
+        } else {
+            const uint32_t at = atomicAdd(s_left, 1u);
+            s_id[at] = g;
+            s_row[at] = (int32_t)threadIdx.x;
+        }
+    }
+    __syncthreads();
+    gather_rows<VEC, false, true>(a, row0, *s_left, s_id, s_row);
 }
 
 // a launch of its own.  When the gathered matrix of this step is larger than the caches can hold for the aggregation that
@@ -784,11 +824,11 @@ __device__ __forceinline__ uint32_t marks32(const uint4 *b)
 }
 
 // Reads a tile's marks, masks them with "seen", and clears them for the hop after next (tagged: a new vertex's byte stays until
-// its tag has been read).  Mark bytes become words in LDS first, 16 bytes per lane.  With JOIN the new vertices join
+// its tag has been read; with `reach` a frontier vertex's byte is the copy's to clear).  Mark bytes become words in LDS first, 16 bytes per lane.  With JOIN the new vertices join
 // "seen" at once: this workgroup is its words' only reader and writer in the launch.  The loads of all rounds are on their
 // way before the first is looked at, and so are the words of "seen".
 template <int NT, int R, bool BYTES, bool JOIN>
-__device__ __forceinline__ void load_tile(const HopArgs &a, size_t tile0, uint32_t np, uint32_t tid, uint4 (&x)[R], uint32_t *s_words)
+__device__ __forceinline__ void load_tile(const HopArgs &a, size_t tile0, uint32_t np, uint32_t tid, uint4 (&x)[R], uint32_t *s_words, bool reach = false)
 {
     uint4 *src = reinterpret_cast<uint4 *>(a.marks_prev) + (BYTES ? tile0 * 2u : tile0 / 4u), *seen = reinterpret_cast<uint4 *>(a.seen + tile0);
     if (BYTES) {
@@ -820,7 +860,7 @@ __device__ __forceinline__ void load_tile(const HopArgs &a, size_t tile0, uint32
             if (JOIN && piece_any(x[u])) seen[q] = make_uint4(sn[u].x | x[u].x, sn[u].y | x[u].y, sn[u].z | x[u].z, sn[u].w | x[u].w);
             if (!BYTES) {
                 src[q] = make_uint4(0u, 0u, 0u, 0u);
-            } else {
+            } else if (JOIN || !reach) {
 #pragma unroll
                 for (uint32_t c = 0; c < 4u; ++c) {
                     const uint32_t w = piece_word(marked, c), fresh = piece_word(x[u], c);
@@ -1462,10 +1502,16 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
             return;
         }
         b -= o.rel.blocks;
-        if (o.gat.vec4)
+        if (BYTES && a.tag.shift != 0 && a.tag.reaches(*o.gat.n_rows)) {
+            if (o.gat.vec4)
+                gather_unreached_block<4>(o.gat, b, reinterpret_cast<uint8_t *>(a.marks_prev), a.local_id, a.tag, s_v);
+            else
+                gather_unreached_block<1>(o.gat, b, reinterpret_cast<uint8_t *>(a.marks_prev), a.local_id, a.tag, s_v);
+        } else if (o.gat.vec4) {
             gather_rows_block<4>(o.gat, b, s_v);
-        else
+        } else {
             gather_rows_block<1>(o.gat, b, s_v);
+        }
         return;
     }
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
@@ -1478,7 +1524,7 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
         tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_drawn);
     }
     const size_t tile0 = (size_t)tile * a.words_per_tile;
-    const bool tagged = BYTES && a.tag.shift != 0;
+    const bool tagged = BYTES && a.tag.shift != 0, reach = tagged && a.tag.reaches(n_old);
     uint8_t *const bytes = reinterpret_cast<uint8_t *>(a.marks_prev);
     uint32_t m, rank0 = 0, room = 0;
     const bool by_words = a.words_per_tile <= (uint32_t)kCloseBlock;
@@ -1539,13 +1585,13 @@ __global__ __launch_bounds__(kCloseBlock, 8) void k_close(HopArgs a, CloseRoles 
                 write_out(gid, c0 + i, mark);
             }
         }
-        if (tid < words && word.marked) clear_marks<BYTES>(a, tile0 + tid, word, tagged);
+        if (!reach && tid < words && word.marked) clear_marks<BYTES>(a, tile0 + tid, word, tagged);
     } else {
         uint32_t *const s_words = s_dyn + kBatch;
         const uint32_t np = a.words_per_tile / 4u;
         uint4 x[R];
         uint32_t lex[R];
-        load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words);
+        load_tile<kCloseBlock, R, BYTES, false>(a, tile0, np, tid, x, s_words, reach);
         m = rank_pieces<kCloseBlock, R>(x, lex, s_wsum, np, wave, lane);
         if (tid == 0) chain_publish(a.status_cnt, tile, m);
         for (uint32_t c0 = 0; c0 == 0 || c0 < m; c0 += kBatch) {
@@ -1731,6 +1777,7 @@ __device__ __forceinline__ void aggregate_block(const RowArgs &a, uint32_t block
     int32_t *s_dst = s_col + a.rows * a.max_fanout; // [rows * max_fanout] when X is written on the way: row of X, or -1
     const uint32_t n = *a.n_rows;
     const uint32_t n_ids = *a.n_cols, n_in = a.col_out ? a.col_limit : n_ids;
+    const int32_t x_from = !a.own && a.tag.shift != 0 && a.tag.reaches(n) ? 0 : (int32_t)n;
     const uint32_t row0 = block * a.rows;
     if (row0 >= n) return;
     const uint32_t rows = n - row0 < a.rows ? n - row0 : a.rows;
@@ -1747,8 +1794,8 @@ __device__ __forceinline__ void aggregate_block(const RowArgs &a, uint32_t block
             const int32_t entry = valid ? a.local_id[c] : -1;
             const int32_t id = a.tag.local_id(entry), lid = (uint32_t)id < n_ids ? id : -1;
             a.col_out[e_begin + t] = lid;
-            // one edge to a vertex writes its row of X, if the vertex is new (the frontier's rows are the gather's)
-            if (a.x_dst) s_dst[t] = lid >= (int32_t)n && (a.own ? a.own[e_begin + t] != 0 : a.tag.owns(entry, (uint32_t)(e_begin + (int32_t)t))) ? lid : -1;
+            // one edge to a vertex writes its row of X, if the vertex is new or the frontier's rows are not the copy's
+            if (a.x_dst) s_dst[t] = lid >= x_from && (a.own ? a.own[e_begin + t] != 0 : a.tag.owns(entry, (uint32_t)(e_begin + (int32_t)t))) ? lid : -1;
         }
     }
     __syncthreads();
@@ -2606,7 +2653,7 @@ int launch_aggregate(const RowArgs &agg, const FinishArgs &fa, Queue &q, const R
 MarkTag mark_tag(const zg_plan_t *p)
 {
     const Layout &L = p->lay;
-    MarkTag t = {0, 0u};
+    MarkTag t = {0, 0u, 0u};
     if (!x_written_by_aggregation(p)) return t;
     int lid_bits = 1;
     while (lid_bits < 31 && ((int64_t)1 << lid_bits) < L.id_rows) ++lid_bits;
@@ -2614,6 +2661,8 @@ MarkTag mark_tag(const zg_plan_t *p)
     if (bits <= 0) return t; // no room for a tag: every edge to a new vertex writes its row
     t.shift = 31 - bits;
     t.mask = (1u << bits) - 1u;
+    const int64_t row = (int64_t)L.feat_dim * 4;
+    t.reach_rows = (uint32_t)(((row >= 1024 ? kReachBytes / 3 : kReachBytes) + row - 1) / row);
     return t;
 }
 
@@ -2790,9 +2839,10 @@ int enqueue_body(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_pl
         if (l == H) {
             // the closing launch can carry the copy of the frontier's rows: D_{H-1} is final since launch H-1
             CloseRoles roles = {ra, ride ? gat : no_rows};
+            if (ha.bytes_prev) roles.rel.tag = ha.tag;
             roles.gat.rows *= kCloseBlock / kBlock;
             roles.gat.blocks = ride ? (uint32_t)((L.node_cap[H - 1] + roles.gat.rows - 1) / roles.gat.rows) : 0u;
-            const size_t lds = std::max(close_lds(ha), ride ? (size_t)roles.gat.rows * 4 : 0);
+            const size_t lds = std::max(close_lds(ha), ride ? ((size_t)roles.gat.rows * 2 + 1) * 4 : 0);
             rc = q.launch(ha.bytes_prev ? k_close<true> : k_close<false>, ha.blocks + ra.blocks + roles.gat.blocks, kCloseBlock, lds, ha, roles);
         } else {
             const HopRoles roles = {ra, ia};

@@ -39,6 +39,7 @@ constexpr int64_t kByteMarkVerticesPerEdge = 30;
 constexpr int kSampleHashBits = 11;      // LDS dedup set of a sampling workgroup: 2048 slots for <= 1024 ids
 constexpr int kSampleHashSlots = 1 << kSampleHashBits;
 constexpr uint64_t kGatherStreamBytes = 160ull << 20; // gathered matrices above this size are copied with non-temporal accesses
+constexpr int64_t kReachBytes = 96ll << 20; // frontier rows from which on those the last hop reaches are written by the aggregation (rows of 1 KB: a third)
 constexpr int kRelabelPerBlock = 1024;  // edges per relabel workgroup (any workgroup size)
 constexpr int kMailboxSlots = 256;      // per-step inputs in flight between host and device
 constexpr int kLogCapacity = 1024;      // records in the device-side step log

@@ -375,3 +375,30 @@ def test_closing_tiles_of_any_width(oracle, nodes, tickets, dim):
         seeds = np.random.RandomState(s).permutation(nodes)[:600].astype(np.int32)
         plan, res, _ = run_and_compare(oracle, g, feat, seeds, (9, 20), 40 + s, env=env, plan=plan, og=og, label=f"step {s}")
     assert not samples_in_one_workgroup(plan)
+
+
+@pytest.mark.parametrize("dim,batch,tickets", [
+    (256, 32767, 0), (256, 32768, 0),  # either side of 32 MB of frontier rows of 1 KB
+    (259, 32389, 0),                   # rows that are no whole pieces
+    (256, 33000, 2),                   # closing tiles of more than a word per lane
+    (8, 32768, 0),                     # 1 MB of frontier rows: copied
+])
+def test_frontier_rows_the_last_hop_reaches_again(oracle, dim, batch, tickets):
+    # sparse rows and a few popular neighbors: the frontier has rows that the hop reaches, once or from many edges, and rows that it does not
+    nodes = 50_000
+    g = W.rmat_graph(nodes, nodes * 6, 33)
+    feat = W.feature_table(nodes, dim, 4)
+    og, plan = to_host_graph(oracle, g), None
+    for s in range(3):
+        seeds = np.random.RandomState(s).permutation(nodes)[:batch].astype(np.int32)
+        plan, res, ref = run_and_compare(oracle, g, feat, seeds, (3,), 50 + s, env=zg.make_envelope(zg.ENV_MAX, max_tickets=tickets), plan=plan, og=og,
+                                         label=f"step {s}")
+        rows = plan.view_X()[: res.n[1], :dim]
+        X = rows.clone()
+        rows[:] = 7
+        plan.replay_features(1)  # the rows the aggregation writes are the same again, the others are the copy's
+        torch.cuda.synchronize()
+        written = (rows != 7).any(1)
+        assert torch.equal(rows[written], X[written]) and bool(written[batch:].all())
+        reached = np.isin(seeds, res.nbr_gid[0]) if dim >= 256 and 4 * dim * batch >= 32 << 20 else np.zeros(batch, bool)
+        assert np.array_equal(written[:batch].cpu().numpy(), reached)
