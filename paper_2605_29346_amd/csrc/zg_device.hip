@@ -1899,10 +1899,12 @@ __global__ void k_validate(const OffT *off, const int32_t *idx, int64_t num_node
 // Sums are kept as 64-bit fixed point (2^-32) so that the result does not depend on the order of the atomics.
 constexpr double kFix = 4294967296.0; // 2^32
 constexpr int kModelBinBlock = 512, kModelWindow = 4096; // threads of a workgroup of k_model_bin, edges it looks at together
-constexpr int kModelAddBlock = 512;
+constexpr int kModelAddBlock(bool terms) { return terms ? 512 : 1024; }
 constexpr uint32_t kModelMaxBins = 32768;                // a counter each in LDS
+constexpr uint32_t kModelSlices = 8;                     // one per XCD
 constexpr uint32_t kModelNoShare = 0xFFFFFFFFu;
 constexpr int64_t kModelMinPart = 16384;
+constexpr int64_t kModelRowsNodes = 1 << 19;             // rows whose terms an XCD's L2 holds
 constexpr int kModelBlock = 1024, kModelGrid = 512; // the sweeps over the vertices
 constexpr int64_t kModelPushWaves = 16384;          // twice what the chip holds at once
 constexpr int64_t kModelRowWork = 1;                // a row of a sweep by atomics, in edges
@@ -2016,32 +2018,86 @@ __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const in
     }
 }
 
-// The sweep with room for 8 bytes per edge: no atomic leaves a compute unit.  The vertices are cut into bins of 2^log2.  Once per
-// call the edges are counted by chunk and bin (k_model_count) and the counts turned into places (k_model_places, k_model_starts); in
-// each hop every edge's term is written to its bin behind those of earlier chunks (k_model_bin: the term, and the vertex within the
-// bin in the low bits), and a workgroup per bin, or several, adds it up in LDS (k_model_add).  The terms are integers: the same sums as above.
-// Three hops at 2.4 M vertices and 115 M edges: 22.8 -> 3.2 ms, k_model_bin 0.59 ms per hop (0.46 GB read, 0.92 GB written in pieces of 8
-// bytes), k_model_add 0.34 ms (2.7 TB/s), the places 0.17 ms once; 40 M vertices and 350 M edges 61 -> 15 ms.  (A window's entries put in
-// the order of their bins in LDS first, so that they leave in runs: 0.56 ms instead of 0.59, 1.06 instead of 1.27 with 1831 bins;
-// left out for its length.)
+// The sweep with room for 9 bytes per edge: no atomic leaves a compute unit.  The vertices are cut into bins of 2^log2.  Once per
+// call the edges are counted by chunk and bin (k_model_count), the counts turned into places (k_model_places, k_model_starts) and every edge
+// written to its neighbor's bin behind those of earlier chunks (k_model_bin): its row's low bits, and the neighbor within the bin.  A chunk's rows
+// are all of one block of rows (k_model_chunks), so a bin's entries are runs of one block each, in which the low bits are enough.  In
+// each hop the rows' terms are worked out once (k_model_terms); a workgroup per bin, or several, goes through its entries, looks
+// their terms up and adds them up in LDS (k_model_add).  The terms are integers: the same sums as above.
+// k_model_bin is bound by its stores, a line for nearly each (115 M edges: 0.47 ms, 245 G/s), so it runs once and not in every hop; k_model_add
+// by its look-ups, whose lines have to come out of the L2: out of memory they come at 58 G/s (0.58 ms a hop at 2.4 M vertices).  Terms of 2^19 rows
+// fit one; up to 2^22 rows, each XCD's workgroups take a slice of them, an eighth, and k_model_update adds the eight slices' sums up (0.28 ms
+// and 0.035, with 2.2 entries per look-up's line; bins half as large 0.33).  Beyond, or where the slices' sums do not fit (fewer than 16 edges
+// per vertex), an entry holds its term and the neighbor, 8 bytes, and k_model_bin runs in every hop (16 M vertices, 144 M edges, two hops:
+// 4.0 ms; by look-ups 6.3).
+// Atomics / 8-byte entries in every hop / now, ms: three hops, 2.4 M vertices and 115 M edges 22.8 / 3.29 / 1.71, one hop 1.23 / 1.03; 250 k and 83 M
+// 2.45 / 1.04; 100 k and 29 M 0.82 / 0.37; 300 k and 3.5 M 0.26 / 0.20; two hops, 3.9 M and 113 M 2.35 / 1.66; 700 k and 13 M 0.34 / 0.29.
 struct ModelBins {
     const int32_t *idx;
     int64_t num_edges, num_nodes;
     uint32_t log2, bins;
-    uint32_t chunk, chunks;    // edges of a chunk, a multiple of kModelWindow
-    uint32_t part, parts;      // most entries a workgroup of k_model_add takes, and how many such parts there are at most
-    uint32_t *place;           // [chunks][bins]: edges of the chunk that lead into the bin; then how many of earlier chunks do
-    uint32_t *start;           // [bins + 1]: where the bin's entries begin
-    uint32_t *share;           // [parts]: a bin, and above its 15 bits which part of it; kModelNoShare behind the last one
-    unsigned long long *entry; // [num_edges]
+    uint32_t block_log2, blocks; // rows of a block, and how many blocks there are
+    uint32_t chunk, chunks;      // edges of a chunk at most, a multiple of kModelWindow, and how many chunks there are at most
+    uint32_t part, parts;        // most entries a workgroup of k_model_add takes, and how many such parts there are at most
+    uint32_t *first_chunk;       // [blocks + 1]: of each block of rows
+    uint32_t *chunk_edge;        // [chunks + 1]: where the chunk begins
+    uint32_t *place;             // [bins][chunks]: edges of the chunk that lead into the bin; then how many of earlier chunks do
+    uint32_t *start;             // [bins + 1]: where the bin's entries begin
+    uint32_t *share;             // [parts]: a bin, and above its 15 bits which part of it; kModelNoShare behind the last one
+    void *entry;                 // [num_edges]: 4 bytes, or 8 where an entry holds its term
+    unsigned long long *term;    // [num_nodes] the rows' terms; null: the entries hold them
+    uint32_t slices;             // of the rows' blocks, a workgroup of k_model_add each
+    unsigned long long *more;    // [slices - 1][num_nodes]: the sums of the slices behind the first (of bins in one part)
+    unsigned long long *sums;    // [2 num_hops]: of all hops
 };
+
+// one workgroup: the blocks' first chunks and all chunks' first edges
+template <typename OffT>
+__global__ __launch_bounds__(1024) void k_model_chunks(ModelBins m, const OffT *off)
+{
+    extern __shared__ uint32_t s_first[]; // [blocks]
+    __shared__ uint32_t s_sum[16];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, each = (m.blocks + 1023u) / 1024u;
+    auto edge_of = [&](uint32_t k) { // block k's first edge
+        const int64_t r = (int64_t)k << m.block_log2;
+        return (uint32_t)(int64_t)off[r < m.num_nodes ? r : m.num_nodes];
+    };
+    const uint32_t k0 = tid * each < m.blocks ? tid * each : m.blocks, k1 = k0 + each < m.blocks ? k0 + each : m.blocks;
+    uint32_t sum = 0;
+    for (uint32_t k = k0; k < k1; ++k) sum += (edge_of(k + 1u) - edge_of(k) + m.chunk - 1u) / m.chunk;
+    const uint32_t incl = wave_incl_scan(sum);
+    if (lane == 63u) s_sum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum, total = 0;
+    for (uint32_t w = 0; w < 16u; ++w) {
+        if (w < wave) run += s_sum[w];
+        total += s_sum[w];
+    }
+    for (uint32_t k = k0; k < k1; ++k) {
+        s_first[k] = m.first_chunk[k] = run;
+        run += (edge_of(k + 1u) - edge_of(k) + m.chunk - 1u) / m.chunk;
+    }
+    if (tid == 0) m.first_chunk[m.blocks] = total;
+    __syncthreads();
+    for (uint32_t c = tid; c <= m.chunks; c += 1024u) {
+        uint32_t lo = 0, hi = m.blocks; // the last block whose first chunk is not behind c (blocks without edges have none of their own)
+        while (hi - lo > 1u) {
+            const uint32_t mid = (lo + hi) / 2u;
+            if (s_first[mid] <= c)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        m.chunk_edge[c] = c < total ? edge_of(lo) + (c - s_first[lo]) * m.chunk : (uint32_t)m.num_edges;
+    }
+}
 
 __global__ __launch_bounds__(1024) void k_model_count(ModelBins m)
 {
     extern __shared__ uint32_t s_count[];
     for (uint32_t b = threadIdx.x; b < m.bins; b += 1024u) s_count[b] = 0u;
     __syncthreads();
-    const int64_t e0 = (int64_t)blockIdx.x * m.chunk, e1 = e0 + m.chunk < m.num_edges ? e0 + m.chunk : m.num_edges;
+    const int64_t e0 = m.chunk_edge[blockIdx.x], e1 = m.chunk_edge[blockIdx.x + 1u];
     typedef int32_t v4i __attribute__((ext_vector_type(4), aligned(4)));
     auto count = [&](int32_t id) {
         const uint32_t g = (uint32_t)id;
@@ -2058,45 +2114,51 @@ __global__ __launch_bounds__(1024) void k_model_count(ModelBins m)
     }
     if (e4 + threadIdx.x < e1) count(m.idx[e4 + threadIdx.x]);
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < m.bins; b += 1024u) m.place[(size_t)blockIdx.x * m.bins + b] = s_count[b];
+    for (uint32_t b = threadIdx.x; b < m.bins; b += 1024u) m.place[(size_t)b * m.chunks + blockIdx.x] = s_count[b];
 }
 
-// 64 bins per workgroup, a lane per bin, a sixteenth of the chunks per wavefront: the running sums over the chunks; start[b] = the bin's total
-__global__ __launch_bounds__(1024) void k_model_places(ModelBins m)
+// a workgroup per bin: the running sums over the chunks; start[b] = the bin's total
+__global__ __launch_bounds__(256) void k_model_places(ModelBins m)
 {
-    __shared__ uint32_t s_sum[16][64];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, b = blockIdx.x * 64u + lane;
-    const uint32_t each = (m.chunks + 15u) / 16u, c0 = wave * each, c1 = c0 + each < m.chunks ? c0 + each : m.chunks;
-    uint32_t sum = 0;
-    if (b < m.bins) {
-#pragma unroll 8
-        for (uint32_t c = c0; c < c1; ++c) sum += m.place[(size_t)c * m.bins + b];
-    }
-    s_sum[wave][lane] = sum;
-    __syncthreads();
-    if (b >= m.bins) return;
+    __shared__ uint32_t s_sum[4];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    uint32_t *const place = m.place + (size_t)blockIdx.x * m.chunks;
     uint32_t run = 0;
-    for (uint32_t w = 0; w < wave; ++w) run += s_sum[w][lane];
-    for (uint32_t c = c0; c < c1; c += 8u) {
-        uint32_t x[8];
+    for (uint32_t c0 = 0; c0 < m.chunks; c0 += 2048u) {
+        uint32_t x[8], sum = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < 8u; ++u) x[u] = c + u < c1 ? m.place[(size_t)(c + u) * m.bins + b] : 0u;
+        for (uint32_t u = 0; u < 8u; ++u) {
+            const uint32_t c = c0 + tid * 8u + u;
+            x[u] = c < m.chunks ? place[c] : 0u;
+        }
 #pragma unroll
-        for (uint32_t u = 0; u < 8u; ++u)
-            if (c + u < c1) {
-                m.place[(size_t)(c + u) * m.bins + b] = run;
-                run += x[u];
-            }
+        for (uint32_t u = 0; u < 8u; ++u) sum += x[u];
+        const uint32_t incl = wave_incl_scan(sum);
+        if (lane == 63u) s_sum[wave] = incl;
+        __syncthreads();
+        uint32_t before = run + incl - sum;
+        for (uint32_t w = 0; w < 4u; ++w) {
+            if (w < wave) before += s_sum[w];
+            run += s_sum[w];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 8u; ++u) {
+            const uint32_t c = c0 + tid * 8u + u;
+            if (c < m.chunks) place[c] = before;
+            before += x[u];
+        }
+        __syncthreads();
     }
-    if (wave == 15u) m.start[b] = run;
+    if (tid == 0) m.start[blockIdx.x] = run;
 }
 
 __device__ __forceinline__ uint32_t model_parts(const ModelBins &m, uint32_t entries) { return entries > m.part ? (entries - 1u) / m.part + 1u : 1u; }
 
-// one workgroup: the bins' totals into their starts, and the bins into parts of at most m.part entries
+// one workgroup: the bins' totals into their starts, and the bins into parts of at most m.part entries; the hops' sums start at zero
 __global__ __launch_bounds__(1024) void k_model_starts(ModelBins m)
 {
     __shared__ uint32_t s_sum[2][16];
+    if (threadIdx.x < 2u * ZG_MAX_HOPS) m.sums[threadIdx.x] = 0ull;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, each = (m.bins + 1023u) / 1024u;
     const uint32_t b0 = threadIdx.x * each < m.bins ? threadIdx.x * each : m.bins, b1 = b0 + each < m.bins ? b0 + each : m.bins;
     uint32_t sum = 0, parts = 0;
@@ -2139,22 +2201,23 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
 }
 
 // A workgroup goes through a chunk of the edges in windows: the rows that begin in the window leave their number at their first
-// edge, a running maximum tells every edge its row, and the row's term - worked out once, by a thread per row - goes to the edge's bin.
-template <typename OffT>
+// edge, a running maximum tells every edge its row, and the row - with TERMS its term, worked out once, by a thread per row - goes to the edge's bin.
+template <typename OffT, bool TERMS>
 __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, const OffT *off, const float *q, int32_t fanout, int32_t replace)
 {
     constexpr uint32_t kEach = kModelWindow / kModelBinBlock, NW = kModelBinBlock / 64;
     typedef int32_t v4i __attribute__((ext_vector_type(4), aligned(4)));
     __shared__ __align__(16) uint16_t s_row[kModelWindow]; // at a row's first edge in the window: the row, counted from the window's first
-    __shared__ unsigned long long s_term[kModelBinBlock];
+    __shared__ unsigned long long s_term[TERMS ? kModelBinBlock : 1];
     __shared__ unsigned long long s_last;
     __shared__ uint32_t s_max[NW];
     extern __shared__ uint32_t s_next[]; // where the bin's next entry goes
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const int64_t n = m.num_nodes;
-    for (uint32_t b = tid; b < m.bins; b += (uint32_t)kModelBinBlock) s_next[b] = m.start[b] + m.place[(size_t)blockIdx.x * m.bins + b];
-    int64_t e = (int64_t)blockIdx.x * m.chunk;
-    const int64_t e1 = e + m.chunk < m.num_edges ? e + m.chunk : m.num_edges;
+    for (uint32_t b = tid; b < m.bins; b += (uint32_t)kModelBinBlock) s_next[b] = m.start[b] + m.place[(size_t)b * m.chunks + blockIdx.x];
+    int64_t e = m.chunk_edge[blockIdx.x];
+    const int64_t e1 = m.chunk_edge[blockIdx.x + 1u];
+    if (e >= e1) return;
     // the row that holds edge e: off[row] <= e < off[row + 1], a thread per probe
     int64_t row = 0, hi = n;
     while (hi - row > 1) {
@@ -2180,7 +2243,7 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
         const int64_t r = row + tid;
         o0_next = (int64_t)off[r < n ? r : n];
         o1_next = (int64_t)off[r + 1 < n ? r + 1 : n];
-        q_next = r < n ? q[r] : 0.0f;
+        q_next = TERMS && r < n ? q[r] : 0.0f;
     };
     load_window();
     while (e < e1) {
@@ -2200,7 +2263,7 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
         if (e < e1) load_window();
         if (o1 > o0 && o1 > e_now && o0 < w1) {
             s_row[o0 > e_now ? o0 - e_now : 0] = (uint16_t)tid;
-            s_term[tid] = model_term(qr, o1 - o0, fanout, replace);
+            if (TERMS) s_term[tid] = model_term(qr, o1 - o0, fanout, replace);
         }
         __syncthreads();
         uint32_t at[kEach], top = 0;
@@ -2219,8 +2282,13 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
 #pragma unroll
         for (uint32_t u = 0; u < kEach; ++u) {
             const uint32_t g = (uint32_t)v[u / 4][u % 4];
-            if (mine + u < w1 && (int64_t)g < n)
-                m.entry[atomicAdd(&s_next[g >> m.log2], 1u)] = (s_term[at[u] > before ? at[u] : before] << m.log2) | (g & ((1u << m.log2) - 1u));
+            if (mine + u < w1 && (int64_t)g < n) {
+                const uint32_t to = atomicAdd(&s_next[g >> m.log2], 1u), x = at[u] > before ? at[u] : before, in_bin = g & ((1u << m.log2) - 1u);
+                if (TERMS)
+                    static_cast<unsigned long long *>(m.entry)[to] = (s_term[x] << m.log2) | in_bin;
+                else
+                    static_cast<uint32_t *>(m.entry)[to] = (((uint32_t)(r - tid) + x) << m.log2) | in_bin; // (the row's low bits)
+            }
         }
     }
 }
@@ -2230,53 +2298,107 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
 // hops at 2.4 M vertices and 115 M edges 64.4 ms with ids in the order of a power law's ranks, 147 ms with half of the edges into
 // one vertex; in parts 3.1 and 4.1 ms (3.0 with even bins).  Parts of one share cut every bin in two, and with them all sums go through
 // atomics (2.4 M more per hop); fewer than 256 bins are cut as if they were 256.
-__global__ __launch_bounds__(kModelAddBlock) void k_model_add(ModelBins m, unsigned long long *ell)
+template <bool TERMS>
+__global__ __launch_bounds__(kModelAddBlock(TERMS)) void k_model_add(ModelBins m, unsigned long long *ell)
 {
+    constexpr uint32_t NT = kModelAddBlock(TERMS);
     extern __shared__ unsigned long long s_ell[];
-    typedef unsigned long long v2u __attribute__((ext_vector_type(2), aligned(8)));
-    const uint32_t share = m.share[blockIdx.x];
+    const uint32_t slice = TERMS ? 0u : blockIdx.x % m.slices, share = m.share[TERMS ? blockIdx.x : blockIdx.x / m.slices];
     if (share == kModelNoShare) return;
     const uint32_t bin = share & (kModelMaxBins - 1u), size = 1u << m.log2, mask = size - 1u;
-    const uint32_t b0 = m.start[bin], b1 = m.start[bin + 1u], e0 = b0 + (share >> 15) * m.part, e1 = b1 - e0 < m.part ? b1 : e0 + m.part;
-    for (uint32_t i = threadIdx.x; i < size; i += (uint32_t)kModelAddBlock) s_ell[i] = 0ull;
+    const uint32_t b0 = m.start[bin], all = m.start[bin + 1u] - b0, e0 = (share >> 15) * m.part, e1 = all - e0 < m.part ? all : e0 + m.part;
+    for (uint32_t i = threadIdx.x; i < size; i += NT) s_ell[i] = 0ull;
     __syncthreads();
-    const uint32_t pairs = (e1 - e0) / 2u;
+    if (TERMS) {
+        typedef unsigned long long v2u __attribute__((ext_vector_type(2), aligned(8)));
+        const unsigned long long *const entry = static_cast<const unsigned long long *>(m.entry) + b0;
+        const uint32_t pairs = (e1 - e0) / 2u;
 #pragma unroll 4
-    for (uint32_t i = threadIdx.x; i < pairs; i += (uint32_t)kModelAddBlock) {
-        const v2u x = *reinterpret_cast<const v2u *>(m.entry + e0 + 2u * (size_t)i);
-        atomicAdd(&s_ell[(uint32_t)x[0] & mask], x[0] >> m.log2);
-        atomicAdd(&s_ell[(uint32_t)x[1] & mask], x[1] >> m.log2);
-    }
-    if (threadIdx.x == 0 && ((e1 - e0) & 1u)) {
-        const unsigned long long x = m.entry[e1 - 1u];
-        atomicAdd(&s_ell[(uint32_t)x & mask], x >> m.log2);
+        for (uint32_t i = threadIdx.x; i < pairs; i += NT) {
+            const v2u x = *reinterpret_cast<const v2u *>(entry + e0 + 2u * (size_t)i);
+            atomicAdd(&s_ell[(uint32_t)x[0] & mask], x[0] >> m.log2);
+            atomicAdd(&s_ell[(uint32_t)x[1] & mask], x[1] >> m.log2);
+        }
+        if (threadIdx.x == 0 && ((e1 - e0) & 1u)) {
+            const unsigned long long x = entry[e1 - 1u];
+            atomicAdd(&s_ell[(uint32_t)x & mask], x >> m.log2);
+        }
+    } else {
+        constexpr uint32_t U = 8; // entries of a lane, and then their terms, on the way at once
+        const uint32_t *const entry = static_cast<const uint32_t *>(m.entry) + b0, *const place = m.place + (size_t)bin * m.chunks;
+        auto run_of = [&](uint32_t k) { // the bin's first entry of block k
+            const uint32_t c = m.first_chunk[k];
+            return c < m.chunks ? place[c] : all;
+        };
+        const uint32_t k0 = m.blocks * slice / m.slices, k1 = m.blocks * (slice + 1u) / m.slices;
+        uint32_t next = run_of(k0);
+        for (uint32_t k = k0; k < k1 && next < e1; ++k) {
+            const uint32_t r0 = next > e0 ? next : e0;
+            next = run_of(k + 1u);
+            const uint32_t r1 = next < e1 ? next : e1;
+            const unsigned long long *const term = m.term + ((size_t)k << m.block_log2);
+            const uint32_t in_block = (1u << m.block_log2) - 1u;
+            for (uint32_t i = r0 + threadIdx.x; i < r1; i += U * NT) {
+                uint32_t x[U];
+                unsigned long long t[U];
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) x[u] = i + u * NT < r1 ? entry[i + u * NT] : 0xFFFFFFFFu;
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u) t[u] = i + u * NT < r1 ? term[(x[u] >> m.log2) & in_block] : 0ull;
+#pragma unroll
+                for (uint32_t u = 0; u < U; ++u)
+                    if (t[u]) atomicAdd(&s_ell[x[u] & mask], t[u]);
+            }
+        }
     }
     __syncthreads();
     const int64_t v0 = (int64_t)bin << m.log2;
-    const bool alone = b1 - b0 <= m.part;
-    for (uint32_t i = threadIdx.x; i < size && v0 + i < m.num_nodes; i += (uint32_t)kModelAddBlock) {
+    const bool alone = all <= m.part;
+    for (uint32_t i = threadIdx.x; i < size && v0 + i < m.num_nodes; i += NT) {
         const unsigned long long x = s_ell[i];
         if (alone)
-            ell[v0 + i] = x;
+            (slice ? m.more + (size_t)(slice - 1u) * m.num_nodes : ell)[v0 + i] = x;
         else if (x)
             atomicAdd(&ell[v0 + i], x);
     }
+}
+
+// the rows' terms of a hop
+template <typename OffT>
+__global__ __launch_bounds__(kBlock) void k_model_terms(const OffT *off, const float *q, unsigned long long *term, int64_t n, int32_t fanout, int32_t replace)
+{
+    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (v < n) term[v] = model_term(q[v], (int64_t)off[v + 1] - (int64_t)off[v], fanout, replace);
 }
 
 // q_v <- 1 - (1 - q_v) exp(-ell_v); ell_v <- 0; sums[0] += q_v, sums[1] += q_v (1 - q_v); with COUNT, sums[2] += the next sweep's
 // work.  Vertices kModelStride apart are added in double, everything else as integers, so the sums do not depend on the launch.  One pair of atomics per workgroup of at most
 // 512: a pair per wavefront queued up on the two words (2.4 M vertices: 905 us, now 16 us).
 constexpr int64_t kModelStride = (int64_t)65536 * kBlock;
+struct ModelSlices { // what k_model_add left beside `ell`
+    const unsigned long long *more;
+    uint32_t count; // arrays of it
+    const uint32_t *start;
+    uint32_t log2, part;
+};
+
 template <bool COUNT>
 __global__ __launch_bounds__(kModelBlock) void k_model_update(float *q, unsigned long long *ell, int64_t n, unsigned long long *sums, ModelGate gate,
-                                                              ModelRows rows)
+                                                              ModelRows rows, ModelSlices slices)
 {
     if (gate.closed()) return;
     unsigned long long sum[COUNT ? 3 : 2] = {};
     for (int64_t t = (int64_t)blockIdx.x * kModelBlock + threadIdx.x; t < n && t < kModelStride; t += (int64_t)gridDim.x * kModelBlock) {
         double a = 0.0, b = 0.0;
         for (int64_t v = t; v < n; v += kModelStride) {
-            const double l = (double)ell[v] / kFix;
+            unsigned long long sum_v = ell[v];
+            if (slices.count) {
+                const uint32_t bin = (uint32_t)(v >> slices.log2);
+                if (slices.start[bin + 1u] - slices.start[bin] <= slices.part)
+#pragma unroll
+                    for (uint32_t i = 0; i < kModelSlices - 1u; ++i) sum_v += slices.more[(size_t)i * n + v];
+            }
+            const double l = (double)sum_v / kFix;
             const double q0 = (double)q[v];
             const double q1 = q0 - (1.0 - q0) * expm1(-l);
             q[v] = (float)q1;
@@ -2312,40 +2434,62 @@ constexpr size_t kStaticSumsBytes = 2 * ZG_MAX_HOPS * 8;
 static __device__ __align__(256) unsigned char scratch[kStaticEllBytes + kStaticQBytes + kStaticSumsBytes];
 
 // How the sweep's edges are binned, laid out behind `used` bytes of the caller's buffer; bins == 0: they are not.  About 256 to 512
-// bins, of up to 8192 vertices (64 KB of sums: two workgroups to a compute unit; bins of 4096 at 2.4 M vertices: k_model_bin 0.70 instead of
-// 0.58 ms, k_model_add 0.31 instead of 0.34; one bin per compute unit at 62 bins: k_model_add 0.77 ms instead of 0.24), beyond 16 M vertices
-// of 16384; a thousand chunks, of at most 65536 edges unless their counters would be more than a byte per edge.  Below
-// ZG_MODEL_BIN_EDGES edges never (see model_bins_work).
+// bins, of up to 8192 vertices (64 KB of sums: two workgroups to a compute unit), beyond 16 M vertices of 16384; half as many where eight workgroups share
+// a bin.  A thousand chunks, of at most 65536 edges (of 262144 with 1024 bins or more: their places are read a line each) unless their
+// counters would be more than a byte per edge.  Below ZG_MODEL_BIN_EDGES edges never (see model_bins_work).
 ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_bytes)
 {
     ModelBins m;
     std::memset(&m, 0, sizeof(m));
     const int64_t n = g->num_nodes, E = g->num_edges;
     if (E < ZG_MODEL_BIN_EDGES || E >= ((int64_t)1 << 32)) return m;
-    uint32_t log2 = 8;
-    while (log2 < 13 && (n >> log2) >= 512) ++log2;
-    while (log2 < 14 && (n >> log2) >= 2048) ++log2;
-    const int64_t bins = (n + ((int64_t)1 << log2) - 1) >> log2;
-    if (bins > (int64_t)kModelMaxBins) return m;
-    const int64_t want = std::max<int64_t>(4 * bins, std::min<int64_t>(65536, E / 1024));
-    const int64_t chunk = (want + kModelWindow - 1) / kModelWindow * kModelWindow, chunks = (E + chunk - 1) / chunk;
-    auto place = [&](size_t bytes) {
-        const size_t at = (used + kAlign - 1) / kAlign * kAlign;
-        used = at + bytes;
-        return static_cast<char *>(temp) + at;
+    uint32_t log2;
+    int64_t bins, chunk, part, parts;
+    auto cut = [&](uint32_t slices) {
+        log2 = 8;
+        while (log2 < (slices > 1 ? 14 : 13) && (n >> log2) >= (slices > 1 ? 256 : 512)) ++log2;
+        while (log2 < 14 && (n >> log2) >= 2048) ++log2;
+        bins = (n + ((int64_t)1 << log2) - 1) >> log2;
+        const int64_t want = std::max<int64_t>(4 * bins, std::min<int64_t>(bins >= 1024 ? 262144 : 65536, E / 1024));
+        chunk = (want + kModelWindow - 1) / kModelWindow * kModelWindow;
+        part = std::max<int64_t>(kModelMinPart, 2 * E / std::max<int64_t>(bins, 256));
+        parts = bins + E / part;
     };
-    m.entry = reinterpret_cast<unsigned long long *>(place((size_t)E * 8));
-    m.place = reinterpret_cast<uint32_t *>(place((size_t)(bins * chunks) * 4));
-    m.start = reinterpret_cast<uint32_t *>(place((size_t)(bins + 1) * 4));
-    const int64_t part = std::max<int64_t>(kModelMinPart, 2 * E / std::max<int64_t>(bins, 256)), parts = bins + E / part;
-    m.share = reinterpret_cast<uint32_t *>(place((size_t)parts * 4));
-    if (used > temp_bytes) return m;
+    auto lay_out = [&](bool terms, uint32_t slices) { // with the terms in the entries
+        cut(slices);
+        uint32_t block_log2 = terms ? 31 : 32 - log2;
+        if (slices > 1)
+            while (block_log2 > 0 && (n >> block_log2) < 8 * slices) --block_log2;
+        const int64_t blocks = ((n - 1) >> block_log2) + 1, chunks = E / chunk + blocks;
+        size_t at = used;
+        auto place = [&](size_t bytes) {
+            at = (at + kAlign - 1) / kAlign * kAlign;
+            at += bytes;
+            return static_cast<char *>(temp) + (at - bytes);
+        };
+        m.entry = place((size_t)E * (terms ? 8 : 4));
+        m.term = terms ? nullptr : reinterpret_cast<unsigned long long *>(place((size_t)n * 8));
+        m.slices = slices;
+        m.more = reinterpret_cast<unsigned long long *>(place((size_t)(slices - 1) * n * 8));
+        m.place = reinterpret_cast<uint32_t *>(place((size_t)(bins * chunks) * 4));
+        m.start = reinterpret_cast<uint32_t *>(place((size_t)(bins + 1) * 4));
+        m.share = reinterpret_cast<uint32_t *>(place((size_t)parts * 4));
+        m.first_chunk = reinterpret_cast<uint32_t *>(place((size_t)(blocks + 1) * 4));
+        m.chunk_edge = reinterpret_cast<uint32_t *>(place((size_t)(chunks + 1) * 4));
+        m.sums = reinterpret_cast<unsigned long long *>(place((size_t)2 * ZG_MAX_HOPS * 8));
+        m.block_log2 = block_log2;
+        m.blocks = (uint32_t)blocks;
+        m.chunks = (uint32_t)chunks;
+        return at <= temp_bytes;
+    };
+    const bool rows = n <= kModelRowsNodes ? lay_out(false, 1) : n <= kModelRowsNodes * kModelSlices && lay_out(false, kModelSlices);
+    if (!rows && !lay_out(true, 1)) return m;
+    if (bins > (int64_t)kModelMaxBins) return m;
     m.idx = g->d_indices;
     m.num_edges = E;
     m.num_nodes = n;
     m.log2 = log2;
     m.chunk = (uint32_t)chunk;
-    m.chunks = (uint32_t)chunks;
     m.part = (uint32_t)part;
     m.parts = (uint32_t)parts;
     m.bins = (uint32_t)bins;
@@ -2359,18 +2503,49 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
 // 242 / 167; 1 M and 2^19 93 / 120, 268 / 305; 1 M and 2^20 108 / 105, 307 / 248; 8 M and 2^20 206 / 286, 577 / 769; 8 M and 2^21 284 / 231, 809 / 600.
 // Power laws of skew 0.65: 40 k and 316 k edges 52 / 73, 148 / 149; 40 k and 473 k 66 / 73, 188 / 146; 10 k and 482 k 73 / 75, 209 / 152; 80 k and 0.6 M
 // 78 / 74, 224 / 160.  2.4 M vertices and 115 M edges, one hop: 1.1 ms by bins; by atomics 0.11, 0.55, 0.94, 1.3 ms with 1, 10, 18, 25 % of the
-// vertices as seeds, 5.6 with all; three hops from 1 % 2.2 ms, 3.0 all by bins.
+// vertices as seeds, 5.6 with all; three hops from 1 % 2.2 ms, 3.0 all by bins.  (All with 8-byte entries.  With terms by row the places take
+// 6 ps per edge more and a sweep 4 to 6 less: 90 k vertices and 1 M edges, one hop, 81 to 85 us with either.)
 int64_t model_bins_work(const ModelBins &m, int hops)
 {
     return m.num_edges / 7 + 180000 + 360000 / hops + 120 * m.num_nodes / m.chunks;
 }
 
-// once per call: places for the edges' terms
-void enqueue_model_places(const ModelBins &m, hipStream_t st)
+template <typename OffT>
+void enqueue_model_bin(const zg_graph_t *g, const ModelBins &m, const float *q, int32_t fanout, int32_t replace, hipStream_t st)
 {
+    const OffT *off = static_cast<const OffT *>(g->d_offsets);
+    const size_t lds = (size_t)m.bins * 4;
+    if (m.term)
+        hipLaunchKernelGGL((k_model_bin<OffT, false>), dim3(m.chunks), dim3(kModelBinBlock), lds, st, m, off, q, fanout, replace);
+    else
+        hipLaunchKernelGGL((k_model_bin<OffT, true>), dim3(m.chunks), dim3(kModelBinBlock), lds, st, m, off, q, fanout, replace);
+}
+
+// once per call: places for the edges, and the edges themselves unless their entries hold a hop's terms
+template <typename OffT>
+void enqueue_model_places(const zg_graph_t *g, const ModelBins &m, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_model_chunks<OffT>, dim3(1), dim3(1024), (size_t)m.blocks * 4, st, m, static_cast<const OffT *>(g->d_offsets));
     hipLaunchKernelGGL(k_model_count, dim3(m.chunks), dim3(1024), (size_t)m.bins * 4, st, m);
-    hipLaunchKernelGGL(k_model_places, dim3((m.bins + 63u) / 64u), dim3(1024), 0, st, m);
+    hipLaunchKernelGGL(k_model_places, dim3(m.bins), dim3(256), 0, st, m);
     hipLaunchKernelGGL(k_model_starts, dim3(1), dim3(1024), 0, st, m);
+    if (m.term) enqueue_model_bin<OffT>(g, m, nullptr, 0, 0, st);
+}
+
+// one hop by bins: the terms, their sums
+template <typename OffT>
+void enqueue_model_sums(const zg_graph_t *g, const ModelBins &m, const float *q, unsigned long long *ell, int32_t fanout, int32_t replace, hipStream_t st)
+{
+    const int64_t n = g->num_nodes;
+    const size_t lds = (size_t)8 << m.log2;
+    if (m.term) {
+        hipLaunchKernelGGL(k_model_terms<OffT>, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, static_cast<const OffT *>(g->d_offsets), q, m.term,
+                           n, fanout, replace);
+        hipLaunchKernelGGL(k_model_add<false>, dim3(m.parts * m.slices), dim3(kModelAddBlock(false)), lds, st, m, ell);
+    } else {
+        enqueue_model_bin<OffT>(g, m, q, fanout, replace, st);
+        hipLaunchKernelGGL(k_model_add<true>, dim3(m.parts), dim3(kModelAddBlock(true)), lds, st, m, ell);
+    }
 }
 
 // the sweep over the vertices that starts the size model
@@ -2402,13 +2577,10 @@ void enqueue_model_hop(const zg_graph_t *g, const ModelBins &m, const ModelHop &
     const int64_t n = g->num_nodes;
     const bool wide = g->offsets_dtype == ZG_I64;
     if (a.binned) {
-        const dim3 grid(m.chunks), block(kModelBinBlock);
-        const size_t lds = (size_t)m.bins * 4;
         if (wide)
-            hipLaunchKernelGGL(k_model_bin<int64_t>, grid, block, lds, st, m, (const int64_t *)g->d_offsets, a.q, a.fanout, a.replace);
+            enqueue_model_sums<int64_t>(g, m, a.q, a.ell, a.fanout, a.replace, st);
         else
-            hipLaunchKernelGGL(k_model_bin<int32_t>, grid, block, lds, st, m, (const int32_t *)g->d_offsets, a.q, a.fanout, a.replace);
-        hipLaunchKernelGGL(k_model_add, dim3(m.parts), dim3(kModelAddBlock), (size_t)8 << m.log2, st, m, a.ell);
+            enqueue_model_sums<int32_t>(g, m, a.q, a.ell, a.fanout, a.replace, st);
     } else {
         int32_t rows = 1;
         while (rows < 64 && n / (2 * rows) >= kModelPushWaves) rows *= 2;
@@ -2422,10 +2594,11 @@ void enqueue_model_hop(const zg_graph_t *g, const ModelBins &m, const ModelHop &
                                rows, a.gate);
     }
     const dim3 sweep((unsigned)std::min<int64_t>(kModelGrid, (n + kModelBlock - 1) / kModelBlock));
+    const ModelSlices slices = {m.more, a.binned && m.slices > 1 ? m.slices - 1u : 0u, m.start, m.log2, m.part};
     if (a.rows.off)
-        hipLaunchKernelGGL(k_model_update<true>, sweep, dim3(kModelBlock), 0, st, a.q, a.ell, n, a.sums, a.gate, a.rows);
+        hipLaunchKernelGGL(k_model_update<true>, sweep, dim3(kModelBlock), 0, st, a.q, a.ell, n, a.sums, a.gate, a.rows, slices);
     else
-        hipLaunchKernelGGL(k_model_update<false>, sweep, dim3(kModelBlock), 0, st, a.q, a.ell, n, a.sums, a.gate, a.rows);
+        hipLaunchKernelGGL(k_model_update<false>, sweep, dim3(kModelBlock), 0, st, a.q, a.ell, n, a.sums, a.gate, a.rows, slices);
 }
 
 #define ZG_HIP(call)                                                                                         \
@@ -3226,22 +3399,25 @@ int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t
         hop.gate.below = (uint64_t)model_bins_work(bins, num_hops);
         binned = false;
     }
-    auto clear_sums = [&]() { hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)8); };
-    if (binned) { // (the longest launches first: the host is ahead of the device from here on)
-        enqueue_model_places(bins, st);
+    auto place_edges = [&]() {
+        if (placed) return;
         placed = true;
-    }
+        if (g->offsets_dtype == ZG_I64)
+            enqueue_model_places<int64_t>(g, bins, st);
+        else
+            enqueue_model_places<int32_t>(g, bins, st);
+    };
+    auto clear_sums = [&]() { hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, reinterpret_cast<uint32_t *>(sums), 0u, (size_t)8); };
+    if (binned) place_edges(); // (the longest launches first: the host is ahead of the device from here on)
     clear_sums();
     enqueue_model_init(g, q, ell, d_seed_prob, batch, hop.rows, &sums[3], st);
     ZG_HIP(hipGetLastError());
     mean[0] = (double)batch;
     sigma[0] = 0.0;
-    for (int h = 0; h < num_hops;) {
-        if (binned && !placed) enqueue_model_places(bins, st);
-        placed = binned;
+    int h = 0;
+    while (h < num_hops && !binned) {
         hop.fanout = fanouts[h];
-        hop.binned = binned;
-        if (binned || h + 1 == num_hops) hop.rows.off = nullptr;
+        if (h + 1 == num_hops) hop.rows.off = nullptr;
         enqueue_model_hop(g, bins, hop, st);
         ZG_HIP(hipGetLastError());
         unsigned long long host[4] = {0, 0, 0, 0};
@@ -3256,8 +3432,27 @@ int zg_envelope_model_graph(const zg_graph_t *g, const int32_t *fanouts, int32_t
         mean[h + 1] = (double)host[0] / kFix;
         sigma[h + 1] = std::sqrt((double)host[1] / kFix);
         if (++h == num_hops) break;
-        binned = binned || (hop.rows.off && by_bins(h, host[2]));
+        binned = hop.rows.off && by_bins(h, host[2]);
         clear_sums();
+    }
+    if (h < num_hops) { // the rest by bins, with nothing left to decide: one look at the end
+        place_edges();
+        hop.binned = true;
+        hop.rows.off = nullptr;
+        const int first = h;
+        for (; h < num_hops; ++h) {
+            hop.fanout = fanouts[h];
+            hop.sums = bins.sums + 2 * h;
+            enqueue_model_hop(g, bins, hop, st);
+        }
+        ZG_HIP(hipGetLastError());
+        unsigned long long host[2 * ZG_MAX_HOPS];
+        ZG_HIP(hipMemcpyAsync(host, bins.sums, sizeof(host), hipMemcpyDeviceToHost, st));
+        ZG_HIP(hipStreamSynchronize(st));
+        for (int i = first; i < num_hops; ++i) {
+            mean[i + 1] = (double)host[2 * i] / kFix;
+            sigma[i + 1] = std::sqrt((double)host[2 * i + 1] / kFix);
+        }
     }
     return ZG_OK;
 }

@@ -419,6 +419,30 @@ def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, by_bi
     assert zg.graph_model(dg, fan, batch, with_replacement=replace) == (want[0][:4], want[1][:4])
 
 
+@pytest.mark.parametrize("nodes,edges,i64", [
+    (1 << 19, 4_000_000, False),          # the rows' terms in one piece
+    ((1 << 19) + 1, 10_000_001, True),    # in eight slices of the rows; the last block of rows has one
+    ((1 << 19) + 1, 2_000_000, False),    # no room for the slices' sums: terms in the entries
+    (1_500_007, 40_000_000, False),       # slices of blocks whose chunks are ragged
+])
+def test_size_model_is_the_same_with_terms_by_row(nodes, edges, i64):
+    # a popular neighbor, whose bin goes in parts, and stretches of empty rows
+    gen = torch.Generator(device="cuda").manual_seed(nodes)
+    weight = torch.rand(nodes, generator=gen, device="cuda").pow_(3)
+    weight[nodes // 3: nodes // 2] = 0
+    deg = (weight * (0.9 * edges / float(weight.sum()))).long()
+    deg[nodes // 2 + 7] += edges - int(deg.sum())
+    offsets = torch.zeros(nodes + 1, dtype=torch.int64, device="cuda")
+    offsets[1:] = torch.cumsum(deg, 0)
+    idx = torch.randint(0, nodes, (edges,), generator=gen, device="cuda", dtype=torch.int32)
+    idx[::5] = 11
+    dg = zg.Graph(offsets if i64 else offsets.int(), idx)
+    fan, batch = (9, 4, 3), 300
+    want, _ = _size_model(dg, fan, batch, edges, large=False)
+    got, used = _size_model(dg, fan, batch, edges, large=True)
+    assert got == want and used
+
+
 def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
     """(mean, sigma) from a scratch buffer with or without room for bins, and whether anything was written behind the smaller one."""
     small = 12 * dg.num_nodes + 576
