@@ -243,6 +243,7 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
         // workgroup, so many that a tile holds about one sampling pass (1024 / G vertices) of new rows at the cap, within
         // the ticket budget and between 32 and 8192 words.
         const int64_t words = (V + 31) / 32;
+        const bool copy_along = feat_dim > 0 && !(env->flags & ZG_PLAN_X_TWO_PASS);
         L.max_tickets = max_tickets;
         L.bitmap_words = (int64_t)align_up((size_t)words, (size_t)kHopFatTileWords) + kHopBlock; // (a last tile reaches < 1024 words past)
         for (int l = 0; l <= num_hops; ++l) {
@@ -255,10 +256,13 @@ static int compute_layout_one(const zg_graph_t *g, const int32_t *fanouts, int32
                 // then 320 rows per tile: a drawn ticket costs 13 ns of the shared counter, and every one a share of the look-backs, its rows only
                 // time of their own while there are few.  (15 k new rows: 245 tiles 18.4 us, 139 tiles 17.0 us; 33 k: 390 tiles
                 // 22.5 us, 204 tiles 19.8 us; 285 k: 256 tickets 79 us, 480 tickets 57 us.)  The closing launch only
-                // ranks: half the budget.  (137 k new vertices: 469 tickets 25 us, 235 tickets 21 us.)
+                // ranks: half the budget (662 k new vertices: 469 tickets 19.9 us, 235 tickets 18.0, 157 18.8); a third beside a copy of the frontier's rows,
+                // unless the tiles then had more than a word per lane (142 k new and 24 MB of rows: 469 tickets 23.4 us, 235 19.0, 157 18.3, 118 19.7;
+                // 31 k rows of 300 bytes 16.0 / 15.4 with 235 / 157).
                 const int64_t fresh = L.node_cap[l] - rows;
                 const int64_t share = (int64_t)((double)max_tickets * (double)fresh / (double)L.node_cap[l]);
-                const int64_t budget = std::max<int64_t>(1, l < num_hops ? std::max(max_tickets / 4, share) : max_tickets / 2);
+                const int64_t closing = copy_along && words <= max_tickets / 3 * kCloseBlock ? max_tickets / 3 : max_tickets / 2;
+                const int64_t budget = std::max<int64_t>(1, l < num_hops ? std::max(max_tickets / 4, share) : closing);
                 const int64_t per_pass = std::min<int64_t>(160, (L.node_cap[l] + T - 1) / T);
                 const int64_t want = std::max<int64_t>(1, std::min(budget, std::max(per_pass, (L.node_cap[l] + 319) / 320)));
                 int64_t W = std::max<int64_t>(kHopMinTileWords, (int64_t)align_up((size_t)((words + want - 1) / want), kHopMinTileWords));
