@@ -142,7 +142,8 @@ def summarize_hipapi(argv) -> None:
     ap.add_argument("--cmd", default="")
     args = ap.parse_args(argv)
     rows = sorted(csv.DictReader(open(args.trace_csv)), key=lambda r: int(r["Start_Timestamp"]))
-    launches = [i for i, r in enumerate(rows) if r["Function"] == "hipLaunchKernel"]
+    # a step's launches are plain hipLaunchKernel calls; those of <<< >>> (torch's, the calibration copy) follow a pop of their configuration
+    launches = [i for i, r in enumerate(rows) if r["Function"] == "hipLaunchKernel" and (i == 0 or rows[i - 1]["Function"] != "__hipPopCallConfiguration")]
     first, launches = launches, launches[-args.launches * (args.warmup + args.steps)::args.launches]  # the steps' first ones: the loop's are the run's last
     print("# rocprofv3 --hip-trace summary: host API calls inside the timed loop")
     if args.cmd:
