@@ -2024,14 +2024,14 @@ __global__ __launch_bounds__(kBlock) void k_model_push(const OffT *off, const in
 // are all of one block of rows (k_model_chunks), so a bin's entries are runs of one block each, in which the low bits are enough.  In
 // each hop the rows' terms are worked out once (k_model_terms); a workgroup per bin, or several, goes through its entries, looks
 // their terms up and adds them up in LDS (k_model_add).  The terms are integers: the same sums as above.
-// k_model_bin is bound by its stores, a line for nearly each (115 M edges: 0.47 ms, 245 G/s), so it runs once and not in every hop; k_model_add
-// by its look-ups, whose lines have to come out of the L2: out of memory they come at 58 G/s (0.58 ms a hop at 2.4 M vertices).  Terms of 2^19 rows
+// k_model_bin's stores are a line for nearly each edge (115 M: 0.47 ms, 245 G/s), so it runs once and not in every hop, and puts a window's entries in the order of
+// their bins in LDS first, from where they leave in runs (0.37 ms); k_model_add is bound by its look-ups, whose lines have to come out of the L2: out of memory they come at 58 G/s (0.58 ms a hop at 2.4 M vertices).  Terms of 2^19 rows
 // fit one; up to 2^22 rows, each XCD's workgroups take a slice of them, an eighth, and k_model_update adds the eight slices' sums up (0.28 ms
 // and 0.035, with 2.2 entries per look-up's line; bins half as large 0.33).  Beyond, or where the slices' sums do not fit (fewer than 16 edges
 // per vertex), an entry holds its term and the neighbor, 8 bytes, and k_model_bin runs in every hop (16 M vertices, 144 M edges, two hops:
 // 4.0 ms; by look-ups 6.3).
-// Atomics / 8-byte entries in every hop / now, ms: three hops, 2.4 M vertices and 115 M edges 22.8 / 3.29 / 1.71, one hop 1.23 / 1.03; 250 k and 83 M
-// 2.45 / 1.04; 100 k and 29 M 0.82 / 0.37; 300 k and 3.5 M 0.26 / 0.20; two hops, 3.9 M and 113 M 2.35 / 1.66; 700 k and 13 M 0.34 / 0.29.
+// Atomics / 8-byte entries in every hop / now, ms: three hops, 2.4 M vertices and 115 M edges 22.8 / 3.29 / 1.61, one hop 1.23 / 0.92; 250 k and 83 M
+// 2.45 / 0.94; 100 k and 29 M 0.82 / 0.31; 300 k and 3.5 M 0.26 / 0.20; two hops, 3.9 M and 113 M 2.35 / 1.53; 700 k and 13 M 0.34 / 0.29.
 struct ModelBins {
     const int32_t *idx;
     int64_t num_edges, num_nodes;
@@ -2210,8 +2210,10 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
     __shared__ __align__(16) uint16_t s_row[kModelWindow]; // at a row's first edge in the window: the row, counted from the window's first
     __shared__ unsigned long long s_term[TERMS ? kModelBinBlock : 1];
     __shared__ unsigned long long s_last;
-    __shared__ uint32_t s_max[NW];
+    __shared__ uint32_t s_max[NW], s_count[TERMS ? 1 : kModelBinBlock];
+    __shared__ uint2 s_first[TERMS ? 1 : kModelBinBlock], s_item[TERMS ? 1 : kModelWindow];
     extern __shared__ uint32_t s_next[]; // where the bin's next entry goes
+    if (!TERMS) s_count[threadIdx.x] = 0u;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const int64_t n = m.num_nodes;
     for (uint32_t b = tid; b < m.bins; b += (uint32_t)kModelBinBlock) s_next[b] = m.start[b] + m.place[(size_t)b * m.chunks + blockIdx.x];
@@ -2266,7 +2268,7 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
             if (TERMS) s_term[tid] = model_term(qr, o1 - o0, fanout, replace);
         }
         __syncthreads();
-        uint32_t at[kEach], top = 0;
+        uint32_t at[kEach], rank[kEach], top = 0;
 #pragma unroll
         for (uint32_t u = 0; u < kEach; ++u) {
             const uint32_t x = s_row[tid * kEach + u];
@@ -2282,12 +2284,38 @@ __global__ __launch_bounds__(kModelBinBlock, 4) void k_model_bin(ModelBins m, co
 #pragma unroll
         for (uint32_t u = 0; u < kEach; ++u) {
             const uint32_t g = (uint32_t)v[u / 4][u % 4];
-            if (mine + u < w1 && (int64_t)g < n) {
-                const uint32_t to = atomicAdd(&s_next[g >> m.log2], 1u), x = at[u] > before ? at[u] : before, in_bin = g & ((1u << m.log2) - 1u);
-                if (TERMS)
-                    static_cast<unsigned long long *>(m.entry)[to] = (s_term[x] << m.log2) | in_bin;
-                else
-                    static_cast<uint32_t *>(m.entry)[to] = (((uint32_t)(r - tid) + x) << m.log2) | in_bin; // (the row's low bits)
+            const bool there = mine + u < w1 && (int64_t)g < n;
+            const uint32_t x = at[u] > before ? at[u] : before, in_bin = g & ((1u << m.log2) - 1u);
+            if (TERMS) {
+                if (there) static_cast<unsigned long long *>(m.entry)[atomicAdd(&s_next[g >> m.log2], 1u)] = (s_term[x] << m.log2) | in_bin;
+            } else { // the row's low bits; the entry's number within the window and its bin
+                at[u] = (((uint32_t)(r - tid) + x) << m.log2) | in_bin;
+                rank[u] = there ? atomicAdd(&s_count[g >> m.log2], 1u) : 0xFFFFFFFFu;
+            }
+        }
+        if (!TERMS) { // the window's entries in the order of their bins, so that they leave in runs
+            __syncthreads();
+            const uint32_t c = tid < m.bins ? s_count[tid] : 0u, sum = wave_incl_scan(c);
+            if (lane == 63u) s_max[wave] = sum;
+            __syncthreads();
+            const uint32_t w = lane < NW ? s_max[lane] : 0u, ws = wave_incl_scan(w), first = lane_value(ws, wave) - lane_value(w, wave) + sum - c, total = lane_value(ws, 63u);
+            if (tid < m.bins) {
+                s_first[tid] = make_uint2(first, s_next[tid]);
+                s_next[tid] += c;
+                s_count[tid] = 0u;
+            }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t u = 0; u < kEach; ++u)
+                if (rank[u] != 0xFFFFFFFFu) {
+                    const uint2 f = s_first[(uint32_t)v[u / 4][u % 4] >> m.log2];
+                    s_item[f.x + rank[u]] = make_uint2(at[u], f.y + rank[u]);
+                }
+            __syncthreads();
+#pragma unroll 2
+            for (uint32_t i = tid; i < total; i += (uint32_t)kModelBinBlock) {
+                const uint2 y = s_item[i];
+                static_cast<uint32_t *>(m.entry)[y.y] = y.x;
             }
         }
     }
@@ -2480,7 +2508,7 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
         m.block_log2 = block_log2;
         m.blocks = (uint32_t)blocks;
         m.chunks = (uint32_t)chunks;
-        return at <= temp_bytes;
+        return at <= temp_bytes && (terms || bins <= kModelBinBlock); // (a thread of k_model_bin per bin)
     };
     const bool rows = n <= kModelRowsNodes ? lay_out(false, 1) : n <= kModelRowsNodes * kModelSlices && lay_out(false, kModelSlices);
     if (!rows && !lay_out(true, 1)) return m;
