@@ -2064,7 +2064,11 @@ __global__ __launch_bounds__(1024) void k_model_chunks(ModelBins m, const OffT *
     };
     const uint32_t k0 = tid * each < m.blocks ? tid * each : m.blocks, k1 = k0 + each < m.blocks ? k0 + each : m.blocks;
     uint32_t sum = 0;
-    for (uint32_t k = k0; k < k1; ++k) sum += (edge_of(k + 1u) - edge_of(k) + m.chunk - 1u) / m.chunk;
+    auto chunks_of = [&](uint32_t k) { // (edges + chunk - 1 may be 2^32 or more)
+        const uint32_t edges = edge_of(k + 1u) - edge_of(k);
+        return edges / m.chunk + (edges % m.chunk != 0u ? 1u : 0u);
+    };
+    for (uint32_t k = k0; k < k1; ++k) sum += chunks_of(k);
     const uint32_t incl = wave_incl_scan(sum);
     if (lane == 63u) s_sum[wave] = incl;
     __syncthreads();
@@ -2075,7 +2079,7 @@ __global__ __launch_bounds__(1024) void k_model_chunks(ModelBins m, const OffT *
     }
     for (uint32_t k = k0; k < k1; ++k) {
         s_first[k] = m.first_chunk[k] = run;
-        run += (edge_of(k + 1u) - edge_of(k) + m.chunk - 1u) / m.chunk;
+        run += chunks_of(k);
     }
     if (tid == 0) m.first_chunk[m.blocks] = total;
     __syncthreads();

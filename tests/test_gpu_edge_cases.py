@@ -443,6 +443,18 @@ def test_size_model_is_the_same_with_terms_by_row(nodes, edges, i64):
     assert got == want and used
 
 
+@pytest.mark.parametrize("nodes", [1 << 19, (1 << 22) + 1])  # terms by row; in the entries
+def test_size_model_of_nearly_2_32_edges(nodes):
+    # all rows are one block, and a chunk more than its edges is more than 32 bits hold
+    edges, fan, batch = (1 << 32) - 1, (4, 3), 300
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    offsets = torch.arange(nodes + 1, device="cuda") * edges // nodes
+    idx = torch.empty(edges, dtype=torch.int32, device="cuda").random_(0, nodes, generator=gen)
+    dg = zg.Graph(offsets, idx)
+    want, _ = _size_model(dg, fan, batch, edges, large=False)
+    assert zg.graph_model(dg, fan, batch) == (want[0][:3], want[1][:3])
+
+
 def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
     """(mean, sigma) from a scratch buffer with or without room for bins, and whether anything was written behind the smaller one."""
     small = 12 * dg.num_nodes + 576
