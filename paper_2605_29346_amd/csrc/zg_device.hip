@@ -2370,13 +2370,15 @@ __global__ __launch_bounds__(kModelAddBlock(TERMS)) void k_model_add(ModelBins m
             const uint32_t r1 = next < e1 ? next : e1;
             const unsigned long long *const term = m.term + ((size_t)k << m.block_log2);
             const uint32_t in_block = (1u << m.block_log2) - 1u;
-            for (uint32_t i = r0 + threadIdx.x; i < r1; i += U * NT) {
+            const uint32_t *const run = entry + r0;
+            const uint32_t count = r1 > r0 ? r1 - r0 : 0u; // at most m.part, 2^25: the sums below stay within 32 bits, which r1 may fill
+            for (uint32_t i = threadIdx.x; i < count; i += U * NT) {
                 uint32_t x[U];
                 unsigned long long t[U];
 #pragma unroll
-                for (uint32_t u = 0; u < U; ++u) x[u] = i + u * NT < r1 ? entry[i + u * NT] : 0xFFFFFFFFu;
+                for (uint32_t u = 0; u < U; ++u) x[u] = i + u * NT < count ? run[i + u * NT] : 0xFFFFFFFFu;
 #pragma unroll
-                for (uint32_t u = 0; u < U; ++u) t[u] = i + u * NT < r1 ? term[(x[u] >> m.log2) & in_block] : 0ull;
+                for (uint32_t u = 0; u < U; ++u) t[u] = i + u * NT < count ? term[(x[u] >> m.log2) & in_block] : 0ull;
 #pragma unroll
                 for (uint32_t u = 0; u < U; ++u)
                     if (t[u]) atomicAdd(&s_ell[x[u] & mask], t[u]);

@@ -443,13 +443,17 @@ def test_size_model_is_the_same_with_terms_by_row(nodes, edges, i64):
     assert got == want and used
 
 
-@pytest.mark.parametrize("nodes", [1 << 19, (1 << 22) + 1])  # terms by row; in the entries
-def test_size_model_of_nearly_2_32_edges(nodes):
+@pytest.mark.parametrize("nodes,reached", [
+    (1 << 19, 1 << 19),              # terms by row
+    (1 << 19, 1 << 11),              # ... and all edges in one bin
+    ((1 << 22) + 1, (1 << 22) + 1),  # terms in the entries
+])
+def test_size_model_of_nearly_2_32_edges(nodes, reached):
     # all rows are one block, and a chunk more than its edges is more than 32 bits hold
     edges, fan, batch = (1 << 32) - 1, (4, 3), 300
     gen = torch.Generator(device="cuda").manual_seed(7)
     offsets = torch.arange(nodes + 1, device="cuda") * edges // nodes
-    idx = torch.empty(edges, dtype=torch.int32, device="cuda").random_(0, nodes, generator=gen)
+    idx = torch.empty(edges, dtype=torch.int32, device="cuda").random_(0, reached, generator=gen)
     dg = zg.Graph(offsets, idx)
     want, _ = _size_model(dg, fan, batch, edges, large=False)
     assert zg.graph_model(dg, fan, batch) == (want[0][:3], want[1][:3])
