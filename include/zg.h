@@ -286,8 +286,9 @@ int zg_plan_outputs(const zg_plan_t *p, zg_outputs *out);
  * stream-ordered one after another and issued from one host thread at a time.  Invalid seeds do not fault:
  * they raise ZG_FLAG_SEED_* bits in the device status word and make the step's outputs undefined.
  * On a stream that is being captured the kernels become part of the caller's graph: each of its replays is a step with these
- * seeds and this key (not with ZG_PLAN_AUTO_FALLBACK, whose graph launch is not recorded).
- * Errors: ZG_EINVAL (null), ZG_ESTATE (no captured graph; device made no progress for 30 s), ZG_EHIP (a launch
+ * seeds and this key.  (A plan with ZG_PLAN_AUTO_FALLBACK, without ZG_PLAN_EAGER, refuses such a stream: its steps take their
+ * inputs from the ring, where a replay would find none.)
+ * Errors: ZG_EINVAL (null), ZG_ESTATE (no captured graph; a stream under capture; device made no progress for 30 s), ZG_EHIP (a launch
  * failed; if it was not the step's first one the plan takes no more steps: ZG_ESTATE). */
 int zg_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, void *stream);
 /* Stand-alone feature gather (section 2.2, "feature copy") for the vertex list the plan's last step left

@@ -3301,6 +3301,10 @@ static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, vo
     if (!p || !d_seeds) return fail(ZG_EINVAL, "null argument");
     if (p->broken) return fail(ZG_ESTATE, "an earlier step of this plan was enqueued in part: its scratch state is undefined");
     Queue q{static_cast<hipStream_t>(stream)};
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (q.st) ZG_HIP(hipStreamIsCapturing(q.st, &capture));
+    // (a replay of the recording would be a step that the host has filled no mailbox slot for, and every later one would read another step's)
+    if (capture != hipStreamCaptureStatusNone && replays_graph(p)) return fail(ZG_ESTATE, "a step of a plan with ZG_PLAN_AUTO_FALLBACK cannot be recorded");
     // back-pressure without touching the device: wait (host only) while every mailbox slot is taken by a
     // step that has not finished yet
     if ((uint32_t)(p->issued - p->mailbox->completed) >= (uint32_t)kMailboxSlots - 1u &&
@@ -3314,8 +3318,6 @@ static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, vo
     if (!probe && replays_graph(p)) {
         ZG_HIP(hipGraphLaunch(p->graph_exec, q.st));
     } else {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (q.st) ZG_HIP(hipStreamIsCapturing(q.st, &capture));
         const int rc = enqueue_step(p, q, StepInputs{d_seeds, rng_key}, probe);
         if (capture != hipStreamCaptureStatusNone) return rc; // recorded into the caller's graph: it runs, and counts as a step, when that is replayed
         if (rc != ZG_OK) {

@@ -358,6 +358,35 @@ def test_a_step_recorded_into_the_callers_graph(oracle, dim, batch):
     plan.close()  # (waits for nothing that was not replayed)
 
 
+def test_a_step_that_replays_the_plans_graph_is_not_recorded(oracle):
+    # refused with nothing enqueued: the caller's recording goes on, and the plan's next steps find their own inputs
+    g = W.rmat_graph(30_000, 600_000, 21)
+    feat = W.feature_table(30_000, 8, 4)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (8, 6), 300, zg.make_envelope(zg.ENV_MAX, flags=zg.PLAN_AUTO_FALLBACK), feat_dim=8)
+    plan.bind_features(feat.cuda())
+    pool, og, stream = W.SeedPool(g, 300, 2), to_host_graph(oracle, g), torch.cuda.Stream()
+    batches = [pool.batch_for(s).cuda() for s in range(3)]
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record(), b.record()
+    mark = torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    rec = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(rec, stream=stream):
+        mark += 1
+        for refused in (lambda: plan.step(batches[0], 70, stream), lambda: plan.step_timed(batches[0], 70, a, b, stream)):
+            with pytest.raises(zg.ZgError) as err:
+                refused()
+            assert err.value.status == zg.ESTATE
+        mark += 1
+    for s in (1, 2):
+        rec.replay()
+        plan.step(batches[s], 70 + s)
+        ref, res = og.sample_blocks(batches[s].cpu().numpy(), (8, 6), 70 + s), plan.read_step()
+        compare_blocks(res, ref, f"batch {s}")
+        compare_features(oracle, res, ref, feat.numpy(), f"batch {s}")
+        assert plan.step_status() == (s, 0) and plan.epoch() == s and float(mark) == 2 * s
+
+
 @pytest.mark.parametrize("nodes,tickets", [
     (32 * 64 * 2, 4),        # closing tiles of 64 words: a lane expands 4 vertices
     (32 * 256 * 2, 4),       # ... 16
