@@ -263,7 +263,8 @@ int zg_plan(zg_plan_t **p, const zg_graph_t *g, const int32_t *fanouts, int32_t 
             const zg_envelope *env, int32_t feat_dim, void *d_workspace, size_t workspace_bytes, void *stream);
 /* Waits until the plan's own last step has finished (its completion counter in pinned host memory, then the
  * stream that step was issued on; other plans' streams are left alone), then releases the plan.  If the device
- * does not finish within 30 s the call falls back to hipDeviceSynchronize. */
+ * does not finish within 30 s the call falls back to hipDeviceSynchronize, and a plan of which a step has been recorded
+ * (see zg_step) is waited for that way: replays in flight may be on any stream.  No recording may be replayed afterwards. */
 int zg_plan_destroy(zg_plan_t *p);
 /* Makes gather + aggregation (section 2.2, "feature copy" and the first GraphSAGE aggregation) part of the
  * step: d_feat is the [num_nodes, ld] fp32 table in device memory (row stride ld elements, >= feat_dim),

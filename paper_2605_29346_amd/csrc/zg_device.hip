@@ -2684,6 +2684,7 @@ struct zg_plan_s {
     uint32_t issued = 0;            // steps enqueued so far (mod 2^32, like the device-side step counter)
     hipStream_t last_stream = nullptr; // stream of the last enqueued step (what zg_plan_destroy waits for)
     bool stepped = false;
+    bool recorded = false;          // a step is part of a caller's graph
     bool broken = false;            // a step was enqueued in part
     zg_plan_s *twin = nullptr;      // worst-case twin (ZG_PLAN_SAFE_TWIN): own outputs, metadata and mailbox, shared scratch
     hipStream_t own_stream = nullptr;
@@ -3231,10 +3232,17 @@ int zg_plan_destroy(zg_plan_t *p)
     if (!p) return ZG_OK;
     // a step still in flight reads the mailbox and the captured graph: wait for this plan's own last step - its
     // completion counter first (host memory only), then the stream it was issued on, so that the launch has
-    // retired as a whole.  Other plans' streams are not waited for.
-    if (p->mailbox && p->stepped) {
-        const bool done = wait_completed(p, p->issued, kHostWaitSeconds);
-        if (!done || hipStreamSynchronize(p->last_stream) != hipSuccess) (void)hipDeviceSynchronize();
+    // retired as a whole.  Other plans' streams are not waited for, unless a recorded step may be in flight: the counter
+    // counts its replays too, and where these went the plan does not know.
+    if (p->mailbox && (p->stepped || p->recorded)) {
+        const bool done = !p->recorded && wait_completed(p, p->issued, kHostWaitSeconds);
+        if (!done || hipStreamSynchronize(p->last_stream) != hipSuccess) {
+            int device = p->device;
+            (void)hipGetDevice(&device);
+            (void)hipSetDevice(p->device);
+            (void)hipDeviceSynchronize();
+            (void)hipSetDevice(device);
+        }
         (void)hipGetLastError();
     }
     if (p->twin) zg_plan_destroy(p->twin);
@@ -3319,7 +3327,10 @@ static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, vo
         ZG_HIP(hipGraphLaunch(p->graph_exec, q.st));
     } else {
         const int rc = enqueue_step(p, q, StepInputs{d_seeds, rng_key}, probe);
-        if (capture != hipStreamCaptureStatusNone) return rc; // recorded into the caller's graph: it runs, and counts as a step, when that is replayed
+        if (capture != hipStreamCaptureStatusNone) { // recorded into the caller's graph: it runs, and counts as a step, when that is replayed
+            p->recorded = p->recorded || q.launched > 0;
+            return rc;
+        }
         if (rc != ZG_OK) {
             p->broken = q.launched > 0; // (else nothing was enqueued: the slot is free again)
             return rc;

@@ -358,6 +358,29 @@ def test_a_step_recorded_into_the_callers_graph(oracle, dim, batch):
     plan.close()  # (waits for nothing that was not replayed)
 
 
+@pytest.mark.parametrize("enqueued", [0, 1])  # without and with a finished step that was not recorded
+def test_destroying_a_plan_waits_for_replays_of_its_steps(oracle, enqueued):
+    g = W.rmat_graph(30_000, 600_000, 21)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (8, 6), 300, zg.make_envelope(zg.ENV_MAX))
+    seeds, key, stream = W.SeedPool(g, 300, 2).batch_for(0), 70, torch.cuda.Stream()
+    seeds_d, rec = seeds.cuda(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(rec, stream=stream):
+        plan.step(seeds_d, key, stream)
+    for _ in range(enqueued):
+        plan.step(seeds_d, key)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(200_000_000)  # the replays are still ahead when the plan is closed
+        for _ in range(3):
+            rec.replay()
+    assert not stream.query() and plan.step_status() == (enqueued, 0)
+    plan.close()
+    assert stream.query()
+    ref = to_host_graph(oracle, g).sample_blocks(seeds.numpy(), (8, 6), key)
+    assert np.array_equal(plan.view_S()[: ref.n[-1]].cpu().numpy(), ref.S) and int(plan.view_counts()[0][-1]) == ref.n[-1]
+
+
 def test_a_step_that_replays_the_plans_graph_is_not_recorded(oracle):
     # refused with nothing enqueued: the caller's recording goes on, and the plan's next steps find their own inputs
     g = W.rmat_graph(30_000, 600_000, 21)
