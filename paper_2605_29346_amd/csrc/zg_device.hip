@@ -3331,10 +3331,12 @@ static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, vo
             p->recorded = p->recorded || q.launched > 0;
             return rc;
         }
-        if (rc != ZG_OK) {
-            p->broken = q.launched > 0; // (else nothing was enqueued: the slot is free again)
-            return rc;
+        if (rc != ZG_OK && q.launched > 0) { // (else nothing was enqueued: the slot is free again)
+            p->broken = true;
+            p->last_stream = q.st;
+            p->stepped = true;
         }
+        if (rc != ZG_OK) return rc;
     }
     // only now may an earlier step copy the slot ahead of time: a slot whose launch failed is filled again later
     p->issued += 1;

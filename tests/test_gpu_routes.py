@@ -1,6 +1,10 @@
 """GPU parity on each of the routes a step can take (marks as bits or bytes, all hops in one workgroup or a launch per hop): steps that
 the caps cut short, and the degenerate shapes - bad seeds, no edges, ragged words and rows - at sizes that reach the hop launches, with the
 route asserted."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -379,6 +383,46 @@ def test_destroying_a_plan_waits_for_replays_of_its_steps(oracle, enqueued):
     assert stream.query()
     ref = to_host_graph(oracle, g).sample_blocks(seeds.numpy(), (8, 6), key)
     assert np.array_equal(plan.view_S()[: ref.n[-1]].cpu().numpy(), ref.S) and int(plan.view_counts()[0][-1]) == ref.n[-1]
+
+
+_REFUSED_LAUNCHES = """
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+import torch
+from paper_2605_29346_amd import workloads as W, zg
+
+left = ctypes.c_int.in_dll(shim, "launches_until_failure")
+g = W.rmat_graph(30_000, 600_000, 21)
+dg, seeds = zg.Graph(g.offsets.cuda(), g.indices.cuda()), W.SeedPool(g, 300, 2).batch_for(0).cuda()
+def status(call):
+    try:
+        call()
+        return zg.OK
+    except zg.ZgError as e:
+        return e.status
+for launched in (0, 1, 3):
+    plan, stream = zg.Plan(dg, (8, 6), 300, zg.make_envelope(zg.ENV_MAX)), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    step = lambda: plan.step(seeds, 70, stream)
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(200_000_000)  # what is enqueued is still ahead when the plan is closed
+    left.value = launched
+    assert status(step) == zg.EHIP and left.value == 0
+    left.value = -1
+    assert status(step) == (zg.ESTATE if launched else zg.OK)  # nothing of the step was enqueued: the plan goes on
+    assert not stream.query()
+    plan.close()
+    assert stream.query()
+print("all closed")
+"""
+
+
+def test_a_step_enqueued_in_part_is_waited_for_and_the_last(tmp_path):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    shim = tmp_path / "launch_shim.so"
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", os.path.join(root, "tests", "launch_shim.cpp"), "-o", str(shim), "-ldl"], check=True)
+    run = subprocess.run([sys.executable, "-c", _REFUSED_LAUNCHES, str(shim)], cwd=root, timeout=100, capture_output=True, text=True)
+    assert run.returncode == 0 and run.stdout.strip() == "all closed", run.stderr[-2000:]
 
 
 def test_a_step_that_replays_the_plans_graph_is_not_recorded(oracle):
