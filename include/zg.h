@@ -280,8 +280,8 @@ int zg_plan_outputs(const zg_plan_t *p, zg_outputs *out);
  * device can read), read when the step runs on `stream`; they must stay valid until then.  The call enqueues
  * the step's kernels - H + 2 or H + 3, 2 or 3 of a small step - and nothing else; with ZG_PLAN_AUTO_FALLBACK exactly ONE
  * hipGraph launch, whose first kernel reads (d_seeds, rng_key) out of a slot of a small ring in pinned host memory.  It
- * never synchronises with the device and never allocates; only when 255 earlier steps of this plan are still unfinished does
- * it wait, on the host, for the oldest one (a counter the device publishes in the same pinned ring); that
+ * never synchronises with the device and never allocates; only when 255 earlier steps of this plan - replays of a recorded one, below, are not among
+ * them - are still unfinished does it wait, on the host, for the oldest one (a counter the device publishes in the same pinned ring); that
  * wait is bounded: after 30 s without progress the call returns ZG_ESTATE and enqueues nothing.
  * Results are in the plan's output buffers once `stream` reaches this point.  Steps of one plan must be
  * stream-ordered one after another and issued from one host thread at a time.  Invalid seeds do not fault:

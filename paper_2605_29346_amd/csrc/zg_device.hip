@@ -220,11 +220,13 @@ struct WaveGroup {
 // graph's arguments are frozen, and a step must be exactly one graph launch.  The host writes slot
 // (steps issued % kMailboxSlots) before it launches the graph; the ingest kernel of step number e (the
 // device-side step counter) reads slot e % kMailboxSlots; the last kernel of a step publishes e + 1 in
-// `completed`, which the host checks (no device synchronisation) before it reuses a slot.
+// `completed`, and how many of those steps the host has enqueued itself - the others are replays of a caller's recording - in `answered`,
+// which it checks (no device synchronisation) before it reuses a slot.
 struct Mailbox {
     uint32_t completed;
     uint32_t issued; // steps the host has handed over so far (their slots are filled)
-    uint32_t pad[2];
+    uint32_t answered;
+    uint32_t pad;
     uint32_t status[kMailboxSlots]; // ZG_FLAG_* bits raised by the step that used the slot
     struct {
         unsigned long long seeds; // device address of the step's seed ids
@@ -1632,6 +1634,7 @@ struct FinishArgs {
     const Drmb *gate;       // gated twin: the plan whose step this launch ends
     Mailbox *gate_mailbox;  // ... and its mailbox: the step counts as completed only now
     int32_t defer_completed; // plan with a gated twin behind it: leave `completed` to the twin's last launch
+    int32_t enqueued;        // by the host, as a step of the plan: counts as answered
     Mailbox *mailbox;
     const int32_t *S;
     uint32_t *seen;
@@ -1650,6 +1653,7 @@ struct FinishArgs {
 // last launch of a step that carries a gated twin: the owner's step is complete whether or not the twin ran
 __device__ __forceinline__ void publish_gate_owner(const FinishArgs &a)
 {
+    __hip_atomic_store(&a.gate_mailbox->answered, a.gate->answered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __hip_atomic_store(&a.gate_mailbox->completed, a.gate->epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -1685,7 +1689,8 @@ __device__ __forceinline__ void finish_block(const FinishArgs &a, uint32_t block
         uint32_t drawn = 0u;
         for (int l = 0; l <= a.num_hops; ++l) drawn += d->ticket[l];
         for (int l = 0; l <= a.num_hops; ++l) d->ticket[l] = 0u;
-        const uint32_t epoch = d->epoch;
+        const uint32_t epoch = d->epoch, answered = d->answered + (uint32_t)a.enqueued;
+        d->answered = answered;
         uint32_t *rec = a.log + (size_t)(epoch % kLogCapacity) * ZG_LOG_STRIDE;
         int p = 0;
         rec[p++] = epoch;
@@ -1700,8 +1705,10 @@ __device__ __forceinline__ void finish_block(const FinishArgs &a, uint32_t block
         d->step_flags = 0; // for the next step: its first kernel raises seed bits from many lanes, so nobody resets there
         d->active = (step_flags & kHopOverflowMask) != 0u && a.defer_completed ? 1u : 0u;
         __hip_atomic_store(&a.mailbox->status[epoch % kMailboxSlots], step_flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        if (!a.defer_completed)
+        if (!a.defer_completed) {
+            __hip_atomic_store(&a.mailbox->answered, answered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(&a.mailbox->completed, epoch + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
         if (a.gate) publish_gate_owner(a);
     }
 }
@@ -2748,7 +2755,8 @@ bool x_written_by_aggregation(const zg_plan_t *p)
 // both cached 194 / 242 us.
 
 // (`blocks_before` of the last launch do something else)
-FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate = nullptr, bool defer_completed = false, uint32_t blocks_before = 0)
+FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate = nullptr, bool defer_completed = false, bool enqueued = false,
+                       uint32_t blocks_before = 0)
 {
     FinishArgs fa;
     std::memset(&fa, 0, sizeof(fa));
@@ -2758,6 +2766,7 @@ FinishArgs finish_args(const zg_plan_t *p, bool present, const zg_plan_t *gate =
     fa.gate = gate ? gate->drmb() : nullptr;
     fa.gate_mailbox = gate ? gate->mailbox_dev : nullptr;
     fa.defer_completed = defer_completed ? 1 : 0;
+    fa.enqueued = enqueued ? 1 : 0;
     fa.mailbox = p->mailbox_dev;
     fa.S = p->S();
     fa.seen = p->seen();
@@ -2828,6 +2837,7 @@ struct StepProbe {
 // error of the caller's own.)
 struct Queue {
     hipStream_t st;
+    bool recorded = false; // into a caller's graph
     int launched = 0;
     template <class... P> int launch(void (*kernel)(P...), unsigned grid, unsigned block, size_t lds, P... a)
     {
@@ -2971,6 +2981,7 @@ int enqueue_body(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_pl
     const zg_graph_t *g = p->graph;
     const int H = L.num_hops;
     const bool feats = p->d_feat && L.feat_dim > 0;
+    const bool enqueued = !gate && !q.recorded;
     const bool ride = features_ride_along(p);
     RowArgs agg, gat, no_rows;
     std::memset(&agg, 0, sizeof(agg));
@@ -3070,7 +3081,7 @@ int enqueue_body(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_pl
     // clean-up}.  (One launch for all four roles was measured: no gain - the two big roles are bound by the same memory fabric.)
     if (!feats) {
         const RelabelArgs ra = relabel_args(p, H - 1, true, gate);
-        const FinishArgs fa = finish_args(p, true, gate, defer_completed, ra.blocks);
+        const FinishArgs fa = finish_args(p, true, gate, defer_completed, enqueued, ra.blocks);
         return q.launch(k_tail, ra.blocks + fa.blocks, kBlock, 0, ra, fa);
     }
     if (!ride) {
@@ -3085,7 +3096,7 @@ int enqueue_body(const zg_plan_t *p, Queue &q, const StepInputs &in, const zg_pl
         if (rc != ZG_OK) return rc;
     }
     if (probe) probe->error = hipEventRecord(probe->before, q.st);
-    const FinishArgs fa = finish_args(p, true, gate, defer_completed, agg.blocks + (copy_along ? gat.blocks : 0u));
+    const FinishArgs fa = finish_args(p, true, gate, defer_completed, enqueued, agg.blocks + (copy_along ? gat.blocks : 0u));
     int rc = launch_aggregate(agg, fa, q, copy_along ? &gat : nullptr);
     if (rc == ZG_OK && probe && probe->error == hipSuccess) probe->error = hipEventRecord(probe->after, q.st);
     return rc;
@@ -3211,10 +3222,10 @@ int zg_plan(zg_plan_t **out, const zg_graph_t *g, const int32_t *fanouts, int32_
     return ZG_OK;
 }
 
-// host-only wait until the device has published `target` finished steps of the plan; false after `seconds`
-static bool wait_completed(const zg_plan_t *p, uint32_t target, double seconds)
+// host-only wait until the device has published that `target` of the steps the host has enqueued are finished; false after `seconds`
+static bool wait_answered(const zg_plan_t *p, uint32_t target, double seconds)
 {
-    const volatile uint32_t *done = &p->mailbox->completed;
+    const volatile uint32_t *done = &p->mailbox->answered;
     const auto t0 = std::chrono::steady_clock::now();
     uint32_t polls = 0;
     while ((int32_t)(*done - target) < 0) {
@@ -3232,10 +3243,10 @@ int zg_plan_destroy(zg_plan_t *p)
     if (!p) return ZG_OK;
     // a step still in flight reads the mailbox and the captured graph: wait for this plan's own last step - its
     // completion counter first (host memory only), then the stream it was issued on, so that the launch has
-    // retired as a whole.  Other plans' streams are not waited for, unless a recorded step may be in flight: the counter
-    // counts its replays too, and where these went the plan does not know.
+    // retired as a whole.  Other plans' streams are not waited for, unless a recorded step may be in flight: where its
+    // replays went the plan does not know.
     if (p->mailbox && (p->stepped || p->recorded)) {
-        const bool done = !p->recorded && wait_completed(p, p->issued, kHostWaitSeconds);
+        const bool done = !p->recorded && wait_answered(p, p->issued, kHostWaitSeconds);
         if (!done || hipStreamSynchronize(p->last_stream) != hipSuccess) {
             int device = p->device;
             (void)hipGetDevice(&device);
@@ -3311,12 +3322,19 @@ static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, vo
     Queue q{static_cast<hipStream_t>(stream)};
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (q.st) ZG_HIP(hipStreamIsCapturing(q.st, &capture));
-    // (a replay of the recording would be a step that the host has filled no mailbox slot for, and every later one would read another step's)
-    if (capture != hipStreamCaptureStatusNone && replays_graph(p)) return fail(ZG_ESTATE, "a step of a plan with ZG_PLAN_AUTO_FALLBACK cannot be recorded");
+    q.recorded = capture != hipStreamCaptureStatusNone;
+    const StepInputs in{d_seeds, rng_key};
+    if (q.recorded) { // it runs, and counts as a step, when the caller replays it
+        // (a replay would be a step that the host has filled no mailbox slot for, and every later one would read another step's)
+        if (replays_graph(p)) return fail(ZG_ESTATE, "a step of a plan with ZG_PLAN_AUTO_FALLBACK cannot be recorded");
+        const int rc = enqueue_step(p, q, in, probe);
+        p->recorded = p->recorded || q.launched > 0;
+        return rc;
+    }
     // back-pressure without touching the device: wait (host only) while every mailbox slot is taken by a
     // step that has not finished yet
-    if ((uint32_t)(p->issued - p->mailbox->completed) >= (uint32_t)kMailboxSlots - 1u &&
-        !wait_completed(p, p->issued - ((uint32_t)kMailboxSlots - 2u), kHostWaitSeconds))
+    if ((uint32_t)(p->issued - p->mailbox->answered) >= (uint32_t)kMailboxSlots - 1u &&
+        !wait_answered(p, p->issued - ((uint32_t)kMailboxSlots - 2u), kHostWaitSeconds))
         return fail(ZG_ESTATE, "the device finished no step of this plan for 30 s while 255 are queued; nothing was enqueued");
     if (!probe && replays_graph(p) && !p->graph_exec) return fail(ZG_ESTATE, "plan has no captured graph");
     const uint32_t slot = p->issued % kMailboxSlots;
@@ -3325,18 +3343,13 @@ static int issue_step(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, vo
     std::atomic_thread_fence(std::memory_order_seq_cst);
     if (!probe && replays_graph(p)) {
         ZG_HIP(hipGraphLaunch(p->graph_exec, q.st));
-    } else {
-        const int rc = enqueue_step(p, q, StepInputs{d_seeds, rng_key}, probe);
-        if (capture != hipStreamCaptureStatusNone) { // recorded into the caller's graph: it runs, and counts as a step, when that is replayed
-            p->recorded = p->recorded || q.launched > 0;
-            return rc;
-        }
-        if (rc != ZG_OK && q.launched > 0) { // (else nothing was enqueued: the slot is free again)
+    } else if (const int rc = enqueue_step(p, q, in, probe)) {
+        if (q.launched > 0) { // (else nothing was enqueued: the slot is free again)
             p->broken = true;
             p->last_stream = q.st;
             p->stepped = true;
         }
-        if (rc != ZG_OK) return rc;
+        return rc;
     }
     // only now may an earlier step copy the slot ahead of time: a slot whose launch failed is filled again later
     p->issued += 1;

@@ -64,6 +64,7 @@ struct Drmb {
     unsigned long long cur_seeds, cur_key; // this step's inputs, where they had to be read from the mailbox: valid once cur_epoch is the step's number + 1
     uint32_t cur_epoch;
     uint32_t step;                     // `epoch` as the step's first launch found it
+    uint32_t answered;                 // those of the steps run so far that the host has enqueued itself
 };
 
 struct Layout {

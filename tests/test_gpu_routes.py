@@ -385,6 +385,27 @@ def test_destroying_a_plan_waits_for_replays_of_its_steps(oracle, enqueued):
     assert np.array_equal(plan.view_S()[: ref.n[-1]].cpu().numpy(), ref.S) and int(plan.view_counts()[0][-1]) == ref.n[-1]
 
 
+def test_replays_do_not_count_against_the_steps_in_flight(oracle):
+    # 300 replays later the host still waits when 255 of its own steps are unfinished, and for these alone
+    g = W.rmat_graph(30_000, 600_000, 21)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (8, 4), 24, zg.make_envelope(zg.ENV_MAX))
+    seeds, key, stream = W.SeedPool(g, 24, 2).batch_for(0), 70, torch.cuda.Stream()
+    seeds_d, rec, replays, steps = seeds.cuda(), torch.cuda.CUDAGraph(), 300, 300
+    torch.cuda.synchronize()
+    with torch.cuda.graph(rec, stream=stream):
+        plan.step(seeds_d, key, stream)
+    for _ in range(replays):
+        rec.replay()
+    torch.cuda.synchronize()
+    assert plan.step_status() == (replays, 0)
+    torch.cuda._sleep(50_000_000)
+    for s in range(steps):
+        plan.step(seeds_d, key)
+    assert plan.step_status()[0] >= replays + steps - 255
+    compare_blocks(plan.read_step(), to_host_graph(oracle, g).sample_blocks(seeds.numpy(), (8, 4), key))
+    assert plan.step_status() == (replays + steps, 0)
+
+
 _REFUSED_LAUNCHES = """
 import ctypes, sys
 shim = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
