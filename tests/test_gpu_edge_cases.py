@@ -419,13 +419,16 @@ def test_size_model_is_the_same_binned_and_with_atomics(nodes, edges, i64, by_bi
     assert zg.graph_model(dg, fan, batch, with_replacement=replace) == (want[0][:4], want[1][:4])
 
 
-@pytest.mark.parametrize("nodes,edges,i64", [
-    (1 << 19, 4_000_000, False),          # the rows' terms in one piece
-    ((1 << 19) + 1, 10_000_001, True),    # in eight slices of the rows; the last block of rows has one
-    ((1 << 19) + 1, 2_000_000, False),    # no room for the slices' sums: terms in the entries
-    (1_500_007, 40_000_000, False),       # slices of blocks whose chunks are ragged
+@pytest.mark.parametrize("nodes,edges,i64,form", [
+    (1 << 19, 4_000_000, False, "rows"),              # the rows' terms in one piece
+    ((1 << 19) + 1, 10_000_001, True, "slices"),      # in eight slices of the rows; the last block of rows has one
+    ((1 << 19) + 1, 2_000_000, False, "entries"),     # no room for the slices' sums: terms in the entries
+    (1_500_007, 40_000_000, False, "slices"),         # blocks whose chunks are ragged
+    ((1 << 21) + 1, 40_000_000, False, "slices"),     # bins of 2^14 vertices
+    (1 << 22, 70_000_000, True, "slices"),            # the most vertices
+    ((1 << 22) + 1, 70_000_000, True, "entries"),
 ])
-def test_size_model_is_the_same_with_terms_by_row(nodes, edges, i64):
+def test_size_model_is_the_same_with_terms_by_row(nodes, edges, i64, form):
     # a popular neighbor, whose bin goes in parts, and stretches of empty rows
     gen = torch.Generator(device="cuda").manual_seed(nodes)
     weight = torch.rand(nodes, generator=gen, device="cuda").pow_(3)
@@ -439,8 +442,31 @@ def test_size_model_is_the_same_with_terms_by_row(nodes, edges, i64):
     dg = zg.Graph(offsets if i64 else offsets.int(), idx)
     fan, batch = (9, 4, 3), 300
     want, _ = _size_model(dg, fan, batch, edges, large=False)
-    got, used = _size_model(dg, fan, batch, edges, large=True)
+    scratch = {}
+    got, used = _size_model(dg, fan, batch, edges, large=True, scratch=scratch)
     assert got == want and used
+    assert _form_of_the_sums(scratch["bytes"], deg, idx) == form
+
+
+def _form_of_the_sums(scratch, deg, idx):
+    """What a sweep by bins has left behind its entries: with 4 bytes each the rows' terms and, with slices, the last slice's sums."""
+    def aligned(at):
+        return -(-at // 256) * 256
+    nodes, edges = deg.numel(), idx.numel()
+    used = aligned(aligned(8 * nodes) + 4 * nodes) + 64  # where the smaller buffer ends
+    at = aligned(aligned(used) + 4 * edges)
+    terms = scratch[at: at + 8 * nodes].view(torch.int64)
+    if not bool((terms[deg == 0] == 0).all()) or float((terms[deg > 0] > 0).float().mean()) < 0.999:  # (a very long row's may round to zero)
+        return "entries"
+    at = aligned(at + 8 * nodes) + 6 * 8 * nodes
+    if at + 8 * nodes > scratch.numel():
+        return "rows"
+    log2 = nodes.bit_length() - 7  # of a block of rows: 64 to 127 whole ones
+    first = ((((nodes - 1) >> log2) + 1) * 7 // 8) << log2
+    sums = torch.zeros(nodes, dtype=torch.int64, device="cuda")
+    sums.index_add_(0, idx[int(deg[:first].sum()):].long(), torch.repeat_interleave(terms[first:], deg[first:]))
+    quiet = 1 << 14  # (the popular neighbor's bin has its sums elsewhere)
+    return "slices" if torch.equal(scratch[at: at + 8 * nodes].view(torch.int64)[quiet:], sums[quiet:]) else "rows"
 
 
 @pytest.mark.parametrize("nodes,reached", [
@@ -459,7 +485,7 @@ def test_size_model_of_nearly_2_32_edges(nodes, reached):
     assert zg.graph_model(dg, fan, batch) == (want[0][:3], want[1][:3])
 
 
-def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
+def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large, scratch=None):
     """(mean, sigma) from a scratch buffer with or without room for bins, and whether anything was written behind the smaller one."""
     small = 12 * dg.num_nodes + 576
     nbytes = small + (9 * edges + (1 << 20) if large else 0)
@@ -469,6 +495,8 @@ def _size_model(dg, fan, batch, edges, *, replace=False, prob=None, large):
     rc = zg.lib().zg_envelope_model_graph(dg._h, f, len(fan), batch, int(replace), prob.data_ptr() if prob is not None else None, temp.data_ptr() + at, nbytes,
                                           None, mean, sigma)
     assert rc == zg.OK and bool((temp[:at] == 0xAB).all()) and bool((temp[at + nbytes:] == 0xAB).all())
+    if scratch is not None:
+        scratch["bytes"] = temp[at: at + nbytes]
     return (list(mean), list(sigma)), large and bool((temp[at + small: at + nbytes] != 0xAB).any())
 
 

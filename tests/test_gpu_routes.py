@@ -519,3 +519,90 @@ def test_frontier_rows_the_last_hop_reaches_again(oracle, dim, batch, tickets):
         assert torch.equal(rows[written], X[written]) and bool(written[batch:].all())
         reached = np.isin(seeds, res.nbr_gid[0]) if dim >= 256 and 4 * dim * batch >= 32 << 20 else np.zeros(batch, bool)
         assert np.array_equal(written[:batch].cpu().numpy(), reached)
+
+
+_LARGE = dict(nodes=100_000, dim=512, batch=15_000, fanouts=(3, 4))  # two hops: more than 32 MB of frontier rows of 2 KB, a third of them reached again
+
+
+def _large_frontier(oracle, steps):
+    """Graph, its host copy, features and per step the seeds and the checker's blocks."""
+    g = W.rmat_graph(_LARGE["nodes"], 8 * _LARGE["nodes"], 33)
+    og, feat = to_host_graph(oracle, g), W.feature_table(_LARGE["nodes"], _LARGE["dim"], 4)
+    seeds = [np.random.RandomState(s).permutation(_LARGE["nodes"])[: _LARGE["batch"]].astype(np.int32) for s in range(steps)]
+    refs = [og.sample_blocks(x, _LARGE["fanouts"], 50 + s) for s, x in enumerate(seeds)]
+    for r in refs:
+        frontier = r.S[: r.n[1]]
+        assert 4 * _LARGE["dim"] * (r.n[1] - 1000) > 32 << 20 and 0.2 < np.isin(frontier, r.nbr_gid[1]).mean() < 0.8
+    return g, og, feat, seeds, refs
+
+
+def _rows_written_by_the_aggregation(plan, n):
+    """Which of X's first n rows a replay of the aggregation writes; it may not change any."""
+    rows = plan.view_X()[:n, : _LARGE["dim"]]
+    X = rows.clone()
+    rows[:] = 7
+    plan.replay_features(1)
+    torch.cuda.synchronize()
+    written = (rows != 7).any(1)
+    assert torch.equal(rows[written], X[written])
+    rows[:] = X
+    return written.cpu().numpy()
+
+
+@pytest.mark.parametrize("flags", [0, zg.PLAN_IMPATIENT])
+def test_entries_are_relabeled_while_the_frontiers_get_their_tags(oracle, flags):
+    # two hops: the closing launch relabels hop 0's edges from the entries to which other workgroups of it add tags
+    g, og, feat, seeds, refs = _large_frontier(oracle, 4)
+    plan = None
+    for s, (x, ref) in enumerate(zip(seeds, refs)):
+        plan, res, _ = run_and_compare(oracle, g, feat, x, _LARGE["fanouts"], 50 + s, env=zg.make_envelope(zg.ENV_MAX, flags=flags), plan=plan, og=og, label=f"step {s}")
+        assert np.array_equal(_rows_written_by_the_aggregation(plan, ref.n[2]), np.isin(ref.S, ref.nbr_gid[1]))
+
+
+@pytest.mark.parametrize("flags", [0, zg.PLAN_IMPATIENT])
+@pytest.mark.parametrize("cut", [(0,), (1,), (0, 1)])  # hops
+def test_reached_frontier_rows_where_a_cap_cuts_the_step(oracle, cut, flags):
+    g, og, feat, seeds, refs = _large_frontier(oracle, 3)
+    caps = [_LARGE["batch"]] + [min(r.n[h + 1] for r in refs) - 700 if h in cut else max(r.n[h + 1] for r in refs) for h in range(2)]
+    table = feat.cuda()
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), _LARGE["fanouts"], _LARGE["batch"], zg.make_envelope(zg.ENV_EXPLICIT, node_caps=caps, flags=flags),
+                   feat_dim=_LARGE["dim"])
+    plan.bind_features(table)
+    for s, x in enumerate(seeds):  # (marks a step leaves behind show in the next)
+        want = truncated_blocks(oracle, g, x, _LARGE["fanouts"], 50 + s, caps)
+        plan.step(torch.as_tensor(x).cuda(), 50 + s)
+        torch.cuda.synchronize()
+        assert plan.step_status()[1] == sum(zg.FLAG_HOP_OVERFLOW(h) for h in range(2) if want[1][h + 1] > caps[h + 1])
+        compare_truncated(plan, want, f"step {s}")
+        n, S = want[0], want[2]
+        assert all((n[h + 1] == caps[h + 1]) for h in cut)
+        assert torch.equal(plan.view_X()[: n[2], : _LARGE["dim"]], table[torch.as_tensor(S).cuda()]), f"step {s}: X"
+        assert np.array_equal(_rows_written_by_the_aggregation(plan, n[2]), np.isin(S, want[3][1][1]))
+
+
+@pytest.mark.parametrize("how", ["graph", "eager", "recorded"])  # the plan's own graph; launches; launches in the caller's graph
+def test_reached_frontier_rows_of_a_step_that_the_twin_redoes(oracle, how):
+    g, og, feat, seeds, refs = _large_frontier(oracle, 3)
+    table = feat.cuda()
+    caps = [0, max(r.n[1] for r in refs), sorted(r.n[2] for r in refs)[1]]  # one of the three steps does not fit
+    assert sum(r.n[2] > caps[2] for r in refs) == 1
+    flags = zg.PLAN_AUTO_FALLBACK | (0 if how == "graph" else zg.PLAN_EAGER)
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), _LARGE["fanouts"], _LARGE["batch"], zg.make_envelope(zg.ENV_EXPLICIT, node_caps=caps, flags=flags),
+                   feat_dim=_LARGE["dim"])
+    plan.bind_features(table)
+    twin, stream, batches, recorded = plan.safe_view(), torch.cuda.Stream(), [torch.as_tensor(x).cuda() for x in seeds], []
+    torch.cuda.synchronize()
+    for s, x in enumerate(batches if how == "recorded" else []):
+        recorded.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(recorded[s], stream=stream):
+            plan.step(x, 50 + s, stream)
+    for rep in range(2):
+        for s, ref in enumerate(refs):
+            recorded[s].replay() if recorded else plan.step(batches[s], 50 + s)
+            torch.cuda.synchronize()
+            active = int(plan.view_active().item())
+            assert active == (ref.n[2] > caps[2]) and plan.step_status() == (3 * rep + s + 1, zg.FLAG_HOP_OVERFLOW(1) if active else 0)
+            res = (twin if active else plan).read_step()
+            res.flags &= ~zg.FLAG_HOP_OVERFLOW(1)  # (the plan's sticky word)
+            compare_blocks(res, ref, f"{rep}: step {s}")
+            compare_features(oracle, res, ref, feat.numpy(), f"{rep}: step {s}")
