@@ -492,7 +492,15 @@ __device__ __forceinline__ void gather_rows_block(const RowArgs &a, uint32_t blo
 // ranking beside it by more than that, which both are bounds of.  us of the closing launch and the aggregation, all rows copied / these
 // left out: 216 k rows of 2400 bytes 930 / 857, 706 k of 512 629 / 601, 722 k of 400 476 / 465, 622 k of 300 377 / 363, 125 k of 1 KB 185 / 175, 28 k
 // of 2400 166 / 163, 33 k of 1 KB 80.2 / 78.0, 15 k of 2400 105.8 / 105.7; but 188 k rows of 400 bytes 156 / 163, 194 k of 256 115 / 117, 60 k of 400
-// 67 / 70.  Hence from 96 MB of frontier rows on (kReachBytes), from 32 MB where they are 1 KB or longer; by the step's own size.
+// 67 / 70.  Hence by the frontier's bytes and the row's (reach_bytes), in the step's own sizes.  Where the lines lie: steps of one to four hops over eight
+// graphs of 0.25 to 3 M vertices, in how many % the step is longer with all rows copied, mean (least, most):
+//     rows of       34 MB              100 MB              140 MB              200 MB              300 MB              450 MB
+//     300 to 400                       -2.2 (-4.1, 0.6)    -1.0 (-3.8, 5.0)    1.2 (-2.5, 9.5)     2.4 (-1.2, 7.3)     2.8 (0.0, 7.0)
+//     512 to 768    0.3 (-0.9, 1.2)    0.3 (-2.4, 2.6)     0.7 (-3.3, 2.5)     1.4 (-2.7, 3.0)     2.9 (-1.0, 4.6)     4.5 (0.2, 6.4)
+//     1000 to 2000  0.2 (-1.9, 1.6)    0.4 (-1.7, 2.7)     0.8 (-3.6, 3.3)     1.3 (-1.1, 4.4)     2.8 (0.8, 6.5)      4.0 (2.0, 6.2)
+//     2048 to 2560  0.3 (-0.5, 1.3)    0.8 (-0.2, 2.3)     1.2 (0.3, 2.9)      1.4 (0.9, 1.9)      2.6 (1.7, 3.5)      4.0 (2.8, 5.2)
+// What is slower above a line all the same: rows that end in partial lines, graphs of skew 0.9, where the copy finds its rows in the caches, and tables
+// of the last-level cache's size.
 template <int VEC>
 __device__ __forceinline__ void gather_unreached_block(const RowArgs &a, uint32_t block, uint8_t *marks, int32_t *local_id, const MarkTag &tag, int32_t *s_mem)
 {
@@ -2880,7 +2888,7 @@ MarkTag mark_tag(const zg_plan_t *p)
     t.shift = 31 - bits;
     t.mask = (1u << bits) - 1u;
     const int64_t row = (int64_t)L.feat_dim * 4;
-    t.reach_rows = (uint32_t)(((row >= 1024 ? kReachBytes / 3 : kReachBytes) + row - 1) / row);
+    t.reach_rows = (uint32_t)((reach_bytes(row) + row - 1) / row);
     return t;
 }
 

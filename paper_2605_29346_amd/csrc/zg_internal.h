@@ -39,7 +39,8 @@ constexpr int64_t kByteMarkVerticesPerEdge = 30;
 constexpr int kSampleHashBits = 11;      // LDS dedup set of a sampling workgroup: 2048 slots for <= 1024 ids
 constexpr int kSampleHashSlots = 1 << kSampleHashBits;
 constexpr uint64_t kGatherStreamBytes = 160ull << 20; // gathered matrices above this size are copied with non-temporal accesses
-constexpr int64_t kReachBytes = 96ll << 20; // frontier rows from which on those the last hop reaches are written by the aggregation (rows of 1 KB: a third)
+// frontier rows in bytes from which on those the last hop reaches are written by the aggregation, by the length of a row
+constexpr int64_t reach_bytes(int64_t row) { return (row >= 1024 ? 32ll : row >= 512 ? 96ll : 160ll) << 20; }
 constexpr int kRelabelPerBlock = 1024;  // edges per relabel workgroup (any workgroup size)
 constexpr int kMailboxSlots = 256;      // per-step inputs in flight between host and device
 constexpr int kLogCapacity = 1024;      // records in the device-side step log

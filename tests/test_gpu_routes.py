@@ -521,6 +521,33 @@ def test_frontier_rows_the_last_hop_reaches_again(oracle, dim, batch, tickets):
         assert np.array_equal(written[:batch].cpu().numpy(), reached)
 
 
+@pytest.mark.parametrize("dim,batch,by_aggregation", [
+    (100, 419_430, False), (100, 419_431, True),  # either side of 160 MB of frontier rows of less than 512 bytes
+    (127, 330_260, False), (127, 330_261, True),
+    (128, 196_607, False), (128, 196_608, True),  # ... of 96 MB from there on
+    (255, 98_689, False), (255, 98_690, True),
+])
+def test_the_frontier_from_which_reached_rows_are_not_copied(dim, batch, by_aggregation):
+    nodes = 700_000
+    g = W.rmat_graph(nodes, 3 * nodes, 35)
+    table = torch.empty((nodes, dim), device="cuda").normal_()
+    plan = zg.Plan(zg.Graph(g.offsets.cuda(), g.indices.cuda()), (2,), batch, zg.make_envelope(zg.ENV_MAX), feat_dim=dim)
+    plan.bind_features(table)
+    for s in range(2):
+        plan.step(torch.randperm(nodes, device="cuda")[:batch].int(), 60 + s)
+        torch.cuda.synchronize()
+        n, E = int(plan.view_counts()[0][1]), int(plan.view_counts()[1][0])
+        S, X = plan.view_S()[:n].long(), plan.view_X()[:n, :dim]
+        assert plan.step_status()[1] == 0 and torch.equal(X, table[S])
+        X[:] = 9  # (further from zero than any entry of the table)
+        plan.replay_features(1)
+        torch.cuda.synchronize()
+        written = (X != 9).any(1)
+        reached = torch.isin(S[:batch], plan.view_block(0)[1][:E].long())
+        assert bool(written[batch:].all()) and 0 < int(reached.sum()) < batch
+        assert torch.equal(written[:batch], reached if by_aggregation else torch.zeros_like(reached)) and torch.equal(X[written], table[S][written])
+
+
 _LARGE = dict(nodes=100_000, dim=512, batch=15_000, fanouts=(3, 4))  # two hops: more than 32 MB of frontier rows of 2 KB, a third of them reached again
 
 
