@@ -2842,7 +2842,7 @@ struct StepProbe {
 };
 
 // Where a step's launches go, and how many of them have gone there.  (What a launch returned, and not hipGetLastError: that may be an earlier
-// error of the caller's own.)
+// error of the caller's own.  An error that was returned does not stay behind for the caller's next launch.)
 struct Queue {
     hipStream_t st;
     bool recorded = false; // into a caller's graph
@@ -2850,7 +2850,11 @@ struct Queue {
     template <class... P> int launch(void (*kernel)(P...), unsigned grid, unsigned block, size_t lds, P... a)
     {
         void *args[] = {&a...};
-        ZG_HIP(hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block), args, lds, st));
+        const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block), args, lds, st);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(ZG_EHIP, std::string("hipLaunchKernel: ") + hipGetErrorString(e));
+        }
         ++launched;
         return ZG_OK;
     }

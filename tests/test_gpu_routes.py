@@ -430,6 +430,7 @@ for launched in (0, 1, 3):
     left.value = launched
     assert status(step) == zg.EHIP and left.value == 0
     left.value = -1
+    torch.zeros(1, device="cuda").add_(1)  # the error is the step's, not the caller's next launch's
     assert status(step) == (zg.ESTATE if launched else zg.OK)  # nothing of the step was enqueued: the plan goes on
     assert not stream.query()
     plan.close()
