@@ -51,7 +51,8 @@ enum zg_dtype { ZG_I32 = 0, ZG_I64 = 1 };
 #define ZG_GRAPH_VALIDATE 1u /* synchronising check: indices in range, rows ascending (hence duplicate-free) */
 
 /* zg_envelope.flags */
-#define ZG_PLAN_EAGER 1u   /* launch the step's kernels one by one with ZG_PLAN_AUTO_FALLBACK too, instead of replaying a hipGraph */
+#define ZG_PLAN_EAGER 1u   /* launch the step's kernels one by one with ZG_PLAN_AUTO_FALLBACK too, instead of replaying a hipGraph (and
+                              make no stream of the plan's own: without ZG_PLAN_AUTO_FALLBACK the only difference) */
 #define ZG_PLAN_REPLACE 2u /* sample with replacement (the setting of the paper's Lemma 1) */
 #define ZG_PLAN_FUSED_INPUT 8u /* X holds the rows of the frontier D_{H-1} only and the aggregation reads its input rows
                                  straight from the feature table; the rows that only feed the mean are never written out.
@@ -287,7 +288,7 @@ int zg_plan_outputs(const zg_plan_t *p, zg_outputs *out);
  * stream-ordered one after another and issued from one host thread at a time.  Invalid seeds do not fault:
  * they raise ZG_FLAG_SEED_* bits in the device status word and make the step's outputs undefined.
  * On a stream that is being captured the kernels become part of the caller's graph: each of its replays is a step with these
- * seeds and this key.  (A plan with ZG_PLAN_AUTO_FALLBACK, without ZG_PLAN_EAGER, refuses such a stream: its steps take their
+ * seeds, this key and the feature table bound now.  (A plan with ZG_PLAN_AUTO_FALLBACK, without ZG_PLAN_EAGER, refuses such a stream: its steps take their
  * inputs from the ring, where a replay would find none.)
  * Errors: ZG_EINVAL (null), ZG_ESTATE (no captured graph; a stream under capture; device made no progress for 30 s), ZG_EHIP (a launch
  * failed; if it was not the step's first one the plan takes no more steps: ZG_ESTATE). */
@@ -312,7 +313,7 @@ int zg_aggregate_mean(zg_plan_t *p, int32_t hop, const float *d_in, int64_t ld_i
  * by itself: ZG_PLAN_AUTO_FALLBACK), otherwise as zg_step. */
 int zg_step_safe(zg_plan_t *p, const int32_t *d_seeds, uint64_t rng_key, void *stream);
 int zg_plan_outputs_safe(const zg_plan_t *p, zg_outputs *out);
-/* Host only, no device call: how many steps of this plan have finished, and the ZG_FLAG_* bits the last
+/* Host only, no device call: how many steps of this plan have finished (replays of a recorded one among them), and the ZG_FLAG_* bits the last
  * finished step raised (0 = its outputs are valid).  Both come from pinned host memory that the last kernel
  * of every step writes, so a caller that already knows step k has finished (its own event or sync) can
  * decide about the fallback without reading device memory. */

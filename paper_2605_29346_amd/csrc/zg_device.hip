@@ -2554,6 +2554,10 @@ ModelBins model_bins(const zg_graph_t *g, void *temp, size_t used, size_t temp_b
 // 78 / 74, 224 / 160.  2.4 M vertices and 115 M edges, one hop: 1.1 ms by bins; by atomics 0.11, 0.55, 0.94, 1.3 ms with 1, 10, 18, 25 % of the
 // vertices as seeds, 5.6 with all; three hops from 1 % 2.2 ms, 3.0 all by bins.  (All with 8-byte entries.  With terms by row the places take
 // 6 ps per edge more and a sweep 4 to 6 less: 90 k vertices and 1 M edges, one hop, 81 to 85 us with either.)
+// The line is that of 8-byte entries, and of seeds that are drawn evenly.  With terms by row, where further hops go by bins anyway, it lies too high: 2.4 M vertices
+// and 111 M edges, seeds from 3 to 13 % of the vertices, us now / all by bins: one hop 1146 to 1576 / 940, two 2265 to 2696 / 1270, three 2601 to 3033 /
+// 1600; from 16 % on, and for 1 % in one hop, the better of the two.  40 k and 2.2 M, 10 to 25 %, two hops 172 to 215 / 134; 8 M and 119 M (8-byte entries), 5 to 13 %, one
+// hop 1948 to 3262 / 1620, two 3743 to 4835 / 2950.
 int64_t model_bins_work(const ModelBins &m, int hops)
 {
     return m.num_edges / 7 + 180000 + 360000 / hops + 120 * m.num_nodes / m.chunks;
@@ -3182,8 +3186,10 @@ static int make_plan_object(zg_plan_t **out, const zg_graph_t *g, const Layout &
         p->mailbox_dev = static_cast<Mailbox *>(dev);
     }
     // A stream of the plan's own, for the capture of a graph - and where there is none all the same: the runtime spreads a process's streams over
-    // four hardware queues as they are made, and callers with a stream per plan and the default one have five.  (110 M vertices, four plans on
-    // four streams: two of them shared a queue, 908 to 945 us for a step of each; 858 with these streams in between.)
+    // four hardware queues as they are made, and callers with a stream per plan and the default one have five.  Which of them share a queue
+    // is the runtime's affair and depends on what else the process makes; with these in between it came out better.  (110 M vertices, four plans on
+    // four streams, a step of each, without / with: streams made before the plans 943 / 857 us, behind them 980 / 906.)  A plan made with
+    // ZG_PLAN_EAGER has none.
     if (!(flags & ZG_PLAN_EAGER) && hipStreamCreateWithFlags(&p->own_stream, hipStreamNonBlocking) != hipSuccess)
         return bail(fail(ZG_EHIP, "hipStreamCreateWithFlags failed"));
     // initial state: metadata, log, both bitmaps and the scan state zero (the id map needs no initial value:
